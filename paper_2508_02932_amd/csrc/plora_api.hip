@@ -87,6 +87,7 @@ struct HostMeta {
     size_t h_elems = 0, hb_elems = 0, zt_elems = 0, at_elems = 0, ap_elems = 0;
     int r16_total = 0, n_active = 0, split_dA = 1, split_dB = 1, bc_dA = 256, bc_dB = 256;
     int split_shrink = 1, split_dh = 1;
+    GemmPlan gemm_fwd, gemm_dx;
     int n_words = 0;
     bool order_is_identity = false;   // the sorted order of the GEMM row tiles is 0, 1, 2, ...: the device need not sort
 };
@@ -141,7 +142,10 @@ static void build_meta(const plora_desc *d, HostMeta &m)
     m.split_dh = skinny_splits(m.hdr, d->d_out);
 
     const bool bf = d->dtype == PLORA_BF16;
-    auto lay_out = [&](WorkspaceLayout &w, size_t ap_elems) {
+    m.gemm_fwd = gemm_plan(d->T, d->d_in, d->d_out);
+    m.gemm_dx = gemm_plan(d->T, d->d_out, d->d_in);
+    auto split_bytes = [&](const GemmPlan &p, int64_t N) { return p.n_split > 1 ? (size_t)p.n_split * d->T * N * 4 : (size_t)0; };
+    auto lay_out = [&](WorkspaceLayout &w, size_t ap_elems, bool split_gemm) {
         size_t o = 0;
         w.zero = o; o += kZeroBytes;
         w.meta_bytes = m.layout.bytes;
@@ -158,12 +162,22 @@ static void build_meta(const plora_desc *d, HostMeta &m)
         const size_t a_bytes = m.split_dA > 1 ? (size_t)m.split_dA * m.r16_total * d->d_in * 4 : 0;
         const size_t b_bytes = m.split_dB > 1 ? (size_t)m.split_dB * m.r16_total * d->d_out * 4 : 0;
         w.wpart = o; o = align_up(o + (bf ? (a_bytes > b_bytes ? a_bytes : b_bytes) : 0), 256);
+        // the GEMMs run when every other partial tile has been summed: theirs take the same place
+        w.gpart = w.part;
+        if (bf && split_gemm)
+            o = std::max(o, align_up(w.gpart + std::max(split_bytes(m.gemm_fwd, d->d_out), split_bytes(m.gemm_dx, d->d_in)), 256));
         w.total = o + 256;
     };
-    lay_out(m.ws, m.ap_elems);
+    // a description that fits the scratch array of plora_linear_fwd_noalloc without split GEMMs must not outgrow it with them
+    lay_out(m.ws, m.ap_elems, false);
+    const bool fits_scratch = m.ws.total <= (size_t)PLORA_NOALLOC_SCRATCH_BYTES;
+    for (lay_out(m.ws, m.ap_elems, true); fits_scratch && m.ws.total > (size_t)PLORA_NOALLOC_SCRATCH_BYTES; lay_out(m.ws, m.ap_elems, true)) {
+        const bool fwd = split_bytes(m.gemm_fwd, d->d_out) > split_bytes(m.gemm_dx, d->d_in);
+        (fwd ? m.gemm_fwd : m.gemm_dx).n_split -= 1;
+    }
     int64_t rp_total = 0;
     for (int32_t k = 0; k < d->n_adapters; ++k) rp_total += m.t.ad[k].rp;
-    lay_out(m.ws_lora, (size_t)(rp_total * std::max(d->d_in, d->d_out)));
+    lay_out(m.ws_lora, (size_t)(rp_total * std::max(d->d_in, d->d_out)), false);
 }
 
 // ---- metadata cache: the last few descriptions and what was derived from them ---------------------
@@ -277,6 +291,17 @@ static MetaView device_view(const HostMeta &m, const WorkspaceLayout &L, char *w
     return view_of(tables_at(ws + L.meta, m.layout));
 }
 
+// Base GEMM of one direction.  w_rows_contract: the contraction index is W's row index.
+static hipError_t run_gemm(const HostMeta &m, const WorkspaceLayout &L, char *ws, const GemmPlan &plan, bool w_rows_contract, int64_t Kd,
+                           int64_t N, const void *S, const void *W, void *C, bool accumulate, hipStream_t st)
+{
+    const MetaView mv = device_view(m, L, ws);
+    if (plan.bm == 0)
+        return launch_gemm_bf16(mv, m.hdr, w_rows_contract, Kd, N, S, W, ws + L.hb, ws + L.ap, ws + L.zero, C, accumulate, st);
+    return launch_gemm_small_bf16(plan, mv, m.hdr, w_rows_contract, Kd, N, S, W, ws + L.hb, ws + L.ap, ws + L.zero, C, accumulate,
+                                  reinterpret_cast<float *>(ws + L.gpart), st);
+}
+
 // Steps of a call, so that a grouped call can run a fused pass of its own between them (a plain call runs them all).
 enum : unsigned {
     kStepPrep = 1u, kStepShrink = 2u, kStepMain = 4u,      // forward: prep, shrink, GEMM (or stand-alone update)
@@ -338,7 +363,7 @@ static plora_status forward_impl(const plora_desc *desc, const void *x, const vo
         return PLORA_OK;
     }
     { Bracket b(0, st);
-      PL_TRY(launch_gemm_bf16(mv, m.hdr, !w_out_in, desc->d_in, desc->d_out, x, W, hb, ws + L.ap, ws + L.zero, y, false, st)); }
+      PL_TRY(run_gemm(m, L, ws, m.gemm_fwd, !w_out_in, desc->d_in, desc->d_out, x, W, y, false, st)); }
     return PLORA_OK;
 }
 
@@ -435,7 +460,7 @@ static plora_status backward_impl(const plora_desc *desc, const void *x, const v
         PL_TRY(launch_expand_bf16(mv, m.hdr, dx, desc->d_in, gb, ap, m.hdr.w_out_in ? desc->d_out : desc->d_in, ws + L.zero, st));
     } else if (dx && desc->T > 0) {
         Bracket b(1, st);
-        PL_TRY(launch_gemm_bf16(mv, m.hdr, m.hdr.w_out_in != 0, desc->d_out, desc->d_in, dy, W, gb, ap, ws + L.zero, dx, dx_accumulate, st));
+        PL_TRY(run_gemm(m, L, ws, m.gemm_dx, m.hdr.w_out_in != 0, desc->d_out, desc->d_in, dy, W, dx, dx_accumulate, st));
     }
     return PLORA_OK;
 }

@@ -443,7 +443,7 @@ PLORA_HD void derive_phase3_place(const Tables &t, int64_t n_tiles, int tid, int
 
 // Byte offsets of the workspace regions, each 256-byte aligned.
 struct WorkspaceLayout {
-    size_t zero, meta, desc, at, ap, hb, zt_h, zt_g, hf, gf, part, wpart, total;
+    size_t zero, meta, desc, at, ap, hb, zt_h, zt_g, hf, gf, part, wpart, gpart, total;
     size_t meta_bytes;
 };
 
@@ -454,7 +454,7 @@ int device_cu_count(hipError_t *err);
 // Lets `kernel` use up to the 160 KB of LDS of a compute unit; done once per device and kernel (slot: a small
 // index that is unique per kernel), thread-safe.
 hipError_t allow_full_lds(const void *kernel, int slot);
-constexpr int kLdsSlots = 16;
+constexpr int kLdsSlots = 48;
 
 // Metadata and the small jobs in front of the heavy kernels, in one launch when the compact description fits a
 // kernel argument (otherwise it is first uploaded in chunks to desc_stage): derived tables and zero page into the
@@ -483,6 +483,15 @@ hipError_t launch_skinny_bf16(const MetaView &mv, const MetaHeader &h, int mode,
 hipError_t launch_gemm_bf16(const MetaView &mv, const MetaHeader &h, bool w_rows_contract, int64_t Kd, int64_t N,
                             const void *S, const void *W, const void *side, const void *ap, const void *zero, void *C,
                             bool accumulate, hipStream_t st);
+// The same product in small tiles with the contraction split over workgroups (gemm_small_bf16.hip).
+struct GemmPlan {
+    int bm;                   // rows of the output tile: 0: k_gemm's 256 x 256 tiles, otherwise tiles of bm x 128
+    int n_split;              // splits of the contraction; above 1 the fp32 partial tiles take n_split * T * N * 4 bytes
+};
+GemmPlan gemm_plan(int64_t T, int64_t Kd, int64_t N);
+hipError_t launch_gemm_small_bf16(const GemmPlan &p, const MetaView &mv, const MetaHeader &h, bool w_rows_contract, int64_t Kd, int64_t N,
+                                  const void *S, const void *W, const void *side, const void *ap, const void *zero, void *C,
+                                  bool accumulate, float *part, hipStream_t st);
 // Stand-alone low-rank update C[T][N] += side * op_k (bf16, one rounding): side = bf16 low-rank factor [len][rp] per
 // segment, opT = padded small matrices [N][rp] (adapter k at N * (ap_off_k / table_rows)).
 hipError_t launch_expand_bf16(const MetaView &mv, const MetaHeader &h, void *C, int64_t N, const void *side, const void *opT,
