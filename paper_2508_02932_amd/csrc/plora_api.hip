@@ -85,7 +85,7 @@ struct HostMeta {
     WorkspaceLayout ws;               // plora_linear_fwd / _bwd
     WorkspaceLayout ws_lora;          // plora_lora_fwd / _bwd: the padded small-matrix region holds [max(d_in, d_out)][rp]
     size_t h_elems = 0, hb_elems = 0, zt_elems = 0, at_elems = 0, ap_elems = 0;
-    int r16_total = 0, n_active = 0, split_dA = 1, split_dB = 1, bc_dA = 256, bc_dB = 256;
+    int r16_total = 0, n_active = 0, max_rank = 0, split_dA = 1, split_dB = 1, bc_dA = 256, bc_dB = 256;
     int split_shrink = 1, split_dh = 1;
     GemmPlan gemm_fwd, gemm_dx;
     int n_words = 0;
@@ -130,6 +130,7 @@ static void build_meta(const plora_desc *d, HostMeta &m)
         at += (int64_t)a.r16 * d->d_in;
         ap += (int64_t)a.rp * (m.hdr.w_out_in ? d->d_out : d->d_in);
         m.r16_total += a.r16;
+        m.max_rank = std::max(m.max_rank, a.r);
         m.n_active += a.tokens > 0;
     }
     m.h_elems = (size_t)h; m.hb_elems = (size_t)hb; m.zt_elems = (size_t)zt;
@@ -421,8 +422,8 @@ static plora_status backward_impl(const plora_desc *desc, const void *x, const v
         }
         if (lora && (steps & kStepDh)) { Bracket b(3, st); PL_TRY(launch_f32_lowrank(mv, m.hdr, 1, dyf, desc->d_out, gf, st)); }
         if (any_w) {
-            if (steps & kStepDb) { Bracket b(4, st); PL_TRY(launch_f32_wgrad(mv, m.hdr, false, dyf, desc->d_out, hf, st)); }
-            if (steps & kStepDa) { Bracket b(5, st); PL_TRY(launch_f32_wgrad(mv, m.hdr, true, xf, desc->d_in, gf, st)); }
+            // (an fp32 call always runs the two steps together: grouped calls do not fuse fp32 projections)
+            if (steps & kStepDb) { Bracket b(4, st); PL_TRY(launch_f32_wgrad(mv, m.hdr, m.max_rank, xf, gf, dyf, hf, st)); }
         }
         if (!(steps & kStepDx)) return PLORA_OK;
         if (dx && desc->T > 0 && lora_only) {

@@ -520,8 +520,9 @@ hipError_t launch_f32_gemm(const MetaView &mv, const MetaHeader &h, bool forward
                            const float *side, float *C, bool accumulate, hipStream_t st);   // W's layout: h.w_out_in
 // to_y: y += scale_k h B_k (side = h);  else dx += g A_k^T (side = g, which carries scale_k).
 hipError_t launch_f32_expand(const MetaView &mv, const MetaHeader &h, bool to_y, float *C, const float *side, hipStream_t st);
-hipError_t launch_f32_wgrad(const MetaView &mv, const MetaHeader &h, bool want_dA, const float *S, int64_t C,
-                            const float *side, hipStream_t st);
+// Both weight gradients: dB from dy and h, dA from x and g (which carries scale_k).  max_rank: over all adapters.
+hipError_t launch_f32_wgrad(const MetaView &mv, const MetaHeader &h, int max_rank, const float *x, const float *gf, const float *dy,
+                            const float *hf, hipStream_t st);
 
 // NF4 base weight: out[i] = level[index_i] * absmax[i / 64] for n_elems elements (a multiple of 64), bf16 or fp32.
 hipError_t launch_nf4_dequant(const void *codes, const float *absmax, int64_t n_elems, bool bf16, void *out, hipStream_t st);
