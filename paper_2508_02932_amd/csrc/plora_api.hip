@@ -104,15 +104,8 @@ static void build_meta(const plora_desc *d, HostMeta &m)
     m.image.assign(m.layout.bytes, 0);
     m.t = tables_at(m.image.data(), m.layout);
     const DescReader<WordsInMemory> in{WordsInMemory{words.data()}};
-    std::vector<int32_t> scratch(3 * (size_t)d->n_adapters + 1);
-    derive_phase1(in, m.t, scratch.data(), nullptr, nullptr, nullptr);
-    derive_phase2(m.t, *m.t.hdr, m.t.seg, m.t.ad, scratch.data() /* tokens */, 0, 1);
-    {
-        int32_t counts[kSortKeys], starts[kSortKeys];
-        derive_phase3_count(m.t, m.layout.n_tiles, 0, 1, counts);
-        derive_phase3_scan(0, 1, counts, starts);
-        derive_phase3_place(m.t, m.layout.n_tiles, 0, 1, starts);
-    }
+    std::vector<int32_t> scratch(2 * (size_t)d->n_adapters + 1);
+    derive_tables(in, m.t, scratch.data());
     m.order_is_identity = true;
     for (int64_t i = 0; i < m.layout.n_tiles; ++i) m.order_is_identity = m.order_is_identity && m.t.tile_order[i] == (int32_t)i;
     m.hdr = *m.t.hdr;
@@ -332,7 +325,7 @@ static plora_status forward_impl(const plora_desc *desc, const void *x, const vo
     if (steps & kStepPrep) {
         Bracket b(6, st);
         PL_TRY(launch_prep(c.words, m.n_words, m.hdr, ws + L.meta, reinterpret_cast<uint32_t *>(ws + L.desc), ws + L.zero,
-                           ws + L.at, ws + L.ap, bf && lora, false, bf && lora && (w_out_in || lora_only), nullptr, nullptr, st));
+                           ws + L.at, ws + L.ap, bf && lora, false, bf && lora && (w_out_in || lora_only), m.max_rank, nullptr, nullptr, st));
     }
     float *hf = h_saved ? h_saved : reinterpret_cast<float *>(ws + L.hf);
 
@@ -407,7 +400,7 @@ static plora_status backward_impl(const plora_desc *desc, const void *x, const v
         const bool dx_ap = dx != nullptr && (lora_only || !m.hdr.w_out_in), dx_at = dx != nullptr && !lora_only && m.hdr.w_out_in;
         Bracket b(6, st);
         PL_TRY(launch_prep(c.words, m.n_words, m.hdr, ws + L.meta, reinterpret_cast<uint32_t *>(ws + L.desc), ws + L.zero,
-                           ws + L.at, ws + L.ap, bf && lora && (need_shrink || dx_at), bf && lora && dx_ap, false,
+                           ws + L.at, ws + L.ap, bf && lora && (need_shrink || dx_at), bf && lora && dx_ap, false, m.max_rank,
                            tr ? h_saved : nullptr, tr ? ws + L.zt_h : nullptr, st));
     }
 

@@ -25,10 +25,9 @@ constexpr int kGemmGroupRows = 4;   // row tiles that the GEMM's tile order keep
 //
 // The host validates the description and ships it to the device in a compact form (a few 32-bit
 // words per segment and adapter, passed by value as a kernel argument).  The tables the kernels
-// read are derived from it by one set of routines (derive_phase1, derive_phase2) compiled for both sides: the
-// device runs them inside the preparation kernel and writes the tables into the workspace; the
-// host runs the very same code to size the workspace, to plan the launches and to export the
-// tables for the brute-force tests.
+// read are derived from it on both sides: the device does it inside the preparation kernel and writes
+// the tables into the workspace; the host does it to size the workspace, to plan the launches and to
+// export the tables for the brute-force tests.
 // ---------------------------------------------------------------------------------------------
 
 // One entry per segment of the call (empty and base-only segments included).
@@ -161,6 +160,12 @@ template <class Src> struct DescReader {
     PLORA_HD int seg_adapter(int s) const { return (int)src.word(kDescHeadWords + kDescSegWords * s + 1); }
     PLORA_HD int ad_base(int k) const { return kDescHeadWords + kDescSegWords * n_seg() + kDescAdWords * k; }
     PLORA_HD const void *ad_ptr(int k, int which) const { return reinterpret_cast<const void *>((uintptr_t)w64(ad_base(k) + 2 * which)); }
+    // operand of the GEMM form with the contraction index as row index (GemmSeg::B) of adapter k, whose packed A^T starts
+    // at element at_off (integer arithmetic: the host derives the tables with a null base)
+    PLORA_HD const void *ext_b(int k, int64_t at_off) const
+    {
+        return w_out_in() ? reinterpret_cast<const void *>((uintptr_t)at_base() + 2 * (uintptr_t)at_off) : ad_ptr(k, 1);
+    }
     PLORA_HD int ad_rank(int k) const { return (int)src.word(ad_base(k) + 8); }
     PLORA_HD float ad_scale(int k) const
     {
@@ -226,55 +231,89 @@ PLORA_HD MetaView view_of(const Tables &t)
     return v;
 }
 
-// ---- derivation of the tables, in two phases ------------------------------------------------------
-// Phase 1 runs on one thread (prefix sums over adapters and segments); phase 2 is loops
-// "for (i = tid; i < n; i += nthreads)" over independent entries.  Phase 2 reads what phase 1 wrote, so
-// the caller separates them with a barrier (device: one workgroup, __syncthreads; host: tid 0 of 1, nothing to do).
+// ---- derivation of the tables ------------------------------------------------------------------------
+// The host walks segments and adapters one after the other (derive_tables); the preparation kernel derives the same
+// tables in parallel (small_kernels.hip) and a test compares the two byte for byte.  The record of a row tile is built by
+// one routine for both (derive_tile).
 
-// scratch: 3 ints per adapter (tokens, non-empty segments, list cursor).  On the device it lies in LDS: the one
-// thread that runs this phase then never waits for a load from memory - everything it reads comes from the
-// description or from the scratch, everything it writes to the tables is a store it does not wait for.
-// seg_copy / ad_copy (either may be null): a second place for the segment records and for what the tile records need
-// of an adapter.  On the device they lie in LDS, so that the phases that follow read them from there and not from the
-// tables in memory (every such read would be a trip to the L2, and the tile derivation chains several).
-struct AdapterGemm {
-    const void *ext_b;
-    int64_t ap_off;
-};
+PLORA_HD bool seg_has_lowrank(const SegInfo &g) { return g.adapter >= 0 && g.row1 > g.row0; }
 
-template <class Src> PLORA_HD void derive_phase1(const DescReader<Src> &in, const Tables &t, int32_t *scratch,
-                                                 SegInfo *seg_copy, AdapterGemm *ad_copy, MetaHeader *hd_copy)
+// Extension steps and the first segments of one GEMM row tile.  in: row0(s), row1(s), adapter(s), rank(s) and hb_off(s) of a
+// segment, ext_b(k) and ap_off(k) of an adapter.
+template <class In> PLORA_HD GemmTile derive_tile(const In &in, int n_seg, int64_t T, int64_t tile)
+{
+    const int64_t m0 = tile * kGemmTileRows;
+    const int64_t m1 = m0 + kGemmTileRows < T ? m0 + kGemmTileRows : T;
+    int lo = 0, hi = n_seg;                     // first segment with row1 > m0
+    while (lo < hi) {
+        const int mid = (lo + hi) / 2;
+        if (in.row1(mid) > m0) hi = mid; else lo = mid + 1;
+    }
+    GemmTile gt;
+    gt.n_ext = 0; gt.n_own = 0; gt.first_seg = n_seg; gt.third_seg = n_seg;
+    for (int i = 0; i < 2; ++i) {
+        gt.s[i].row0 = 0; gt.s[i].row1 = 0; gt.s[i].rp = 0; gt.s[i].r = 0;
+        gt.s[i].hb_off = 0; gt.s[i].B = nullptr; gt.s[i].ap_off = 0;
+    }
+    for (int s = lo; s < n_seg && in.row0(s) < m1; ++s) {
+        const int k = in.adapter(s);
+        if (k < 0 || in.row1(s) <= in.row0(s)) continue;
+        const int r = in.rank(s);
+        if (gt.n_own < 2) {
+            GemmSeg &q = gt.s[gt.n_own];
+            q.row0 = in.row0(s); q.row1 = in.row1(s); q.rp = pad_to(r, kRankPadGemm); q.r = r; q.hb_off = in.hb_off(s);
+            q.B = in.ext_b(k); q.ap_off = in.ap_off(k);
+            if (gt.n_own == 0) gt.first_seg = s;
+        } else if (gt.n_own == 2) {
+            gt.third_seg = s;
+        }
+        gt.n_own += 1;
+        gt.n_ext += pad_to(r, kRankPadGemm) / kRankPadGemm;
+    }
+    return gt;
+}
+
+// The order in which the GEMMs walk their row tiles.  Workgroups that run side by side on one XCD work on a group of
+// kGemmGroupRows consecutive entries of this order and share the columns of W they stream; they only stay in step if
+// their tiles have the same number of contraction steps, so the row tiles are sorted by their extension steps, most
+// first, tiles of equal length in row order (lengths of kSortKeys - 1 steps and more count as one class).
+constexpr int kSortKeys = 9;
+
+PLORA_HD int sort_key(int32_t n_ext) { return n_ext < kSortKeys - 1 ? n_ext : kSortKeys - 1; }
+
+// The host's derivation.  tokens: scratch, two ints per adapter.
+template <class Src> inline void derive_tables(const DescReader<Src> &in, const Tables &t, int32_t *tokens)
 {
     const int n_seg = in.n_seg(), n_ad = in.n_adapters();
-    const int64_t D = in.D();
+    const int64_t D = in.D(), T = in.T();
     const int64_t ap_rows = in.w_out_in() ? in.K() : D;   // rows of the padded operand [rows][rp], see GemmSeg
-    int32_t *tokens = scratch, *n_own = scratch + n_ad, *cursor = scratch + 2 * n_ad;
-    for (int k = 0; k < n_ad; ++k) { tokens[k] = 0; n_own[k] = 0; }
+    int32_t *cursor = tokens + n_ad;
+    for (int k = 0; k < n_ad; ++k) { tokens[k] = 0; cursor[k] = 0; t.ad[k].n_own = 0; }
     int64_t h = 0, hb = 0, zt = 0;
-    int32_t blk = 0, max_r16 = 0, row0 = 0;
+    int32_t blk = 0, max_r16 = 0;
     for (int s = 0; s < n_seg; ++s) {
         SegInfo g;
-        g.row0 = row0; g.row1 = in.seg_row1(s); row0 = g.row1;
+        g.row0 = in.seg_row0(s); g.row1 = in.seg_row1(s);
         g.adapter = in.seg_adapter(s);
         const int32_t len = g.row1 - g.row0;
-        const int32_t r = g.adapter >= 0 ? in.ad_rank(g.adapter) : 0;
-        g.r = r;
-        g.rp = pad_to(r, kRankPadGemm);
-        g.r16 = pad_to(r, kRankPadMfma);
+        g.r = g.adapter >= 0 ? in.ad_rank(g.adapter) : 0;
+        g.rp = pad_to(g.r, kRankPadGemm);
+        g.r16 = pad_to(g.r, kRankPadMfma);
         g.lp = pad_to(len, kTokPad);
         g.blk0 = blk;
         g.h_off = h; g.hb_off = hb; g.zt_off = zt;
         if (g.adapter >= 0) {
-            blk += (len + kSkinnyRows - 1) / kSkinnyRows;
+            const int32_t nb = (len + kSkinnyRows - 1) / kSkinnyRows;
+            for (int32_t b = 0; b < nb; ++b) t.blk_seg[blk + b] = s;
+            blk += nb;
             if (len > 0 && g.r16 > max_r16) max_r16 = g.r16;
             h += (int64_t)len * g.r;
             hb += (int64_t)len * g.rp;
             zt += (int64_t)g.r16 * g.lp;
             tokens[g.adapter] += len;
-            n_own[g.adapter] += len > 0;
+            t.ad[g.adapter].n_own += len > 0;
         }
         t.seg[s] = g;
-        if (seg_copy) seg_copy[s] = g;
     }
     int64_t at = 0, ap = 0;
     int32_t r16_off = 0, list0 = 0;
@@ -289,156 +328,50 @@ template <class Src> PLORA_HD void derive_phase1(const DescReader<Src> &in, cons
         a.r16 = pad_to(a.r, kRankPadMfma);
         a.scale = in.ad_scale(k);
         a.at_off = at; at += (int64_t)a.r16 * D;
-        // (integer arithmetic: the host derives the tables with a null base, and an offset from a null pointer is undefined)
-        a.ext_b = in.w_out_in() ? reinterpret_cast<const void *>((uintptr_t)in.at_base() + 2 * (uintptr_t)a.at_off) : a.B;
+        a.ext_b = in.ext_b(k, a.at_off);
         a.ap_off = ap; ap += (int64_t)a.rp * ap_rows;
         a.r16_off = r16_off; r16_off += a.r16;
-        a.by_tokens = 0;                    // filled in by phase 2
-        a.seg_list0 = list0; a.n_own = n_own[k]; a.tokens = tokens[k]; a.reserved = 0;
+        a.by_tokens = 0;                    // filled in below
+        a.seg_list0 = list0; a.n_own = t.ad[k].n_own; a.tokens = tokens[k]; a.reserved = 0;
         cursor[k] = list0;
-        list0 += n_own[k];
+        list0 += a.n_own;
         t.ad[k] = a;
-        if (ad_copy) { ad_copy[k].ext_b = a.ext_b; ad_copy[k].ap_off = a.ap_off; }
     }
     // per-adapter lists of non-empty segments, in segment order
-    int32_t prev = 0;
-    for (int s = 0; s < n_seg; ++s) {
-        const int32_t row1 = in.seg_row1(s);
-        const int a = in.seg_adapter(s);
-        if (a >= 0 && row1 > prev) t.seg_list[cursor[a]++] = s;
-        prev = row1;
+    for (int s = 0; s < n_seg; ++s)
+        if (seg_has_lowrank(t.seg[s])) t.seg_list[cursor[t.seg[s].adapter]++] = s;
+    // place of each adapter in the order by token count, longest first (the weight-gradient kernels hand out
+    // adapters in that order, so the last workgroups are short)
+    for (int k = 0; k < n_ad; ++k) {
+        int rank = 0;
+        for (int j = 0; j < n_ad; ++j) rank += tokens[j] > tokens[k] || (tokens[j] == tokens[k] && j < k);
+        t.ad[rank].by_tokens = k;
     }
     MetaHeader hd;
-    hd.T = in.T(); hd.D = D; hd.K = in.K();
+    hd.T = T; hd.D = D; hd.K = in.K();
     hd.n_seg = n_seg; hd.n_adapters = n_ad; hd.n_blocks = blk; hd.max_r16 = max_r16;
     hd.w_out_in = in.w_out_in(); hd.reserved = 0; hd.at_base = in.at_base();
     *t.hdr = hd;
-    if (hd_copy) *hd_copy = hd;
-}
-
-PLORA_HD bool seg_has_lowrank(const SegInfo &g) { return g.adapter >= 0 && g.row1 > g.row0; }
-
-// The segment that holds token block `blk` (only segments with an adapter and rows own blocks).
-PLORA_HD int seg_of_block(const SegInfo *seg, int n_seg, int blk)
-{
-    int lo = 0, hi = n_seg - 1;                 // last segment with blk0 <= blk
-    while (lo < hi) {
-        const int mid = (lo + hi + 1) / 2;
-        if (seg[mid].blk0 <= blk) lo = mid; else hi = mid - 1;
-    }
-    // blk < n_blocks lies in some owner o (o.blk0 <= blk < o.blk0 + blocks of o); every later segment starts at or
-    // behind the end of o's blocks, so the last segment with blk0 <= blk is o itself
-    return lo;
-}
-
-// Extension steps and the first segments of one GEMM row tile.  seg / ad: where to read the segment records and the
-// adapters' GEMM operands from (the tables themselves, or the copies phase 1 made).
-template <class AdSrc>
-PLORA_HD void derive_tile(const Tables &t, const SegInfo *seg, const AdSrc *ad, int n_seg, int64_t T, int64_t tile)
-{
-    const int64_t m0 = tile * kGemmTileRows;
-    const int64_t m1 = m0 + kGemmTileRows < T ? m0 + kGemmTileRows : T;
-    int lo = 0, hi = n_seg;                     // first segment with row1 > m0
-    while (lo < hi) {
-        const int mid = (lo + hi) / 2;
-        if (seg[mid].row1 > m0) hi = mid; else lo = mid + 1;
-    }
-    GemmTile gt;
-    gt.n_ext = 0; gt.n_own = 0; gt.first_seg = n_seg; gt.third_seg = n_seg;
-    for (int i = 0; i < 2; ++i) {
-        gt.s[i].row0 = 0; gt.s[i].row1 = 0; gt.s[i].rp = 0; gt.s[i].r = 0;
-        gt.s[i].hb_off = 0; gt.s[i].B = nullptr; gt.s[i].ap_off = 0;
-    }
-    for (int s = lo; s < n_seg && seg[s].row0 < m1; ++s) {
-        const SegInfo g = seg[s];
-        if (!seg_has_lowrank(g)) continue;
-        if (gt.n_own < 2) {
-            GemmSeg &q = gt.s[gt.n_own];
-            q.row0 = g.row0; q.row1 = g.row1; q.rp = g.rp; q.r = g.r; q.hb_off = g.hb_off;
-            q.B = ad[g.adapter].ext_b; q.ap_off = ad[g.adapter].ap_off;
-            if (gt.n_own == 0) gt.first_seg = s;
-        } else if (gt.n_own == 2) {
-            gt.third_seg = s;
-        }
-        gt.n_own += 1;
-        gt.n_ext += g.rp / kRankPadGemm;
-    }
-    t.tile[tile] = gt;
-}
-
-// hd: the header as phase 1 wrote it (passed by value so that nobody has to read it back); tokens: per-adapter token
-// counts (phase 1's scratch).
-template <class AdSrc>
-PLORA_HD void derive_phase2(const Tables &t, const MetaHeader &hd, const SegInfo *seg, const AdSrc *ad, const int32_t *tokens,
-                            int tid, int nthreads)
-{
-    const int n_seg = hd.n_seg, n_ad = hd.n_adapters, n_blocks = hd.n_blocks;
-    const int64_t T = hd.T;
+    struct FromTables {
+        const Tables &t;
+        int row0(int s) const { return t.seg[s].row0; }
+        int row1(int s) const { return t.seg[s].row1; }
+        int adapter(int s) const { return t.seg[s].adapter; }
+        int rank(int s) const { return t.seg[s].r; }
+        int64_t hb_off(int s) const { return t.seg[s].hb_off; }
+        const void *ext_b(int k) const { return t.ad[k].ext_b; }
+        int64_t ap_off(int k) const { return t.ad[k].ap_off; }
+    };
+    const FromTables from{t};
     const int64_t n_tiles = (T + kGemmTileRows - 1) / kGemmTileRows;
-    for (int b = tid; b < n_blocks; b += nthreads) t.blk_seg[b] = seg_of_block(seg, n_seg, b);
-    for (int64_t tile = tid; tile < n_tiles; tile += nthreads) derive_tile(t, seg, ad, n_seg, T, tile);
-    // place of each adapter in the order by token count, longest first (the weight-gradient kernels hand out
-    // adapters in that order, so the last workgroups are short)
-    for (int k = tid; k < n_ad; k += nthreads) {
-        const int32_t mine = tokens[k];
-        int rank = 0;
-        for (int j = 0; j < n_ad; ++j) {
-            const int32_t theirs = tokens[j];
-            if (theirs > mine || (theirs == mine && j < k)) ++rank;
-        }
-        t.ad[rank].by_tokens = k;
+    int32_t start[kSortKeys + 1];
+    for (int k = 0; k <= kSortKeys; ++k) start[k] = 0;
+    for (int64_t i = 0; i < n_tiles; ++i) {
+        t.tile[i] = derive_tile(from, n_seg, T, i);
+        start[sort_key(t.tile[i].n_ext)] += 1;
     }
-}
-
-// Phase 3 (after phase 2): the order in which the GEMMs walk their row tiles.  Workgroups that run side by side
-// on one XCD work on a group of kGemmGroupRows consecutive entries of this order and share the columns of W they
-// stream; they only stay in step if their tiles have the same number of contraction steps, so the row tiles are
-// sorted by their extension steps, most first, tiles of equal length in row order (lengths of kSortKeys - 1 steps
-// and more count as one class).  A counting sort in three steps with a barrier between them: every thread counts
-// the classes in its own contiguous chunk of tiles, one thread per class turns the counts into start positions,
-// every thread places its chunk.  counts: kSortKeys ints per thread (device: LDS; host: one thread).
-constexpr int kSortKeys = 9;
-
-PLORA_HD int sort_key(int32_t n_ext) { return n_ext < kSortKeys - 1 ? n_ext : kSortKeys - 1; }
-
-PLORA_HD void tile_chunk(int64_t n_tiles, int tid, int nthreads, int64_t &lo, int64_t &hi)
-{
-    const int64_t per = (n_tiles + nthreads - 1) / nthreads;
-    lo = per * tid < n_tiles ? per * tid : n_tiles;
-    hi = lo + per < n_tiles ? lo + per : n_tiles;
-}
-
-PLORA_HD void derive_phase3_count(const Tables &t, int64_t n_tiles, int tid, int nthreads, int32_t *counts)
-{
-    int64_t lo, hi;
-    tile_chunk(n_tiles, tid, nthreads, lo, hi);
-    int32_t c[kSortKeys];
-    for (int k = 0; k < kSortKeys; ++k) c[k] = 0;
-    for (int64_t i = lo; i < hi; ++i) c[sort_key(t.tile[i].n_ext)] += 1;
-    for (int k = 0; k < kSortKeys; ++k) counts[tid * kSortKeys + k] = c[k];
-}
-
-// counts[thread][class] -> starts[thread][class]: position of the first tile of that class in that thread's chunk
-PLORA_HD void derive_phase3_scan(int tid, int nthreads, const int32_t *counts, int32_t *starts)
-{
-    for (int k = tid; k < kSortKeys; k += nthreads) {       // one thread per class
-        int32_t base = 0;
-        for (int kk = kSortKeys - 1; kk > k; --kk)          // all tiles of the longer classes come first
-            for (int th = 0; th < nthreads; ++th) base += counts[th * kSortKeys + kk];
-        for (int th = 0; th < nthreads; ++th) {
-            starts[th * kSortKeys + k] = base;
-            base += counts[th * kSortKeys + k];
-        }
-    }
-}
-
-PLORA_HD void derive_phase3_place(const Tables &t, int64_t n_tiles, int tid, int nthreads, const int32_t *starts)
-{
-    int64_t lo, hi;
-    tile_chunk(n_tiles, tid, nthreads, lo, hi);
-    int32_t pos[kSortKeys];
-    for (int k = 0; k < kSortKeys; ++k) pos[k] = starts[tid * kSortKeys + k];
-    for (int64_t i = lo; i < hi; ++i) t.tile_order[pos[sort_key(t.tile[i].n_ext)]++] = (int32_t)i;
+    for (int k = kSortKeys - 1, base = 0; k >= 0; --k) { const int n = start[k]; start[k] = base; base += n; }
+    for (int64_t i = 0; i < n_tiles; ++i) t.tile_order[start[sort_key(t.tile[i].n_ext)]++] = (int32_t)i;
 }
 
 // Byte offsets of the workspace regions, each 256-byte aligned.
@@ -462,7 +395,7 @@ constexpr int kLdsSlots = 48;
 // columns); transposed bf16 copy of a saved activation, zt[j][t] = bf16(h[t][j]) (bf16 backward).
 // want_bp (instead of want_ap, W stored [d_out][d_in]): B_k^T [d_out][rp] with zero columns beyond r into `ap`.
 hipError_t launch_prep(const uint32_t *desc_host, int n_words, const MetaHeader &h, char *meta_dev, uint32_t *desc_stage,
-                       void *zero_dev, void *at, void *ap, bool want_at, bool want_ap, bool want_bp, const float *hf,
+                       void *zero_dev, void *at, void *ap, bool want_at, bool want_ap, bool want_bp, int max_rank, const float *hf,
                        void *zt, hipStream_t st);
 
 // bf16 path -------------------------------------------------------------------------------------

@@ -64,12 +64,52 @@ static hipError_t upload_words(uint32_t *dst_dev, const uint32_t *src_host, int 
     return hipSuccess;
 }
 
+// ---- what the workgroups of the preparation kernel read of the description -------------------------
+// Offsets are prefix sums over adapters or segments.  Every lane of a wave takes one entry and the wave sums or scans them
+// with shuffles: one trip to memory instead of one per entry (a loop over 32 adapters and 32 segments on one thread was
+// 25 us of every call).
+__device__ inline int wave_sum(int v)
+{
+#pragma unroll
+    for (int d = 32; d; d >>= 1) v += __shfl_xor(v, d);
+    return v;
+}
+
+__device__ inline int wave_scan(int v, int lane)         // inclusive
+{
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+        const int u = __shfl_up(v, d);
+        if (lane >= d) v += u;
+    }
+    return v;
+}
+
+__device__ inline int64_t wave_scan(int64_t v, int lane)
+{
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+        const int64_t u = __shfl_up(v, d);
+        if (lane >= d) v += u;
+    }
+    return v;
+}
+
+// Sum over the adapters before k of their ranks, each padded to a multiple of `pad`.
+template <class Src> __device__ inline int64_t rank_rows_before(const DescReader<Src> &in, int k, int pad)
+{
+    const int lane = threadIdx.x & 63;
+    int v = 0;
+    for (int j = lane; j < k; j += 64) v += pad_to(in.ad_rank(j), pad);
+    return wave_sum(v);
+}
+
 // ---- packing of A_k ------------------------------------------------------------------------------
 // at: A_k^T as [r16][D] (rows j >= r are zero) - the "row = output column, contraction contiguous"
 //     operand of the shrink kernel.
 // ap: A_k as [D][rp] with columns j >= r zero - the low-rank K-extension operand of the dX GEMM.
 // One block handles 64 rows i of one adapter; the tile goes through LDS so that both the reads of
-// A_k (contiguous in j) and the writes of A_k^T (contiguous in i) are coalesced.
+// A_k (contiguous in j) and the writes of A_k^T (contiguous in i) are coalesced, 16 bytes per thread.
 struct PackJob {
     const uint16_t *A;
     int r, rp, r16;
@@ -83,18 +123,25 @@ __device__ inline void pack_block(const PackJob &a, int64_t D, int bx, uint16_t 
     // (16 bytes per thread and step), then write both layouts from there.
     const int64_t i0 = (int64_t)bx * 64;
     const int r = a.r;
-    const int rows = (int)((D - i0 < 64) ? D - i0 : 64);
+    const int rows = (int)((D - i0 < 64) ? D - i0 : 64);                 // a multiple of 8
     const uint4 *src = reinterpret_cast<const uint4 *>(a.A + i0 * r);
-    const int n_vec = rows * r / 8;                    // r * 2 bytes * rows is a multiple of 16 when rows == 64
+    const int n_vec = rows * r / 8;                                      // rows * r * 2 bytes is a multiple of 16
     for (int v = threadIdx.x; v < n_vec; v += 256) reinterpret_cast<uint4 *>(tile)[v] = src[v];
-    for (int e = n_vec * 8 + threadIdx.x; e < rows * r; e += 256) tile[e] = a.A[i0 * r + e];
     __syncthreads();
     if (want_at) {
-        // A_k^T rows j: 64 consecutive elements each; a wave writes one row segment of 128 bytes
-        uint16_t *dst = at + a.at_off;
-        const int ii = threadIdx.x & 63;
-        for (int j = threadIdx.x >> 6; j < a.r16; j += 4)
-            if (ii < rows) dst[(int64_t)j * D + i0 + ii] = (j < r) ? tile[ii * r + j] : (uint16_t)0;
+        // A_k^T rows j: 64 consecutive elements each, 8 per thread
+        uint16_t *dst = at + a.at_off + i0;
+        const int ii0 = (threadIdx.x & 7) * 8;
+        if (ii0 < rows)
+            for (int j = threadIdx.x >> 3; j < a.r16; j += 32) {
+                union { uint4 q; uint16_t h[8]; } u;
+                u.q = make_uint4(0u, 0u, 0u, 0u);
+                if (j < r) {
+#pragma unroll
+                    for (int t = 0; t < 8; ++t) u.h[t] = tile[(ii0 + t) * r + j];
+                }
+                *reinterpret_cast<uint4 *>(dst + (int64_t)j * D + ii0) = u.q;
+            }
     }
     if (want_ap) {
         // padded A_k: rows of rp elements, 8 elements (16 bytes) per thread and step
@@ -104,8 +151,12 @@ __device__ inline void pack_block(const PackJob &a, int64_t D, int bx, uint16_t 
         for (int ii = ii0; ii < rows; ii += 256 / lanes_per_row)
             for (int v = l; v < vec_per_row; v += lanes_per_row) {
                 union { uint4 q; uint16_t h[8]; } u;
+                if ((r & 7) == 0) {
+                    u.q = v * 8 < r ? *reinterpret_cast<const uint4 *>(tile + ii * r + v * 8) : make_uint4(0u, 0u, 0u, 0u);
+                } else {
 #pragma unroll
-                for (int t = 0; t < 8; ++t) { const int j = v * 8 + t; u.h[t] = (j < r) ? tile[ii * r + j] : (uint16_t)0; }
+                    for (int t = 0; t < 8; ++t) { const int j = v * 8 + t; u.h[t] = (j < r) ? tile[ii * r + j] : (uint16_t)0; }
+                }
                 reinterpret_cast<uint4 *>(dst + (int64_t)ii * a.rp)[v] = u.q;
             }
     }
@@ -153,167 +204,349 @@ __device__ inline uint16_t f32_to_bf16_rne(float f)
 }
 
 // zt[j][t] = bf16(h[t][j]); rows j >= r and the padding tokens are written as zero.  One workgroup per
-// (token block of kSkinnyRows rows, slice of 16 rows inside it).
+// (token block of kSkinnyRows rows, half of it): 64 tokens, so that every row of zt is written in whole 128-byte pieces.
 struct TransposeJob {
     int len, r, r16, lp, t_block;    // segment length and rank; first token of the block inside the segment
     int64_t h_off, zt_off;
 };
+constexpr int kTrRows = 64;
+typedef float f32x4_a4 __attribute__((ext_vector_type(4), aligned(4)));
+typedef float f32x4_a16 __attribute__((ext_vector_type(4)));
 
 __device__ inline void h_to_zt_slice(const TransposeJob &g, int slice, const float *hf, uint16_t *zt, float *tile)
 {
-    constexpr int FR = 16;
-    const int t0 = g.t_block + slice * FR;          // first token of the slice inside the segment
+    const int t0 = g.t_block + slice * kTrRows;     // first token of the slice inside the segment
     if (t0 >= g.lp) return;
     int nt = g.len - t0;
-    nt = nt < 0 ? 0 : (nt < FR ? nt : FR);
-    // the nt rows of r floats are contiguous: flat copy, then transposed reads (thread -> rank row j, token tt)
+    nt = nt < 0 ? 0 : (nt < kTrRows ? nt : kTrRows);
+    // the nt rows of r floats are contiguous: flat copy, then transposed reads
     const float *src = hf + g.h_off + (int64_t)t0 * g.r;
-    for (int e = threadIdx.x; e < nt * g.r; e += 256) tile[e] = src[e];
+    const int n = nt * g.r;
+    for (int e = threadIdx.x * 4; e + 4 <= n; e += 1024)
+        *reinterpret_cast<f32x4_a16 *>(tile + e) = *reinterpret_cast<const f32x4_a4 *>(src + e);
+    if ((int)threadIdx.x < (n & 3)) tile[(n & ~3) + threadIdx.x] = src[(n & ~3) + threadIdx.x];
     __syncthreads();
-    uint16_t *dst = zt + g.zt_off + t0;
-    const int tt = threadIdx.x & 15;
-    for (int j = threadIdx.x >> 4; j < g.r16; j += 16)
-        dst[(int64_t)j * g.lp + tt] = (j < g.r && tt < nt) ? f32_to_bf16_rne(tile[tt * g.r + j]) : (uint16_t)0;
+    const int tt = (threadIdx.x & 7) * 8;
+    uint16_t *dst = zt + g.zt_off + t0 + tt;
+    for (int j = threadIdx.x >> 3; j < g.r16; j += 32) {
+        union { uint4 q; uint16_t h[8]; } u;
+#pragma unroll
+        for (int t = 0; t < 8; ++t) u.h[t] = (j < g.r && tt + t < nt) ? f32_to_bf16_rne(tile[(tt + t) * g.r + j]) : (uint16_t)0;
+        *reinterpret_cast<uint4 *>(dst + (int64_t)j * g.lp) = u.q;
+    }
+}
+
+// ---- derivation of the metadata tables by one workgroup of 256 threads --------------------------------
+// LDS of that workgroup.  The sizes that depend on the description come behind it: the description's words, then per
+// segment the offset hb_off, then the first token block.
+struct DeriveShared {
+    int64_t at_off[PLORA_MAX_ADAPTERS], ap_off[PLORA_MAX_ADAPTERS];
+    int32_t tokens[PLORA_MAX_ADAPTERS], n_own[PLORA_MAX_ADAPTERS], list0[PLORA_MAX_ADAPTERS], by_tokens[PLORA_MAX_ADAPTERS];
+    int64_t wave_tot[4][4];
+    int32_t totals[kSortKeys], base[kSortKeys], wave_cnt[4][kSortKeys], max_r16;
+};
+static size_t derive_lds_bytes(int n_words, int n_seg)
+{
+    return align_up(sizeof(DeriveShared) + align_up((size_t)n_words * 4, 8) + (size_t)n_seg * 12, 16);
+}
+
+// Exclusive prefix sums of four values per thread over the workgroup; tot receives the sums.
+__device__ inline void block_scan4(int64_t v[4], int64_t tot[4], int64_t (*wave_tot)[4])
+{
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    int64_t inc[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) inc[i] = wave_scan(v[i], lane);
+    if (lane == 63) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) wave_tot[wave][i] = inc[i];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        int64_t before = 0;
+        tot[i] = 0;
+        for (int w = 0; w < 4; ++w) {
+            if (w < wave) before += wave_tot[w][i];
+            tot[i] += wave_tot[w][i];
+        }
+        v[i] = before + inc[i] - v[i];
+    }
+    __syncthreads();
+}
+
+template <class Src> __device__ inline void derive_on_device(const DescReader<Src> &src, char *meta_dst, char *shared_mem)
+{
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    DeriveShared &sh = *reinterpret_cast<DeriveShared *>(shared_mem);
+    uint32_t *words = reinterpret_cast<uint32_t *>(shared_mem + sizeof(DeriveShared));
+    const int n_seg = src.n_seg(), n_ad = src.n_adapters(), n_words = desc_words(n_seg, n_ad);
+    int64_t *seg_hb = reinterpret_cast<int64_t *>(shared_mem + sizeof(DeriveShared) + align_up((size_t)n_words * 4, 8));
+    int32_t *seg_blk0 = reinterpret_cast<int32_t *>(seg_hb + n_seg);
+    for (int i = tid; i < n_words; i += 256) words[i] = src.src.word(i);
+    sh.tokens[tid] = 0; sh.n_own[tid] = 0;
+    if (tid < kSortKeys) sh.totals[tid] = 0;
+    if (tid == 0) sh.max_r16 = 0;
+    __syncthreads();
+    const DescReader<WordsInMemory> in{WordsInMemory{words}};
+    const int64_t T = in.T(), D = in.D(), K = in.K(), ap_rows = in.w_out_in() ? K : D;
+    const TableLayout lay = table_layout(T, n_seg, n_ad, in.n_blocks());
+    const Tables t = tables_at(meta_dst, lay);
+    const int64_t n_tiles = lay.n_tiles;
+    const int n_blocks = in.n_blocks();
+
+    // segments: 256 at a time, running sums carried along
+    int64_t carry[4] = {0, 0, 0, 0};                 // token blocks, h, hb, zt
+    for (int s0 = 0; s0 < n_seg; s0 += 256) {
+        const int s = s0 + tid;
+        SegInfo g;
+        int64_t v[4] = {0, 0, 0, 0}, tot[4];
+        if (s < n_seg) {
+            g.row0 = in.seg_row0(s); g.row1 = in.seg_row1(s); g.adapter = in.seg_adapter(s);
+            const int len = g.row1 - g.row0;
+            g.r = g.adapter >= 0 ? in.ad_rank(g.adapter) : 0;
+            g.rp = pad_to(g.r, kRankPadGemm); g.r16 = pad_to(g.r, kRankPadMfma); g.lp = pad_to(len, kTokPad);
+            if (g.adapter >= 0) {
+                v[0] = (len + kSkinnyRows - 1) / kSkinnyRows;
+                v[1] = (int64_t)len * g.r; v[2] = (int64_t)len * g.rp; v[3] = (int64_t)g.r16 * g.lp;
+                if (len > 0) {
+                    atomicMax(&sh.max_r16, g.r16);
+                    atomicAdd(&sh.tokens[g.adapter], len);
+                    atomicAdd(&sh.n_own[g.adapter], 1);
+                }
+            }
+        }
+        block_scan4(v, tot, sh.wave_tot);
+        if (s < n_seg) {
+            g.blk0 = (int32_t)(carry[0] + v[0]);
+            g.h_off = carry[1] + v[1]; g.hb_off = carry[2] + v[2]; g.zt_off = carry[3] + v[3];
+            seg_hb[s] = g.hb_off; seg_blk0[s] = g.blk0;
+            t.seg[s] = g;
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) carry[i] += tot[i];
+    }
+    // adapters: one per thread.  (The scan's barriers also publish the counts and the segments' LDS records.)
+    {
+        const int k = tid;
+        AdapterInfo a;
+        int64_t v[4] = {0, 0, 0, 0}, tot[4];
+        __syncthreads();
+        if (k < n_ad) {
+            a.A = in.ad_ptr(k, 0); a.B = in.ad_ptr(k, 1);
+            a.dA = static_cast<float *>(const_cast<void *>(in.ad_ptr(k, 2)));
+            a.dB = static_cast<float *>(const_cast<void *>(in.ad_ptr(k, 3)));
+            a.r = in.ad_rank(k); a.rp = pad_to(a.r, kRankPadGemm); a.r16 = pad_to(a.r, kRankPadMfma);
+            a.scale = in.ad_scale(k);
+            a.n_own = sh.n_own[k]; a.tokens = sh.tokens[k]; a.reserved = 0;
+            v[0] = (int64_t)a.r16 * D; v[1] = (int64_t)a.rp * ap_rows; v[2] = a.r16; v[3] = a.n_own;
+        }
+        block_scan4(v, tot, sh.wave_tot);
+        if (k < n_ad) {
+            a.at_off = v[0]; a.ap_off = v[1]; a.r16_off = (int32_t)v[2]; a.seg_list0 = (int32_t)v[3];
+            a.ext_b = in.ext_b(k, a.at_off);
+            sh.at_off[k] = a.at_off; sh.ap_off[k] = a.ap_off; sh.list0[k] = a.seg_list0;
+            // place of this adapter in the order by token count, longest first, ties by index
+            int rank = 0;
+            for (int j = 0; j < n_ad; ++j) rank += sh.tokens[j] > a.tokens || (sh.tokens[j] == a.tokens && j < k);
+            sh.by_tokens[rank] = k;
+        }
+        __syncthreads();
+        if (k < n_ad) {
+            a.by_tokens = sh.by_tokens[k];
+            t.ad[k] = a;
+        }
+    }
+    if (tid == 0) {
+        MetaHeader hd;
+        hd.T = T; hd.D = D; hd.K = K;
+        hd.n_seg = n_seg; hd.n_adapters = n_ad; hd.n_blocks = n_blocks; hd.max_r16 = sh.max_r16;
+        hd.w_out_in = in.w_out_in(); hd.reserved = 0; hd.at_base = in.at_base();
+        *t.hdr = hd;
+    }
+    // per-adapter lists of non-empty segments: a segment's place is the number of earlier ones of its adapter
+    for (int s = tid; s < n_seg; s += 256) {
+        const int k = in.seg_adapter(s);
+        if (k < 0 || in.seg_row1(s) <= in.seg_row0(s)) continue;
+        int place = sh.list0[k];
+        for (int q = 0; q < s; ++q) place += in.seg_adapter(q) == k && in.seg_row1(q) > in.seg_row0(q);
+        t.seg_list[place] = s;
+    }
+    for (int b = tid; b < n_blocks; b += 256) {      // the last segment with blk0 <= b owns block b
+        int lo = 0, hi = n_seg - 1;
+        while (lo < hi) {
+            const int mid = (lo + hi + 1) / 2;
+            if (seg_blk0[mid] <= b) lo = mid; else hi = mid - 1;
+        }
+        t.blk_seg[b] = lo;
+    }
+    // row tiles of the GEMMs, and the order they are walked in
+    struct FromLds {
+        const DescReader<WordsInMemory> &in;
+        const DeriveShared &sh;
+        const int64_t *hb;
+        __device__ int row0(int s) const { return in.seg_row0(s); }
+        __device__ int row1(int s) const { return in.seg_row1(s); }
+        __device__ int adapter(int s) const { return in.seg_adapter(s); }
+        __device__ int rank(int s) const { return in.ad_rank(in.seg_adapter(s)); }
+        __device__ int64_t hb_off(int s) const { return hb[s]; }
+        __device__ const void *ext_b(int k) const { return in.ext_b(k, sh.at_off[k]); }
+        __device__ int64_t ap_off(int k) const { return sh.ap_off[k]; }
+    };
+    const FromLds from{in, sh, seg_hb};
+    const bool sorted = !in.order_is_identity();
+    int key = -1;                                    // class of this thread's latest tile
+    for (int64_t i = tid; i < n_tiles; i += 256) {
+        const GemmTile gt = derive_tile(from, n_seg, T, i);
+        t.tile[i] = gt;
+        key = sort_key(gt.n_ext);
+        if (sorted) atomicAdd(&sh.totals[key], 1);
+        else t.tile_order[i] = (int32_t)i;
+    }
+    if (!sorted) return;
+    // counting sort, 256 tiles at a time: the place of a tile is the start of its class, plus the tiles of that class in
+    // the earlier rounds, the earlier waves and the earlier lanes
+    __syncthreads();
+    if (tid < kSortKeys) {
+        int b = 0;
+        for (int k = kSortKeys - 1; k > tid; --k) b += sh.totals[k];
+        sh.base[tid] = b;
+    }
+    const bool one_round = n_tiles <= 256;
+    for (int64_t i0 = 0; i0 < n_tiles; i0 += 256) {
+        const int64_t i = i0 + tid;
+        if (!one_round) key = i < n_tiles ? sort_key(t.tile[i].n_ext) : -1;     // written by this thread above
+        int before = 0;
+#pragma unroll
+        for (int k = 0; k < kSortKeys; ++k) {
+            const uint64_t m = __ballot(key == k);
+            if (key == k) before = __popcll(m & ((1ull << lane) - 1));
+            if (lane == 0) sh.wave_cnt[wave][k] = __popcll(m);
+        }
+        __syncthreads();
+        if (key >= 0) {
+            int place = sh.base[key] + before;
+            for (int w = 0; w < wave; ++w) place += sh.wave_cnt[w][key];
+            t.tile_order[place] = (int32_t)i;
+        }
+        __syncthreads();
+        if (tid < kSortKeys)
+            for (int w = 0; w < 4; ++w) sh.base[tid] += sh.wave_cnt[w][tid];
+        __syncthreads();
+    }
 }
 
 // ---- the preparation kernel ----------------------------------------------------------------------
 // Workgroup 0 derives the metadata tables into the workspace and clears the zero page; the next
 // n_pack workgroups pack the A_k, the next n_pack_b the B_k (only when W is stored [d_out][d_in]); the
-// last ones make the transposed bf16 copy of a saved activation.  The packing and copy workgroups work out the few offsets they need from the compact
-// description themselves, so they do not wait for workgroup 0.
+// last ones make the transposed bf16 copy of a saved activation.  The packing and copy workgroups work out the few
+// offsets they need from the compact description themselves, so they do not wait for workgroup 0.
+// Bound by latency: a launch, one trip to the description, a handful of workgroup-wide scans.  Per call, before (tables by
+// one thread, a serial counting sort, 2-byte stores in the packing) and now: 32 adapters in 32 ragged segments 60 and 57 us
+// -> 22 and 28 us (forward, backward); 16 equal segments 18 -> 10 us; 8 segments in 7 row tiles, fp32, 23 -> 9 us.
 struct WordsInArg {
     const DescChunk &c;
     __device__ inline uint32_t word(int i) const { return c.w[i]; }
 };
 
-constexpr int kPrepSegCopies = 64 * PLORA_MAX_RANK * 2 / (int)sizeof(SegInfo);   // segment records that fit the pack tile
-
 template <class Src>
 __device__ inline void prep_body(const DescReader<Src> &in, char *meta_dst, uint32_t *zero_page, uint16_t *at, uint16_t *ap,
                                  int want_at, int want_ap, int pack_bx, int n_pack, int pack_bx_b, int n_pack_b,
-                                 const float *hf, uint16_t *zt, void *shared_mem, int32_t *sort_counts, int32_t *sort_starts)
+                                 const float *hf, uint16_t *zt, char *shared_mem)
 {
     int b = blockIdx.x;
     if (b == 0) {
         zero_page[threadIdx.x] = 0u;     // kZeroBytes = 256 * 4
-        const TableLayout lay = table_layout(in.T(), in.n_seg(), in.n_adapters(), in.n_blocks());
-        const Tables t = tables_at(meta_dst, lay);
-        // LDS of this workgroup (it packs nothing): the pack tile holds a copy of the segment records when they fit,
-        // the second sort array the adapters' GEMM operands and the header; the first sort array is phase 1's scratch
-        SegInfo *seg_copy = in.n_seg() <= kPrepSegCopies ? static_cast<SegInfo *>(shared_mem) : nullptr;
-        AdapterGemm *ad_copy = reinterpret_cast<AdapterGemm *>(sort_starts);
-        MetaHeader *hd_copy = reinterpret_cast<MetaHeader *>(ad_copy + PLORA_MAX_ADAPTERS);
-        if (threadIdx.x == 0) derive_phase1(in, t, sort_counts, seg_copy, ad_copy, hd_copy);
-        __threadfence_block();
-        __syncthreads();
-        const MetaHeader hd = *hd_copy;
-        const int64_t n_tiles = (hd.T + kGemmTileRows - 1) / kGemmTileRows;
-        derive_phase2(t, hd, seg_copy ? seg_copy : t.seg, ad_copy, sort_counts /* tokens */, (int)threadIdx.x, 256);
-        if (in.order_is_identity()) {           // all row tiles equally long, or already in order: nothing to sort
-            for (int64_t i = threadIdx.x; i < n_tiles; i += 256) t.tile_order[i] = (int32_t)i;
-            return;
-        }
-        __threadfence_block();
-        __syncthreads();                        // also: everybody is done with the token counts and the copies
-        derive_phase3_count(t, n_tiles, (int)threadIdx.x, 256, sort_counts);
-        __syncthreads();
-        derive_phase3_scan((int)threadIdx.x, 256, sort_counts, sort_starts);
-        __syncthreads();
-        derive_phase3_place(t, n_tiles, (int)threadIdx.x, 256, sort_starts);
+        derive_on_device(in, meta_dst, shared_mem);
         return;
     }
     b -= 1;
     if (b < n_pack) {
         const int k = b / pack_bx;
-        PackJob a;
-        int64_t at_rows = 0, ap_rows = 0;
-        for (int j = 0; j < k; ++j) {
-            const int rj = in.ad_rank(j);
-            at_rows += pad_to(rj, kRankPadMfma);
-            ap_rows += pad_to(rj, kRankPadGemm);
-        }
         const int64_t D = in.D();
+        PackJob a;
         a.A = static_cast<const uint16_t *>(in.ad_ptr(k, 0));
         a.r = in.ad_rank(k);
         a.rp = pad_to(a.r, kRankPadGemm);
         a.r16 = pad_to(a.r, kRankPadMfma);
-        a.at_off = at_rows * D;
-        a.ap_off = ap_rows * D;
-        pack_block(a, D, b % pack_bx, at, ap, want_at, want_ap, static_cast<uint16_t *>(shared_mem));
+        a.at_off = rank_rows_before(in, k, kRankPadMfma) * D;
+        a.ap_off = rank_rows_before(in, k, kRankPadGemm) * D;
+        pack_block(a, D, b % pack_bx, at, ap, want_at, want_ap, reinterpret_cast<uint16_t *>(shared_mem));
         return;
     }
     b -= n_pack;
     if (b < n_pack_b) {
         const int k = b / pack_bx_b;
-        int64_t rows = 0;
-        for (int j = 0; j < k; ++j) rows += pad_to(in.ad_rank(j), kRankPadGemm);
         const int64_t K = in.K();
         PackBJob a;
         a.B = static_cast<const uint16_t *>(in.ad_ptr(k, 1));
         a.r = in.ad_rank(k);
         a.rp = pad_to(a.r, kRankPadGemm);
-        a.bp_off = rows * K;
-        pack_bt_block(a, K, b % pack_bx_b, ap, static_cast<uint16_t *>(shared_mem));
+        a.bp_off = rank_rows_before(in, k, kRankPadGemm) * K;
+        pack_bt_block(a, K, b % pack_bx_b, ap, reinterpret_cast<uint16_t *>(shared_mem));
         return;
     }
     b -= n_pack_b;
-    const int blk = b / (kSkinnyRows / 16), slice = b % (kSkinnyRows / 16);
-    // walk the segments up to the one that owns token block blk, keeping the running offsets
-    const int n_seg = in.n_seg();
+    constexpr int kSlices = kSkinnyRows / kTrRows;
+    const int blk = b / kSlices, slice = b % kSlices;
+    // the segment that owns token block blk, 64 segments at a time, with the running offsets
+    const int n_seg = in.n_seg(), lane = threadIdx.x & 63;
     int64_t h = 0, zto = 0;
-    int blk0 = 0, row0 = 0;
+    int blk0 = 0;
     TransposeJob g;
     g.len = 0; g.r = 0; g.r16 = 0; g.lp = 0; g.t_block = 0; g.h_off = 0; g.zt_off = 0;
-    for (int s = 0; s < n_seg; ++s) {
-        const int row1 = in.seg_row1(s), a = in.seg_adapter(s);
-        const int len = row1 - row0;
-        row0 = row1;
-        if (a < 0) continue;
-        const int r = in.ad_rank(a), r16 = pad_to(r, kRankPadMfma), lp = pad_to(len, kTokPad);
-        const int nb = (len + kSkinnyRows - 1) / kSkinnyRows;
-        if (blk < blk0 + nb) {
-            g.len = len; g.r = r; g.r16 = r16; g.lp = lp; g.t_block = (blk - blk0) * kSkinnyRows;
-            g.h_off = h; g.zt_off = zto;
+    for (int s0 = 0; s0 < n_seg; s0 += 64) {
+        const int s = s0 + lane;
+        int len = 0, r = 0, nb = 0;
+        if (s < n_seg) {
+            const int a = in.seg_adapter(s);
+            if (a >= 0) {
+                len = in.seg_row1(s) - in.seg_row0(s);
+                r = in.ad_rank(a);
+                nb = (len + kSkinnyRows - 1) / kSkinnyRows;
+            }
+        }
+        const int r16 = pad_to(r, kRankPadMfma), lp = pad_to(len, kTokPad);
+        const int64_t he = (int64_t)len * r, ze = (int64_t)r16 * lp;
+        const int nb_inc = wave_scan(nb, lane);
+        const int64_t h_inc = wave_scan(he, lane), z_inc = wave_scan(ze, lane);
+        const uint64_t own = __ballot(blk < blk0 + nb_inc && blk >= blk0 + nb_inc - nb);
+        if (own) {
+            const int l = __builtin_ctzll(own);
+            g.len = __shfl(len, l); g.r = __shfl(r, l); g.r16 = __shfl(r16, l); g.lp = __shfl(lp, l);
+            g.t_block = (blk - (blk0 + __shfl(nb_inc, l) - __shfl(nb, l))) * kSkinnyRows;
+            g.h_off = h + __shfl(h_inc - he, l);
+            g.zt_off = zto + __shfl(z_inc - ze, l);
             break;
         }
-        blk0 += nb;
-        h += (int64_t)len * r;
-        zto += (int64_t)r16 * lp;
+        blk0 += __shfl(nb_inc, 63); h += __shfl(h_inc, 63); zto += __shfl(z_inc, 63);
     }
-    h_to_zt_slice(g, slice, hf, zt, static_cast<float *>(shared_mem));
+    h_to_zt_slice(g, slice, hf, zt, reinterpret_cast<float *>(shared_mem));
 }
-
-union PrepShared {
-    uint16_t pack[64 * PLORA_MAX_RANK];
-    float tr[16 * PLORA_MAX_RANK];
-};
 
 __global__ void __launch_bounds__(256) k_prep_arg(DescChunk c, char *meta_dst, uint32_t *zero_page, uint16_t *at, uint16_t *ap,
                                                  int want_at, int want_ap, int pack_bx, int n_pack, int pack_bx_b,
                                                  int n_pack_b, const float *hf, uint16_t *zt)
 {
-    __shared__ __attribute__((aligned(16))) PrepShared sh;
-    __shared__ int32_t sort_counts[256 * kSortKeys], sort_starts[256 * kSortKeys];
+    extern __shared__ __attribute__((aligned(16))) char prep_lds[];
     const DescReader<WordsInArg> in{WordsInArg{c}};
-    prep_body(in, meta_dst, zero_page, at, ap, want_at, want_ap, pack_bx, n_pack, pack_bx_b, n_pack_b, hf, zt, &sh, sort_counts,
-              sort_starts);
+    prep_body(in, meta_dst, zero_page, at, ap, want_at, want_ap, pack_bx, n_pack, pack_bx_b, n_pack_b, hf, zt, prep_lds);
 }
 
 __global__ void __launch_bounds__(256) k_prep_mem(const uint32_t *desc, char *meta_dst, uint32_t *zero_page, uint16_t *at,
                                                  uint16_t *ap, int want_at, int want_ap, int pack_bx, int n_pack,
                                                  int pack_bx_b, int n_pack_b, const float *hf, uint16_t *zt)
 {
-    __shared__ __attribute__((aligned(16))) PrepShared sh;
-    __shared__ int32_t sort_counts[256 * kSortKeys], sort_starts[256 * kSortKeys];
+    extern __shared__ __attribute__((aligned(16))) char prep_lds[];
     const DescReader<WordsInMemory> in{WordsInMemory{desc}};
-    prep_body(in, meta_dst, zero_page, at, ap, want_at, want_ap, pack_bx, n_pack, pack_bx_b, n_pack_b, hf, zt, &sh, sort_counts,
-              sort_starts);
+    prep_body(in, meta_dst, zero_page, at, ap, want_at, want_ap, pack_bx, n_pack, pack_bx_b, n_pack_b, hf, zt, prep_lds);
 }
 
 hipError_t launch_prep(const uint32_t *desc_host, int n_words, const MetaHeader &h, char *meta_dev, uint32_t *desc_stage,
-                       void *zero_dev, void *at, void *ap, bool want_at, bool want_ap, bool want_bp, const float *hf,
+                       void *zero_dev, void *at, void *ap, bool want_at, bool want_ap, bool want_bp, int max_rank, const float *hf,
                        void *zt, hipStream_t st)
 {
+    static_assert(PLORA_MAX_ADAPTERS == 256, "one adapter per thread of workgroup 0");
     static_assert(kZeroBytes == 1024, "the zero page is written by one 256-thread workgroup");
     if (want_ap && want_bp) return hipErrorInvalidValue;            // both live in `ap`
     const bool pack = h.n_adapters > 0 && (want_at || want_ap);
@@ -321,12 +554,16 @@ hipError_t launch_prep(const uint32_t *desc_host, int n_words, const MetaHeader 
     const int n_pack = pack ? pack_bx * h.n_adapters : 0;
     const int pack_bx_b = (int)((h.K + 63) / 64);
     const int n_pack_b = (want_bp && h.n_adapters > 0) ? pack_bx_b * h.n_adapters : 0;
-    const int n_tr = (hf && zt) ? h.n_blocks * (kSkinnyRows / 16) : 0;
+    const int n_tr = (hf && zt) ? h.n_blocks * (kSkinnyRows / kTrRows) : 0;
+    // LDS: the derivation of workgroup 0, a pack tile of 64 rows, or 64 tokens of a saved activation
+    size_t lds = derive_lds_bytes(n_words, h.n_seg);
+    if ((n_pack || n_pack_b) && lds < (size_t)128 * max_rank) lds = (size_t)128 * max_rank;
+    if (n_tr && lds < (size_t)256 * max_rank) lds = (size_t)256 * max_rank;
     const dim3 grid((unsigned)(1 + n_pack + n_pack_b + n_tr));
     if (n_words <= kChunkWords) {
         DescChunk c;
         std::memcpy(c.w, desc_host, (size_t)n_words * 4);
-        hipLaunchKernelGGL(k_prep_arg, grid, dim3(256), 0, st, c, meta_dev, static_cast<uint32_t *>(zero_dev),
+        hipLaunchKernelGGL(k_prep_arg, grid, dim3(256), lds, st, c, meta_dev, static_cast<uint32_t *>(zero_dev),
                            static_cast<uint16_t *>(at), static_cast<uint16_t *>(ap), want_at ? 1 : 0, want_ap ? 1 : 0,
                            pack_bx > 0 ? pack_bx : 1, n_pack, pack_bx_b > 0 ? pack_bx_b : 1, n_pack_b, hf,
                            static_cast<uint16_t *>(zt));
@@ -334,7 +571,7 @@ hipError_t launch_prep(const uint32_t *desc_host, int n_words, const MetaHeader 
     }
     hipError_t e = upload_words(desc_stage, desc_host, n_words, st);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_prep_mem, grid, dim3(256), 0, st, static_cast<const uint32_t *>(desc_stage), meta_dev,
+    hipLaunchKernelGGL(k_prep_mem, grid, dim3(256), lds, st, static_cast<const uint32_t *>(desc_stage), meta_dev,
                        static_cast<uint32_t *>(zero_dev), static_cast<uint16_t *>(at), static_cast<uint16_t *>(ap),
                        want_at ? 1 : 0, want_ap ? 1 : 0, pack_bx > 0 ? pack_bx : 1, n_pack, pack_bx_b > 0 ? pack_bx_b : 1,
                        n_pack_b, hf, static_cast<uint16_t *>(zt));
