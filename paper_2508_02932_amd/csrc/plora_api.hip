@@ -139,6 +139,7 @@ static void build_meta(const plora_desc *d, HostMeta &m)
     m.gemm_fwd = gemm_plan(d->T, d->d_in, d->d_out);
     m.gemm_dx = gemm_plan(d->T, d->d_out, d->d_in);
     auto split_bytes = [&](const GemmPlan &p, int64_t N) { return p.n_split > 1 ? (size_t)p.n_split * d->T * N * 4 : (size_t)0; };
+    int skinny_cap = 8;
     auto lay_out = [&](WorkspaceLayout &w, size_t ap_elems, bool split_gemm) {
         size_t o = 0;
         w.zero = o; o += kZeroBytes;
@@ -152,7 +153,7 @@ static void build_meta(const plora_desc *d, HostMeta &m)
         w.zt_g = o; o = align_up(o + (bf ? m.zt_elems * 2 : 0), 256);
         w.hf = o;   o = align_up(o + m.h_elems * 4, 256);
         w.gf = o;   o = align_up(o + (bf ? 0 : m.h_elems * 4), 256);
-        w.part = o; o = align_up(o + (bf ? (size_t)kSkinnyMaxSplits * m.hdr.n_blocks * kSkinnyRows * m.hdr.max_r16 * 4 : 0), 256);
+        w.part = o; o = align_up(o + (bf ? (size_t)skinny_cap * m.hdr.n_blocks * kSkinnyRows * m.hdr.max_r16 * 4 : 0), 256);
         const size_t a_bytes = m.split_dA > 1 ? (size_t)m.split_dA * m.r16_total * d->d_in * 4 : 0;
         const size_t b_bytes = m.split_dB > 1 ? (size_t)m.split_dB * m.r16_total * d->d_out * 4 : 0;
         w.wpart = o; o = align_up(o + (bf ? (a_bytes > b_bytes ? a_bytes : b_bytes) : 0), 256);
@@ -162,10 +163,22 @@ static void build_meta(const plora_desc *d, HostMeta &m)
             o = std::max(o, align_up(w.gpart + std::max(split_bytes(m.gemm_fwd, d->d_out), split_bytes(m.gemm_dx, d->d_in)), 256));
         w.total = o + 256;
     };
-    // a description that fits the scratch array of plora_linear_fwd_noalloc without split GEMMs must not outgrow it with them
+    // a description that fits the scratch array of plora_linear_fwd_noalloc with eight skinny splits and no split GEMM must
+    // not outgrow it with more
     lay_out(m.ws, m.ap_elems, false);
     const bool fits_scratch = m.ws.total <= (size_t)PLORA_NOALLOC_SCRATCH_BYTES;
-    for (lay_out(m.ws, m.ap_elems, true); fits_scratch && m.ws.total > (size_t)PLORA_NOALLOC_SCRATCH_BYTES; lay_out(m.ws, m.ap_elems, true)) {
+    auto outgrown = [&]() {
+        lay_out(m.ws, m.ap_elems, true);
+        return fits_scratch && m.ws.total > (size_t)PLORA_NOALLOC_SCRATCH_BYTES;
+    };
+    skinny_cap = std::max(8, std::max(m.split_shrink, m.split_dh));
+    while (outgrown()) {
+        if (skinny_cap > 8) {
+            skinny_cap = 8;
+            m.split_shrink = std::min(m.split_shrink, 8);
+            m.split_dh = std::min(m.split_dh, 8);
+            continue;
+        }
         const bool fwd = split_bytes(m.gemm_fwd, d->d_out) > split_bytes(m.gemm_dx, d->d_in);
         (fwd ? m.gemm_fwd : m.gemm_dx).n_split -= 1;
     }
@@ -347,7 +360,7 @@ static plora_status forward_impl(const plora_desc *desc, const void *x, const vo
     float *part = reinterpret_cast<float *>(ws + L.part);
     if (lora && (steps & kStepShrink)) {
         Bracket b(2, st);
-        PL_TRY(launch_skinny_bf16(mv, m.hdr, 0, x, desc->d_in, at, ws + L.zero, part, h_saved, hb, nullptr, false, st));
+        PL_TRY(launch_skinny_bf16(mv, m.hdr, 0, x, desc->d_in, at, ws + L.zero, part, m.split_shrink, h_saved, hb, nullptr, false, st));
     }
     if (!(steps & kStepMain)) return PLORA_OK;
     if (lora_only) {
@@ -436,11 +449,11 @@ static plora_status backward_impl(const plora_desc *desc, const void *x, const v
     if (lora) {
         if (any_w && !h_saved && (steps & kStepShrink)) {
             Bracket b(2, st);
-            PL_TRY(launch_skinny_bf16(mv, m.hdr, 0, x, desc->d_in, at, ws + L.zero, part, nullptr, nullptr, zt_h, false, st));
+            PL_TRY(launch_skinny_bf16(mv, m.hdr, 0, x, desc->d_in, at, ws + L.zero, part, m.split_shrink, nullptr, nullptr, zt_h, false, st));
         }
         if (steps & kStepDh) {
             Bracket b(3, st);
-            PL_TRY(launch_skinny_bf16(mv, m.hdr, 1, dy, desc->d_out, nullptr, ws + L.zero, part, nullptr, gb, any_w ? zt_g : nullptr, true, st));
+            PL_TRY(launch_skinny_bf16(mv, m.hdr, 1, dy, desc->d_out, nullptr, ws + L.zero, part, m.split_dh, nullptr, gb, any_w ? zt_g : nullptr, true, st));
         }
     }
     if (any_w) {

@@ -16,7 +16,7 @@ constexpr int kRankPadMfma = 16;   // ranks are padded to one MFMA block in the 
 constexpr int kTokPad = 64;        // segment lengths are padded to this in the transposed side buffers
 constexpr int kZeroBytes = 1024;   // zero page at the head of the workspace
 constexpr int kTokMaxSplits = 8;    // the dA / dB kernels split the token walk over at most this many workgroups
-constexpr int kSkinnyMaxSplits = 8; // the skinny kernels split the contraction over at most this many workgroups
+constexpr int kSkinnyMaxSplits = 32; // the skinny kernels split the contraction over at most this many workgroups
 constexpr int kGemmTileRows = 256;  // row tile of the base GEMMs
 constexpr int kGemmGroupRows = 4;   // row tiles that the GEMM's tile order keeps together on one XCD (they share W columns in its L2)
 
@@ -401,11 +401,11 @@ hipError_t launch_prep(const uint32_t *desc_host, int n_words, const MetaHeader 
 // bf16 path -------------------------------------------------------------------------------------
 // Skinny product over token blocks: acc[t][j] = sum_c S[t][c] * Bm_k[j][c]  (c < C).
 //   mode 0 (shrink): S = x (C = d_in), Bm_k = packed A_k^T;  mode 1 (dH): S = dy (C = d_out), Bm_k = B_k.
-//   `part` receives the fp32 partial tiles of the contraction splits; a finishing kernel sums them and
+//   `part` receives the fp32 partial tiles of the n_split contraction splits (skinny_splits); a finishing kernel sums them and
 //   writes (each optional): hf fp32 [len][r] (unscaled in mode 0); hb bf16 [len][rp] = scale_k*acc;
 //   zt bf16 [r16][lp] transposed, = (zt_scaled ? scale_k : 1) * acc.
 hipError_t launch_skinny_bf16(const MetaView &mv, const MetaHeader &h, int mode, const void *S, int64_t C,
-                              const void *at, const void *zero, float *part, float *hf, void *hb, void *zt,
+                              const void *at, const void *zero, float *part, int n_split, float *hf, void *hb, void *zt,
                               bool zt_scaled, hipStream_t st);
 // C[T][N] = S[T][Kd] * Wop + side[T][rp] * ext_k, rounded to bf16.
 //   w_rows_contract : Wop = W [Kd][N] (contraction index is the row index),  ext_k = GemmSeg::B   [r][N]

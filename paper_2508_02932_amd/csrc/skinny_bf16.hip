@@ -224,16 +224,54 @@ __global__ void __launch_bounds__(64 * SK_NW) k_skinny(MetaView mv, int mode, co
             }
 }
 
-// Sums the partial tiles of the splits (fixed order) and writes, each optional:
+// Where the sums go, each optional:
 //   hf fp32 [len][r]   (mode 0: the activation itself; mode 1: scaled by scale_k)
 //   hb bf16 [len][rp]  scale_k * sum, zero beyond r           (K-extension operand of the GEMM)
 //   zt bf16 [r16][lp]  transposed, zero for padding tokens and rows >= r; scaled if zt_scaled
+struct SkinnyOut {
+    float *hf;
+    uint16_t *hb, *zt;
+    int32_t zt_scaled;
+};
+
+// ROWS token rows from t0 on, of which the first nt exist; tile [ROWS][r16] in LDS, 256 threads.
+template <int ROWS>
+__device__ inline void write_outputs(const SegInfo &g, float mult, int mode, const float *tile, int r16, int t0, int nt, const SkinnyOut &out)
+{
+    constexpr int TPR = 256 / ROWS;                   // threads per row
+    const int hi = threadIdx.x / TPR, lo = threadIdx.x % TPR, r = g.r;
+    if (out.hf && hi < nt) {
+        float *dst = out.hf + g.h_off + (int64_t)(t0 + hi) * r;
+        const float m = mode == 0 ? 1.f : mult;
+        for (int j = lo; j < r; j += TPR) dst[j] = m * tile[hi * r16 + j];
+    }
+    if (out.hb && hi < nt) {
+        uint4 *dst = reinterpret_cast<uint4 *>(out.hb + g.hb_off + (int64_t)(t0 + hi) * g.rp);
+        for (int v = lo; v < g.rp / 8; v += TPR) {
+            union { uint4 q; uint16_t h[8]; } u;
+#pragma unroll
+            for (int i = 0; i < 8; ++i) { const int j = v * 8 + i; u.h[i] = j < r ? bf16_rne(mult * tile[hi * r16 + j]) : (uint16_t)0; }
+            dst[v] = u.q;
+        }
+    }
+    if (out.zt) {
+        const float zm = out.zt_scaled ? mult : 1.f;
+        const int tt = (threadIdx.x % (ROWS / 8)) * 8;                       // 8 tokens per thread
+        uint16_t *dst = out.zt + g.zt_off + t0 + tt;
+        for (int j = threadIdx.x / (ROWS / 8); j < r16; j += 256 / (ROWS / 8)) {
+            union { uint4 q; uint16_t h[8]; } u;
+#pragma unroll
+            for (int i = 0; i < 8; ++i) u.h[i] = (j < r && tt + i < nt) ? bf16_rne(zm * tile[(tt + i) * r16 + j]) : (uint16_t)0;
+            *reinterpret_cast<uint4 *>(dst + (int64_t)j * g.lp) = u.q;
+        }
+    }
+}
+
+// Sums the partial tiles of the splits (fixed order) and writes the outputs, 16 rows of a token block per workgroup.
 // GROUP: the partial tiles are those of a fused pass (pitch = the fused rank of the segment's adapter); mv is the view of
 // projection `proj`, whose columns start behind those of the projections before it.
 template <bool GROUP>
-__global__ void __launch_bounds__(256) k_skinny_finish(MetaView mv, int mode, const float *__restrict__ part,
-                                                      int n_split, float *__restrict__ hf, uint16_t *__restrict__ hb,
-                                                      uint16_t *__restrict__ zt, int zt_scaled,
+__global__ void __launch_bounds__(256) k_skinny_finish(MetaView mv, int mode, const float *__restrict__ part, int n_split, SkinnyOut out,
                                                       std::conditional_t<GROUP, GroupView, NoGroup> gv, int proj)
 {
     constexpr int FR = 16;                            // token rows per workgroup (grid.y slices of a block)
@@ -241,89 +279,70 @@ __global__ void __launch_bounds__(256) k_skinny_finish(MetaView mv, int mode, co
     const int blk = blockIdx.x;
     const SegInfo g = mv.seg[mv.blk_seg[blk]];
     const float mult = mv.ad[g.adapter].scale;
-    const int tb = (blk - g.blk0) * kSkinnyRows;      // first token of the block inside the segment
     const int r0 = blockIdx.y * FR;                   // first row of this slice inside the block
-    const int t0 = tb + r0;
-    int nt = g.row1 - g.row0 - t0;                    // valid tokens in this slice
-    nt = nt < 0 ? 0 : (nt < FR ? nt : FR);
+    const int t0 = (blk - g.blk0) * kSkinnyRows + r0; // first token of the slice inside the segment
+    const int nt = g.row1 - g.row0 - t0;              // valid tokens from there on
     if (t0 >= g.lp) return;                           // slice lies past the padded segment: nothing to write
-    const int r = g.r, r16 = g.r16;
+    const int r16 = g.r16;
+    int pitch = r16, col0 = 0;
+    int64_t tile_elems;
     if constexpr (GROUP) {
-        int pitch = 0, col0 = 0;
+        pitch = 0;
         for (int p = 0; p < gv.n_proj; ++p) {
             const int rp16 = gv.mv[p].ad[g.adapter].r16;
             if (p < proj) col0 += rp16;
             pitch += rp16;
         }
-        const int64_t tile_elems = (int64_t)kSkinnyRows * gv.max_r16;
-        const int64_t split_stride = (int64_t)gridDim.x * tile_elems;
-        const float *src = part + (int64_t)blk * tile_elems + (int64_t)r0 * pitch + col0;
-        const int q = r16 / 4;                        // float4 per row of this projection's columns
-        for (int e = threadIdx.x; e < FR * q; e += 256) {
-            const int row = e / q, c4 = e - row * q;
-            const float *s0 = src + row * pitch + c4 * 4;
-            float4 sum = *reinterpret_cast<const float4 *>(s0);
-            for (int sp = 1; sp < n_split; ++sp) {    // fixed order
-                const float4 v = *reinterpret_cast<const float4 *>(s0 + sp * split_stride);
-                sum.x += v.x; sum.y += v.y; sum.z += v.z; sum.w += v.w;
-            }
-            reinterpret_cast<float4 *>(tile)[e] = sum;
-        }
+        tile_elems = (int64_t)kSkinnyRows * gv.max_r16;
     } else {
-        const int64_t tile_elems = (int64_t)kSkinnyRows * mv.hdr->max_r16;
-        const int64_t split_stride = (int64_t)gridDim.x * tile_elems;
-        // the FR rows of r16 partial sums are contiguous in every split: flat walk, four floats per thread
-        const float4 *src = reinterpret_cast<const float4 *>(part + (int64_t)blk * tile_elems + (int64_t)r0 * r16);
-        for (int e = threadIdx.x; e < FR * r16 / 4; e += 256) {
-            float4 sum = src[e];
-            for (int sp = 1; sp < n_split; ++sp) {        // fixed order
-                const float4 v = src[sp * (split_stride / 4) + e];
-                sum.x += v.x; sum.y += v.y; sum.z += v.z; sum.w += v.w;
-            }
-            reinterpret_cast<float4 *>(tile)[e] = sum;
+        tile_elems = (int64_t)kSkinnyRows * mv.hdr->max_r16;
+    }
+    const int64_t split_stride = (int64_t)gridDim.x * tile_elems;
+    const float *src = part + (int64_t)blk * tile_elems + (int64_t)r0 * pitch + col0;
+    const int q = r16 / 4;                            // float4 per row of these columns
+    for (int e = threadIdx.x; e < FR * q; e += 256) {
+        const int row = e / q, c4 = e - row * q;
+        const float *s0 = src + row * pitch + c4 * 4;
+        float4 sum = make_float4(0.f, 0.f, 0.f, 0.f);
+        for (int sp0 = 0; sp0 < n_split; sp0 += 8) {  // eight tiles requested at a time
+            float4 v[8];
+#pragma unroll
+            for (int sp = 0; sp < 8; ++sp)
+                if (sp0 + sp < n_split) v[sp] = *reinterpret_cast<const float4 *>(s0 + (sp0 + sp) * split_stride);
+#pragma unroll
+            for (int sp = 0; sp < 8; ++sp)
+                if (sp0 + sp < n_split) { sum.x += v[sp].x; sum.y += v[sp].y; sum.z += v[sp].z; sum.w += v[sp].w; }
         }
+        reinterpret_cast<float4 *>(tile)[e] = sum;
     }
     __syncthreads();
-    // outputs: thread -> (token tt = tid / 16, columns j = tid % 16 + 16 m), or transposed for zt
-    const int hi = threadIdx.x >> 4, lo = threadIdx.x & 15;
-    if (hf && hi < nt) {
-        float *dst = hf + g.h_off + (int64_t)(t0 + hi) * r;
-        for (int j = lo; j < r; j += 16) {
-            const float v = tile[hi * r16 + j];
-            dst[j] = (mode == 0) ? v : mult * v;
-        }
-    }
-    if (hb && hi < nt) {
-        uint16_t *dst = hb + g.hb_off + (int64_t)(t0 + hi) * g.rp;
-        for (int j = lo; j < g.rp; j += 16) dst[j] = (j < r) ? bf16_rne(mult * tile[hi * r16 + j]) : (uint16_t)0;
-    }
-    if (zt) {
-        uint16_t *dst = zt + g.zt_off + t0;
-        const float zm = zt_scaled ? mult : 1.f;
-        for (int j = hi; j < r16; j += 16)
-            dst[(int64_t)j * g.lp + lo] = (j < r && lo < nt) ? bf16_rne(zm * tile[lo * r16 + j]) : (uint16_t)0;
-    }
+    write_outputs<FR>(g, mult, mode, tile, r16, t0, nt, out);
 }
 
+// Splits of the contraction over workgroups: three workgroups per compute unit, eight stages or more per split.  A short
+// batch cannot fill the chip with eight splits, and one workgroup walks its stages at about 0.9 us each whatever the rest of
+// the chip does, so up to 32 token blocks the contraction is cut further, to four stages: 512 tokens x 14336 columns, 28
+// stages per split 24 us, 7 stages 9 us; 1024 tokens 26 -> 12.6 us.  (A function of the token blocks and the contraction alone: the fused pass of a
+// grouped call then sums in the order of the plain one.)
 int skinny_splits(const MetaHeader &h, int64_t C)
 {
     if (h.n_blocks == 0) return 1;
     const int n_stage_all = (int)((C + SK_BK - 1) / SK_BK);
-    int want = (768 + h.n_blocks - 1) / h.n_blocks;          // aim at >= 3 workgroups per CU
-    int cap = n_stage_all / 8;                                // keep at least 8 stages per split
-    if (cap < 1) cap = 1;
-    if (want > cap) want = cap;
-    if (want > kSkinnyMaxSplits) want = kSkinnyMaxSplits;
-    if (want < 1) want = 1;
-    return want;
+    const int want = (768 + h.n_blocks - 1) / h.n_blocks;
+    int n = want < 8 ? want : 8;
+    if (n > n_stage_all / 8) n = n_stage_all / 8;
+    if (n < 1) n = 1;
+    int fine = 256 / h.n_blocks;
+    if (fine > kSkinnyMaxSplits) fine = kSkinnyMaxSplits;
+    if (fine > n_stage_all / 4) fine = n_stage_all / 4;
+    return fine > n ? fine : n;
 }
 
 hipError_t launch_skinny_bf16(const MetaView &mv, const MetaHeader &h, int mode, const void *S, int64_t C,
-                              const void *at, const void *zero, float *part, float *hf, void *hb, void *zt,
+                              const void *at, const void *zero, float *part, int n_split, float *hf, void *hb, void *zt,
                               bool zt_scaled, hipStream_t st)
 {
     if (h.n_blocks == 0) return hipSuccess;
-    const int n_split = skinny_splits(h, C);
     const int n_stage_all = (int)((C + SK_BK - 1) / SK_BK);
     const int per = (n_stage_all + n_split - 1) / n_split;
     const size_t lds = (size_t)SK_NST * (SK_XT + h.max_r16 * SK_BK * 2);
@@ -336,8 +355,9 @@ hipError_t launch_skinny_bf16(const MetaView &mv, const MetaHeader &h, int mode,
                        static_cast<const uint16_t *>(zero), part, per, NoGroup{0});
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_skinny_finish<false>, dim3((unsigned)h.n_blocks, kSkinnyRows / 16), dim3(256), 0, st, mv, mode, part, n_split, hf,
-                       static_cast<uint16_t *>(hb), static_cast<uint16_t *>(zt), zt_scaled ? 1 : 0, NoGroup{0}, 0);
+    const SkinnyOut out{hf, static_cast<uint16_t *>(hb), static_cast<uint16_t *>(zt), zt_scaled ? 1 : 0};
+    hipLaunchKernelGGL(k_skinny_finish<false>, dim3((unsigned)h.n_blocks, kSkinnyRows / 16), dim3(256), 0, st, mv, mode, part, n_split, out,
+                       NoGroup{0}, 0);
     return hipGetLastError();
 }
 
@@ -359,8 +379,9 @@ hipError_t launch_skinny_group(const GroupView &gv, const MetaHeader &hv, const 
                        static_cast<const uint16_t *>(zero), part, per, gv);
     hipError_t e = hipGetLastError();
     for (int p = 0; p < gv.n_proj && e == hipSuccess; ++p) {
+        const SkinnyOut out{hf[p], static_cast<uint16_t *>(hb[p]), static_cast<uint16_t *>(zt[p]), 0};
         hipLaunchKernelGGL(k_skinny_finish<true>, dim3((unsigned)hv.n_blocks, kSkinnyRows / 16), dim3(256), 0, st, gv.mv[p], 0, part,
-                           n_split, hf[p], static_cast<uint16_t *>(hb[p]), static_cast<uint16_t *>(zt[p]), 0, gv, p);
+                           n_split, out, gv, p);
         e = hipGetLastError();
     }
     return e;
