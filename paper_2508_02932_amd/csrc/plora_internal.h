@@ -97,6 +97,29 @@ struct GemmTile {
     GemmSeg s[2];
 };
 
+// What the skinny kernels need to know about a token block of kSkinnyRows rows: one record, so that a workgroup waits for
+// one load instead of a chain of three (block -> segment -> adapter; about 1 us each, in kernels of 5 to 10 us).
+struct BlkInfo {
+    SegInfo g;
+    int32_t t0;           // first token of the block inside its segment
+    float scale;
+    int64_t at_off;       // of the adapter
+    const void *B;
+};
+
+// The same for the weight-gradient kernels, one entry per adapter in the order by token count: the adapter, and the first
+// of its segments (most adapters have one).
+struct TokJob {
+    float *dA, *dB;
+    int64_t zt_off;               // first segment: its transposed factor,
+    int32_t row0, len, lp;        // first row, rows, pitch of that factor
+    int32_t k;                    // the adapter
+    int32_t r, r16, r16_off;
+    float scale;
+    int32_t seg_list0, n_own, n_steps;    // n_steps: 64-token steps over all of its segments
+    int32_t reserved;
+};
+
 // Device view of the derived tables (all pointers into the workspace, laid out by table_layout).
 struct MetaView {
     const MetaHeader *hdr;
@@ -106,6 +129,8 @@ struct MetaView {
     const int32_t *blk_seg;   // segment of each token block of kSkinnyRows rows
     const int32_t *seg_list;  // non-empty segments grouped by adapter (see AdapterInfo)
     const int32_t *tile_order;  // the GEMM row tiles ordered by extension steps, most first (ties: lower tile first)
+    const BlkInfo *blk;       // one per token block
+    const TokJob *job;        // one per adapter, longest first
 };
 
 // Several projections that read the same x (q / k / v, gate / up), fused along the rank: for adapter k the fused pass
@@ -180,7 +205,7 @@ PLORA_HD size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
 // Byte offsets of the derived tables inside the metadata region of the workspace.
 struct TableLayout {
-    size_t hdr, seg, ad, tile, blk_seg, seg_list, tile_order, bytes;
+    size_t hdr, seg, ad, tile, blk_seg, seg_list, tile_order, blk, job, bytes;
     int64_t n_tiles;
 };
 
@@ -196,6 +221,8 @@ PLORA_HD TableLayout table_layout(int64_t T, int n_seg, int n_adapters, int n_bl
     l.blk_seg = o;  o = align_up(o + (size_t)n_blocks * sizeof(int32_t), 64);
     l.seg_list = o; o = align_up(o + (size_t)n_seg * sizeof(int32_t), 64);
     l.tile_order = o; o = align_up(o + (size_t)l.n_tiles * sizeof(int32_t), 64);
+    l.blk = o;      o = align_up(o + (size_t)n_blocks * sizeof(BlkInfo), 64);
+    l.job = o;      o = align_up(o + (size_t)n_adapters * sizeof(TokJob), 64);
     l.bytes = o;
     return l;
 }
@@ -209,6 +236,8 @@ struct Tables {
     int32_t *blk_seg;
     int32_t *seg_list;
     int32_t *tile_order;
+    BlkInfo *blk;
+    TokJob *job;
 };
 
 PLORA_HD Tables tables_at(char *base, const TableLayout &l)
@@ -221,6 +250,8 @@ PLORA_HD Tables tables_at(char *base, const TableLayout &l)
     t.blk_seg = reinterpret_cast<int32_t *>(base + l.blk_seg);
     t.seg_list = reinterpret_cast<int32_t *>(base + l.seg_list);
     t.tile_order = reinterpret_cast<int32_t *>(base + l.tile_order);
+    t.blk = reinterpret_cast<BlkInfo *>(base + l.blk);
+    t.job = reinterpret_cast<TokJob *>(base + l.job);
     return t;
 }
 
@@ -228,6 +259,7 @@ PLORA_HD MetaView view_of(const Tables &t)
 {
     MetaView v;
     v.hdr = t.hdr; v.seg = t.seg; v.ad = t.ad; v.tile = t.tile; v.blk_seg = t.blk_seg; v.seg_list = t.seg_list; v.tile_order = t.tile_order;
+    v.blk = t.blk; v.job = t.job;
     return v;
 }
 
@@ -346,6 +378,23 @@ template <class Src> inline void derive_tables(const DescReader<Src> &in, const 
         int rank = 0;
         for (int j = 0; j < n_ad; ++j) rank += tokens[j] > tokens[k] || (tokens[j] == tokens[k] && j < k);
         t.ad[rank].by_tokens = k;
+    }
+    for (int s = 0; s < n_seg; ++s) {
+        const SegInfo &g = t.seg[s];
+        if (!seg_has_lowrank(g)) continue;
+        const AdapterInfo &a = t.ad[g.adapter];
+        for (int32_t t0 = 0, b = g.blk0; t0 < g.row1 - g.row0; t0 += kSkinnyRows, ++b) t.blk[b] = BlkInfo{g, t0, a.scale, a.at_off, a.B};
+    }
+    for (int i = 0; i < n_ad; ++i) {
+        const int k = t.ad[i].by_tokens;
+        const AdapterInfo &a = t.ad[k];
+        TokJob j{a.dA, a.dB, 0, 0, 0, 0, k, a.r, a.r16, a.r16_off, a.scale, a.seg_list0, a.n_own, 0, 0};
+        for (int li = 0; li < a.n_own; ++li) {
+            const SegInfo &g = t.seg[t.seg_list[a.seg_list0 + li]];
+            if (li == 0) { j.zt_off = g.zt_off; j.row0 = g.row0; j.len = g.row1 - g.row0; j.lp = g.lp; }
+            j.n_steps += g.lp / kTokPad;
+        }
+        t.job[i] = j;
     }
     MetaHeader hd;
     hd.T = T; hd.D = D; hd.K = in.K();

@@ -60,16 +60,16 @@ __device__ inline void wait_vmcnt_dyn(int n)
 template <bool GROUP>
 __global__ void __launch_bounds__(64 * SK_NW) k_skinny(MetaView mv, int mode, const uint16_t *__restrict__ S, int C,
                                                const uint16_t *__restrict__ at, const uint16_t *__restrict__ zero,
-                                               float *__restrict__ part, int stages_per_split,
+                                               float *__restrict__ part, int stages_per_split, int max_r16,
                                                std::conditional_t<GROUP, GroupView, NoGroup> gv)
 {
     extern __shared__ __attribute__((aligned(1024))) char lds[];
     const int blk = blockIdx.x;
-    const SegInfo g = mv.seg[mv.blk_seg[blk]];
-    const AdapterInfo a = mv.ad[g.adapter];
-    const int t0 = (blk - g.blk0) * kSkinnyRows;
+    const BlkInfo a = mv.blk[blk];
+    const SegInfo g = a.g;
+    const int t0 = a.t0;
     const int nt = (g.row1 - g.row0 - t0 < kSkinnyRows) ? g.row1 - g.row0 - t0 : kSkinnyRows;
-    int r16 = g.r16, max_r16;
+    int r16 = g.r16;
     int p_r16[kMaxGroup];                              // GROUP: rows of each projection's block of the small matrix
     int64_t p_at[kMaxGroup];                           // ... and where the block starts in that projection's buffer
     if constexpr (GROUP) {
@@ -83,9 +83,6 @@ __global__ void __launch_bounds__(64 * SK_NW) k_skinny(MetaView mv, int mode, co
                 r16 += ap.r16;
             }
         }
-        max_r16 = gv.max_r16;
-    } else {
-        max_r16 = mv.hdr->max_r16;
     }
     const int nb = r16 / 16;
     const int stage_bytes = SK_XT + max_r16 * SK_BK * 2;
@@ -271,21 +268,22 @@ __device__ inline void write_outputs(const SegInfo &g, float mult, int mode, con
 // GROUP: the partial tiles are those of a fused pass (pitch = the fused rank of the segment's adapter); mv is the view of
 // projection `proj`, whose columns start behind those of the projections before it.
 template <bool GROUP>
-__global__ void __launch_bounds__(256) k_skinny_finish(MetaView mv, int mode, const float *__restrict__ part, int n_split, SkinnyOut out,
+__global__ void __launch_bounds__(256) k_skinny_finish(MetaView mv, int mode, const float *__restrict__ part, int n_split, int max_r16, SkinnyOut out,
                                                       std::conditional_t<GROUP, GroupView, NoGroup> gv, int proj)
 {
     constexpr int FR = 16;                            // token rows per workgroup (grid.y slices of a block)
     __shared__ float tile[FR * PLORA_MAX_RANK];       // [FR][r16], pitch r16
     const int blk = blockIdx.x;
-    const SegInfo g = mv.seg[mv.blk_seg[blk]];
-    const float mult = mv.ad[g.adapter].scale;
+    const BlkInfo bi = mv.blk[blk];
+    const SegInfo g = bi.g;
+    const float mult = bi.scale;
     const int r0 = blockIdx.y * FR;                   // first row of this slice inside the block
-    const int t0 = (blk - g.blk0) * kSkinnyRows + r0; // first token of the slice inside the segment
+    const int t0 = bi.t0 + r0;                        // first token of the slice inside the segment
     const int nt = g.row1 - g.row0 - t0;              // valid tokens from there on
     if (t0 >= g.lp) return;                           // slice lies past the padded segment: nothing to write
     const int r16 = g.r16;
     int pitch = r16, col0 = 0;
-    int64_t tile_elems;
+    const int64_t tile_elems = (int64_t)kSkinnyRows * max_r16;
     if constexpr (GROUP) {
         pitch = 0;
         for (int p = 0; p < gv.n_proj; ++p) {
@@ -293,9 +291,6 @@ __global__ void __launch_bounds__(256) k_skinny_finish(MetaView mv, int mode, co
             if (p < proj) col0 += rp16;
             pitch += rp16;
         }
-        tile_elems = (int64_t)kSkinnyRows * gv.max_r16;
-    } else {
-        tile_elems = (int64_t)kSkinnyRows * mv.hdr->max_r16;
     }
     const int64_t split_stride = (int64_t)gridDim.x * tile_elems;
     const float *src = part + (int64_t)blk * tile_elems + (int64_t)r0 * pitch + col0;
@@ -352,11 +347,11 @@ hipError_t launch_skinny_bf16(const MetaView &mv, const MetaHeader &h, int mode,
     }
     hipLaunchKernelGGL(k_skinny<false>, dim3((unsigned)h.n_blocks, (unsigned)n_split), dim3(64 * SK_NW), lds, st, mv, mode,
                        static_cast<const uint16_t *>(S), (int)C, static_cast<const uint16_t *>(at),
-                       static_cast<const uint16_t *>(zero), part, per, NoGroup{0});
+                       static_cast<const uint16_t *>(zero), part, per, (int)h.max_r16, NoGroup{0});
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     const SkinnyOut out{hf, static_cast<uint16_t *>(hb), static_cast<uint16_t *>(zt), zt_scaled ? 1 : 0};
-    hipLaunchKernelGGL(k_skinny_finish<false>, dim3((unsigned)h.n_blocks, kSkinnyRows / 16), dim3(256), 0, st, mv, mode, part, n_split, out,
+    hipLaunchKernelGGL(k_skinny_finish<false>, dim3((unsigned)h.n_blocks, kSkinnyRows / 16), dim3(256), 0, st, mv, mode, part, n_split, (int)h.max_r16, out,
                        NoGroup{0}, 0);
     return hipGetLastError();
 }
@@ -376,12 +371,12 @@ hipError_t launch_skinny_group(const GroupView &gv, const MetaHeader &hv, const 
     }
     hipLaunchKernelGGL(k_skinny<true>, dim3((unsigned)hv.n_blocks, (unsigned)n_split), dim3(64 * SK_NW), lds, st, gv.mv[0], 0,
                        static_cast<const uint16_t *>(x), (int)C, static_cast<const uint16_t *>(nullptr),
-                       static_cast<const uint16_t *>(zero), part, per, gv);
+                       static_cast<const uint16_t *>(zero), part, per, (int)gv.max_r16, gv);
     hipError_t e = hipGetLastError();
     for (int p = 0; p < gv.n_proj && e == hipSuccess; ++p) {
         const SkinnyOut out{hf[p], static_cast<uint16_t *>(hb[p]), static_cast<uint16_t *>(zt[p]), 0};
         hipLaunchKernelGGL(k_skinny_finish<true>, dim3((unsigned)hv.n_blocks, kSkinnyRows / 16), dim3(256), 0, st, gv.mv[p], 0, part,
-                           n_split, out, gv, p);
+                           n_split, (int)gv.max_r16, out, gv, p);
         e = hipGetLastError();
     }
     return e;

@@ -238,16 +238,17 @@ __device__ inline void h_to_zt_slice(const TransposeJob &g, int slice, const flo
 
 // ---- derivation of the metadata tables by one workgroup of 256 threads --------------------------------
 // LDS of that workgroup.  The sizes that depend on the description come behind it: the description's words, then per
-// segment the offset hb_off, then the first token block.
+// segment the offsets h_off, hb_off and zt_off, then the first token block.
 struct DeriveShared {
     int64_t at_off[PLORA_MAX_ADAPTERS], ap_off[PLORA_MAX_ADAPTERS];
     int32_t tokens[PLORA_MAX_ADAPTERS], n_own[PLORA_MAX_ADAPTERS], list0[PLORA_MAX_ADAPTERS], by_tokens[PLORA_MAX_ADAPTERS];
+    int32_t r16_off[PLORA_MAX_ADAPTERS], n_steps[PLORA_MAX_ADAPTERS], first_seg[PLORA_MAX_ADAPTERS];
     int64_t wave_tot[4][4];
     int32_t totals[kSortKeys], base[kSortKeys], wave_cnt[4][kSortKeys], max_r16;
 };
 static size_t derive_lds_bytes(int n_words, int n_seg)
 {
-    return align_up(sizeof(DeriveShared) + align_up((size_t)n_words * 4, 8) + (size_t)n_seg * 12, 16);
+    return align_up(sizeof(DeriveShared) + align_up((size_t)n_words * 4, 8) + (size_t)n_seg * 28, 16);
 }
 
 // Exclusive prefix sums of four values per thread over the workgroup; tot receives the sums.
@@ -282,9 +283,10 @@ template <class Src> __device__ inline void derive_on_device(const DescReader<Sr
     uint32_t *words = reinterpret_cast<uint32_t *>(shared_mem + sizeof(DeriveShared));
     const int n_seg = src.n_seg(), n_ad = src.n_adapters(), n_words = desc_words(n_seg, n_ad);
     int64_t *seg_hb = reinterpret_cast<int64_t *>(shared_mem + sizeof(DeriveShared) + align_up((size_t)n_words * 4, 8));
-    int32_t *seg_blk0 = reinterpret_cast<int32_t *>(seg_hb + n_seg);
+    int64_t *seg_h = seg_hb + n_seg, *seg_zt = seg_h + n_seg;
+    int32_t *seg_blk0 = reinterpret_cast<int32_t *>(seg_zt + n_seg);
     for (int i = tid; i < n_words; i += 256) words[i] = src.src.word(i);
-    sh.tokens[tid] = 0; sh.n_own[tid] = 0;
+    sh.tokens[tid] = 0; sh.n_own[tid] = 0; sh.n_steps[tid] = 0; sh.first_seg[tid] = n_seg;
     if (tid < kSortKeys) sh.totals[tid] = 0;
     if (tid == 0) sh.max_r16 = 0;
     __syncthreads();
@@ -313,6 +315,8 @@ template <class Src> __device__ inline void derive_on_device(const DescReader<Sr
                     atomicMax(&sh.max_r16, g.r16);
                     atomicAdd(&sh.tokens[g.adapter], len);
                     atomicAdd(&sh.n_own[g.adapter], 1);
+                    atomicAdd(&sh.n_steps[g.adapter], g.lp / kTokPad);
+                    atomicMin(&sh.first_seg[g.adapter], s);
                 }
             }
         }
@@ -320,7 +324,7 @@ template <class Src> __device__ inline void derive_on_device(const DescReader<Sr
         if (s < n_seg) {
             g.blk0 = (int32_t)(carry[0] + v[0]);
             g.h_off = carry[1] + v[1]; g.hb_off = carry[2] + v[2]; g.zt_off = carry[3] + v[3];
-            seg_hb[s] = g.hb_off; seg_blk0[s] = g.blk0;
+            seg_h[s] = g.h_off; seg_hb[s] = g.hb_off; seg_zt[s] = g.zt_off; seg_blk0[s] = g.blk0;
             t.seg[s] = g;
         }
 #pragma unroll
@@ -345,7 +349,7 @@ template <class Src> __device__ inline void derive_on_device(const DescReader<Sr
         if (k < n_ad) {
             a.at_off = v[0]; a.ap_off = v[1]; a.r16_off = (int32_t)v[2]; a.seg_list0 = (int32_t)v[3];
             a.ext_b = in.ext_b(k, a.at_off);
-            sh.at_off[k] = a.at_off; sh.ap_off[k] = a.ap_off; sh.list0[k] = a.seg_list0;
+            sh.at_off[k] = a.at_off; sh.ap_off[k] = a.ap_off; sh.list0[k] = a.seg_list0; sh.r16_off[k] = a.r16_off;
             // place of this adapter in the order by token count, longest first, ties by index
             int rank = 0;
             for (int j = 0; j < n_ad; ++j) rank += sh.tokens[j] > a.tokens || (sh.tokens[j] == a.tokens && j < k);
@@ -355,6 +359,15 @@ template <class Src> __device__ inline void derive_on_device(const DescReader<Sr
         if (k < n_ad) {
             a.by_tokens = sh.by_tokens[k];
             t.ad[k] = a;
+            const int kj = a.by_tokens, s = sh.first_seg[kj];          // entry k of the jobs is adapter kj
+            TokJob j;
+            j.dA = static_cast<float *>(const_cast<void *>(in.ad_ptr(kj, 2)));
+            j.dB = static_cast<float *>(const_cast<void *>(in.ad_ptr(kj, 3)));
+            j.zt_off = 0; j.row0 = 0; j.len = 0; j.lp = 0;
+            if (s < n_seg) { j.zt_off = seg_zt[s]; j.row0 = in.seg_row0(s); j.len = in.seg_row1(s) - j.row0; j.lp = pad_to(j.len, kTokPad); }
+            j.k = kj; j.r = in.ad_rank(kj); j.r16 = pad_to(j.r, kRankPadMfma); j.r16_off = sh.r16_off[kj];
+            j.scale = in.ad_scale(kj); j.seg_list0 = sh.list0[kj]; j.n_own = sh.n_own[kj]; j.n_steps = sh.n_steps[kj]; j.reserved = 0;
+            t.job[k] = j;
         }
     }
     if (tid == 0) {
@@ -379,6 +392,15 @@ template <class Src> __device__ inline void derive_on_device(const DescReader<Sr
             if (seg_blk0[mid] <= b) lo = mid; else hi = mid - 1;
         }
         t.blk_seg[b] = lo;
+        BlkInfo bi;
+        const int k = in.seg_adapter(lo);
+        bi.g.row0 = in.seg_row0(lo); bi.g.row1 = in.seg_row1(lo); bi.g.adapter = k;
+        bi.g.r = in.ad_rank(k); bi.g.rp = pad_to(bi.g.r, kRankPadGemm); bi.g.r16 = pad_to(bi.g.r, kRankPadMfma);
+        bi.g.blk0 = seg_blk0[lo]; bi.g.lp = pad_to(bi.g.row1 - bi.g.row0, kTokPad);
+        bi.g.h_off = seg_h[lo]; bi.g.hb_off = seg_hb[lo]; bi.g.zt_off = seg_zt[lo];
+        bi.t0 = (b - bi.g.blk0) * kSkinnyRows;
+        bi.scale = in.ad_scale(k); bi.at_off = sh.at_off[k]; bi.B = in.ad_ptr(k, 1);
+        t.blk[b] = bi;
     }
     // row tiles of the GEMMs, and the order they are walked in
     struct FromLds {

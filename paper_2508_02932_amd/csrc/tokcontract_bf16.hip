@@ -58,7 +58,7 @@ __device__ inline void tc_wait_vmcnt(int n)
 template <bool WANT_DA, int BC, bool GROUP = false>
 __global__ void __launch_bounds__(2 * BC) __attribute__((amdgpu_waves_per_eu(2, 2))) k_tokc(MetaView mv, const uint16_t *__restrict__ S, int C,
                                              const uint16_t *__restrict__ zt, const uint16_t *__restrict__ zero,
-                                             float *__restrict__ part, int r16_total, int nst,
+                                             float *__restrict__ part, int r16_total, int max_r16, int nst,
                                              std::conditional_t<GROUP, GroupView, NoGroup> gv)
 {
     static_assert(!GROUP || WANT_DA, "");
@@ -73,10 +73,10 @@ __global__ void __launch_bounds__(2 * BC) __attribute__((amdgpu_waves_per_eu(2, 
         return BC == 256 ? 4 * (u & 3) + 2 * ((u >> 3) & 1) : 2 * (u & 3) + 8 * ((u >> 3) & 1);
     };
     extern __shared__ __attribute__((aligned(1024))) char lds[];
-    const int k = mv.ad[blockIdx.y].by_tokens;       // longest adapters first
-    const AdapterInfo a = mv.ad[k];
+    const TokJob a = mv.job[blockIdx.y];             // longest adapters first
+    const int k = a.k;
     const int c0 = blockIdx.x * TC_BC;
-    int r16 = a.r16, max_r16;
+    int r16 = a.r16;
     int p_r16[kMaxGroup];                            // GROUP: rank rows (padded to 16) of each projection
     if constexpr (GROUP) {
         r16 = 0;
@@ -85,9 +85,6 @@ __global__ void __launch_bounds__(2 * BC) __attribute__((amdgpu_waves_per_eu(2, 
             p_r16[p] = p < gv.n_proj ? gv.mv[p].ad[k].r16 : 0;
             r16 += p_r16[p];
         }
-        max_r16 = gv.max_r16;
-    } else {
-        max_r16 = mv.hdr->max_r16;
     }
     const int nb = r16 / 16;
     const int lane = threadIdx.x & 63;
@@ -95,15 +92,10 @@ __global__ void __launch_bounds__(2 * BC) __attribute__((amdgpu_waves_per_eu(2, 
     const uint32_t lds_base = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)LDS_PTR(char, lds));
     const int stage_bytes = TC_S_BYTES + max_r16 * TC_BT * 2;
 
-    // steps (TC_BT tokens each) of this adapter over its own segments (list built on the host), and the
+    // steps (TC_BT tokens each) of this adapter over its own segments, and the
     // slice of them that belongs to this split
     const int32_t *own = mv.seg_list + a.seg_list0;
-    const int n_own = a.n_own;
-    int n_steps_all = 0;
-    for (int li = 0; li < n_own; ++li) {
-        const SegInfo g = mv.seg[own[li]];
-        n_steps_all += (g.row1 - g.row0 + TC_BT - 1) / TC_BT;
-    }
+    const int n_own = a.n_own, n_steps_all = a.n_steps;
     const int per = (n_steps_all + gridDim.z - 1) / gridDim.z;
     const int step0 = blockIdx.z * per;
     int n_steps = n_steps_all - step0;
@@ -115,8 +107,8 @@ __global__ void __launch_bounds__(2 * BC) __attribute__((amdgpu_waves_per_eu(2, 
     // issue right behind the barrier does not wait for a metadata fetch)
     int cur_li = 0, cur_t = 0;
     for (int skip = step0; skip > 0 && cur_li < n_own;) {
-        const SegInfo g = mv.seg[own[cur_li]];
-        const int st_here = (g.row1 - g.row0 + TC_BT - 1) / TC_BT;
+        const int len = cur_li ? mv.seg[own[cur_li]].row1 - mv.seg[own[cur_li]].row0 : a.len;
+        const int st_here = (len + TC_BT - 1) / TC_BT;
         if (skip >= st_here) { skip -= st_here; ++cur_li; }
         else { cur_t = skip * TC_BT; skip = 0; }
     }
@@ -141,6 +133,10 @@ __global__ void __launch_bounds__(2 * BC) __attribute__((amdgpu_waves_per_eu(2, 
     int64_t seg_zt = 0;
     const uint16_t *seg_zp[ZL];                      // GROUP: start of the current segment's rows in projection zp[jj]'s buffer
     auto load_desc = [&]() {
+        if (!GROUP && cur_li == 0) {                 // the first segment came with the job
+            seg_row0 = a.row0; seg_len = a.len; seg_lp = a.lp; seg_zt = a.zt_off;
+            return;
+        }
         if (cur_li < n_own) {
             const int sidx = own[cur_li];
             const SegInfo g = mv.seg[sidx];
@@ -312,55 +308,69 @@ __global__ void __launch_bounds__(2 * BC) __attribute__((amdgpu_waves_per_eu(2, 
     }
 }
 
-// Sums the partial tiles [split][r16 rows][C] in split order and writes dA_k[c][j] or scale_k-scaled
-// dB_k[j][c].  grid (C / 256, rank rows of all adapters); one output element per thread.
+// Sums the partial tiles [split][r16 rows][C] of one matrix in split order, for 64 columns and all of its r rows (the first
+// at row0): dB_k[j][c] scaled by scale_k straight from the sums, dA_k[c][j] through LDS, so that both leave in whole rows.
+// 16 threads x 4 columns per row, all splits of a row requested at once.
+constexpr int TF_COLS = 64;
 template <bool WANT_DA>
-__global__ void __launch_bounds__(256) k_tokc_finish(MetaView mv, const float *__restrict__ part, int C, int n_split,
-                                                    int r16_total)
+__device__ inline void finish_matrix(const float *__restrict__ part, int64_t split_stride, int n_split, int row0, int r, int C, int c0,
+                                     float scale, float *__restrict__ dst, float *lds)
 {
-    const int row = blockIdx.y;                      // row of the concatenated [r16_total][C] partial tile
-    const int n_ad = mv.hdr->n_adapters;
-    int k = 0;
-    for (int q = 0; q < n_ad; ++q)
-        if (row >= mv.ad[q].r16_off) k = q;
-    const AdapterInfo a = mv.ad[k];
-    const int j = row - a.r16_off;
-    const int c = blockIdx.x * 256 + threadIdx.x;
-    if (j >= a.r || c >= C) return;
-    float v[kTokMaxSplits];
+    const int c = c0 + (threadIdx.x & 15) * 4, jt = threadIdx.x >> 4;
+    const int pitch = r | 1;                         // LDS rows of one column: an odd pitch keeps the banks apart
+    for (int j = jt; j < r; j += 16) {
+        if (c < C) {
+            const float *src = part + (int64_t)(row0 + j) * C + c;
+            float4 v[kTokMaxSplits];
 #pragma unroll
-    for (int sp = 0; sp < kTokMaxSplits; ++sp)
-        v[sp] = (sp < n_split) ? part[((int64_t)sp * r16_total + row) * C + c] : 0.f;
-    float sum = v[0];
+            for (int sp = 0; sp < kTokMaxSplits; ++sp)
+                if (sp < n_split) v[sp] = *reinterpret_cast<const float4 *>(src + sp * split_stride);
+            float4 sum = v[0];
 #pragma unroll
-    for (int sp = 1; sp < kTokMaxSplits; ++sp) sum += v[sp];
-    if (WANT_DA) a.dA[(int64_t)c * a.r + j] = sum;
-    else a.dB[(int64_t)j * C + c] = a.scale * sum;
+            for (int sp = 1; sp < kTokMaxSplits; ++sp)
+                if (sp < n_split) { sum.x += v[sp].x; sum.y += v[sp].y; sum.z += v[sp].z; sum.w += v[sp].w; }
+            if (WANT_DA) {
+                float *q = lds + (c - c0) * pitch + j;
+                q[0] = sum.x; q[pitch] = sum.y; q[2 * pitch] = sum.z; q[3 * pitch] = sum.w;
+            } else {
+                sum.x *= scale; sum.y *= scale; sum.z *= scale; sum.w *= scale;
+                *reinterpret_cast<float4 *>(dst + (int64_t)j * C + c) = sum;
+            }
+        }
+    }
+    if (WANT_DA) {
+        __syncthreads();
+        const int cols = C - c0 < TF_COLS ? C - c0 : TF_COLS;
+        float *out = dst + (int64_t)c0 * r;
+        for (int e = threadIdx.x; e < cols * r; e += 256) {
+            const int cc = e / r;
+            out[e] = lds[cc * pitch + e - cc * r];
+        }
+        __syncthreads();
+    }
 }
 
-// The same for the partial tiles of a fused dA pass: row -> adapter -> projection -> that projection's dA_k.
+// grid (C / 64, adapters)
+template <bool WANT_DA>
+__global__ void __launch_bounds__(256) k_tokc_finish(MetaView mv, const float *__restrict__ part, int C, int n_split, int r16_total)
+{
+    extern __shared__ __attribute__((aligned(16))) float tf_lds[];
+    const TokJob a = mv.job[blockIdx.y];
+    finish_matrix<WANT_DA>(part, (int64_t)r16_total * C, n_split, a.r16_off, a.r, C, blockIdx.x * TF_COLS, a.scale, WANT_DA ? a.dA : a.dB, tf_lds);
+}
+
+// The same for the partial tiles of a fused dA pass: the rows of adapter k's projections lie one below the other.
 __global__ void __launch_bounds__(256) k_tokc_finish_group(GroupView gv, const float *__restrict__ part, int C, int n_split)
 {
-    const int row = blockIdx.y;                      // row of the concatenated [r16_total][C] partial tile
-    const int n_ad = gv.mv[0].hdr->n_adapters;
-    int k = 0, k_off = 0;
-    for (int q = 0; q < n_ad; ++q) {
-        int off = 0;
-        for (int p = 0; p < gv.n_proj; ++p) off += gv.mv[p].ad[q].r16_off;
-        if (row >= off) { k = q; k_off = off; }
+    extern __shared__ __attribute__((aligned(16))) float tf_lds[];
+    const int k = blockIdx.y;
+    int row = 0;
+    for (int p = 0; p < gv.n_proj; ++p) row += gv.mv[p].ad[k].r16_off;
+    for (int p = 0; p < gv.n_proj; ++p) {
+        const AdapterInfo a = gv.mv[p].ad[k];
+        finish_matrix<true>(part, (int64_t)gv.r16_total * C, n_split, row, a.r, C, blockIdx.x * TF_COLS, 1.f, a.dA, tf_lds);
+        row += a.r16;
     }
-    int j = row - k_off, pj = 0;                     // row inside the fused factor of adapter k -> projection, local row
-    for (; pj < gv.n_proj - 1; ++pj) {
-        const int r16 = gv.mv[pj].ad[k].r16;
-        if (j < r16) break;
-        j -= r16;
-    }
-    const AdapterInfo a = gv.mv[pj].ad[k];
-    const int c = blockIdx.x * 256 + threadIdx.x;
-    if (j >= a.r || c >= C) return;
-    float sum = part[(int64_t)row * C + c];
-    for (int sp = 1; sp < n_split; ++sp) sum += part[((int64_t)sp * gv.r16_total + row) * C + c];   // fixed order
-    a.dA[(int64_t)c * a.r + j] = sum;
 }
 
 // Launch shape: column-tile width and number of token splits.  128-column tiles throughout: two workgroups then
@@ -419,7 +429,8 @@ static hipError_t launch_tokc(const MetaView &mv, const MetaHeader &h, const uin
         if (e != hipSuccess) return e;
     }
     const dim3 grid((unsigned)((C + BC - 1) / BC), (unsigned)h.n_adapters, (unsigned)n_split);
-    hipLaunchKernelGGL(kern, grid, dim3(2 * BC), lds, st, mv, S, C, zt, zero, n_split > 1 ? part : nullptr, r16_total, nst, NoGroup{0});
+    hipLaunchKernelGGL(kern, grid, dim3(2 * BC), lds, st, mv, S, C, zt, zero, n_split > 1 ? part : nullptr, r16_total,
+                       (int)(h.max_r16 > 0 ? h.max_r16 : 16), nst, NoGroup{0});
     return hipGetLastError();
 }
 
@@ -444,11 +455,11 @@ hipError_t launch_tokc_group_dA(const GroupView &gv, const MetaHeader &hv, const
     const dim3 grid((unsigned)((C + BC - 1) / BC), (unsigned)hv.n_adapters, (unsigned)n_split);
     hipLaunchKernelGGL(kern, grid, dim3(2 * BC), nst * stage, st, gv.mv[0], static_cast<const uint16_t *>(x), (int)C,
                        static_cast<const uint16_t *>(nullptr), static_cast<const uint16_t *>(zero), n_split > 1 ? part : nullptr,
-                       gv.r16_total, nst, gv);
+                       gv.r16_total, (int)(gv.max_r16 > 0 ? gv.max_r16 : 16), nst, gv);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || n_split <= 1) return e;
-    hipLaunchKernelGGL(k_tokc_finish_group, dim3((unsigned)((C + 255) / 256), (unsigned)gv.r16_total), dim3(256), 0, st, gv, part,
-                       (int)C, n_split);
+    hipLaunchKernelGGL(k_tokc_finish_group, dim3((unsigned)((C + TF_COLS - 1) / TF_COLS), (unsigned)hv.n_adapters), dim3(256),
+                       TF_COLS * (PLORA_MAX_RANK + 1) * 4, st, gv, part, (int)C, n_split);
     return hipGetLastError();
 }
 
@@ -467,8 +478,8 @@ hipError_t launch_tokcontract_bf16(const MetaView &mv, const MetaHeader &h, bool
     else e = bc == 256 ? PL_TOKC(false, 256) : PL_TOKC(false, 128);
 #undef PL_TOKC
     if (e != hipSuccess || n_split <= 1) return e;
-    const dim3 g2((unsigned)((C + 255) / 256), (unsigned)r16_total);
-    if (want_dA) hipLaunchKernelGGL(k_tokc_finish<true>, g2, dim3(256), 0, st, mv, part, (int)C, n_split, r16_total);
+    const dim3 g2((unsigned)((C + TF_COLS - 1) / TF_COLS), (unsigned)h.n_adapters);
+    if (want_dA) hipLaunchKernelGGL(k_tokc_finish<true>, g2, dim3(256), TF_COLS * (PLORA_MAX_RANK + 1) * 4, st, mv, part, (int)C, n_split, r16_total);
     else hipLaunchKernelGGL(k_tokc_finish<false>, g2, dim3(256), 0, st, mv, part, (int)C, n_split, r16_total);
     return hipGetLastError();
 }
