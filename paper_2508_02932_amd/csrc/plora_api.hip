@@ -364,9 +364,9 @@ static plora_status forward_impl(const plora_desc *desc, const void *x, const vo
     }
     if (!(steps & kStepMain)) return PLORA_OK;
     if (lora_only) {
-        // the padded buffer holds B_k^T [d_out][rp]; the tables carry its offsets for d_in rows unless W's layout says d_out
+        // the padded buffer holds B_k^T [d_out][rp]
         Bracket b(8, st);
-        PL_TRY(launch_expand_bf16(mv, m.hdr, y, desc->d_out, hb, ws + L.ap, w_out_in ? desc->d_out : desc->d_in, ws + L.zero, st));
+        PL_TRY(launch_expand_bf16(mv, m.hdr, y, desc->d_out, hb, ws + L.ap, ws + L.zero, st));
         return PLORA_OK;
     }
     { Bracket b(0, st);
@@ -462,9 +462,9 @@ static plora_status backward_impl(const plora_desc *desc, const void *x, const v
     }
     if (!(steps & kStepDx)) return PLORA_OK;
     if (dx && desc->T > 0 && lora_only) {
-        // padded A_k [d_in][rp]; the tables carry its offsets for d_in rows unless W's layout says d_out
+        // the padded buffer holds A_k [d_in][rp]
         Bracket b(8, st);
-        PL_TRY(launch_expand_bf16(mv, m.hdr, dx, desc->d_in, gb, ap, m.hdr.w_out_in ? desc->d_out : desc->d_in, ws + L.zero, st));
+        PL_TRY(launch_expand_bf16(mv, m.hdr, dx, desc->d_in, gb, ap, ws + L.zero, st));
     } else if (dx && desc->T > 0) {
         Bracket b(1, st);
         PL_TRY(run_gemm(m, L, ws, m.gemm_dx, m.hdr.w_out_in != 0, desc->d_out, desc->d_in, dy, W, dx, dx_accumulate, st));

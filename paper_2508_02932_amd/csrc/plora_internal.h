@@ -105,6 +105,8 @@ struct BlkInfo {
     float scale;
     int64_t at_off;       // of the adapter
     const void *B;
+    int32_t rp_off;       // sum of rp over the adapters before this one (rows of the padded operand, in units of its row count)
+    int32_t reserved;
 };
 
 // The same for the weight-gradient kernels, one entry per adapter in the order by token count: the adapter, and the first
@@ -383,7 +385,8 @@ template <class Src> inline void derive_tables(const DescReader<Src> &in, const 
         const SegInfo &g = t.seg[s];
         if (!seg_has_lowrank(g)) continue;
         const AdapterInfo &a = t.ad[g.adapter];
-        for (int32_t t0 = 0, b = g.blk0; t0 < g.row1 - g.row0; t0 += kSkinnyRows, ++b) t.blk[b] = BlkInfo{g, t0, a.scale, a.at_off, a.B};
+        for (int32_t t0 = 0, b = g.blk0; t0 < g.row1 - g.row0; t0 += kSkinnyRows, ++b)
+            t.blk[b] = BlkInfo{g, t0, a.scale, a.at_off, a.B, (int32_t)(a.ap_off / ap_rows), 0};
     }
     for (int i = 0; i < n_ad; ++i) {
         const int k = t.ad[i].by_tokens;
@@ -475,9 +478,9 @@ hipError_t launch_gemm_small_bf16(const GemmPlan &p, const MetaView &mv, const M
                                   const void *S, const void *W, const void *side, const void *ap, const void *zero, void *C,
                                   bool accumulate, float *part, hipStream_t st);
 // Stand-alone low-rank update C[T][N] += side * op_k (bf16, one rounding): side = bf16 low-rank factor [len][rp] per
-// segment, opT = padded small matrices [N][rp] (adapter k at N * (ap_off_k / table_rows)).
+// segment, opT = padded small matrices [N][rp], one behind the other.
 hipError_t launch_expand_bf16(const MetaView &mv, const MetaHeader &h, void *C, int64_t N, const void *side, const void *opT,
-                              int64_t table_rows, const void *zero, hipStream_t st);
+                              const void *zero, hipStream_t st);
 // Token contraction: out_k = mult * sum_t S[t][c] * zt[j][t] over all segments of adapter k.
 //   want_dA: S = x, out = dA_k[c][j], mult = 1;  else S = dy, out = dB_k[j][c], mult = scale_k.
 //   n_split > 1: the token walk is split, partial tiles go through `part` ([split][r16_total][C] fp32).

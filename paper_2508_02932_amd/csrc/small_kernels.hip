@@ -242,7 +242,7 @@ __device__ inline void h_to_zt_slice(const TransposeJob &g, int slice, const flo
 struct DeriveShared {
     int64_t at_off[PLORA_MAX_ADAPTERS], ap_off[PLORA_MAX_ADAPTERS];
     int32_t tokens[PLORA_MAX_ADAPTERS], n_own[PLORA_MAX_ADAPTERS], list0[PLORA_MAX_ADAPTERS], by_tokens[PLORA_MAX_ADAPTERS];
-    int32_t r16_off[PLORA_MAX_ADAPTERS], n_steps[PLORA_MAX_ADAPTERS], first_seg[PLORA_MAX_ADAPTERS];
+    int32_t r16_off[PLORA_MAX_ADAPTERS], rp_off[PLORA_MAX_ADAPTERS], n_steps[PLORA_MAX_ADAPTERS], first_seg[PLORA_MAX_ADAPTERS];
     int64_t wave_tot[4][4];
     int32_t totals[kSortKeys], base[kSortKeys], wave_cnt[4][kSortKeys], max_r16;
 };
@@ -343,11 +343,11 @@ template <class Src> __device__ inline void derive_on_device(const DescReader<Sr
             a.r = in.ad_rank(k); a.rp = pad_to(a.r, kRankPadGemm); a.r16 = pad_to(a.r, kRankPadMfma);
             a.scale = in.ad_scale(k);
             a.n_own = sh.n_own[k]; a.tokens = sh.tokens[k]; a.reserved = 0;
-            v[0] = (int64_t)a.r16 * D; v[1] = (int64_t)a.rp * ap_rows; v[2] = a.r16; v[3] = a.n_own;
+            v[0] = (int64_t)a.r16 * D; v[1] = a.rp; v[2] = a.r16; v[3] = a.n_own;
         }
         block_scan4(v, tot, sh.wave_tot);
         if (k < n_ad) {
-            a.at_off = v[0]; a.ap_off = v[1]; a.r16_off = (int32_t)v[2]; a.seg_list0 = (int32_t)v[3];
+            a.at_off = v[0]; a.ap_off = v[1] * ap_rows; sh.rp_off[k] = (int32_t)v[1]; a.r16_off = (int32_t)v[2]; a.seg_list0 = (int32_t)v[3];
             a.ext_b = in.ext_b(k, a.at_off);
             sh.at_off[k] = a.at_off; sh.ap_off[k] = a.ap_off; sh.list0[k] = a.seg_list0; sh.r16_off[k] = a.r16_off;
             // place of this adapter in the order by token count, longest first, ties by index
@@ -399,7 +399,7 @@ template <class Src> __device__ inline void derive_on_device(const DescReader<Sr
         bi.g.blk0 = seg_blk0[lo]; bi.g.lp = pad_to(bi.g.row1 - bi.g.row0, kTokPad);
         bi.g.h_off = seg_h[lo]; bi.g.hb_off = seg_hb[lo]; bi.g.zt_off = seg_zt[lo];
         bi.t0 = (b - bi.g.blk0) * kSkinnyRows;
-        bi.scale = in.ad_scale(k); bi.at_off = sh.at_off[k]; bi.B = in.ad_ptr(k, 1);
+        bi.scale = in.ad_scale(k); bi.at_off = sh.at_off[k]; bi.B = in.ad_ptr(k, 1); bi.rp_off = sh.rp_off[k]; bi.reserved = 0;
         t.blk[b] = bi;
     }
     // row tiles of the GEMMs, and the order they are walked in

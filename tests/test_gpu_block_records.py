@@ -12,7 +12,7 @@ pytestmark = pytest.mark.gpu
 
 SEG = [("row0", "<i4"), ("row1", "<i4"), ("adapter", "<i4"), ("r", "<i4"), ("rp", "<i4"), ("r16", "<i4"), ("blk0", "<i4"), ("lp", "<i4"),
        ("h_off", "<i8"), ("hb_off", "<i8"), ("zt_off", "<i8")]
-BLK = np.dtype(SEG + [("t0", "<i4"), ("scale", "<f4"), ("at_off", "<i8"), ("B", "<u8")])
+BLK = np.dtype(SEG + [("t0", "<i4"), ("scale", "<f4"), ("at_off", "<i8"), ("B", "<u8"), ("rp_off", "<i4"), ("reserved", "<i4")])
 JOB = np.dtype([("dA", "<u8"), ("dB", "<u8"), ("zt_off", "<i8")] + [(n, "<i4") for n in ("row0", "len", "lp", "k", "r", "r16", "r16_off")]
                + [("scale", "<f4")] + [(n, "<i4") for n in ("seg_list0", "n_own", "n_steps", "reserved")])
 
@@ -46,6 +46,7 @@ def test_records_repeat_the_tables():
         a = tab["ad"][int(rec["adapter"])]
         assert rec["t0"] == 128 * (b - int(rec["blk0"]))
         assert (rec["scale"], rec["at_off"], rec["B"]) == (a["scale"], a["at_off"], a["B"])
+        assert int(rec["rp_off"]) * 136 == int(a["ap_off"])                 # the padded operand has d_in rows here
     for i, rec in enumerate(job):
         k = int(rec["k"])
         assert k == int(tab["ad"][i]["by_tokens"])
