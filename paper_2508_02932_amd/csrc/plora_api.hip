@@ -316,9 +316,24 @@ enum : unsigned {
     kStepsAll = 127u
 };
 
+// Preparation jobs of a grouped call, launched together once every projection has added its own.
+struct PrepList {
+    PrepJob job[kMaxGroup];
+    std::vector<uint32_t> words[kMaxGroup];
+    int n = 0;
+    void add(const PrepJob &j)
+    {
+        words[n].assign(j.desc_host, j.desc_host + j.n_words);       // the description lives in the projection's call frame
+        job[n] = j;
+        job[n].desc_host = words[n].data();
+        ++n;
+    }
+};
+
 static plora_status forward_impl(const plora_desc *desc, const void *x, const void *W, const void *const *A,
                                  const void *const *B, void *y, float *h_saved, void *workspace, size_t ws_bytes,
-                                 void *hip_stream, bool lora_only = false, bool check_only = false, unsigned steps = kStepsAll)
+                                 void *hip_stream, bool lora_only = false, bool check_only = false, unsigned steps = kStepsAll,
+                                 PrepList *later = nullptr)
 {
     Call c;
     plora_status ps = prepare(desc, x, W, A, B, nullptr, nullptr, workspace, ws_bytes, lora_only, c);
@@ -336,9 +351,10 @@ static plora_status forward_impl(const plora_desc *desc, const void *x, const vo
     const bool bf = desc->dtype == PLORA_BF16;
     const bool w_out_in = m.hdr.w_out_in != 0;
     if (steps & kStepPrep) {
-        Bracket b(6, st);
-        PL_TRY(launch_prep(c.words, m.n_words, m.hdr, ws + L.meta, reinterpret_cast<uint32_t *>(ws + L.desc), ws + L.zero,
-                           ws + L.at, ws + L.ap, bf && lora, false, bf && lora && (w_out_in || lora_only), m.max_rank, nullptr, nullptr, st));
+        const PrepJob job{c.words, m.n_words, m.max_rank, m.hdr, ws + L.meta, reinterpret_cast<uint32_t *>(ws + L.desc), ws + L.zero,
+                          ws + L.at, ws + L.ap, bf && lora, false, bf && lora && (w_out_in || lora_only), nullptr, nullptr};
+        if (later) later->add(job);
+        else { Bracket b(6, st); PL_TRY(launch_prep(&job, 1, st)); }
     }
     float *hf = h_saved ? h_saved : reinterpret_cast<float *>(ws + L.hf);
 
@@ -377,7 +393,8 @@ static plora_status forward_impl(const plora_desc *desc, const void *x, const vo
 static plora_status backward_impl(const plora_desc *desc, const void *x, const void *W, const void *const *A,
                                   const void *const *B, const void *dy, const float *h_saved, void *dx, float *const *dA,
                                   float *const *dB, void *workspace, size_t ws_bytes, void *hip_stream, bool lora_only = false,
-                                  bool check_only = false, unsigned steps = kStepsAll, bool dx_accumulate = false)
+                                  bool check_only = false, unsigned steps = kStepsAll, bool dx_accumulate = false,
+                                  PrepList *later = nullptr)
 {
     const bool want_w = (dA != nullptr) || (dB != nullptr);
     if (desc && want_w && desc->n_adapters > 0 && (!dA || !dB)) {
@@ -411,10 +428,11 @@ static plora_status backward_impl(const plora_desc *desc, const void *x, const v
         // the low-rank operand of the dX GEMM: padded A_k, or - W stored [d_out][d_in] - the packed A_k^T
         // (the stand-alone low-rank update always reads the padded A_k)
         const bool dx_ap = dx != nullptr && (lora_only || !m.hdr.w_out_in), dx_at = dx != nullptr && !lora_only && m.hdr.w_out_in;
-        Bracket b(6, st);
-        PL_TRY(launch_prep(c.words, m.n_words, m.hdr, ws + L.meta, reinterpret_cast<uint32_t *>(ws + L.desc), ws + L.zero,
-                           ws + L.at, ws + L.ap, bf && lora && (need_shrink || dx_at), bf && lora && dx_ap, false, m.max_rank,
-                           tr ? h_saved : nullptr, tr ? ws + L.zt_h : nullptr, st));
+        const PrepJob job{c.words, m.n_words, m.max_rank, m.hdr, ws + L.meta, reinterpret_cast<uint32_t *>(ws + L.desc), ws + L.zero,
+                          ws + L.at, ws + L.ap, bf && lora && (need_shrink || dx_at), bf && lora && dx_ap, false,
+                          tr ? h_saved : nullptr, tr ? ws + L.zt_h : nullptr};
+        if (later) later->add(job);
+        else { Bracket b(6, st); PL_TRY(launch_prep(&job, 1, st)); }
     }
 
     if (desc->dtype == PLORA_F32) {
@@ -580,9 +598,10 @@ static plora_status group_forward(const plora_group *g, const void *x, const voi
     if (!workspace || ws_bytes < gp.total) return PLORA_ERR_WORKSPACE;
     if ((reinterpret_cast<uintptr_t>(workspace) & 255u) != 0) return PLORA_ERR_ALIGN;
     char *ws = static_cast<char *>(workspace);
+    PrepList preps;
     auto run = [&](int p, bool check, unsigned steps) {
         return forward_impl(&g->desc[p], x, W[p], A ? A[p] : nullptr, B ? B[p] : nullptr, y[p], h_saved ? h_saved[p] : nullptr,
-                            ws + gp.ws_off[p], gp.m[p]->ws.total, hip_stream, false, check, steps);
+                            ws + gp.ws_off[p], gp.m[p]->ws.total, hip_stream, false, check, steps, &preps);
     };
     for (int p = 0; p < gp.n; ++p)
         if ((ps = run(p, true, kStepsAll)) != PLORA_OK) return ps;
@@ -592,7 +611,10 @@ static plora_status group_forward(const plora_group *g, const void *x, const voi
     for (int p = 0; p < gp.n; ++p)
         for (int q = 0; q < gp.n; ++q) fused[p] = fused[p] || (q != p && gp.cell_of[q] == gp.cell_of[p]);
     for (int p = 0; p < gp.n; ++p)
-        if ((ps = run(p, false, kStepPrep | (fused[p] ? 0u : kStepShrink))) != PLORA_OK) return ps;
+        if ((ps = run(p, false, kStepPrep)) != PLORA_OK) return ps;
+    { Bracket b(6, st); PL_TRY(launch_prep(preps.job, preps.n, st)); }
+    for (int p = 0; p < gp.n; ++p)
+        if (!fused[p] && (ps = run(p, false, kStepShrink)) != PLORA_OK) return ps;
     for (int c = 0; c < gp.n_cells; ++c) {
         int members[kMaxGroup], nm = 0;
         for (int p = 0; p < gp.n; ++p)
@@ -628,10 +650,11 @@ static plora_status group_backward(const plora_group *g, const void *x, const vo
     if ((reinterpret_cast<uintptr_t>(workspace) & 255u) != 0) return PLORA_ERR_ALIGN;
     char *ws = static_cast<char *>(workspace);
     // dx_sum: every projection's dX GEMM targets the one tensor, the first overwriting it, the others adding to it
+    PrepList preps;
     auto run = [&](int p, bool check, unsigned steps) {
         return backward_impl(&g->desc[p], x, W[p], A ? A[p] : nullptr, B ? B[p] : nullptr, dy[p], h_saved ? h_saved[p] : nullptr,
                              dx_sum ? dx_sum : (dx ? dx[p] : nullptr), dA ? dA[p] : nullptr, dB ? dB[p] : nullptr, ws + gp.ws_off[p],
-                             gp.m[p]->ws.total, hip_stream, false, check, steps, dx_sum != nullptr && p > 0);
+                             gp.m[p]->ws.total, hip_stream, false, check, steps, dx_sum != nullptr && p > 0, &preps);
     };
     for (int p = 0; p < gp.n; ++p)
         if ((ps = run(p, true, kStepsAll)) != PLORA_OK) return ps;
@@ -650,7 +673,10 @@ static plora_status group_backward(const plora_group *g, const void *x, const vo
             fuse_a[p] = fuse_a[p] || (want_w[p] && want_w[q]);
         }
     for (int p = 0; p < gp.n; ++p)
-        if ((ps = run(p, false, kStepPrep | (fuse_s[p] ? 0u : kStepShrink))) != PLORA_OK) return ps;
+        if ((ps = run(p, false, kStepPrep)) != PLORA_OK) return ps;
+    if (preps.n > 0) { Bracket b(6, st); PL_TRY(launch_prep(preps.job, preps.n, st)); }
+    for (int p = 0; p < gp.n; ++p)
+        if (!fuse_s[p] && (ps = run(p, false, kStepShrink)) != PLORA_OK) return ps;
     for (int c = 0; c < gp.n_cells; ++c) {
         int members[kMaxGroup], nm = 0;
         for (int p = 0; p < gp.n; ++p)

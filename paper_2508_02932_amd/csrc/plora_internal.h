@@ -294,10 +294,11 @@ template <class In> PLORA_HD GemmTile derive_tile(const In &in, int n_seg, int64
         if (k < 0 || in.row1(s) <= in.row0(s)) continue;
         const int r = in.rank(s);
         if (gt.n_own < 2) {
-            GemmSeg &q = gt.s[gt.n_own];
+            GemmSeg q;
             q.row0 = in.row0(s); q.row1 = in.row1(s); q.rp = pad_to(r, kRankPadGemm); q.r = r; q.hb_off = in.hb_off(s);
             q.B = in.ext_b(k); q.ap_off = in.ap_off(k);
-            if (gt.n_own == 0) gt.first_seg = s;
+            if (gt.n_own == 0) { gt.s[0] = q; gt.first_seg = s; }     // (no indexed access: the record stays in registers)
+            else gt.s[1] = q;
         } else if (gt.n_own == 2) {
             gt.third_seg = s;
         }
@@ -446,9 +447,19 @@ constexpr int kLdsSlots = 48;
 // workspace; packing of A_k (bf16 path: A_k^T [r16][d_in] with zero rows beyond r, and / or A_k padded to rp
 // columns); transposed bf16 copy of a saved activation, zt[j][t] = bf16(h[t][j]) (bf16 backward).
 // want_bp (instead of want_ap, W stored [d_out][d_in]): B_k^T [d_out][rp] with zero columns beyond r into `ap`.
-hipError_t launch_prep(const uint32_t *desc_host, int n_words, const MetaHeader &h, char *meta_dev, uint32_t *desc_stage,
-                       void *zero_dev, void *at, void *ap, bool want_at, bool want_ap, bool want_bp, int max_rank, const float *hf,
-                       void *zt, hipStream_t st);
+// A grouped call prepares its projections in one launch when their descriptions fit one kernel argument together.
+struct PrepJob {
+    const uint32_t *desc_host;    // the compact description
+    int n_words, max_rank;        // max_rank: over all adapters
+    MetaHeader h;
+    char *meta_dev;
+    uint32_t *desc_stage;
+    void *zero_dev, *at, *ap;
+    bool want_at, want_ap, want_bp;
+    const float *hf;
+    void *zt;
+};
+hipError_t launch_prep(const PrepJob *jobs, int n_jobs, hipStream_t st);
 
 // bf16 path -------------------------------------------------------------------------------------
 // Skinny product over token blocks: acc[t][j] = sum_c S[t][c] * Bm_k[j][c]  (c < C).

@@ -265,12 +265,19 @@ __device__ inline void write_outputs(const SegInfo &g, float mult, int mode, con
 }
 
 // Sums the partial tiles of the splits (fixed order) and writes the outputs, 16 rows of a token block per workgroup.
-// GROUP: the partial tiles are those of a fused pass (pitch = the fused rank of the segment's adapter); mv is the view of
-// projection `proj`, whose columns start behind those of the projections before it.
+// GROUP: the partial tiles are those of a fused pass (pitch = the fused rank of the segment's adapter); blockIdx.z is the
+// projection, whose columns start behind those of the projections before it.
+struct GroupOut { SkinnyOut p[kMaxGroup]; };
 template <bool GROUP>
-__global__ void __launch_bounds__(256) k_skinny_finish(MetaView mv, int mode, const float *__restrict__ part, int n_split, int max_r16, SkinnyOut out,
-                                                      std::conditional_t<GROUP, GroupView, NoGroup> gv, int proj)
+__global__ void __launch_bounds__(256) k_skinny_finish(MetaView mv0, int mode, const float *__restrict__ part, int n_split, int max_r16,
+                                                      std::conditional_t<GROUP, GroupOut, SkinnyOut> outs,
+                                                      std::conditional_t<GROUP, GroupView, NoGroup> gv)
 {
+    const int proj = GROUP ? blockIdx.z : 0;
+    MetaView mv = mv0;
+    SkinnyOut out;
+    if constexpr (GROUP) { mv = gv.mv[proj]; out = outs.p[proj]; }
+    else out = outs;
     constexpr int FR = 16;                            // token rows per workgroup (grid.y slices of a block)
     __shared__ float tile[FR * PLORA_MAX_RANK];       // [FR][r16], pitch r16
     const int blk = blockIdx.x;
@@ -352,7 +359,7 @@ hipError_t launch_skinny_bf16(const MetaView &mv, const MetaHeader &h, int mode,
     if (e != hipSuccess) return e;
     const SkinnyOut out{hf, static_cast<uint16_t *>(hb), static_cast<uint16_t *>(zt), zt_scaled ? 1 : 0};
     hipLaunchKernelGGL(k_skinny_finish<false>, dim3((unsigned)h.n_blocks, kSkinnyRows / 16), dim3(256), 0, st, mv, mode, part, n_split, (int)h.max_r16, out,
-                       NoGroup{0}, 0);
+                       NoGroup{0});
     return hipGetLastError();
 }
 
@@ -373,12 +380,15 @@ hipError_t launch_skinny_group(const GroupView &gv, const MetaHeader &hv, const 
                        static_cast<const uint16_t *>(x), (int)C, static_cast<const uint16_t *>(nullptr),
                        static_cast<const uint16_t *>(zero), part, per, (int)gv.max_r16, gv);
     hipError_t e = hipGetLastError();
-    for (int p = 0; p < gv.n_proj && e == hipSuccess; ++p) {
-        const SkinnyOut out{hf[p], static_cast<uint16_t *>(hb[p]), static_cast<uint16_t *>(zt[p]), 0};
-        hipLaunchKernelGGL(k_skinny_finish<true>, dim3((unsigned)hv.n_blocks, kSkinnyRows / 16), dim3(256), 0, st, gv.mv[p], 0, part,
-                           n_split, (int)gv.max_r16, out, gv, p);
-        e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    GroupOut outs;
+    for (int p = 0; p < kMaxGroup; ++p) {
+        const int q = p < gv.n_proj ? p : 0;
+        outs.p[p] = SkinnyOut{hf[q], static_cast<uint16_t *>(hb[q]), static_cast<uint16_t *>(zt[q]), 0};
     }
+    hipLaunchKernelGGL(k_skinny_finish<true>, dim3((unsigned)hv.n_blocks, kSkinnyRows / 16, (unsigned)gv.n_proj), dim3(256), 0, st, gv.mv[0], 0,
+                       part, n_split, (int)gv.max_r16, outs, gv);
+    e = hipGetLastError();
     return e;
 }
 

@@ -66,38 +66,32 @@ static hipError_t upload_words(uint32_t *dst_dev, const uint32_t *src_host, int 
 
 // ---- what the workgroups of the preparation kernel read of the description -------------------------
 // Offsets are prefix sums over adapters or segments.  Every lane of a wave takes one entry and the wave sums or scans them
-// with shuffles: one trip to memory instead of one per entry (a loop over 32 adapters and 32 segments on one thread was
+// in registers: one trip to memory instead of one per entry (a loop over 32 adapters and 32 segments on one thread was
 // 25 us of every call).
-__device__ inline int wave_sum(int v)
+__device__ inline int wave_scan(int v)                    // inclusive; lane moves inside the vector ALU (DPP)
 {
-#pragma unroll
-    for (int d = 32; d; d >>= 1) v += __shfl_xor(v, d);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);       // row_shr 1, 2, 4, 8 within 16 lanes
+    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);       // last lane of a row into the next row
+    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);       // lane 31 into the upper half
     return v;
 }
 
-__device__ inline int wave_scan(int v, int lane)         // inclusive
-{
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-        const int u = __shfl_up(v, d);
-        if (lane >= d) v += u;
-    }
-    return v;
-}
+__device__ inline int wave_sum(int v) { return __builtin_amdgcn_readlane(wave_scan(v), 63); }
 
-__device__ inline int64_t wave_scan(int64_t v, int lane)
+__device__ inline int64_t wave_scan(int64_t v)
 {
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-        const int64_t u = __shfl_up(v, d);
-        if (lane >= d) v += u;
-    }
-    return v;
+    // three 22-bit digits: 64 of them sum to 28 bits, so each digit is scanned in 32 bits (v < 2^63)
+    const int64_t a = wave_scan((int)(v & 0x3fffff)), b = wave_scan((int)((v >> 22) & 0x3fffff)), c = wave_scan((int)(v >> 44));
+    return a + (b << 22) + (c << 44);
 }
 
 // Sum over the adapters before k of their ranks, each padded to a multiple of `pad`.
 template <class Src> __device__ inline int64_t rank_rows_before(const DescReader<Src> &in, int k, int pad)
 {
+    if (k == 0) return 0;
     const int lane = threadIdx.x & 63;
     int v = 0;
     for (int j = lane; j < k; j += 64) v += pad_to(in.ad_rank(j), pad);
@@ -257,7 +251,7 @@ __device__ inline void block_scan4(int64_t v[4], int64_t tot[4], int64_t (*wave_
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     int64_t inc[4];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) inc[i] = wave_scan(v[i], lane);
+    for (int i = 0; i < 4; ++i) inc[i] = wave_scan(v[i]);
     if (lane == 63) {
 #pragma unroll
         for (int i = 0; i < 4; ++i) wave_tot[wave][i] = inc[i];
@@ -466,25 +460,40 @@ template <class Src> __device__ inline void derive_on_device(const DescReader<Sr
 // Bound by latency: a launch, one trip to the description, a handful of workgroup-wide scans.  Per call, before (tables by
 // one thread, a serial counting sort, 2-byte stores in the packing) and now: 32 adapters in 32 ragged segments 60 and 57 us
 // -> 22 and 28 us (forward, backward); 16 equal segments 18 -> 10 us; 8 segments in 7 row tiles, fp32, 23 -> 9 us.
+// What one description's part of a preparation launch reads and writes.
+struct PrepArgs {
+    char *meta_dst;
+    uint32_t *zero_page;
+    uint16_t *at, *ap, *zt;
+    const float *hf;
+    int32_t want_at, want_ap, pack_bx, n_pack, pack_bx_b, n_pack_b;
+    int32_t word0, block0;        // of this description: first word of the argument, first workgroup of the launch
+};
+// Several descriptions in one launch (the projections of a grouped call).
+constexpr int kPrepBatchWords = 768;
+struct PrepBatch {
+    int32_t n, pad;
+    PrepArgs a[kMaxGroup];
+    uint32_t w[kPrepBatchWords];
+};
+static_assert(sizeof(PrepBatch) <= 3584, "the batch must fit a kernel argument");
+
 struct WordsInArg {
-    const DescChunk &c;
-    __device__ inline uint32_t word(int i) const { return c.w[i]; }
+    const uint32_t *w;
+    __device__ inline uint32_t word(int i) const { return w[i]; }
 };
 
 template <class Src>
-__device__ inline void prep_body(const DescReader<Src> &in, char *meta_dst, uint32_t *zero_page, uint16_t *at, uint16_t *ap,
-                                 int want_at, int want_ap, int pack_bx, int n_pack, int pack_bx_b, int n_pack_b,
-                                 const float *hf, uint16_t *zt, char *shared_mem)
+__device__ inline void prep_body(const DescReader<Src> &in, const PrepArgs &pa, int b, char *shared_mem)
 {
-    int b = blockIdx.x;
     if (b == 0) {
-        zero_page[threadIdx.x] = 0u;     // kZeroBytes = 256 * 4
-        derive_on_device(in, meta_dst, shared_mem);
+        pa.zero_page[threadIdx.x] = 0u;  // kZeroBytes = 256 * 4
+        derive_on_device(in, pa.meta_dst, shared_mem);
         return;
     }
     b -= 1;
-    if (b < n_pack) {
-        const int k = b / pack_bx;
+    if (b < pa.n_pack) {
+        const int k = b / pa.pack_bx;
         const int64_t D = in.D();
         PackJob a;
         a.A = static_cast<const uint16_t *>(in.ad_ptr(k, 0));
@@ -493,22 +502,22 @@ __device__ inline void prep_body(const DescReader<Src> &in, char *meta_dst, uint
         a.r16 = pad_to(a.r, kRankPadMfma);
         a.at_off = rank_rows_before(in, k, kRankPadMfma) * D;
         a.ap_off = rank_rows_before(in, k, kRankPadGemm) * D;
-        pack_block(a, D, b % pack_bx, at, ap, want_at, want_ap, reinterpret_cast<uint16_t *>(shared_mem));
+        pack_block(a, D, b % pa.pack_bx, pa.at, pa.ap, pa.want_at, pa.want_ap, reinterpret_cast<uint16_t *>(shared_mem));
         return;
     }
-    b -= n_pack;
-    if (b < n_pack_b) {
-        const int k = b / pack_bx_b;
+    b -= pa.n_pack;
+    if (b < pa.n_pack_b) {
+        const int k = b / pa.pack_bx_b;
         const int64_t K = in.K();
         PackBJob a;
         a.B = static_cast<const uint16_t *>(in.ad_ptr(k, 1));
         a.r = in.ad_rank(k);
         a.rp = pad_to(a.r, kRankPadGemm);
         a.bp_off = rank_rows_before(in, k, kRankPadGemm) * K;
-        pack_bt_block(a, K, b % pack_bx_b, ap, reinterpret_cast<uint16_t *>(shared_mem));
+        pack_bt_block(a, K, b % pa.pack_bx_b, pa.ap, reinterpret_cast<uint16_t *>(shared_mem));
         return;
     }
-    b -= n_pack_b;
+    b -= pa.n_pack_b;
     constexpr int kSlices = kSkinnyRows / kTrRows;
     const int blk = b / kSlices, slice = b % kSlices;
     // the segment that owns token block blk, 64 segments at a time, with the running offsets
@@ -530,8 +539,8 @@ __device__ inline void prep_body(const DescReader<Src> &in, char *meta_dst, uint
         }
         const int r16 = pad_to(r, kRankPadMfma), lp = pad_to(len, kTokPad);
         const int64_t he = (int64_t)len * r, ze = (int64_t)r16 * lp;
-        const int nb_inc = wave_scan(nb, lane);
-        const int64_t h_inc = wave_scan(he, lane), z_inc = wave_scan(ze, lane);
+        const int nb_inc = wave_scan(nb);
+        const int64_t h_inc = wave_scan(he), z_inc = wave_scan(ze);
         const uint64_t own = __ballot(blk < blk0 + nb_inc && blk >= blk0 + nb_inc - nb);
         if (own) {
             const int l = __builtin_ctzll(own);
@@ -543,60 +552,101 @@ __device__ inline void prep_body(const DescReader<Src> &in, char *meta_dst, uint
         }
         blk0 += __shfl(nb_inc, 63); h += __shfl(h_inc, 63); zto += __shfl(z_inc, 63);
     }
-    h_to_zt_slice(g, slice, hf, zt, reinterpret_cast<float *>(shared_mem));
+    h_to_zt_slice(g, slice, pa.hf, pa.zt, reinterpret_cast<float *>(shared_mem));
 }
 
-__global__ void __launch_bounds__(256) k_prep_arg(DescChunk c, char *meta_dst, uint32_t *zero_page, uint16_t *at, uint16_t *ap,
-                                                 int want_at, int want_ap, int pack_bx, int n_pack, int pack_bx_b,
-                                                 int n_pack_b, const float *hf, uint16_t *zt)
+__global__ void __launch_bounds__(256) k_prep_arg(DescChunk c, PrepArgs pa)
 {
     extern __shared__ __attribute__((aligned(16))) char prep_lds[];
-    const DescReader<WordsInArg> in{WordsInArg{c}};
-    prep_body(in, meta_dst, zero_page, at, ap, want_at, want_ap, pack_bx, n_pack, pack_bx_b, n_pack_b, hf, zt, prep_lds);
+    prep_body(DescReader<WordsInArg>{WordsInArg{c.w}}, pa, blockIdx.x, prep_lds);
 }
 
-__global__ void __launch_bounds__(256) k_prep_mem(const uint32_t *desc, char *meta_dst, uint32_t *zero_page, uint16_t *at,
-                                                 uint16_t *ap, int want_at, int want_ap, int pack_bx, int n_pack,
-                                                 int pack_bx_b, int n_pack_b, const float *hf, uint16_t *zt)
+__global__ void __launch_bounds__(256) k_prep_batch(PrepBatch c)
 {
     extern __shared__ __attribute__((aligned(16))) char prep_lds[];
-    const DescReader<WordsInMemory> in{WordsInMemory{desc}};
-    prep_body(in, meta_dst, zero_page, at, ap, want_at, want_ap, pack_bx, n_pack, pack_bx_b, n_pack_b, hf, zt, prep_lds);
+    int i = 0;
+    for (int q = 1; q < kMaxGroup; ++q)
+        if (q < c.n && (int)blockIdx.x >= c.a[q].block0) i = q;
+    prep_body(DescReader<WordsInArg>{WordsInArg{c.w + c.a[i].word0}}, c.a[i], (int)blockIdx.x - c.a[i].block0, prep_lds);
 }
 
-hipError_t launch_prep(const uint32_t *desc_host, int n_words, const MetaHeader &h, char *meta_dev, uint32_t *desc_stage,
-                       void *zero_dev, void *at, void *ap, bool want_at, bool want_ap, bool want_bp, int max_rank, const float *hf,
-                       void *zt, hipStream_t st)
+__global__ void __launch_bounds__(256) k_prep_mem(const uint32_t *desc, PrepArgs pa)
+{
+    extern __shared__ __attribute__((aligned(16))) char prep_lds[];
+    prep_body(DescReader<WordsInMemory>{WordsInMemory{desc}}, pa, blockIdx.x, prep_lds);
+}
+
+// The launch arguments of one description, its number of workgroups and the LDS they need.
+static hipError_t prep_args(const PrepJob &j, PrepArgs &pa, int64_t &n_wg, size_t &lds)
 {
     static_assert(PLORA_MAX_ADAPTERS == 256, "one adapter per thread of workgroup 0");
     static_assert(kZeroBytes == 1024, "the zero page is written by one 256-thread workgroup");
-    if (want_ap && want_bp) return hipErrorInvalidValue;            // both live in `ap`
-    const bool pack = h.n_adapters > 0 && (want_at || want_ap);
-    const int pack_bx = (int)((h.D + 63) / 64);
-    const int n_pack = pack ? pack_bx * h.n_adapters : 0;
-    const int pack_bx_b = (int)((h.K + 63) / 64);
-    const int n_pack_b = (want_bp && h.n_adapters > 0) ? pack_bx_b * h.n_adapters : 0;
-    const int n_tr = (hf && zt) ? h.n_blocks * (kSkinnyRows / kTrRows) : 0;
+    if (j.want_ap && j.want_bp) return hipErrorInvalidValue;            // both live in `ap`
+    const MetaHeader &h = j.h;
+    const bool pack = h.n_adapters > 0 && (j.want_at || j.want_ap);
+    pa.meta_dst = j.meta_dev; pa.zero_page = static_cast<uint32_t *>(j.zero_dev);
+    pa.at = static_cast<uint16_t *>(j.at); pa.ap = static_cast<uint16_t *>(j.ap);
+    pa.zt = static_cast<uint16_t *>(j.zt); pa.hf = j.hf;
+    pa.want_at = j.want_at ? 1 : 0; pa.want_ap = j.want_ap ? 1 : 0;
+    pa.pack_bx = (int)((h.D + 63) / 64);
+    pa.n_pack = pack ? pa.pack_bx * h.n_adapters : 0;
+    pa.pack_bx_b = (int)((h.K + 63) / 64);
+    pa.n_pack_b = (j.want_bp && h.n_adapters > 0) ? pa.pack_bx_b * h.n_adapters : 0;
+    pa.word0 = 0; pa.block0 = 0;
+    const int n_tr = (j.hf && j.zt) ? h.n_blocks * (kSkinnyRows / kTrRows) : 0;
+    n_wg = 1 + (int64_t)pa.n_pack + pa.n_pack_b + n_tr;
     // LDS: the derivation of workgroup 0, a pack tile of 64 rows, or 64 tokens of a saved activation
-    size_t lds = derive_lds_bytes(n_words, h.n_seg);
-    if ((n_pack || n_pack_b) && lds < (size_t)128 * max_rank) lds = (size_t)128 * max_rank;
-    if (n_tr && lds < (size_t)256 * max_rank) lds = (size_t)256 * max_rank;
-    const dim3 grid((unsigned)(1 + n_pack + n_pack_b + n_tr));
-    if (n_words <= kChunkWords) {
+    lds = derive_lds_bytes(j.n_words, h.n_seg);
+    if ((pa.n_pack || pa.n_pack_b) && lds < (size_t)128 * j.max_rank) lds = (size_t)128 * j.max_rank;
+    if (n_tr && lds < (size_t)256 * j.max_rank) lds = (size_t)256 * j.max_rank;
+    return hipSuccess;
+}
+
+static hipError_t launch_prep_one(const PrepJob &j, hipStream_t st)
+{
+    PrepArgs pa;
+    int64_t n_wg;
+    size_t lds;
+    hipError_t e = prep_args(j, pa, n_wg, lds);
+    if (e != hipSuccess) return e;
+    if (j.n_words <= kChunkWords) {
         DescChunk c;
-        std::memcpy(c.w, desc_host, (size_t)n_words * 4);
-        hipLaunchKernelGGL(k_prep_arg, grid, dim3(256), lds, st, c, meta_dev, static_cast<uint32_t *>(zero_dev),
-                           static_cast<uint16_t *>(at), static_cast<uint16_t *>(ap), want_at ? 1 : 0, want_ap ? 1 : 0,
-                           pack_bx > 0 ? pack_bx : 1, n_pack, pack_bx_b > 0 ? pack_bx_b : 1, n_pack_b, hf,
-                           static_cast<uint16_t *>(zt));
+        std::memcpy(c.w, j.desc_host, (size_t)j.n_words * 4);
+        hipLaunchKernelGGL(k_prep_arg, dim3((unsigned)n_wg), dim3(256), lds, st, c, pa);
         return hipGetLastError();
     }
-    hipError_t e = upload_words(desc_stage, desc_host, n_words, st);
+    e = upload_words(j.desc_stage, j.desc_host, j.n_words, st);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_prep_mem, grid, dim3(256), lds, st, static_cast<const uint32_t *>(desc_stage), meta_dev,
-                       static_cast<uint32_t *>(zero_dev), static_cast<uint16_t *>(at), static_cast<uint16_t *>(ap),
-                       want_at ? 1 : 0, want_ap ? 1 : 0, pack_bx > 0 ? pack_bx : 1, n_pack, pack_bx_b > 0 ? pack_bx_b : 1,
-                       n_pack_b, hf, static_cast<uint16_t *>(zt));
+    hipLaunchKernelGGL(k_prep_mem, dim3((unsigned)n_wg), dim3(256), lds, st, static_cast<const uint32_t *>(j.desc_stage), pa);
+    return hipGetLastError();
+}
+
+hipError_t launch_prep(const PrepJob *jobs, int n_jobs, hipStream_t st)
+{
+    int words = 0;
+    for (int i = 0; i < n_jobs; ++i) words += jobs[i].n_words;
+    if (n_jobs == 1 || n_jobs > kMaxGroup || words > kPrepBatchWords) {
+        for (int i = 0; i < n_jobs; ++i) {
+            const hipError_t e = launch_prep_one(jobs[i], st);
+            if (e != hipSuccess) return e;
+        }
+        return hipSuccess;
+    }
+    PrepBatch c;
+    c.n = n_jobs; c.pad = 0;
+    int64_t blocks = 0;
+    size_t lds = 0;
+    for (int i = 0, w = 0; i < n_jobs; ++i) {
+        int64_t n_wg;
+        size_t one;
+        const hipError_t e = prep_args(jobs[i], c.a[i], n_wg, one);
+        if (e != hipSuccess) return e;
+        c.a[i].word0 = w; c.a[i].block0 = (int32_t)blocks;
+        std::memcpy(c.w + w, jobs[i].desc_host, (size_t)jobs[i].n_words * 4);
+        w += jobs[i].n_words; blocks += n_wg;
+        lds = one > lds ? one : lds;
+    }
+    hipLaunchKernelGGL(k_prep_batch, dim3((unsigned)blocks), dim3(256), lds, st, c);
     return hipGetLastError();
 }
 
