@@ -6,7 +6,7 @@
 // 48 tokens, 4096 -> 4096, 83 -> 12 us; 512 tokens, contraction 14336 -> 4096 columns, 250 -> 71 us; 1024 tokens, the
 // same, 261 -> 127 us.  What bounds it when the chip is full is the traffic from L2 into LDS (64 KB per compute unit and
 // stage of 64, 0.95 us: 17 TB/s): a loop that reads the operands of the next step during the multiplications, rings of
-// 4 and 6 stages and 256 x 128 tiles of eight waves were all no faster.
+// 4 and 6 stages and 256 x 128 tiles of eight waves were all no faster, and stages of 32 (64-byte pieces of rows) 20 % slower.
 #include "plora_internal.h"
 
 namespace plora {
@@ -290,11 +290,15 @@ __global__ void __launch_bounds__(256, 2) k_gemm_small(MetaView mv, const uint16
             }
 #pragma unroll
             for (int mb = 0; mb < MB; ++mb) xf[mb] = *LDS_PTR(const bf16x8, sb + (xoff[mb] ^ (ks * 64)));
+            // the workgroup that multiplies goes first: its partner on the compute unit is then fetching, and they stay out of
+            // step (128 rows: 4 - 6 % of the kernel; 64 rows: slower by 1 %, left alone)
+            if constexpr (BM == 128) __builtin_amdgcn_s_setprio(1);
 #pragma unroll
             for (int nb = 0; nb < 4; ++nb)
 #pragma unroll
                 for (int mb = 0; mb < MB; ++mb)
                     acc[nb][mb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[nb], xf[mb], acc[nb][mb], 0, 0, 0);
+            if constexpr (BM == 128) __builtin_amdgcn_s_setprio(0);
         }
     }
 
