@@ -439,7 +439,9 @@ GemmPlan gemm_plan(int64_t T, int64_t Kd, int64_t N)
         const double rounds = wgs <= slots ? 1.0 : (double)(int64_t)((wgs + slots - 1.0) / slots);
         return rounds * (t0 + t1 * wgs / (rounds * slots));
     };
-    const double stream_us = (double)Kd * N * 2 / 4.5e6;       // W from HBM
+    // W from HBM, which takes a workgroup on every compute unit (48 tokens, 4096 -> 4096: 128, 256 and 384 workgroups 19.7,
+    // 17.5 and 20.8 us)
+    const double stream_us = (double)Kd * N * 2 / 4.5e6;
     GemmPlan best{0, 1};
     double best_us = nk * stage_us(tiles_of(256, 256), kCus, 0.92, 0.78);
     for (int bm = 64; bm <= 128; bm += 64) {
@@ -448,7 +450,8 @@ GemmPlan gemm_plan(int64_t T, int64_t Kd, int64_t N)
             if (tiles * z > 4.0 * kCus || (z > 1 && (nk < 4.0 * z || (double)z * T * N * 4 > 64e6))) break;
             const double steps = (double)(int64_t)((nk + z - 1.0) / z);
             double us = steps * stage_us(tiles * z, 2.0 * kCus, 0.38, bm == 64 ? 0.24 : 0.62);
-            if (us < stream_us) us = stream_us;
+            const double stream = stream_us * (tiles * z < kCus ? kCus / (tiles * z) : 1.0);
+            if (us < stream) us = stream;
             if (z > 1) us += 4.0 + 0.2 * z + (double)z * T * N * 8 / 5.0e6;
             if (us < best_us) { best_us = us; best.bm = bm; best.n_split = z; }
         }
