@@ -333,7 +333,7 @@ struct PrepList {
 static plora_status forward_impl(const plora_desc *desc, const void *x, const void *W, const void *const *A,
                                  const void *const *B, void *y, float *h_saved, void *workspace, size_t ws_bytes,
                                  void *hip_stream, bool lora_only = false, bool check_only = false, unsigned steps = kStepsAll,
-                                 PrepList *later = nullptr)
+                                 PrepList *later = nullptr, const Nf4Job *nf4 = nullptr)
 {
     Call c;
     plora_status ps = prepare(desc, x, W, A, B, nullptr, nullptr, workspace, ws_bytes, lora_only, c);
@@ -354,6 +354,7 @@ static plora_status forward_impl(const plora_desc *desc, const void *x, const vo
         const PrepJob job{c.words, m.n_words, m.max_rank, m.hdr, ws + L.meta, reinterpret_cast<uint32_t *>(ws + L.desc), ws + L.zero,
                           ws + L.at, ws + L.ap, bf && lora, false, bf && lora && (w_out_in || lora_only), nullptr, nullptr};
         if (later) later->add(job);
+        else if (nf4) { Bracket b(9, st); PL_TRY(launch_prep_nf4(job, *nf4, desc->dtype == PLORA_BF16, st)); }
         else { Bracket b(6, st); PL_TRY(launch_prep(&job, 1, st)); }
     }
     float *hf = h_saved ? h_saved : reinterpret_cast<float *>(ws + L.hf);
@@ -394,7 +395,7 @@ static plora_status backward_impl(const plora_desc *desc, const void *x, const v
                                   const void *const *B, const void *dy, const float *h_saved, void *dx, float *const *dA,
                                   float *const *dB, void *workspace, size_t ws_bytes, void *hip_stream, bool lora_only = false,
                                   bool check_only = false, unsigned steps = kStepsAll, bool dx_accumulate = false,
-                                  PrepList *later = nullptr)
+                                  PrepList *later = nullptr, const Nf4Job *nf4 = nullptr)
 {
     const bool want_w = (dA != nullptr) || (dB != nullptr);
     if (desc && want_w && desc->n_adapters > 0 && (!dA || !dB)) {
@@ -432,6 +433,7 @@ static plora_status backward_impl(const plora_desc *desc, const void *x, const v
                           ws + L.at, ws + L.ap, bf && lora && (need_shrink || dx_at), bf && lora && dx_ap, false,
                           tr ? h_saved : nullptr, tr ? ws + L.zt_h : nullptr};
         if (later) later->add(job);
+        else if (nf4) { Bracket b(9, st); PL_TRY(launch_prep_nf4(job, *nf4, desc->dtype == PLORA_BF16, st)); }
         else { Bracket b(6, st); PL_TRY(launch_prep(&job, 1, st)); }
     }
 
@@ -994,11 +996,8 @@ plora_status plora_linear_fwd_nf4(const plora_desc *desc, const void *x, const v
         // every other argument is checked before the weight is expanded, so that an error enqueues nothing
         ps = forward_impl(desc, x, W, A, B, y, h_saved, workspace, inner, hip_stream, false, true);
         if (ps != PLORA_OK) return ps;
-        if (desc->T > 0) {
-            ps = plora_nf4_dequantize(W_codes, W_absmax, desc->d_in * desc->d_out, desc->dtype, W, hip_stream);
-            if (ps != PLORA_OK) return ps;
-        }
-        return forward_impl(desc, x, W, A, B, y, h_saved, workspace, inner, hip_stream);
+        const Nf4Job job{static_cast<const uint32_t *>(W_codes), W_absmax, W, desc->d_in * desc->d_out};
+        return forward_impl(desc, x, W, A, B, y, h_saved, workspace, inner, hip_stream, false, false, kStepsAll, nullptr, &job);
     )
 }
 
@@ -1013,11 +1012,9 @@ plora_status plora_linear_bwd_nf4(const plora_desc *desc, const void *x, const v
         if (ps != PLORA_OK) return ps;
         ps = backward_impl(desc, x, W, A, B, dy, h_saved, dx, dA, dB, workspace, inner, hip_stream, false, true);
         if (ps != PLORA_OK) return ps;
-        if (dx && desc->T > 0) {
-            ps = plora_nf4_dequantize(W_codes, W_absmax, desc->d_in * desc->d_out, desc->dtype, W, hip_stream);
-            if (ps != PLORA_OK) return ps;
-        }
-        return backward_impl(desc, x, W, A, B, dy, h_saved, dx, dA, dB, workspace, inner, hip_stream);
+        const Nf4Job job{static_cast<const uint32_t *>(W_codes), W_absmax, W, desc->d_in * desc->d_out};
+        return backward_impl(desc, x, W, A, B, dy, h_saved, dx, dA, dB, workspace, inner, hip_stream, false, false, kStepsAll, false, nullptr,
+                             dx && desc->T > 0 ? &job : nullptr);
     )
 }
 

@@ -448,6 +448,14 @@ constexpr int kLdsSlots = 48;
 // columns); transposed bf16 copy of a saved activation, zt[j][t] = bf16(h[t][j]) (bf16 backward).
 // want_bp (instead of want_ap, W stored [d_out][d_in]): B_k^T [d_out][rp] with zero columns beyond r into `ap`.
 // A grouped call prepares its projections in one launch when their descriptions fit one kernel argument together.
+// An NF4 weight to expand in the same launch (the two do not depend on each other).
+struct Nf4Job {
+    const uint32_t *codes;
+    const float *absmax;
+    void *out;
+    int64_t n_elems;
+};
+int nf4_workgroups(int64_t n_elems);      // 0: no device
 struct PrepJob {
     const uint32_t *desc_host;    // the compact description
     int n_words, max_rank;        // max_rank: over all adapters
@@ -460,6 +468,7 @@ struct PrepJob {
     void *zt;
 };
 hipError_t launch_prep(const PrepJob *jobs, int n_jobs, hipStream_t st);
+hipError_t launch_prep_nf4(const PrepJob &job, const Nf4Job &w, bool bf16, hipStream_t st);
 
 // bf16 path -------------------------------------------------------------------------------------
 // Skinny product over token blocks: acc[t][j] = sum_c S[t][c] * Bm_k[j][c]  (c < C).
