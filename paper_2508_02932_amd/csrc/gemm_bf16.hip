@@ -582,9 +582,10 @@ __global__ void __launch_bounds__(512) k_gemm(const GemmTile *__restrict__ tiles
 
 template <bool FWD, bool ACC>
 static hipError_t launch_variant(const MetaView &mv, const MetaHeader &h, int64_t Kd, int64_t N, const void *S, const void *W,
-                                 const void *side, const void *ap, const void *zero, void *C, hipStream_t st)
+                                 const void *side, const void *ap, const void *zero, void *C, int row_tiles,
+                                 hipStream_t st)
 {
-    const int tiles_m = (int)((h.T + BM - 1) / BM), tiles_n = (int)((N + BN - 1) / BN);
+    const int tiles_m = row_tiles, tiles_n = (int)((N + BN - 1) / BN);
     auto kern = k_gemm<FWD, ACC>;
     {
         hipError_t e = allow_full_lds(reinterpret_cast<const void *>(kern), (FWD ? 5 : 6) + (ACC ? 4 : 0));
@@ -606,15 +607,16 @@ static hipError_t launch_variant(const MetaView &mv, const MetaHeader &h, int64_
 
 hipError_t launch_gemm_bf16(const MetaView &mv, const MetaHeader &h, bool w_rows_contract, int64_t Kd, int64_t N,
                             const void *S, const void *W, const void *side, const void *ap, const void *zero, void *C,
-                            bool accumulate, hipStream_t st)
+                            bool accumulate, int row_tiles, hipStream_t st)
 {
     if (h.T == 0) return hipSuccess;
+    if (row_tiles < 1 || row_tiles > (int)((h.T + BM - 1) / BM)) return hipErrorInvalidValue;
     if (accumulate) {
-        if (w_rows_contract) return launch_variant<true, true>(mv, h, Kd, N, S, W, side, ap, zero, C, st);
-        return launch_variant<false, true>(mv, h, Kd, N, S, W, side, ap, zero, C, st);
+        if (w_rows_contract) return launch_variant<true, true>(mv, h, Kd, N, S, W, side, ap, zero, C, row_tiles, st);
+        return launch_variant<false, true>(mv, h, Kd, N, S, W, side, ap, zero, C, row_tiles, st);
     }
-    if (w_rows_contract) return launch_variant<true, false>(mv, h, Kd, N, S, W, side, ap, zero, C, st);
-    return launch_variant<false, false>(mv, h, Kd, N, S, W, side, ap, zero, C, st);
+    if (w_rows_contract) return launch_variant<true, false>(mv, h, Kd, N, S, W, side, ap, zero, C, row_tiles, st);
+    return launch_variant<false, false>(mv, h, Kd, N, S, W, side, ap, zero, C, row_tiles, st);
 }
 
 }  // namespace plora

@@ -52,13 +52,14 @@ __device__ inline int64_t gs_readlane64(int64_t v, int l)
 // One workgroup per (row tile of BM, column tile of 128, split z of the contraction); BM / 32 waves, each 64 (32 when
 // BM = 64) x 64 outputs on MFMA 16x16x32.  Stages of 64 contraction elements go HBM -> LDS directly through a ring of NST.
 // Split z multiplies its share of the main steps and every n_split-th extension step.
+// row_tile0 > 0: the rows are those of the 256-row tiles from entry row_tile0 of the tile order on (tiles_m counts them).
 // part != nullptr: the fp32 partial tile goes to part[z][M][N] (summed by k_gemm_finish), else bf16 to Cout.
 template <bool FWD, int BM, int NST, bool ACC>
 __global__ void __launch_bounds__(256, 2) k_gemm_small(MetaView mv, const uint16_t *__restrict__ S,
                                               const uint16_t *__restrict__ W, const uint16_t *__restrict__ side,
                                               const uint16_t *__restrict__ ap, const uint16_t *__restrict__ zero,
                                               uint16_t *__restrict__ Cout, float *__restrict__ part, int tiles_m, int tiles_n,
-                                              int n_split, int M, int Kd, int N, int n_seg)
+                                              int n_split, int row_tile0, int M, int Kd, int N, int n_seg)
 {
     static_assert(BM == 64 || BM == 128, "");
     constexpr int NW = 4;                                      // waves, two by two
@@ -76,7 +77,11 @@ __global__ void __launch_bounds__(256, 2) k_gemm_small(MetaView mv, const uint16
         const int per = n_wg / 8;
         if (id < per * 8) id = (id % 8) * per + id / 8;
     }
-    const int m0 = (id % tiles_m) * BM;
+    int m0 = (id % tiles_m) * BM;
+    if (row_tile0 > 0) {                                       // the rest of a product that the 256-row kernel began
+        m0 = mv.tile_order[row_tile0 + m0 / kGemmTileRows] * kGemmTileRows + m0 % kGemmTileRows;
+        if (m0 >= M) return;
+    }
     const int rest = id / tiles_m;
     const int n0 = (rest % tiles_n) * GS_BN, z = rest / tiles_n;
     const int m1 = m0 + BM < M ? m0 + BM : M;
@@ -380,18 +385,19 @@ __global__ void __launch_bounds__(256) k_gemm_finish(const float *__restrict__ p
 
 template <bool FWD, int BM, int NST, bool ACC>
 static hipError_t launch_small(const MetaView &mv, const MetaHeader &h, int64_t Kd, int64_t N, const void *S, const void *W,
-                               const void *side, const void *ap, const void *zero, void *C, float *part, int n_split, int slot,
-                               hipStream_t st)
+                               const void *side, const void *ap, const void *zero, void *C, float *part, int n_split, int row_tile0,
+                               int slot, hipStream_t st)
 {
     constexpr size_t lds = (size_t)NST * (BM + GS_BN) * GS_BK * 2;
-    const int tiles_m = (int)((h.T + BM - 1) / BM), tiles_n = (int)((N + GS_BN - 1) / GS_BN);
+    const int all256 = (int)((h.T + kGemmTileRows - 1) / kGemmTileRows);
+    const int tiles_m = row_tile0 > 0 ? (all256 - row_tile0) * (kGemmTileRows / BM) : (int)((h.T + BM - 1) / BM), tiles_n = (int)((N + GS_BN - 1) / GS_BN);
     auto kern = k_gemm_small<FWD, BM, NST, ACC>;
     hipError_t e = allow_full_lds(reinterpret_cast<const void *>(kern), slot);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(kern, dim3((unsigned)(tiles_m * tiles_n * n_split)), dim3(256), lds, st, mv, static_cast<const uint16_t *>(S),
                        static_cast<const uint16_t *>(W), static_cast<const uint16_t *>(side), static_cast<const uint16_t *>(ap),
                        static_cast<const uint16_t *>(zero), static_cast<uint16_t *>(C), n_split > 1 ? part : nullptr, tiles_m, tiles_n,
-                       n_split, (int)h.T, (int)Kd, (int)N, (int)h.n_seg);
+                       n_split, row_tile0, (int)h.T, (int)Kd, (int)N, (int)h.n_seg);
     e = hipGetLastError();
     if (e != hipSuccess || n_split <= 1) return e;
     const int64_t n_vec = h.T * N / 4;
@@ -404,8 +410,8 @@ static hipError_t dispatch_small(const GemmPlan &p, const MetaView &mv, const Me
                                  const void *W, const void *side, const void *ap, const void *zero, void *C, float *part, hipStream_t st)
 {
     constexpr int slot = 16 + (FWD ? 1 : 0) + (ACC ? 2 : 0);
-    if (p.bm == 64) return launch_small<FWD, 64, 3, ACC>(mv, h, Kd, N, S, W, side, ap, zero, C, part, p.n_split, slot, st);
-    return launch_small<FWD, 128, 2, ACC>(mv, h, Kd, N, S, W, side, ap, zero, C, part, p.n_split, slot + 4, st);
+    if (p.bm == 64) return launch_small<FWD, 64, 3, ACC>(mv, h, Kd, N, S, W, side, ap, zero, C, part, p.n_split, p.big_tiles, slot, st);
+    return launch_small<FWD, 128, 2, ACC>(mv, h, Kd, N, S, W, side, ap, zero, C, part, p.n_split, p.big_tiles, slot + 4, st);
 }
 
 hipError_t launch_gemm_small_bf16(const GemmPlan &p, const MetaView &mv, const MetaHeader &h, bool w_rows_contract, int64_t Kd, int64_t N,
@@ -429,7 +435,9 @@ hipError_t launch_gemm_small_bf16(const GemmPlan &p, const MetaView &mv, const M
 // choice changes both sides were timed (256-tile kernel against the small tiles): 2048 x 4096 -> 4096 83 against 65 us,
 // 3072 x 4096 -> 4096 92 against 112 us, 1024 x 4096 -> 14336 103 against 118 us, 512 x 4096 -> 14336 85 against 62 us.
 // From three rounds on the small tiles lose (L2 traffic and power: 8192 x 4096 -> 4096 301 against 214 us), so they are
-// not considered there.  A split keeps four stages or more; the partial tiles stay below 64 MB.
+// not considered there.  Between one and eight rounds of the 256-tile kernel a last round that is mostly empty goes to the
+// small tiles instead (two launches; us, 256-tile kernel alone and now: 4400 x 4096 -> 4096 184 and 151, 5000 tokens 182 and
+// 157, 10000 x 2048 -> 2048 99 and 87, 9000 x 4096 -> 4096 286 and 261, 13000 393 and 366, 6144 183 and 179).  A split keeps four stages or more; the partial tiles stay below 64 MB.
 GemmPlan gemm_plan(int64_t T, int64_t Kd, int64_t N)
 {
     constexpr double kCus = 256.0;                             // compute units of an MI355X
@@ -442,19 +450,28 @@ GemmPlan gemm_plan(int64_t T, int64_t Kd, int64_t N)
     // W from HBM, which takes a workgroup on every compute unit (48 tokens, 4096 -> 4096: 128, 256 and 384 workgroups 19.7,
     // 17.5 and 20.8 us)
     const double stream_us = (double)Kd * N * 2 / 4.5e6;
-    GemmPlan best{0, 1};
+    const int64_t all256 = (T + kGemmTileRows - 1) / kGemmTileRows;
+    GemmPlan best{0, 1, (int)all256};
     double best_us = nk * stage_us(tiles_of(256, 256), kCus, 0.92, 0.78);
     for (int bm = 64; bm <= 128; bm += 64) {
-        const double tiles = tiles_of(bm, GS_BN);
+        const double tiles = tiles_of(bm, GS_BN), t1 = bm == 64 ? 0.24 : 0.62;
         for (int z = 1; z <= 16; ++z) {
             if (tiles * z > 4.0 * kCus || (z > 1 && (nk < 4.0 * z || (double)z * T * N * 4 > 64e6))) break;
             const double steps = (double)(int64_t)((nk + z - 1.0) / z);
-            double us = steps * stage_us(tiles * z, 2.0 * kCus, 0.38, bm == 64 ? 0.24 : 0.62);
+            double us = steps * stage_us(tiles * z, 2.0 * kCus, 0.38, t1);
             const double stream = stream_us * (tiles * z < kCus ? kCus / (tiles * z) : 1.0);
             if (us < stream) us = stream;
             if (z > 1) us += 4.0 + 0.2 * z + (double)z * T * N * 8 / 5.0e6;
-            if (us < best_us) { best_us = us; best.bm = bm; best.n_split = z; }
+            if (us < best_us) { best_us = us; best = GemmPlan{bm, z, 0}; }
         }
+        // whole rounds of 256 x 256 tiles, the row tiles left over in small tiles (a launch more: 3 us)
+        const int64_t cols256 = (N + 255) / 256, rounds = (int64_t)(tiles_of(256, 256) / kCus);
+        const int64_t big = rounds * (int64_t)kCus / cols256;
+        if (rounds < 1 || rounds > 8 || big < 1 || big >= all256) continue;
+        const double rest = (double)(all256 - big) * (kGemmTileRows / bm) * (double)((N + GS_BN - 1) / GS_BN);
+        if (rest > 4.0 * kCus) continue;
+        const double us = 3.0 + nk * (stage_us((double)(big * cols256), kCus, 0.92, 0.78) + stage_us(rest, 2.0 * kCus, 0.38, t1));
+        if (us < 0.97 * best_us) { best_us = us; best = GemmPlan{bm, 1, (int)big}; }
     }
     return best;
 }

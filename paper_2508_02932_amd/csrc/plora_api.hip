@@ -303,8 +303,11 @@ static hipError_t run_gemm(const HostMeta &m, const WorkspaceLayout &L, char *ws
                            int64_t N, const void *S, const void *W, void *C, bool accumulate, hipStream_t st)
 {
     const MetaView mv = device_view(m, L, ws);
-    if (plan.bm == 0)
-        return launch_gemm_bf16(mv, m.hdr, w_rows_contract, Kd, N, S, W, ws + L.hb, ws + L.ap, ws + L.zero, C, accumulate, st);
+    if (plan.big_tiles > 0) {
+        const hipError_t e = launch_gemm_bf16(mv, m.hdr, w_rows_contract, Kd, N, S, W, ws + L.hb, ws + L.ap, ws + L.zero, C, accumulate,
+                                              plan.big_tiles, st);
+        if (e != hipSuccess || plan.bm == 0) return e;
+    }
     return launch_gemm_small_bf16(plan, mv, m.hdr, w_rows_contract, Kd, N, S, W, ws + L.hb, ws + L.ap, ws + L.zero, C, accumulate,
                                   reinterpret_cast<float *>(ws + L.gpart), st);
 }

@@ -484,14 +484,16 @@ hipError_t launch_skinny_bf16(const MetaView &mv, const MetaHeader &h, int mode,
 //   otherwise       : Wop = W [N][Kd] (contraction index is contiguous),     ext_k = ap + GemmSeg::ap_off [N][rp]
 //   W[d_in][d_out]: forward (S = x, Kd = d_in, N = d_out) is the first form, backward (S = dy, Kd = d_out, N = d_in)
 //   the second; W[d_out][d_in]: the other way round.
+//   row_tiles: how many row tiles to compute, in the order of the tile_order table
 //   accumulate: C += the product (C is read in the epilogue and the sum rounded once more), otherwise C is overwritten
 hipError_t launch_gemm_bf16(const MetaView &mv, const MetaHeader &h, bool w_rows_contract, int64_t Kd, int64_t N,
                             const void *S, const void *W, const void *side, const void *ap, const void *zero, void *C,
-                            bool accumulate, hipStream_t st);
+                            bool accumulate, int row_tiles, hipStream_t st);
 // The same product in small tiles with the contraction split over workgroups (gemm_small_bf16.hip).
 struct GemmPlan {
     int bm;                   // rows of the output tile: 0: k_gemm's 256 x 256 tiles, otherwise tiles of bm x 128
     int n_split;              // splits of the contraction; above 1 the fp32 partial tiles take n_split * T * N * 4 bytes
+    int big_tiles;            // row tiles that k_gemm computes (all of them when bm is 0); the small tiles compute the rest
 };
 GemmPlan gemm_plan(int64_t T, int64_t Kd, int64_t N);
 hipError_t launch_gemm_small_bf16(const GemmPlan &p, const MetaView &mv, const MetaHeader &h, bool w_rows_contract, int64_t Kd, int64_t N,

@@ -48,11 +48,14 @@ def test_more_than_64_segments_in_the_call_and_in_a_later_row_tile():
 
 
 @pytest.mark.parametrize("w_layout", [0, 1])
-def test_256_row_tiles_with_several_segments_and_ragged_edges(w_layout):
-    """Enough row tiles for the 256 x 256 kernel: tiles with one, two and more than two segments, partial last tiles and step."""
+@pytest.mark.parametrize("D,K,tail", [(264, 648, 77), (512, 512, 12501)])
+def test_256_row_tiles_with_several_segments_and_ragged_edges(D, K, tail, w_layout):
+    """Enough row tiles for the 256 x 256 kernel: tiles with one, two and more than two segments, partial last tiles and step.
+    35336 tokens: whole rounds in 256-row tiles and the rest of the row tiles (in the order that kernel walks them) in small
+    ones; 32760 tokens, 512 -> 512: one full round."""
     import oracle
-    lengths = [300, 7, 90, 0, 61, 4000, 1, 2, 30, 9000, 255, 513, 21000, 77]
-    lin = wl.small("gemm_256_ragged", "bf16", 264, 648, lengths=lengths, seg_adapter=[i % 4 if i % 6 else -1 for i in range(len(lengths))],
+    lengths = [300, 7, 90, 0, 61, 4000, 1, 2, 30, 9000, 255, 513, 21000 if tail == 77 else 6000, tail]
+    lin = wl.small(f"gemm_256_ragged_{D}", "bf16", D, K, lengths=lengths, seg_adapter=[i % 4 if i % 6 else -1 for i in range(len(lengths))],
                    ranks=[8, 72, 3, 128], scales=[2.0, 1.0, 0.5, 0.25], seed=229)
     run_and_compare(lin, impl=oracle.matmul, w_layout=w_layout)
 
