@@ -19,6 +19,9 @@ typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;
 
 constexpr int GS_BN = 128;                 // output columns per workgroup
 constexpr int GS_BK = 64;                  // contraction elements per stage
+// Ring slots of the two tiles; two workgroups share the 160 KB of a compute unit.  deep: a third slot of the W tile (80 KB).
+constexpr int gs_ring_x(int bm) { return bm == 128 ? 2 : 3; }
+constexpr int gs_ring_w(int bm, bool deep) { return bm == 128 && !deep ? 2 : 3; }
 
 __device__ inline uint32_t gs_pack_bf16x2(float lo, float hi)
 {
@@ -50,11 +53,11 @@ __device__ inline int64_t gs_readlane64(int64_t v, int l)
 
 // FWD names the form of the weight operand as in gemm_bf16.hip: W[Kd][N] (contraction index = row index), else W[N][Kd].
 // One workgroup per (row tile of BM, column tile of 128, split z of the contraction); BM / 32 waves, each 64 (32 when
-// BM = 64) x 64 outputs on MFMA 16x16x32.  Stages of 64 contraction elements go HBM -> LDS directly through a ring of NST.
+// BM = 64) x 64 outputs on MFMA 16x16x32.  Stages of 64 contraction elements go HBM -> LDS directly, through one ring for the token tile and one for W.
 // Split z multiplies its share of the main steps and every n_split-th extension step.
 // row_tile0 > 0: the rows are those of the 256-row tiles from entry row_tile0 of the tile order on (tiles_m counts them).
 // part != nullptr: the fp32 partial tile goes to part[z][M][N] (summed by k_gemm_finish), else bf16 to Cout.
-template <bool FWD, int BM, int NST, bool ACC>
+template <bool FWD, int BM, bool DEEP, bool ACC>
 __global__ void __launch_bounds__(256, 2) k_gemm_small(MetaView mv, const uint16_t *__restrict__ S,
                                               const uint16_t *__restrict__ W, const uint16_t *__restrict__ side,
                                               const uint16_t *__restrict__ ap, const uint16_t *__restrict__ zero,
@@ -65,7 +68,10 @@ __global__ void __launch_bounds__(256, 2) k_gemm_small(MetaView mv, const uint16
     constexpr int NW = 4;                                      // waves, two by two
     constexpr int WM = BM / 2;                                 // rows per wave
     constexpr int MB = WM / 16;                                // 16-row blocks per wave
-    constexpr int XT = BM * GS_BK * 2, STAGE = XT + GS_BN * GS_BK * 2;
+    constexpr int XT = BM * GS_BK * 2, WT = GS_BN * GS_BK * 2;
+    constexpr int NX = gs_ring_x(BM), NWR = gs_ring_w(BM, DEEP);               // ring slots of the token tile and of the W tile
+    // equal rings: the two tiles of a stage side by side; deep: the W ring behind the token ring
+    constexpr int XSLOT = DEEP ? XT : XT + WT, WSLOT = DEEP ? WT : XT + WT, kW = DEEP ? NX * XT : XT;
     constexpr int XL = BM / 8 / NW, WL = 16 / NW, LPS = XL + WL;   // load instructions (1 KB) per wave per stage
     extern __shared__ __attribute__((aligned(1024))) char lds[];
 
@@ -93,7 +99,8 @@ __global__ void __launch_bounds__(256, 2) k_gemm_small(MetaView mv, const uint16
 
     // ---- the segments that overlap this row tile: a window of up to 64 records of the segment table, one per lane, from
     // which the extension steps are looked up (tiles with segments beyond the window move it; rare)
-    int win = n_seg <= 64 ? 0 : mv.tile[m0 / kGemmTileRows].first_seg;
+    const int win0 = n_seg <= 64 ? 0 : mv.tile[m0 / kGemmTileRows].first_seg;
+    int win = win0;
     int s_row0, s_row1, s_rp, s_r, s_cnt, s_cum, win_first = 0, win_ext;
     int64_t s_hb, s_op;                                        // s_op: GemmSeg::B (as address) or ap_off
     auto load_window = [&]() {
@@ -121,7 +128,7 @@ __global__ void __launch_bounds__(256, 2) k_gemm_small(MetaView mv, const uint16
     load_window();
     int n_ext = win_ext;
     if (n_seg > 64) {                                          // count the extension steps of the segments beyond the window
-        for (int w = win + 64; w < n_seg; w += 64) {
+        for (int w = win0 + 64; w < n_seg; w += 64) {
             const int idx = w + lane;
             int cnt = 0, past = 1;
             if (idx < n_seg) {
@@ -178,40 +185,35 @@ __global__ void __launch_bounds__(256, 2) k_gemm_small(MetaView mv, const uint16
     auto load_off = [&](uint32_t off, const char *base, uint32_t dst) {
         asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(off), "s"(base), "s"(dst));
     };
-    auto issue = [&](int it, int slot) {
-        const uint32_t dx = lds_base + slot * STAGE + wave * 1024, dw = dx + XT;
-        if (it < n_main) {
-            const int k0 = (k_lo + it) * GS_BK;
-            const char *gx = base_x + (int64_t)k0 * 2;
-            const char *gw = base_w + (FWD ? (int64_t)k0 * ldw * 2 : (int64_t)k0 * 2);
-            if (k0 + GS_BK <= Kd) {
-#pragma unroll
-                for (int jj = 0; jj < WL; ++jj) load_off(off_w[jj], gw, dw + jj * (NW * 1024));
-#pragma unroll
-                for (int jj = 0; jj < XL; ++jj) load_off(off_x[jj], gx, dx + jj * (NW * 1024));
-            } else {                                           // last, partial step: chunks past the end read the zero page
-#pragma unroll
-                for (int jj = 0; jj < WL; ++jj) {
-                    const int u = FWD ? (wave + NW * jj) * 4 + (lane >> 4) : (wave + NW * jj) * 8 + lrow;
-                    const bool ok = FWD ? k0 + u < Kd : k0 + row_chunk(u) * 8 < Kd;
-                    load_ptr(ok ? static_cast<const void *>(gw + off_w[jj]) : zero, dw + jj * (NW * 1024));
-                }
-#pragma unroll
-                for (int jj = 0; jj < XL; ++jj) {
-                    const int u = (wave + NW * jj) * 8 + lrow;
-                    load_ptr(k0 + row_chunk(u) * 8 < Kd ? static_cast<const void *>(gx + off_x[jj]) : zero, dx + jj * (NW * 1024));
-                }
-            }
-            return;
-        }
-        const int e = z + (it - n_main) * n_split;             // extension step
+    // extension step e -> lane that holds its segment's record, and the rank column it starts at
+    auto find_ext = [&](int e, int &kk) {
+        if (DEEP && e < win_first) { win = win0; win_first = 0; load_window(); }
         while (e - win_first >= win_ext) { win_first += win_ext; win += 64; load_window(); }
         const int le = e - win_first;
         const int l = __builtin_ctzll(__ballot(s_cum <= le && le < s_cum + s_cnt));
-        const int row0 = __builtin_amdgcn_readlane(s_row0, l), row1 = __builtin_amdgcn_readlane(s_row1, l);
+        kk = (le - __builtin_amdgcn_readlane(s_cum, l)) * kRankPadGemm;
+        return l;
+    };
+    auto main_w = [&](int it, int slot) {
+        const uint32_t dw = lds_base + kW + slot * WSLOT + wave * 1024;
+        const int k0 = (k_lo + it) * GS_BK;
+        const char *gw = base_w + (FWD ? (int64_t)k0 * ldw * 2 : (int64_t)k0 * 2);
+        if (k0 + GS_BK <= Kd) {
+#pragma unroll
+            for (int jj = 0; jj < WL; ++jj) load_off(off_w[jj], gw, dw + jj * (NW * 1024));
+        } else {                                           // last, partial step: chunks past the end read the zero page
+#pragma unroll
+            for (int jj = 0; jj < WL; ++jj) {
+                const int u = FWD ? (wave + NW * jj) * 4 + (lane >> 4) : (wave + NW * jj) * 8 + lrow;
+                const bool ok = FWD ? k0 + u < Kd : k0 + row_chunk(u) * 8 < Kd;
+                load_ptr(ok ? static_cast<const void *>(gw + off_w[jj]) : zero, dw + jj * (NW * 1024));
+            }
+        }
+    };
+    auto ext_w = [&](int l, int kk, int slot) {
+        const uint32_t dw = lds_base + kW + slot * WSLOT + wave * 1024;
         const int rp = __builtin_amdgcn_readlane(s_rp, l), r = __builtin_amdgcn_readlane(s_r, l);
-        const int kk = (le - __builtin_amdgcn_readlane(s_cum, l)) * kRankPadGemm;
-        const int64_t hb = gs_readlane64(s_hb, l), op = gs_readlane64(s_op, l);
+        const int64_t op = gs_readlane64(s_op, l);
 #pragma unroll
         for (int jj = 0; jj < WL; ++jj) {
             const uint16_t *gw;
@@ -229,6 +231,27 @@ __global__ void __launch_bounds__(256, 2) k_gemm_small(MetaView mv, const uint16
             }
             load_ptr(gw, dw + jj * (NW * 1024));
         }
+    };
+    auto main_x = [&](int it, int slot) {
+        const uint32_t dx = lds_base + slot * XSLOT + wave * 1024;
+        const int k0 = (k_lo + it) * GS_BK;
+        const char *gx = base_x + (int64_t)k0 * 2;
+        if (k0 + GS_BK <= Kd) {
+#pragma unroll
+            for (int jj = 0; jj < XL; ++jj) load_off(off_x[jj], gx, dx + jj * (NW * 1024));
+        } else {
+#pragma unroll
+            for (int jj = 0; jj < XL; ++jj) {
+                const int u = (wave + NW * jj) * 8 + lrow;
+                load_ptr(k0 + row_chunk(u) * 8 < Kd ? static_cast<const void *>(gx + off_x[jj]) : zero, dx + jj * (NW * 1024));
+            }
+        }
+    };
+    auto ext_x = [&](int l, int kk, int slot) {
+        const uint32_t dx = lds_base + slot * XSLOT + wave * 1024;
+        const int row0 = __builtin_amdgcn_readlane(s_row0, l), row1 = __builtin_amdgcn_readlane(s_row1, l);
+        const int rp = __builtin_amdgcn_readlane(s_rp, l);
+        const int64_t hb = gs_readlane64(s_hb, l);
 #pragma unroll
         for (int jj = 0; jj < XL; ++jj) {
             const int u = (wave + NW * jj) * 8 + lrow;
@@ -236,6 +259,26 @@ __global__ void __launch_bounds__(256, 2) k_gemm_small(MetaView mv, const uint16
             const bool in = row >= row0 && row < row1;         // rows of other segments contribute nothing
             load_ptr(in ? side + hb + (int64_t)(row - row0) * rp + kk + row_chunk(u) * 8 : zero, dx + jj * (NW * 1024));
         }
+    };
+
+    auto issue_w = [&](int it, int slot) {
+        if (it < n_main) { main_w(it, slot); return; }
+        int kk;
+        const int l = find_ext(z + (it - n_main) * n_split, kk);
+        ext_w(l, kk, slot);
+    };
+    auto issue_x = [&](int it, int slot) {
+        if (it < n_main) { main_x(it, slot); return; }
+        int kk;
+        const int l = find_ext(z + (it - n_main) * n_split, kk);
+        ext_x(l, kk, slot);
+    };
+    auto issue = [&](int it, int slot) {                       // both tiles of a stage (rings of equal length)
+        if (it < n_main) { main_w(it, slot); main_x(it, slot); return; }
+        int kk;
+        const int l = find_ext(z + (it - n_main) * n_split, kk);
+        ext_w(l, kk, slot);
+        ext_x(l, kk, slot);
     };
 
     // ---- MFMA operands: lane (lm, kg) reads row lm of its 16-row block, chunk 4 ks + kg
@@ -252,10 +295,10 @@ __global__ void __launch_bounds__(256, 2) k_gemm_small(MetaView mv, const uint16
         if (FWD) {                                             // transposing read: see tokcontract_bf16.hip
             const int u = kg * 8 + (lm >> 2);
             const int cl = wn0 + nb * 16 + (lm & 3) * 4;
-            woff[nb] = XT + u * 256 + ((((cl >> 3) ^ (2 * (u & 3) + 8 * ((u >> 3) & 1))) * 16) + (cl & 7) * 2);
+            woff[nb] = u * 256 + ((((cl >> 3) ^ (2 * (u & 3) + 8 * ((u >> 3) & 1))) * 16) + (cl & 7) * 2);
         } else {
             const int u = wn0 + nb * 16 + lm;
-            woff[nb] = XT + u * 128 + ((kg ^ ((u >> 1) & 7)) * 16);
+            woff[nb] = u * 128 + ((kg ^ ((u >> 1) & 7)) * 16);
         }
     }
     f32x4 acc[4][MB];
@@ -264,37 +307,56 @@ __global__ void __launch_bounds__(256, 2) k_gemm_small(MetaView mv, const uint16
 #pragma unroll
         for (int mb = 0; mb < MB; ++mb) acc[nb][mb] = f32x4{0.f, 0.f, 0.f, 0.f};
 
+    // Stage `it` of the token tile is requested NX - 1 stages ahead, of the W tile NWR - 1.  Loads complete in order, so what
+    // may still fly when stage `it` is needed is what was requested behind the later of its two tiles: the stages after it,
+    // or - deep: the token tile goes out in front of a W tile that is one stage further on - that W tile.
+    static_assert(!DEEP || (BM == 128 && NX == 2 && NWR == 3), "the deep ring is counted for these slots");
+    constexpr int FLY = DEEP ? WL : (NX - 2) * LPS;
 #pragma unroll
-    for (int p = 0; p < NST - 1; ++p)
-        if (p < n_it) issue(p, p);
-    int rd = 0, wr = NST - 1;
+    for (int p = 0; p < NWR - 1; ++p) {
+        if (p >= n_it) break;
+        if constexpr (DEEP) {
+            if (p < NX - 1) issue_x(p, p);
+            issue_w(p, p);
+        } else {
+            issue(p, p);
+        }
+    }
+    int rx = 0, rw = 0, wr = NX - 1;
     for (int it = 0; it < n_it; ++it) {
-        if (it + NST - 1 <= n_it) gs_wait_vmcnt<(NST - 2) * LPS>();   // this wave's loads of stage `it` have landed ...
+        // this wave's loads of stage `it` have landed ...
+        if (it + NWR - 1 <= n_it) gs_wait_vmcnt<FLY>();
         else gs_wait_vmcnt<0>();
-        __builtin_amdgcn_s_waitcnt(0xc07f);                    // ... its LDS reads of the slot about to be refilled are done ...
+        __builtin_amdgcn_s_waitcnt(0xc07f);                    // ... its LDS reads of the slots about to be refilled are done ...
         __builtin_amdgcn_sched_barrier(0);
         __builtin_amdgcn_s_barrier();                          // ... and so are everyone else's
         __builtin_amdgcn_sched_barrier(0);
-        if (it + NST - 1 < n_it) issue(it + NST - 1, wr);
-        const char *sb = lds + rd * STAGE;
-        rd = rd + 1 == NST ? 0 : rd + 1;
-        wr = wr + 1 == NST ? 0 : wr + 1;
+        if constexpr (DEEP) {
+            if (it + NX - 1 < n_it) issue_x(it + NX - 1, rx == 0 ? NX - 1 : rx - 1);
+            if (it + NWR - 1 < n_it) issue_w(it + NWR - 1, rw == 0 ? NWR - 1 : rw - 1);
+        } else {
+            if (it + NX - 1 < n_it) issue(it + NX - 1, wr);
+            wr = wr + 1 == NX ? 0 : wr + 1;
+        }
+        const char *sx = lds + rx * XSLOT, *sw = DEEP ? lds + kW + rw * WSLOT : sx + kW;
+        rx = rx + 1 == NX ? 0 : rx + 1;
+        if constexpr (DEEP) rw = rw + 1 == NWR ? 0 : rw + 1;
 #pragma unroll
         for (int ks = 0; ks < 2; ++ks) {
             bf16x8 xf[MB], wf[4];
 #pragma unroll
             for (int nb = 0; nb < 4; ++nb) {
                 if (FWD) {
-                    const char *p = sb + woff[nb] + ks * 32 * 256;
+                    const char *p = sw + woff[nb] + ks * 32 * 256;
                     const bf16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16(LDS_PTR(bf16x4, p));
                     const bf16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16(LDS_PTR(bf16x4, p + 4 * 256));
                     wf[nb] = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
                 } else {
-                    wf[nb] = *LDS_PTR(const bf16x8, sb + (woff[nb] ^ (ks * 64)));
+                    wf[nb] = *LDS_PTR(const bf16x8, sw + (woff[nb] ^ (ks * 64)));
                 }
             }
 #pragma unroll
-            for (int mb = 0; mb < MB; ++mb) xf[mb] = *LDS_PTR(const bf16x8, sb + (xoff[mb] ^ (ks * 64)));
+            for (int mb = 0; mb < MB; ++mb) xf[mb] = *LDS_PTR(const bf16x8, sx + (xoff[mb] ^ (ks * 64)));
             // the workgroup that multiplies goes first: its partner on the compute unit is then fetching, and they stay out of
             // step (128 rows: 4 - 6 % of the kernel; 64 rows: slower by 1 %, left alone)
             if constexpr (BM == 128) __builtin_amdgcn_s_setprio(1);
@@ -383,15 +445,15 @@ __global__ void __launch_bounds__(256) k_gemm_finish(const float *__restrict__ p
     *dst = v;
 }
 
-template <bool FWD, int BM, int NST, bool ACC>
+template <bool FWD, int BM, bool DEEP, bool ACC>
 static hipError_t launch_small(const MetaView &mv, const MetaHeader &h, int64_t Kd, int64_t N, const void *S, const void *W,
                                const void *side, const void *ap, const void *zero, void *C, float *part, int n_split, int row_tile0,
                                int slot, hipStream_t st)
 {
-    constexpr size_t lds = (size_t)NST * (BM + GS_BN) * GS_BK * 2;
+    constexpr size_t lds = (size_t)(gs_ring_x(BM) * BM + gs_ring_w(BM, DEEP) * GS_BN) * GS_BK * 2;
     const int all256 = (int)((h.T + kGemmTileRows - 1) / kGemmTileRows);
     const int tiles_m = row_tile0 > 0 ? (all256 - row_tile0) * (kGemmTileRows / BM) : (int)((h.T + BM - 1) / BM), tiles_n = (int)((N + GS_BN - 1) / GS_BN);
-    auto kern = k_gemm_small<FWD, BM, NST, ACC>;
+    auto kern = k_gemm_small<FWD, BM, DEEP, ACC>;
     hipError_t e = allow_full_lds(reinterpret_cast<const void *>(kern), slot);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(kern, dim3((unsigned)(tiles_m * tiles_n * n_split)), dim3(256), lds, st, mv, static_cast<const uint16_t *>(S),
@@ -410,8 +472,14 @@ static hipError_t dispatch_small(const GemmPlan &p, const MetaView &mv, const Me
                                  const void *W, const void *side, const void *ap, const void *zero, void *C, float *part, hipStream_t st)
 {
     constexpr int slot = 16 + (FWD ? 1 : 0) + (ACC ? 2 : 0);
-    if (p.bm == 64) return launch_small<FWD, 64, 3, ACC>(mv, h, Kd, N, S, W, side, ap, zero, C, part, p.n_split, p.big_tiles, slot, st);
-    return launch_small<FWD, 128, 2, ACC>(mv, h, Kd, N, S, W, side, ap, zero, C, part, p.n_split, p.big_tiles, slot + 4, st);
+    // up to four row tiles every W tile is met by few workgroups and comes from HBM: the deeper W ring, although the requests
+    // then go out in the worse order (512 tokens, 4096 -> 14336 step, W from HBM, 209 -> 202 us; 1024 tokens with W in the
+    // last-level cache 338 -> 350 us without the rule)
+    const bool deep = h.T <= 512;
+#define PL_GS(BM_, DEEP_, SLOT_) launch_small<FWD, BM_, DEEP_, ACC>(mv, h, Kd, N, S, W, side, ap, zero, C, part, p.n_split, p.big_tiles, slot + 4 * SLOT_, st)
+    if (p.bm == 64) return PL_GS(64, false, 0);
+    return deep ? PL_GS(128, true, 1) : PL_GS(128, false, 2);
+#undef PL_GS
 }
 
 hipError_t launch_gemm_small_bf16(const GemmPlan &p, const MetaView &mv, const MetaHeader &h, bool w_rows_contract, int64_t Kd, int64_t N,
