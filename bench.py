@@ -464,7 +464,8 @@ def main():
                     "dequant_kernel": {"ms": round(ms_k, 4), "bound": "hbm", "achieved": round(a, 1), "unit": "GB/s",
                                        "frac": round(a / PEAK_HBM_GBS, 4), "algorithmic_bytes": int(by)},
                     "weight_bytes": {"nf4": int(D * K * (0.5 + 4.0 / 64)), "bf16": int(D * K * 2)},
-                    "note": "plora_linear_fwd_nf4 + plora_linear_bwd_nf4 (two expansions per step); synthetic indices and "
+                    "note": "plora_linear_fwd_nf4 + plora_linear_bwd_nf4 (two expansions per step, each in one launch with "
+                            "the call's preparation, whose time dequant_kernel includes); synthetic indices and "
                             "block constants; the stored weight is read as W" + ("[d_out][d_in]" if w_layout == 1 else "[d_in][d_out]")}
         del codes_d, absmax_d, ws_q
         torch.cuda.empty_cache()
