@@ -505,7 +505,7 @@ struct GroupPlan {
     size_t ws_off[kMaxGroup] = {};
     int cell_of[kMaxGroup] = {};      // cell index of each projection
     int n_cells = 0;
-    size_t part_off = 0, total = 0;
+    size_t part_off = 0, part_bytes = 0, total = 0;
 };
 
 struct CellShape { int max_r16 = 0, r16_total = 0; };
@@ -524,14 +524,26 @@ static CellShape cell_shape(const GroupPlan &gp, const int *members, int n_membe
     return c;
 }
 
-static size_t cell_part_bytes(const GroupPlan &gp, const plora_desc *d0, const CellShape &c)
+// Partial tiles of the fused passes of one cell: the most that any two or more of its projections need together.  (A call may
+// leave projections out of a pass, and fewer rank rows per adapter can mean more splits of the dA pass, so the whole cell is
+// not the largest.)
+static size_t cell_part_bytes(const GroupPlan &gp, const plora_desc *d0, const int *cell, int n_cell)
 {
-    MetaHeader hv = gp.m[0]->hdr;
-    hv.max_r16 = c.max_r16;
-    const size_t shrink = (size_t)skinny_splits(hv, d0->d_in) * hv.n_blocks * kSkinnyRows * c.max_r16 * 4;
-    const int sp = tokc_splits(hv, d0->d_in, gp.m[0]->n_active);
-    const size_t da = sp > 1 ? (size_t)sp * c.r16_total * d0->d_in * 4 : 0;
-    return std::max(shrink, da);
+    size_t most = 0;
+    for (unsigned mask = 1; mask < (1u << n_cell); ++mask) {
+        int members[kMaxGroup], nm = 0;
+        for (int i = 0; i < n_cell; ++i)
+            if (mask >> i & 1u) members[nm++] = cell[i];
+        if (nm < 2) continue;
+        const CellShape c = cell_shape(gp, members, nm);
+        MetaHeader hv = gp.m[members[0]]->hdr;
+        hv.max_r16 = c.max_r16;
+        const size_t shrink = (size_t)skinny_splits(hv, d0->d_in) * hv.n_blocks * kSkinnyRows * c.max_r16 * 4;
+        const int sp = tokc_splits(hv, d0->d_in, gp.m[0]->n_active);
+        const size_t da = sp > 1 ? (size_t)sp * c.r16_total * d0->d_in * 4 : 0;
+        most = std::max(most, std::max(shrink, da));
+    }
+    return most;
 }
 
 static plora_status plan_group(const plora_group *g, GroupPlan &gp)
@@ -563,15 +575,16 @@ static plora_status plan_group(const plora_group *g, GroupPlan &gp)
     for (int p = 0; p < gp.n; ++p) {
         members[nm] = p;
         if (nm > 0 && (!fuse || cell_shape(gp, members, nm + 1).max_r16 > PLORA_MAX_RANK)) {
-            if (nm > 1) part = std::max(part, cell_part_bytes(gp, d0, cell_shape(gp, members, nm)));
+            part = std::max(part, cell_part_bytes(gp, d0, members, nm));
             ++cell; members[0] = p; nm = 0;
         }
         gp.cell_of[p] = cell;
         ++nm;
     }
-    if (nm > 1) part = std::max(part, cell_part_bytes(gp, d0, cell_shape(gp, members, nm)));
+    part = std::max(part, cell_part_bytes(gp, d0, members, nm));
     gp.n_cells = cell + 1;
     gp.part_off = o;
+    gp.part_bytes = part;
     gp.total = align_up(o + part, 256) + 256;
     return PLORA_OK;
 }
@@ -634,7 +647,7 @@ static plora_status group_forward(const plora_group *g, const void *x, const voi
         }
         Bracket b(2, st);
         PL_TRY(launch_skinny_group(gv, hv, x, g->desc[0].d_in, ws + gp.ws_off[members[0]] + gp.m[members[0]]->ws.zero,
-                                   reinterpret_cast<float *>(ws + gp.part_off), hf, hb, zt, st));
+                                   reinterpret_cast<float *>(ws + gp.part_off), gp.part_bytes, hf, hb, zt, st));
     }
     for (int p = 0; p < gp.n; ++p)
         if ((ps = run(p, false, kStepMain)) != PLORA_OK) return ps;
@@ -693,7 +706,7 @@ static plora_status group_backward(const plora_group *g, const void *x, const vo
         for (int i = 0; i < nm; ++i) zt[i] = ws + gp.ws_off[members[i]] + gp.m[members[i]]->ws.zt_h;
         Bracket b(2, st);
         PL_TRY(launch_skinny_group(gv, hv, x, d0->d_in, ws + gp.ws_off[members[0]] + gp.m[members[0]]->ws.zero,
-                                   reinterpret_cast<float *>(ws + gp.part_off), hf, hb, zt, st));
+                                   reinterpret_cast<float *>(ws + gp.part_off), gp.part_bytes, hf, hb, zt, st));
     }
     for (int p = 0; p < gp.n; ++p)
         if ((ps = run(p, false, kStepDh | kStepDb | (fuse_a[p] ? 0u : kStepDa) | kStepDx)) != PLORA_OK) return ps;
@@ -706,7 +719,7 @@ static plora_status group_backward(const plora_group *g, const void *x, const vo
         group_view(gp, ws, members, nm, false, gv, hv);
         Bracket b(5, st);
         PL_TRY(launch_tokc_group_dA(gv, hv, x, d0->d_in, ws + gp.ws_off[members[0]] + gp.m[members[0]]->ws.zero,
-                                    reinterpret_cast<float *>(ws + gp.part_off), tokc_splits(hv, d0->d_in, gp.m[0]->n_active),
+                                    reinterpret_cast<float *>(ws + gp.part_off), gp.part_bytes, tokc_splits(hv, d0->d_in, gp.m[0]->n_active),
                                     gp.m[0]->n_active, st));
     }
     return PLORA_OK;

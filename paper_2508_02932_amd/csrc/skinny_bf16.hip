@@ -364,11 +364,12 @@ hipError_t launch_skinny_bf16(const MetaView &mv, const MetaHeader &h, int mode,
 }
 
 hipError_t launch_skinny_group(const GroupView &gv, const MetaHeader &hv, const void *x, int64_t C, const void *zero, float *part,
-                               float *const *hf, void *const *hb, void *const *zt, hipStream_t st)
+                               size_t part_bytes, float *const *hf, void *const *hb, void *const *zt, hipStream_t st)
 {
     if (hv.n_blocks == 0) return hipSuccess;
     if (gv.n_proj < 2 || gv.n_proj > kMaxGroup || gv.max_r16 > PLORA_MAX_RANK || hv.max_r16 != gv.max_r16) return hipErrorInvalidValue;
     const int n_split = skinny_splits(hv, C);
+    if ((size_t)n_split * hv.n_blocks * kSkinnyRows * gv.max_r16 * 4 > part_bytes) return hipErrorInvalidValue;
     const int n_stage_all = (int)((C + SK_BK - 1) / SK_BK);
     const int per = (n_stage_all + n_split - 1) / n_split;
     const size_t lds = (size_t)SK_NST * (SK_XT + gv.max_r16 * SK_BK * 2);

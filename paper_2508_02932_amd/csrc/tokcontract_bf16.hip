@@ -435,12 +435,13 @@ static hipError_t launch_tokc(const MetaView &mv, const MetaHeader &h, const uin
 }
 
 hipError_t launch_tokc_group_dA(const GroupView &gv, const MetaHeader &hv, const void *x, int64_t C, const void *zero,
-                                float *part, int n_split, int n_active_adapters, hipStream_t st)
+                                float *part, size_t part_bytes, int n_split, int n_active_adapters, hipStream_t st)
 {
     if (hv.n_adapters == 0) return hipSuccess;
     if (gv.n_proj < 2 || gv.n_proj > kMaxGroup || gv.max_r16 > PLORA_MAX_RANK || hv.max_r16 != gv.max_r16) return hipErrorInvalidValue;
     int bc = 128;
     if (tokc_plan(hv, C, n_active_adapters, &bc) != n_split || bc != 128) return hipErrorInvalidValue;
+    if (n_split > 1 && (size_t)n_split * gv.r16_total * C * 4 > part_bytes) return hipErrorInvalidValue;
     constexpr int BC = 128;
     const size_t stage = (size_t)TC_BT * BC * 2 + (size_t)(gv.max_r16 > 0 ? gv.max_r16 : 16) * TC_BT * 2;
     size_t budget = (size_t)TC_LDS_BYTES * BC / 256;

@@ -56,6 +56,9 @@ CASES = {
                           seg_adapter=tuple((11 * i) % 100 for i in range(140)),
                           ranks=(tuple(1 + (5 * k) % 40 for k in range(100)), tuple(8 + (3 * k) % 50 for k in range(100))),
                           scales=((1.0,) * 100, (0.5,) * 100)),
+    # gradients of two of the three: the fused dA pass of two is split although that of all three would not be
+    "two_of_three": dict(dtype="bf16", D=8192, Ks=(64, 64, 64), lengths=(1250,) * 4, seg_adapter=(0, 1, 2, 3),
+                         ranks=((32,) * 4,) * 3, scales=((2.0, 1.0, 0.5, 1.0),) * 3),
     "f32": dict(dtype="f32", D=64, Ks=(48, 32), lengths=(40, 50), seg_adapter=(0, 1),
                 ranks=((4, 8), (8, 2)), scales=((4.0, 2.0), (2.0, 8.0))),
     "single": dict(dtype="bf16", D=64, Ks=(64,), lengths=(40,), seg_adapter=(0,), ranks=((8,),), scales=((2.0,),)),
@@ -117,7 +120,7 @@ def check_against_oracle(lins, tens, dps, save_h, want_w, want_dx):
             assert np.isfinite(v) and v <= tol, (lin.name, p, k, v, tol)
 
 
-@pytest.mark.parametrize("case", list(CASES))
+@pytest.mark.parametrize("case", [c for c in CASES if c != "two_of_three"])
 @pytest.mark.parametrize("save_h", [True, False])
 def test_group_equals_each_projection_alone(case, save_h):
     n = len(CASES[case]["Ks"])
@@ -129,7 +132,7 @@ def test_group_equals_each_projection_alone(case, save_h):
     check_against_oracle(lins, tens, dps, sh, ww, wd)
 
 
-@pytest.mark.parametrize("case", ["qkv_one_pass", "cut_in_two", "four"])
+@pytest.mark.parametrize("case", ["qkv_one_pass", "cut_in_two", "four", "two_of_three"])
 def test_group_per_projection_options(case):
     """Saved activation for some projections only, weight gradients for some only, dx for some only: the fused passes
     take the projections that need them, the others run alone or not at all."""
