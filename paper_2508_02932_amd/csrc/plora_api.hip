@@ -498,7 +498,8 @@ static plora_status backward_impl(const plora_desc *desc, const void *x, const v
 // ---- grouped calls: several projections on one x -------------------------------------------------------
 // Each projection keeps a workspace of its own inside the group's (so every table and side buffer is where the plain
 // call would put it); behind them lies the partial-tile region of the fused passes.  Projections are fused in cells:
-// consecutive projections whose ranks, each padded to 16, sum to at most PLORA_MAX_RANK for every adapter.
+// consecutive projections whose ranks, each padded to 16, sum to at most PLORA_MAX_RANK for every adapter, and whose
+// plain calls split the shrink alike.
 struct GroupPlan {
     int n = 0;
     std::shared_ptr<const HostMeta> m[kMaxGroup];
@@ -538,7 +539,7 @@ static size_t cell_part_bytes(const GroupPlan &gp, const plora_desc *d0, const i
         const CellShape c = cell_shape(gp, members, nm);
         MetaHeader hv = gp.m[members[0]]->hdr;
         hv.max_r16 = c.max_r16;
-        const size_t shrink = (size_t)skinny_splits(hv, d0->d_in) * hv.n_blocks * kSkinnyRows * c.max_r16 * 4;
+        const size_t shrink = (size_t)gp.m[members[0]]->split_shrink * hv.n_blocks * kSkinnyRows * c.max_r16 * 4;
         const int sp = tokc_splits(hv, d0->d_in, gp.m[0]->n_active);
         const size_t da = sp > 1 ? (size_t)sp * c.r16_total * d0->d_in * 4 : 0;
         most = std::max(most, std::max(shrink, da));
@@ -574,7 +575,9 @@ static plora_status plan_group(const plora_group *g, GroupPlan &gp)
     size_t part = 0;
     for (int p = 0; p < gp.n; ++p) {
         members[nm] = p;
-        if (nm > 0 && (!fuse || cell_shape(gp, members, nm + 1).max_r16 > PLORA_MAX_RANK)) {
+        // (a fused shrink sums in the order of the plain calls, so its projections split the contraction alike)
+        if (nm > 0 && (!fuse || cell_shape(gp, members, nm + 1).max_r16 > PLORA_MAX_RANK ||
+                       gp.m[p]->split_shrink != gp.m[members[0]]->split_shrink)) {
             part = std::max(part, cell_part_bytes(gp, d0, members, nm));
             ++cell; members[0] = p; nm = 0;
         }
@@ -647,7 +650,7 @@ static plora_status group_forward(const plora_group *g, const void *x, const voi
         }
         Bracket b(2, st);
         PL_TRY(launch_skinny_group(gv, hv, x, g->desc[0].d_in, ws + gp.ws_off[members[0]] + gp.m[members[0]]->ws.zero,
-                                   reinterpret_cast<float *>(ws + gp.part_off), gp.part_bytes, hf, hb, zt, st));
+                                   reinterpret_cast<float *>(ws + gp.part_off), gp.part_bytes, gp.m[members[0]]->split_shrink, hf, hb, zt, st));
     }
     for (int p = 0; p < gp.n; ++p)
         if ((ps = run(p, false, kStepMain)) != PLORA_OK) return ps;
@@ -706,7 +709,7 @@ static plora_status group_backward(const plora_group *g, const void *x, const vo
         for (int i = 0; i < nm; ++i) zt[i] = ws + gp.ws_off[members[i]] + gp.m[members[i]]->ws.zt_h;
         Bracket b(2, st);
         PL_TRY(launch_skinny_group(gv, hv, x, d0->d_in, ws + gp.ws_off[members[0]] + gp.m[members[0]]->ws.zero,
-                                   reinterpret_cast<float *>(ws + gp.part_off), gp.part_bytes, hf, hb, zt, st));
+                                   reinterpret_cast<float *>(ws + gp.part_off), gp.part_bytes, gp.m[members[0]]->split_shrink, hf, hb, zt, st));
     }
     for (int p = 0; p < gp.n; ++p)
         if ((ps = run(p, false, kStepDh | kStepDb | (fuse_a[p] ? 0u : kStepDa) | kStepDx)) != PLORA_OK) return ps;

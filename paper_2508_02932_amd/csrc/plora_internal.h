@@ -510,11 +510,12 @@ hipError_t launch_tokcontract_bf16(const MetaView &mv, const MetaHeader &h, bool
                                    int64_t C, const void *zt, const void *zero, float *part, int n_split,
                                    int r16_total, int n_active_adapters, hipStream_t st);
 // The same two passes for several projections at once (see GroupView).  hv: projection 0's header with max_r16 replaced
-// by the fused one.  Shrink: hf / hb / zt per projection as in launch_skinny_bf16 (mode 0).  dA: the results go to each
+// by the fused one.  Shrink: hf / hb / zt per projection as in launch_skinny_bf16 (mode 0);
+// n_split: that of the projections' plain calls.  dA: the results go to each
 // projection's own dA_k; n_split must be tokc_splits(hv, C, n_active_adapters).
 // part_bytes: size of `part`; a pass whose partial tiles do not fit is refused.
 hipError_t launch_skinny_group(const GroupView &gv, const MetaHeader &hv, const void *x, int64_t C, const void *zero, float *part,
-                               size_t part_bytes, float *const *hf, void *const *hb, void *const *zt, hipStream_t st);
+                               size_t part_bytes, int n_split, float *const *hf, void *const *hb, void *const *zt, hipStream_t st);
 hipError_t launch_tokc_group_dA(const GroupView &gv, const MetaHeader &hv, const void *x, int64_t C, const void *zero,
                                 float *part, size_t part_bytes, int n_split, int n_active_adapters, hipStream_t st);
 int tokc_splits(const MetaHeader &h, int64_t C, int n_active_adapters);

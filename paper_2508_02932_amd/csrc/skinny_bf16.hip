@@ -324,8 +324,8 @@ __global__ void __launch_bounds__(256) k_skinny_finish(MetaView mv0, int mode, c
 // Splits of the contraction over workgroups: three workgroups per compute unit, eight stages or more per split.  A short
 // batch cannot fill the chip with eight splits, and one workgroup walks its stages at about 0.9 us each whatever the rest of
 // the chip does, so up to 32 token blocks the contraction is cut further, to four stages: 512 tokens x 14336 columns, 28
-// stages per split 24 us, 7 stages 9 us; 1024 tokens 26 -> 12.6 us.  (A function of the token blocks and the contraction alone: the fused pass of a
-// grouped call then sums in the order of the plain one.)
+// stages per split 24 us, 7 stages 9 us; 1024 tokens 26 -> 12.6 us.  (A function of the token blocks and the contraction alone; the workspace may
+// allow fewer.)
 int skinny_splits(const MetaHeader &h, int64_t C)
 {
     if (h.n_blocks == 0) return 1;
@@ -364,12 +364,11 @@ hipError_t launch_skinny_bf16(const MetaView &mv, const MetaHeader &h, int mode,
 }
 
 hipError_t launch_skinny_group(const GroupView &gv, const MetaHeader &hv, const void *x, int64_t C, const void *zero, float *part,
-                               size_t part_bytes, float *const *hf, void *const *hb, void *const *zt, hipStream_t st)
+                               size_t part_bytes, int n_split, float *const *hf, void *const *hb, void *const *zt, hipStream_t st)
 {
     if (hv.n_blocks == 0) return hipSuccess;
     if (gv.n_proj < 2 || gv.n_proj > kMaxGroup || gv.max_r16 > PLORA_MAX_RANK || hv.max_r16 != gv.max_r16) return hipErrorInvalidValue;
-    const int n_split = skinny_splits(hv, C);
-    if ((size_t)n_split * hv.n_blocks * kSkinnyRows * gv.max_r16 * 4 > part_bytes) return hipErrorInvalidValue;
+    if (n_split < 1 || (size_t)n_split * hv.n_blocks * kSkinnyRows * gv.max_r16 * 4 > part_bytes) return hipErrorInvalidValue;
     const int n_stage_all = (int)((C + SK_BK - 1) / SK_BK);
     const int per = (n_stage_all + n_split - 1) / n_split;
     const size_t lds = (size_t)SK_NST * (SK_XT + gv.max_r16 * SK_BK * 2);

@@ -165,6 +165,32 @@ def test_group_forward_is_bitwise_the_plain_call(case):
         assert torch.equal(ref.y, dps[p].y), f"projection {p}: y differs"
 
 
+@pytest.mark.parametrize("w_layouts", [(0, 0), (0, 1)], ids=["cut_alike", "one_cut"])
+def test_group_forward_is_bitwise_the_plain_call_when_the_workspace_cuts_the_splits(w_layouts):
+    """Many adapters bring the workspace close to the scratch array's size, and the shrink is split less often than its rule
+    says, in one projection or in both: the grouped call still sums as the plain calls do."""
+    import torch
+    import gpu_harness as gh
+    from paper_2508_02932_amd import plora
+    print(f"[case] group bitwise, cut splits {w_layouts}", flush=True)
+    n_ad = 28
+    lins, tens = make_group("bf16", 8192, (64, 64), (150,) * 4 + (0,) * (n_ad - 4), tuple(range(n_ad)), ((64,) * n_ad,) * 2,
+                            ((1.0,) * n_ad,) * 2, seed=7)
+    dps = [gh.upload(l, t, w) for l, t, w in zip(lins, tens, w_layouts)]
+    splits = [int(plora.plora_debug_metadata(dp.desc)[0].shrink_splits) for dp in dps]
+    assert splits[0] < 32 and splits[1] == (splits[0] if w_layouts[1] == 0 else 32), splits
+    group = plora.Group([dp.desc for dp in dps])
+    ws = torch.empty(plora.plora_group_workspace_bytes(group), dtype=torch.uint8, device="cuda")
+    lists = lambda name: [getattr(dp, name) for dp in dps]
+    plora.plora_group_fwd(group, dps[0].x, lists("W"), lists("A"), lists("B"), lists("y"), lists("h"), ws)
+    for p, dp in enumerate(dps):
+        h, y = dp.h.clone(), dp.y.clone()
+        gh.forward(dp, save_h=True)
+        torch.cuda.synchronize()
+        nh = lins[p].layout.sum_Lr()
+        assert torch.equal(h[:nh], dp.h[:nh]) and torch.equal(y, dp.y), f"projection {p}"
+
+
 @pytest.mark.parametrize("members", [(0, 1, 2), (4, 5)], ids=["q_k_v", "gate_up"])
 def test_config4_groups_full_size(members):
     """The decoder layer's two groups at full size (16384 tokens, 16 adapters; q / k / v differ in width): every
