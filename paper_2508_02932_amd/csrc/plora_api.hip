@@ -171,16 +171,19 @@ static void build_meta(const plora_desc *d, HostMeta &m)
         lay_out(m.ws, m.ap_elems, true);
         return fits_scratch && m.ws.total > (size_t)PLORA_NOALLOC_SCRATCH_BYTES;
     };
+    // What sticks out is cut: the split GEMM's partial tiles where they reach furthest, else the skinny ones (the two overlay
+    // each other; cutting the one that ends earlier would cost its splits and gain no room: 1228 tokens, 4096 -> 28672, 8
+    // adapters of rank 8: shrink and dH keep 16 splits instead of 8).
     skinny_cap = std::max(8, std::max(m.split_shrink, m.split_dh));
     while (outgrown()) {
-        if (skinny_cap > 8) {
-            skinny_cap = 8;
-            m.split_shrink = std::min(m.split_shrink, 8);
-            m.split_dh = std::min(m.split_dh, 8);
-            continue;
+        const size_t fwd = split_bytes(m.gemm_fwd, d->d_out), dx = split_bytes(m.gemm_dx, d->d_in);
+        if (align_up(m.ws.gpart + std::max(fwd, dx), 256) + 256 == m.ws.total && fwd + dx > 0) {
+            (fwd > dx ? m.gemm_fwd : m.gemm_dx).n_split -= 1;
+        } else {
+            skinny_cap -= 1;
+            m.split_shrink = std::min(m.split_shrink, skinny_cap);
+            m.split_dh = std::min(m.split_dh, skinny_cap);
         }
-        const bool fwd = split_bytes(m.gemm_fwd, d->d_out) > split_bytes(m.gemm_dx, d->d_in);
-        (fwd ? m.gemm_fwd : m.gemm_dx).n_split -= 1;
     }
     int64_t rp_total = 0;
     for (int32_t k = 0; k < d->n_adapters; ++k) rp_total += m.t.ad[k].rp;
