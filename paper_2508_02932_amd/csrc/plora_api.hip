@@ -57,7 +57,7 @@ static void fill_desc_words(const plora_desc *d, int32_t n_blocks, const void *c
     auto put64 = [&](int i, uint64_t v) { w[i] = (uint32_t)v; w[i + 1] = (uint32_t)(v >> 32); };
     put64(0, (uint64_t)d->T); put64(2, (uint64_t)d->d_in); put64(4, (uint64_t)d->d_out);
     w[6] = (uint32_t)d->n_seg; w[7] = (uint32_t)d->n_adapters; w[8] = (uint32_t)n_blocks;
-    w[9] = (d->w_layout == PLORA_W_OUT_IN ? 1u : 0u) | (order_is_identity ? 2u : 0u);
+    w[9] = (d->w_layout == PLORA_W_OUT_IN ? 1u : 0u) | (order_is_identity ? 2u : 0u) | (d->dtype == PLORA_BF16 ? 4u : 0u);
     put64(10, (uint64_t)(uintptr_t)at_base);
     uint32_t *p = w + kDescHeadWords;
     for (int32_t s = 0; s < d->n_seg; ++s) { *p++ = (uint32_t)d->seg_off[s + 1]; *p++ = (uint32_t)d->seg_adapter[s]; }
@@ -100,7 +100,7 @@ static void build_meta(const plora_desc *d, HostMeta &m)
     m.n_words = desc_words(d->n_seg, d->n_adapters);
     std::vector<uint32_t> words((size_t)m.n_words);
     fill_desc_words(d, n_blocks, nullptr, nullptr, nullptr, nullptr, nullptr, false, words.data());
-    m.layout = table_layout(d->T, d->n_seg, d->n_adapters, n_blocks);
+    m.layout = table_layout(d->T, d->n_seg, d->n_adapters, n_blocks, d->dtype == PLORA_BF16);
     m.image.assign(m.layout.bytes, 0);
     m.t = tables_at(m.image.data(), m.layout);
     const DescReader<WordsInMemory> in{WordsInMemory{words.data()}};
@@ -140,14 +140,15 @@ static void build_meta(const plora_desc *d, HostMeta &m)
     m.gemm_dx = gemm_plan(d->T, d->d_out, d->d_in);
     auto split_bytes = [&](const GemmPlan &p, int64_t N) { return p.n_split > 1 ? (size_t)p.n_split * d->T * N * 4 : (size_t)0; };
     int skinny_cap = 8;
-    auto lay_out = [&](WorkspaceLayout &w, size_t ap_elems, bool split_gemm) {
+    bool packed = bf;                            // A_k and B_k packed: only ever read by tokens with an adapter
+    auto lay_out = [&](WorkspaceLayout &w, size_t meta_bytes, size_t ap_elems, bool split_gemm) {
         size_t o = 0;
         w.zero = o; o += kZeroBytes;
-        w.meta_bytes = m.layout.bytes;
+        w.meta_bytes = meta_bytes;
         w.meta = o; o = align_up(o + w.meta_bytes, 256);
         w.desc = o; o = align_up(o + (m.n_words > kChunkWords ? (size_t)m.n_words * 4 : 0), 256);
-        w.at = o;   o = align_up(o + (bf ? m.at_elems * 2 : 0), 256);
-        w.ap = o;   o = align_up(o + (bf ? ap_elems * 2 : 0), 256);
+        w.at = o;   o = align_up(o + (packed ? m.at_elems * 2 : 0), 256);
+        w.ap = o;   o = align_up(o + (packed ? ap_elems * 2 : 0), 256);
         w.hb = o;   o = align_up(o + (bf ? m.hb_elems * 2 : 0), 256);
         w.zt_h = o; o = align_up(o + (bf ? m.zt_elems * 2 : 0), 256);
         w.zt_g = o; o = align_up(o + (bf ? m.zt_elems * 2 : 0), 256);
@@ -163,31 +164,39 @@ static void build_meta(const plora_desc *d, HostMeta &m)
             o = std::max(o, align_up(w.gpart + std::max(split_bytes(m.gemm_fwd, d->d_out), split_bytes(m.gemm_dx, d->d_in)), 256));
         w.total = o + 256;
     };
-    // a description that fits the scratch array of plora_linear_fwd_noalloc with eight skinny splits and no split GEMM must
-    // not outgrow it with more
-    lay_out(m.ws, m.ap_elems, false);
+    // What plora_linear_fwd_noalloc takes: a description that fits its scratch array with eight skinny splits, no split GEMM
+    // and the tables without their records.  The workspace of such a description must not outgrow the array; any other
+    // workspace is larger than the array, so its size alone tells the two apart.
+    lay_out(m.ws, m.layout.blk, m.ap_elems, false);
     const bool fits_scratch = m.ws.total <= (size_t)PLORA_NOALLOC_SCRATCH_BYTES;
     auto outgrown = [&]() {
-        lay_out(m.ws, m.ap_elems, true);
+        lay_out(m.ws, m.layout.bytes, m.ap_elems, true);
         return fits_scratch && m.ws.total > (size_t)PLORA_NOALLOC_SCRATCH_BYTES;
     };
     // What sticks out is cut: the split GEMM's partial tiles where they reach furthest, else the skinny ones (the two overlay
     // each other; cutting the one that ends earlier would cost its splits and gain no room: 1228 tokens, 4096 -> 28672, 8
-    // adapters of rank 8: shrink and dH keep 16 splits instead of 8).
+    // adapters of rank 8: shrink and dH keep 16 splits instead of 8), first what they have in reserve.  The records (some
+    // 100 bytes per token block and adapter) are less than seven skinny splits of 8 KB and more per token block; without token
+    // blocks they are less than the packed matrices, which nothing reads then.
     skinny_cap = std::max(8, std::max(m.split_shrink, m.split_dh));
     while (outgrown()) {
         const size_t fwd = split_bytes(m.gemm_fwd, d->d_out), dx = split_bytes(m.gemm_dx, d->d_in);
         if (align_up(m.ws.gpart + std::max(fwd, dx), 256) + 256 == m.ws.total && fwd + dx > 0) {
             (fwd > dx ? m.gemm_fwd : m.gemm_dx).n_split -= 1;
-        } else {
+        } else if (m.hdr.n_blocks > 0 && skinny_cap > 1) {
             skinny_cap -= 1;
             m.split_shrink = std::min(m.split_shrink, skinny_cap);
             m.split_dh = std::min(m.split_dh, skinny_cap);
+        } else if (m.hdr.n_blocks == 0 && packed) {
+            packed = false;
+        } else {
+            break;
         }
     }
+    packed = bf;
     int64_t rp_total = 0;
     for (int32_t k = 0; k < d->n_adapters; ++k) rp_total += m.t.ad[k].rp;
-    lay_out(m.ws_lora, (size_t)(rp_total * std::max(d->d_in, d->d_out)), false);
+    lay_out(m.ws_lora, m.layout.bytes, (size_t)(rp_total * std::max(d->d_in, d->d_out)), false);
 }
 
 // ---- metadata cache: the last few descriptions and what was derived from them ---------------------

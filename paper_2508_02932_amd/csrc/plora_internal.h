@@ -180,6 +180,7 @@ template <class Src> struct DescReader {
     PLORA_HD int n_adapters() const { return (int)src.word(7); }
     PLORA_HD int n_blocks() const { return (int)src.word(8); }
     PLORA_HD int w_out_in() const { return (int)(src.word(9) & 1u); }
+    PLORA_HD int records() const { return (int)((src.word(9) >> 2) & 1u); }
     PLORA_HD int order_is_identity() const { return (int)((src.word(9) >> 1) & 1u); }
     PLORA_HD const void *at_base() const { return reinterpret_cast<const void *>((uintptr_t)w64(10)); }
     PLORA_HD int seg_row1(int s) const { return (int)src.word(kDescHeadWords + kDescSegWords * s); }
@@ -211,7 +212,7 @@ struct TableLayout {
     int64_t n_tiles;
 };
 
-PLORA_HD TableLayout table_layout(int64_t T, int n_seg, int n_adapters, int n_blocks)
+PLORA_HD TableLayout table_layout(int64_t T, int n_seg, int n_adapters, int n_blocks, bool records)
 {
     TableLayout l;
     size_t o = 0;
@@ -223,8 +224,8 @@ PLORA_HD TableLayout table_layout(int64_t T, int n_seg, int n_adapters, int n_bl
     l.blk_seg = o;  o = align_up(o + (size_t)n_blocks * sizeof(int32_t), 64);
     l.seg_list = o; o = align_up(o + (size_t)n_seg * sizeof(int32_t), 64);
     l.tile_order = o; o = align_up(o + (size_t)l.n_tiles * sizeof(int32_t), 64);
-    l.blk = o;      o = align_up(o + (size_t)n_blocks * sizeof(BlkInfo), 64);
-    l.job = o;      o = align_up(o + (size_t)n_adapters * sizeof(TokJob), 64);
+    l.blk = o;      o = align_up(o + (records ? (size_t)n_blocks * sizeof(BlkInfo) : 0), 64);
+    l.job = o;      o = align_up(o + (records ? (size_t)n_adapters * sizeof(TokJob) : 0), 64);
     l.bytes = o;
     return l;
 }
@@ -382,14 +383,14 @@ template <class Src> inline void derive_tables(const DescReader<Src> &in, const 
         for (int j = 0; j < n_ad; ++j) rank += tokens[j] > tokens[k] || (tokens[j] == tokens[k] && j < k);
         t.ad[rank].by_tokens = k;
     }
-    for (int s = 0; s < n_seg; ++s) {
+    for (int s = 0; s < n_seg && in.records(); ++s) {
         const SegInfo &g = t.seg[s];
         if (!seg_has_lowrank(g)) continue;
         const AdapterInfo &a = t.ad[g.adapter];
         for (int32_t t0 = 0, b = g.blk0; t0 < g.row1 - g.row0; t0 += kSkinnyRows, ++b)
             t.blk[b] = BlkInfo{g, t0, a.scale, a.at_off, a.B, (int32_t)(a.ap_off / ap_rows), 0};
     }
-    for (int i = 0; i < n_ad; ++i) {
+    for (int i = 0; i < n_ad && in.records(); ++i) {
         const int k = t.ad[i].by_tokens;
         const AdapterInfo &a = t.ad[k];
         TokJob j{a.dA, a.dB, 0, 0, 0, 0, k, a.r, a.r16, a.r16_off, a.scale, a.seg_list0, a.n_own, 0, 0};

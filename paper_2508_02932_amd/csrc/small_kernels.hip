@@ -287,7 +287,7 @@ template <class Src> __device__ inline void derive_on_device(const DescReader<Sr
     __syncthreads();
     const DescReader<WordsInMemory> in{WordsInMemory{words}};
     const int64_t T = in.T(), D = in.D(), K = in.K(), ap_rows = in.w_out_in() ? K : D;
-    const TableLayout lay = table_layout(T, n_seg, n_ad, in.n_blocks());
+    const TableLayout lay = table_layout(T, n_seg, n_ad, in.n_blocks(), in.records() != 0);
     const Tables t = tables_at(meta_dst, lay);
     const int64_t n_tiles = lay.n_tiles;
     const int n_blocks = in.n_blocks();
@@ -354,6 +354,8 @@ template <class Src> __device__ inline void derive_on_device(const DescReader<Sr
         if (k < n_ad) {
             a.by_tokens = sh.by_tokens[k];
             t.ad[k] = a;
+        }
+        if (k < n_ad && in.records()) {
             const int kj = a.by_tokens, s = sh.first_seg[kj];          // entry k of the jobs is adapter kj
             TokJob j;
             j.dA = static_cast<float *>(const_cast<void *>(in.ad_ptr(kj, 2)));
@@ -387,6 +389,7 @@ template <class Src> __device__ inline void derive_on_device(const DescReader<Sr
             if (seg_blk0[mid] <= b) lo = mid; else hi = mid - 1;
         }
         t.blk_seg[b] = lo;
+        if (!in.records()) continue;
         BlkInfo bi;
         const int k = in.seg_adapter(lo);
         bi.g.row0 = in.seg_row0(lo); bi.g.row1 = in.seg_row1(lo); bi.g.adapter = k;

@@ -35,3 +35,60 @@ def test_the_skinny_passes_are_cut_only_as_far_as_needed():
     assert info.ws_total <= LIMIT and 8 < info.shrink_splits < 32
     per_split = info.n_blocks * 128 * 64 * 4
     assert info.ws_total + per_split > LIMIT
+
+
+def size_without_records(d):
+    """What decides whether plora_linear_fwd_noalloc takes a description: its workspace with eight skinny splits, no split
+    GEMM, and tables without the records that the bf16 kernels start from."""
+    al = lambda v, a=256: (v + a - 1) // a * a
+    info, tab, _ = plora.plora_debug_metadata(d)
+    bf = d.dtype == plora.PLORA_BF16
+    e2 = 2 if bf else 0
+    own = [g for g in tab["seg"] if g["adapter"] >= 0]
+    o = 1024 + al(al(int(info.off_tile_order) + 4 * int(info.n_tiles), 64))
+    o += al(4 * int(info.desc_words) if info.desc_words > 896 else 0)
+    o += al(sum(int(a["r16"]) for a in tab["ad"]) * d.d_in * e2)
+    o += al(sum(int(a["rp"]) for a in tab["ad"]) * (d.d_out if d.w_layout else d.d_in) * e2)
+    o += al(sum(int(g["row1"] - g["row0"]) * int(g["rp"]) for g in own) * e2)
+    o += 2 * al(sum(int(g["r16"]) * int(g["lp"]) for g in own) * e2)
+    o += al(4 * int(info.h_elems)) * (1 if bf else 2)
+    if bf:
+        o += al(8 * int(info.n_blocks) * 128 * int(info.max_r16) * 4)
+        o += al(max([s * int(info.r16_total) * w * 4 for s, w in ((info.da_splits, d.d_in), (info.db_splits, d.d_out)) if s > 1] + [0]))
+    return o + 256
+
+
+FAMILIES = {
+    # D, K, dtype, ranks, segments of T tokens
+    "few_adapters": (512, 512, plora.PLORA_BF16, [16] * 4, lambda T: ([T // 4] * 3 + [T - T // 4 * 3], [0, 1, 2, 3])),
+    "f32": (8, 16, plora.PLORA_F32, [1], lambda T: ([T], [0])),
+    "f32_ranks": (64, 64, plora.PLORA_F32, [8, 3], lambda T: ([T // 3, T - T // 3], [1, 0])),
+    "no_tokens_with_an_adapter": (1184, 64, plora.PLORA_BF16, [64] * 220, lambda T: ([T], [-1])),
+    "many_adapters_one_block": (808, 64, plora.PLORA_BF16, [64] * 256, lambda T: ([T, 3], [-1, 7])),
+    "eight_splits": (8192, 512, plora.PLORA_BF16, [64] * 29, lambda T: ([T - 5, 5], [3, 4])),
+}
+
+
+@pytest.mark.parametrize("w_layout", [0, 1])
+@pytest.mark.parametrize("family", sorted(FAMILIES))
+def test_the_records_refuse_nothing_that_fitted_the_scratch_array(family, w_layout):
+    """Around the number of tokens at which a description stops fitting: at and below it the workspace is within the scratch
+    array, above it is not, so that what was accepted is accepted and what was refused is refused."""
+    D, K, dtype, ranks, cut = FAMILIES[family]
+    make = lambda T: desc(D, K, *cut(T), ranks, w_layout, dtype)
+    lo, hi = 16, 4000000
+    assert size_without_records(make(lo)) <= LIMIT
+    if size_without_records(make(hi)) <= LIMIT:
+        hi = lo
+    while hi - lo > 1:
+        mid = (lo + hi) // 2
+        lo, hi = (mid, hi) if size_without_records(make(mid)) <= LIMIT else (lo, mid)
+    for T in (max(16, lo - 700), max(16, lo - 100), max(16, lo - 1), lo, lo + 1, lo + 200):
+        d = make(T)
+        assert (plora.plora_workspace_bytes(d) <= LIMIT) == (size_without_records(d) <= LIMIT), T
+
+
+def test_the_scratch_array_takes_a_description_within_100_kb_of_its_size():
+    """85400 tokens of four adapters of rank 16: 67 061 504 bytes without the records, 67 108 864 is the limit."""
+    d = desc(512, 512, [21350] * 4, range(4), [16] * 4)
+    assert size_without_records(d) == 67061504 and plora.plora_workspace_bytes(d) <= LIMIT
