@@ -41,15 +41,15 @@ __device__ inline uint32_t ex_pack_bf16x2(float lo, float hi)
 // side by side then cover whole rows of C, and with a multiple of 8 tiles an XCD keeps meeting the same columns of opT.
 //   side : bf16 low-rank factor, segment s at side + hb_off, rows of rp elements
 //   opT  : small matrices [N][rp], adapter k behind N * rp elements of every adapter before it
-// KS: 32-rank MFMA steps that the largest rank of the launch needs (1, 2 or 4).
+// part0: the first half block of the launch.  KS: 32-rank MFMA steps that the largest rank of the launch needs (1, 2 or 4).
 template <int KS>
-__global__ void __launch_bounds__(64 * EX_NW, KS == 4 ? 3 : 4) k_expand(MetaView mv, uint16_t *__restrict__ C, int N, int tiles_n,
+__global__ void __launch_bounds__(64 * EX_NW, KS == 4 ? 3 : 4) k_expand(MetaView mv, uint16_t *__restrict__ C, int N, int tiles_n, int part0,
                                                        const uint16_t *__restrict__ side, const uint16_t *__restrict__ opT,
                                                        const uint16_t *__restrict__ zero)
 {
     __shared__ __attribute__((aligned(1024))) char lds[EX_LDS];
     constexpr int kHalves = kSkinnyRows / EX_ROWS;
-    const int part = blockIdx.x / tiles_n, n_tile = blockIdx.x - part * tiles_n;
+    const int rel = blockIdx.x / tiles_n, n_tile = blockIdx.x - rel * tiles_n, part = part0 + rel;
     const BlkInfo bi = mv.blk[part / kHalves];
     const SegInfo g = bi.g;
     const int t0 = bi.t0 + (part % kHalves) * EX_ROWS;
@@ -142,16 +142,22 @@ hipError_t launch_expand_bf16(const MetaView &mv, const MetaHeader &h, void *C, 
 {
     if (h.n_blocks == 0) return hipSuccess;
     const int64_t tiles_n = (N + EX_COLS - 1) / EX_COLS;
-    const int64_t n_wg = (int64_t)h.n_blocks * (kSkinnyRows / EX_ROWS) * tiles_n;
-    if (n_wg * 64 * EX_NW >= (int64_t)1 << 32) return hipErrorInvalidValue;   // C itself would be more than 500 GB
-#define PL_EX(KS_) hipLaunchKernelGGL(k_expand<KS_>, dim3((unsigned)n_wg), dim3(64 * EX_NW), 0, st, mv, static_cast<uint16_t *>(C), \
-                                      (int)N, (int)tiles_n, static_cast<const uint16_t *>(side), static_cast<const uint16_t *>(opT), \
+    // A launch has fewer than 2^32 threads, which one-row segments of a very wide C exceed (1024 of them, 2^22 columns: 2^33):
+    // as many launches as it takes, whole half blocks in each.
+    const int64_t parts = (int64_t)h.n_blocks * (kSkinnyRows / EX_ROWS), per_launch = ((((int64_t)1 << 32) - 1) / (64 * EX_NW)) / tiles_n;
+    for (int64_t p0 = 0; p0 < parts; p0 += per_launch) {
+        const unsigned n_wg = (unsigned)((parts - p0 < per_launch ? parts - p0 : per_launch) * tiles_n);
+#define PL_EX(KS_) hipLaunchKernelGGL(k_expand<KS_>, dim3(n_wg), dim3(64 * EX_NW), 0, st, mv, static_cast<uint16_t *>(C), \
+                                      (int)N, (int)tiles_n, (int)p0, static_cast<const uint16_t *>(side), static_cast<const uint16_t *>(opT), \
                                       static_cast<const uint16_t *>(zero))
-    if (h.max_r16 <= 32) PL_EX(1);
-    else if (h.max_r16 <= 64) PL_EX(2);
-    else PL_EX(4);
+        if (h.max_r16 <= 32) PL_EX(1);
+        else if (h.max_r16 <= 64) PL_EX(2);
+        else PL_EX(4);
 #undef PL_EX
-    return hipGetLastError();
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 }  // namespace plora

@@ -193,3 +193,25 @@ def test_lora_only_config5_mlp_up_full_size():
     assert bool(torch.isfinite(dy_rows).all()) and bool(torch.isfinite(ddx_rows).all())
     assert float(dy_rows.min()) > 0 and float(ddx_rows.min()) > 0
     assert float(dy_rows.max()) < 64 and float(ddx_rows.max()) < 64
+
+
+def test_lora_only_more_threads_than_one_launch_holds():
+    """1024 one-token segments and 2^22 columns: the update of y takes two launches.  Rank 1 and a zero base: every element is
+    one product of two bf16 values, rounded once."""
+    import torch
+    from paper_2508_02932_amd import plora
+    T, D, K = 1024, 8, 1 << 22
+    say("[case] lora-only 1024 segments x 2^22 columns")
+    d = plora.Desc(T, D, K, np.arange(T + 1), np.zeros(T), np.array([1]), np.array([2.0]), plora.PLORA_BF16)
+    g = torch.Generator(device="cuda").manual_seed(5)
+    x, A, B = (torch.randn(*s, device="cuda", generator=g).to(torch.bfloat16) for s in ((T, D), (D, 1), (1, K)))
+    y = torch.zeros(T, K, dtype=torch.bfloat16, device="cuda")
+    h = torch.empty(T, dtype=torch.float32, device="cuda")
+    ws = torch.empty(plora.plora_lora_workspace_bytes(d), dtype=torch.uint8, device="cuda")
+    plora.plora_lora_fwd(d, x, [A], [B], y, h, ws)
+    torch.cuda.synchronize()
+    want_h = x.float() @ A.float()
+    assert float((h - want_h[:, 0]).abs().max()) < 1e-4 * float(want_h.abs().max())
+    for lo in range(0, T, 64):
+        side = (2.0 * h[lo:lo + 64]).to(torch.bfloat16).float()
+        assert torch.equal(y[lo:lo + 64], (side[:, None] * B.float()).to(torch.bfloat16)), lo
