@@ -6,7 +6,8 @@ followed by plora_linear_bwd, inputs resident in HBM.  The headline workload is 
 single-GPU configuration: the 70B-shaped MLP up projection (configuration 5, second linear:
 d_in = 8192, d_out = 28672, 32768 tokens, 32 adapters of rank 8..128 in unequal segments).
 
-Prints ONE JSON line:
+Prints ONE JSON line with the headline figures, short enough for a log that keeps the last 2000 characters of a run; all that
+was measured goes to the file that its "record" names (--record):
   value / tokens_per_s  whole-step rate of the headline workload; FLOPs = 4 T D K + 6 (D+K) sum(L r)
   roofline              the dominant kernel (forward base GEMM with the fused expand): algorithmic FLOPs /
                         average launch duration, HIP events on the call's own stream (library timing hook)
@@ -29,6 +30,7 @@ import ctypes as C
 import json
 import os
 import sys
+import tempfile
 import time
 
 ROOT = os.path.dirname(os.path.abspath(__file__))
@@ -41,8 +43,27 @@ PEAK_HBM_GBS = 8000.0              # MI355X HBM3E peak
 ROTATE_BYTES = 600 << 20           # distinct input bytes a kernel sees before a buffer comes round again
 
 
+LINE_CHARS = 1900                  # length that the printed line keeps to
+
+
+def headline(full, record):
+    """What is printed of a full record: the metric, its workload, the roofline of the dominant kernel, the CPU baseline, and of
+    every other kernel its time and fraction of the peak."""
+    out = {k: v for k, v in full.items() if k in (
+        "metric", "value", "unit", "tokens_per_s", "n_gpus", "steps", "warmup", "ms_per_step", "step_ms", "higher_is_better", "scaling",
+        "vs_baseline", "dtype", "data", "config", "frac_of_bf16_mfma_peak", "roofline", "cpu_baseline")}
+    out["kernels"] = {n: {k: e[k] for k in ("ms", "frac") if k in e} for n, e in full["kernels"].items()}
+    out["record"] = record
+    for k in ("kernels", "step_ms"):                    # the first to go where a workload's own text is long
+        if len(json.dumps(out)) > LINE_CHARS:
+            del out[k]
+    return out
+
+
 def main():
     ap = argparse.ArgumentParser()
+    ap.add_argument("--record", default=os.path.join(tempfile.gettempdir(), "plora_bench_record.json"),
+                    help="file that receives the full record (every configuration and variant, ceilings, context figures)")
     ap.add_argument("--gpus", type=int, default=1)
     ap.add_argument("--steps", type=int, default=20)
     ap.add_argument("--warmup", type=int, default=5)
@@ -751,7 +772,9 @@ def main():
         "planner": planner,
         "cpu_baseline": cpu,
     }
-    print(json.dumps(out))
+    with open(args.record, "w") as f:
+        json.dump(out, f, indent=1)
+    print(json.dumps(headline(out, args.record)))
 
 
 if __name__ == "__main__":
