@@ -43,6 +43,27 @@ PEAK_HBM_GBS = 8000.0              # MI355X HBM3E peak
 ROTATE_BYTES = 600 << 20           # distinct input bytes a kernel sees before a buffer comes round again
 
 
+def work_of(lin):
+    """Bound and algorithmic work of each kernel class of a linear's step.  An fp32 call makes both weight gradients in one
+    launch, which the timing hook counts as class db."""
+    lay = lin.layout
+    T, D, K = lay.T, lin.D, lin.K
+    e = 2 if lin.dtype == "bf16" else 4
+    sum_Lr = lay.sum_Lr()
+    R = int(sum(int(r) for r in lay.rank))
+    work = {
+        "gemm_fwd": ("mfma", 2.0 * T * D * K + 2.0 * K * sum_Lr),
+        "gemm_dx": ("mfma", 2.0 * T * D * K + 2.0 * D * sum_Lr),
+        "shrink": ("hbm", T * D * e + D * R * e + sum_Lr * 4.0),
+        "dh": ("hbm", T * K * e + R * K * e + sum_Lr * 4.0),
+        "db": ("hbm", T * K * e + sum_Lr * 4.0 + R * K * 4.0),
+        "da": ("hbm", T * D * e + sum_Lr * 4.0 + D * R * 4.0),
+    }
+    if lin.dtype != "bf16":
+        work["db"] = ("hbm", work["db"][1] + work.pop("da")[1])
+    return work
+
+
 LINE_CHARS = 1900                  # length that the printed line keeps to
 
 
@@ -177,21 +198,6 @@ def main():
         def step(self, i):
             self.fwd(i)
             self.bwd(i)
-
-    def work_of(lin):
-        lay = lin.layout
-        T, D, K = lay.T, lin.D, lin.K
-        e = 2 if lin.dtype == "bf16" else 4
-        sum_Lr = lay.sum_Lr()
-        R = int(sum(int(r) for r in lay.rank))
-        return {
-            "gemm_fwd": ("mfma", 2.0 * T * D * K + 2.0 * K * sum_Lr),
-            "gemm_dx": ("mfma", 2.0 * T * D * K + 2.0 * D * sum_Lr),
-            "shrink": ("hbm", T * D * e + D * R * e + sum_Lr * 4.0),
-            "dh": ("hbm", T * K * e + R * K * e + sum_Lr * 4.0),
-            "db": ("hbm", T * K * e + sum_Lr * 4.0 + R * K * 4.0),
-            "da": ("hbm", T * D * e + sum_Lr * 4.0 + D * R * 4.0),
-        }
 
     def kernel_table(lin, kern_ms):
         out = {}

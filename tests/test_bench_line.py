@@ -1,4 +1,4 @@
-"""The line that bench.py prints: one JSON object with the required keys, short enough that a log which keeps the last 2000
+"""The work that bench.py divides a kernel class's time by, and the line that bench.py prints: one JSON object with the required keys, short enough that a log which keeps the last 2000
 characters of a run keeps all of it, whatever else was measured."""
 import json
 
@@ -41,3 +41,12 @@ def test_the_printed_line_is_whole_in_a_short_log():
     long["config"]["workload"] += " " * 400
     got = json.loads(json.dumps(bench.headline(long, "/tmp/plora_bench_record.json")))
     assert len(json.dumps(got)) <= bench.LINE_CHARS and all(k in got for k in REQUIRED) and "kernels" not in got
+
+
+def test_work_of_the_fp32_weight_gradients_is_that_of_their_one_launch():
+    from paper_2508_02932_amd import workloads as wl
+    f, b = (wl.small("work", t, 64, 48, lengths=[30, 20], seg_adapter=[0, 1], ranks=[8, 4], scales=[1.0, 1.0], seed=1) for t in ("f32", "bf16"))
+    T, D, K, R, Lr = 50, 64, 48, 12, 30 * 8 + 20 * 4
+    assert "da" not in bench.work_of(f)
+    assert bench.work_of(f)["db"] == ("hbm", T * (D + K) * 4 + 2 * Lr * 4 + R * (D + K) * 4)
+    assert bench.work_of(b)["db"] == ("hbm", T * K * 2 + Lr * 4 + R * K * 4) and bench.work_of(b)["da"] == ("hbm", T * D * 2 + Lr * 4 + D * R * 4)
