@@ -55,13 +55,17 @@ typedef struct {
     int32_t n_seg, n_adapters, n_blocks, max_r16;
     int32_t seg_stride, ad_stride, tile_stride, desc_words;
     uint64_t off_hdr, off_seg, off_ad, off_tile, off_blk_seg, off_seg_list, table_bytes;
-    /* launch plans: contraction splits of shrink / dH, token splits and tile widths of dA / dB */
+    /* launch plans: contraction splits of shrink / dH, token splits and tile widths of dA / dB
+     * (the base products' at the end) */
     int32_t shrink_splits, dh_splits, da_splits, da_tile_cols, db_splits, db_tile_cols;
     int32_t r16_total, n_active;     /* sum of r16 over adapters; adapters that own tokens */
     /* byte offsets of the workspace regions */
     uint64_t ws_zero, ws_meta, ws_desc, ws_at, ws_ap, ws_hb, ws_zt_h, ws_zt_g, ws_hf, ws_gf, ws_part, ws_wpart, ws_total;
     uint64_t h_elems;
     uint64_t off_tile_order;
+    /* how the base products are cut, [0] forward, [1] dX: rows of the small output tiles (64 or 128; 0: 256 x 256 tiles
+     * alone), splits of the contraction, and the 256-row tiles that are left to the 256 x 256 kernel */
+    int32_t gemm_rows[2], gemm_splits[2], gemm_big_tiles[2];
 } plora_debug_info;
 
 /* Fills *info and, if tables_out is not NULL, copies the table image (info->table_bytes bytes;

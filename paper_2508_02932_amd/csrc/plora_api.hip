@@ -862,6 +862,10 @@ int plora_debug_metadata(const plora_desc *desc, plora_debug_info *info, void *t
         info->ws_total = m.ws.total;
         info->h_elems = m.h_elems;
         info->desc_words = m.n_words;
+        for (int i = 0; i < 2; ++i) {
+            const GemmPlan &p = i == 0 ? m.gemm_fwd : m.gemm_dx;
+            info->gemm_rows[i] = p.bm; info->gemm_splits[i] = p.n_split; info->gemm_big_tiles[i] = p.big_tiles;
+        }
         if (tables_out) {
             if (cap < m.layout.bytes) return -1;
             std::memcpy(tables_out, m.image.data(), m.layout.bytes);

@@ -144,9 +144,23 @@ def test_config5_mlp_up_full_size_weight_stored_out_in():
     check_full_size(wl.config(5)[1], w_layout=plora.PLORA_W_OUT_IN)
 
 
+def test_odd_shapes_more_big_tiles_than_workgroups():
+    """Both products in 256 x 256 tiles alone, and more of them than workgroups of the persistent grid (137 x 18 and 137 x 5,
+    counts that the XCD remap does not divide): workgroups walk several tiles each; ragged in every dimension."""
+    import gpu_harness as gh
+    from paper_2508_02932_amd import plora
+    lin = wl.small("odd_more_big_tiles", "bf16", 1096, 4360,
+                   lengths=[4611, 9290, 3, 0, 7977, 2258, 8031, 2830],
+                   seg_adapter=[0, 1, 2, 3, -1, 4, 1, 5],
+                   ranks=[128, 1, 24, 8, 72, 33], scales=[2.0, 0.5, 1.0, 4.0, 2.0, 0.25], seed=97)
+    info, _, _ = plora.plora_debug_metadata(gh.desc_of(lin))
+    assert list(info.gemm_rows) == [0, 0] and list(info.gemm_big_tiles) == [137, 137] and info.n_tiles == 137
+    check_full_size(lin)
+
+
 def test_odd_shapes_many_tiles():
-    """More GEMM tiles than workgroups of the persistent grid (18 x 18 of them, a count that the XCD
-    remap does not divide), ragged in every dimension: rows, columns and contraction length are no
+    """18 x 18 tiles of 256 x 256, more than one round of the chip: the forward product runs 14 of the 18 row tiles in
+    256 x 256 tiles and the rest in 128-row tiles, dX in 128-row tiles alone; ragged in every dimension: rows, columns and contraction length are no
     multiples of the tile, segments of unequal length with a base-only one and an adapter that owns
     two segments, ranks from 1 to 128.  The narrow hidden sizes also send dA and dB through the
     128-column tiles with a split token walk."""
@@ -154,6 +168,10 @@ def test_odd_shapes_many_tiles():
                    lengths=[611, 1290, 3, 0, 977, 258, 1031, 307],
                    seg_adapter=[0, 1, 2, 3, -1, 4, 1, 5],
                    ranks=[128, 1, 24, 8, 72, 33], scales=[2.0, 0.5, 1.0, 4.0, 2.0, 0.25], seed=83)
+    import gpu_harness as gh
+    from paper_2508_02932_amd import plora
+    info, _, _ = plora.plora_debug_metadata(gh.desc_of(lin))
+    assert list(info.gemm_rows) == [128, 128] and list(info.gemm_big_tiles) == [14, 0]
     assert ((lin.layout.T + 255) // 256) * ((lin.K + 255) // 256) > 256
     check_full_size(lin)
     # and with the roles of the hidden sizes swapped (wide contraction, narrow output)
