@@ -67,7 +67,7 @@ def work_of(lin):
 LINE_CHARS = 1900                  # length that the printed line keeps to
 
 
-def headline(full, record):
+def printed_line(full, record):
     """What is printed of a full record: the metric, its workload, the roofline of the dominant kernel, the CPU baseline, and of
     every other kernel its time and fraction of the peak."""
     out = {k: v for k, v in full.items() if k in (
@@ -780,7 +780,7 @@ def main():
     }
     with open(args.record, "w") as f:
         json.dump(out, f, indent=1)
-    print(json.dumps(headline(out, args.record)))
+    print(json.dumps(printed_line(out, args.record)))
 
 
 if __name__ == "__main__":

@@ -32,14 +32,14 @@ def full_record():
 
 
 def test_the_printed_line_is_whole_in_a_short_log():
-    line = json.dumps(bench.headline(full_record(), "/tmp/plora_bench_record.json"))
+    line = json.dumps(bench.printed_line(full_record(), "/tmp/plora_bench_record.json"))
     assert len(line) <= bench.LINE_CHARS < 2000
     got = json.loads(line)
     assert all(k in got for k in REQUIRED) and got["roofline"]["frac"] == 0.1234 and got["cpu_baseline"]["value"] == 0.091234
     assert got["kernels"]["gemm_fwd"] == {"ms": 12.3456, "frac": 0.1234} and got["kernels"]["prep"] == {"ms": 0.0229}
     long = full_record()
     long["config"]["workload"] += " " * 400
-    got = json.loads(json.dumps(bench.headline(long, "/tmp/plora_bench_record.json")))
+    got = json.loads(json.dumps(bench.printed_line(long, "/tmp/plora_bench_record.json")))
     assert len(json.dumps(got)) <= bench.LINE_CHARS and all(k in got for k in REQUIRED) and "kernels" not in got
 
 
@@ -50,3 +50,8 @@ def test_work_of_the_fp32_weight_gradients_is_that_of_their_one_launch():
     assert "da" not in bench.work_of(f)
     assert bench.work_of(f)["db"] == ("hbm", T * (D + K) * 4 + 2 * Lr * 4 + R * (D + K) * 4)
     assert bench.work_of(b)["db"] == ("hbm", T * K * 2 + Lr * 4 + R * K * 4) and bench.work_of(b)["da"] == ("hbm", T * D * 2 + Lr * 4 + D * R * 4)
+
+
+def test_main_shadows_no_function_of_the_module():
+    functions = {n for n, v in vars(bench).items() if callable(v) and getattr(v, "__module__", None) == "bench"}
+    assert not functions & set(bench.main.__code__.co_varnames + bench.main.__code__.co_cellvars)
