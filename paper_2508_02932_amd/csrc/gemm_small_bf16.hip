@@ -4,8 +4,10 @@
 // 34 MB, against 2 GFLOP) or by idle compute units, so the tiles are small and the contraction is
 // split over workgroups until about two of them sit on every compute unit.  Against the 256 x 256 kernel:
 // 48 tokens, 4096 -> 4096, 83 -> 12 us; 512 tokens, contraction 14336 -> 4096 columns, 250 -> 71 us; 1024 tokens, the
-// same, 261 -> 127 us.  What bounds it when the chip is full is the traffic from L2 into LDS (64 KB per compute unit and
-// stage of 64, 0.95 us: 17 TB/s): a loop that reads the operands of the next step during the multiplications, rings of
+// same, 261 -> 127 us.  What bounds it when the chip is full and W lies in the last-level cache is the traffic from L2 into LDS
+// (64 KB per compute unit and stage of 64, 0.95 us: 17 TB/s); with W from HBM, as in a model that walks its layers, it is the
+// round trip of a direct load with the few stages that fit beside a second workgroup (512 tokens, 4096 -> 14336, three W slots:
+// 65 us from the cache, 72 from HBM).  A loop that reads the operands of the next step during the multiplications, rings of
 // 4 and 6 stages and 256 x 128 tiles of eight waves were all no faster, and stages of 32 (64-byte pieces of rows) 20 % slower.
 #include "plora_internal.h"
 
@@ -472,9 +474,12 @@ static hipError_t dispatch_small(const GemmPlan &p, const MetaView &mv, const Me
                                  const void *W, const void *side, const void *ap, const void *zero, void *C, float *part, hipStream_t st)
 {
     constexpr int slot = 16 + (FWD ? 1 : 0) + (ACC ? 2 : 0);
-    // up to four row tiles every W tile is met by few workgroups and comes from HBM: the deeper W ring, although the requests
-    // then go out in the worse order (512 tokens, 4096 -> 14336 step, W from HBM, 209 -> 202 us; 1024 tokens with W in the
-    // last-level cache 338 -> 350 us without the rule)
+    // A third W slot pays where W comes from HBM and four row tiles share it, and costs the better order of the requests: two
+    // and three slots, us, W from HBM (in the last-level cache): 4096 -> 14336, 384 tokens 71 and 73 (56 and 64), 512 tokens 80
+    // and 72 (60 and 65); 14336 -> 4096, 384 tokens 64 and 66, 512 tokens 85 and 77, 513 to 896 tokens 5 to 9 % slower with
+    // three, 1024 tokens 144 and 132 (114 and 123); 8192 -> 8192, 513 to 896 tokens the same to 2 % slower (10 to 20 % slower), 1024
+    // tokens 134 and 133 (117 and 127).  The line is drawn for W from HBM, at four row tiles; at eight the split weight gains
+    // as well, but the others lose more with W in the cache.
     const bool deep = h.T <= 512;
 #define PL_GS(BM_, DEEP_, SLOT_) launch_small<FWD, BM_, DEEP_, ACC>(mv, h, Kd, N, S, W, side, ap, zero, C, part, p.n_split, p.big_tiles, slot + 4 * SLOT_, st)
     if (p.bm == 64) return PL_GS(64, false, 0);
@@ -499,6 +504,8 @@ hipError_t launch_gemm_small_bf16(const GemmPlan &p, const MetaView &mv, const M
 //   256 x 256 tiles, one workgroup per compute unit     0.92 + 0.78 f     (1.12 at 64 tiles, 1.30 at 128, 1.70 at 256)
 //   128 x 128 tiles, two per compute unit               0.38 + 0.62 f     (0.69 at 256 workgroups, 1.00 at 512)
 //    64 x 128 tiles, two per compute unit               0.38 + 0.24 f     (0.50 at 256 workgroups, 0.62 at 512)
+// (with W in the last-level cache; from HBM the 128 x 128 tiles take up to a third longer, 512 x 4096 -> 14336 80 us against 60
+// with two W slots, 72 with the three it runs).
 // A split adds the summing launch (4 us) and a write and a read of the fp32 partial tiles.  At the sizes where the
 // choice changes both sides were timed (256-tile kernel against the small tiles): 2048 x 4096 -> 4096 83 against 65 us,
 // 3072 x 4096 -> 4096 92 against 112 us, 1024 x 4096 -> 14336 103 against 118 us, 512 x 4096 -> 14336 85 against 62 us.
