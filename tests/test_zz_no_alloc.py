@@ -39,3 +39,27 @@ def test_noalloc_forward_equals_forward_twice_in_a_row():
     with pytest.raises(plora.PloraError) as e:
         plora.plora_linear_fwd_noalloc(d, dp.x, dp.W, dp.A, dp.B, dp.y, dp.h)
     assert e.value.code == 7
+
+
+@pytest.mark.parametrize("case", ["token_blocks", "adapters_without_tokens"])
+def test_descriptions_that_fit_the_scratch_array_only_without_the_records(case):
+    """The workspace gives up skinny splits held in reserve, or - no token has an adapter - the packed matrices: forward and
+    backward are what the oracle says, nothing is written past the smaller workspace, and the call on the scratch array gives
+    the same bits."""
+    import torch
+    import gpu_harness as gh
+    import oracle
+    from paper_2508_02932_amd import plora
+    from test_gpu_parity import run_and_compare
+    if case == "token_blocks":
+        lin = wl.small("records_blocks", "bf16", 512, 512, lengths=[21350] * 4, seg_adapter=[0, 1, 2, 3], ranks=[16] * 4, scales=[2.0] * 4, seed=139)
+    else:
+        lin = wl.small("records_idle", "bf16", 1048, 64, lengths=[300], seg_adapter=[-1], ranks=[64] * 250, scales=[2.0] * 250, seed=149)
+    assert plora.plora_workspace_bytes(gh.desc_of(lin)) <= plora.NOALLOC_SCRATCH_BYTES
+    dp, _ = run_and_compare(lin, impl=oracle.matmul)
+    y = dp.y.clone()
+    dp.y.fill_(float("nan"))
+    plora.plora_linear_fwd_noalloc(dp.desc, dp.x, dp.W, dp.A, dp.B, dp.y, dp.h)
+    torch.cuda.synchronize()
+    gh.check_guards(dp)
+    assert torch.equal(y, dp.y)
