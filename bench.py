@@ -44,8 +44,8 @@ ROTATE_BYTES = 600 << 20           # distinct input bytes a kernel sees before a
 
 
 def work_of(lin):
-    """Bound and algorithmic work of each kernel class of a linear's step.  An fp32 call makes both weight gradients in one
-    launch, which the timing hook counts as class db."""
+    """Bound and algorithmic work of each kernel class of a linear's step.  A call makes both weight gradients in one launch,
+    which the timing hook counts as class db (an fp32 call always; for bf16 see kernel_table)."""
     lay = lin.layout
     T, D, K = lay.T, lin.D, lin.K
     e = 2 if lin.dtype == "bf16" else 4
@@ -201,7 +201,10 @@ def main():
 
     def kernel_table(lin, kern_ms):
         out = {}
-        for name, (bound, work) in work_of(lin).items():
+        of = work_of(lin)
+        if kern_ms.get("db") and not kern_ms.get("da") and "da" in of:      # both weight gradients in one launch, class db
+            of["db"] = (of["db"][0], of["db"][1] + of.pop("da")[1])
+        for name, (bound, work) in of.items():
             ms = kern_ms.get(name)
             if not ms:
                 continue
@@ -628,9 +631,11 @@ def main():
                                    "graph_replay_ms_per_step": round(graph_ms(layer_step, min(r.n_sets for r in runs)), 4),
                                    "grouped": {"ms_per_step": round(ms4g, 4), "tflops": round(f4 / (ms4g * 1e-3) / 1e12, 1),
                                                "graph_replay_ms_per_step": round(graph_ms(grouped_step, min(r.n_sets for r in runs)), 4),
-                                               "ms_per_step_in_kernel": {k: {"plain_7_launches": round(7 * kp[k], 4),
-                                                                             "grouped_4_launches": round(4 * kg[k], 4)}
-                                                                         for k in ("shrink", "da") if kp.get(k) and kg.get(k)},
+                                               "ms_per_step_in_kernel": {
+                                                   "shrink": {"plain_7_launches": round(7 * kp["shrink"], 4),
+                                                              "grouped_4_launches": round(4 * kg["shrink"], 4)},
+                                                   "weight_gradients": {"plain_7_launches": round(7 * kp["db"], 4),
+                                                                        "grouped_6_launches": round(4 * kg["db"] + 2 * (kg["da"] or 0.0), 4)}},
                                                "with_input_gradients_summed": {
                                                    "plain_calls_plus_three_additions_ms": round(ms4ps, 4),
                                                    "grouped_dx_sum_ms": round(ms4gs, 4),

@@ -85,10 +85,11 @@ struct HostMeta {
     WorkspaceLayout ws;               // plora_linear_fwd / _bwd
     WorkspaceLayout ws_lora;          // plora_lora_fwd / _bwd: the padded small-matrix region holds [max(d_in, d_out)][rp]
     size_t h_elems = 0, hb_elems = 0, zt_elems = 0, at_elems = 0, ap_elems = 0;
-    int r16_total = 0, n_active = 0, max_rank = 0, split_dA = 1, split_dB = 1, bc_dA = 256, bc_dB = 256;
+    int r16_total = 0, n_active = 0, max_rank = 0, split_dA = 1, split_dB = 1;
     int split_shrink = 1, split_dh = 1;
     GemmPlan gemm_fwd, gemm_dx;
     int n_words = 0;
+    bool small_part_is_dB = false;    // which of dB and dA has the smaller set of partial tiles
     bool order_is_identity = false;   // the sorted order of the GEMM row tiles is 0, 1, 2, ...: the device need not sort
 };
 
@@ -128,10 +129,8 @@ static void build_meta(const plora_desc *d, HostMeta &m)
     }
     m.h_elems = (size_t)h; m.hb_elems = (size_t)hb; m.zt_elems = (size_t)zt;
     m.at_elems = (size_t)at; m.ap_elems = (size_t)ap;
-    m.split_dA = tokc_splits(m.hdr, d->d_in, m.n_active);
-    m.split_dB = tokc_splits(m.hdr, d->d_out, m.n_active);
-    m.bc_dA = tokc_tile_columns(m.hdr, d->d_in, m.n_active);
-    m.bc_dB = tokc_tile_columns(m.hdr, d->d_out, m.n_active);
+    m.split_dA = tokc_splits(m.hdr, d->d_in, d->d_out, m.n_active);
+    m.split_dB = tokc_splits(m.hdr, d->d_out, d->d_in, m.n_active);
     m.split_shrink = skinny_splits(m.hdr, d->d_in);
     m.split_dh = skinny_splits(m.hdr, d->d_out);
 
@@ -194,6 +193,15 @@ static void build_meta(const plora_desc *d, HostMeta &m)
         }
     }
     packed = bf;
+    // dB and dA share a launch: the larger set of their partial tiles has the region of its own, the smaller lies over the
+    // skinny ones and is split no further than fits there
+    {
+        const size_t room = (size_t)skinny_cap * m.hdr.n_blocks * kSkinnyRows * m.hdr.max_r16 * 4;
+        auto bytes = [&](int n, int64_t C) { return n > 1 ? (size_t)n * m.r16_total * C * 4 : (size_t)0; };
+        m.small_part_is_dB = bytes(m.split_dB, d->d_out) <= bytes(m.split_dA, d->d_in);
+        int &n = m.small_part_is_dB ? m.split_dB : m.split_dA;
+        while (bytes(n, m.small_part_is_dB ? d->d_out : d->d_in) > room) n -= 1;
+    }
     int64_t rp_total = 0;
     for (int32_t k = 0; k < d->n_adapters; ++k) rp_total += m.t.ad[k].rp;
     lay_out(m.ws_lora, m.layout.bytes, (size_t)(rp_total * std::max(d->d_in, d->d_out)), false);
@@ -345,6 +353,12 @@ struct PrepList {
     }
 };
 
+// Weight-gradient products, launched together: of one call, or of every projection of a grouped call.
+struct TokcList {
+    TokcOperands op[kTokMaxPasses];
+    int n = 0;
+};
+
 static plora_status forward_impl(const plora_desc *desc, const void *x, const void *W, const void *const *A,
                                  const void *const *B, void *y, float *h_saved, void *workspace, size_t ws_bytes,
                                  void *hip_stream, bool lora_only = false, bool check_only = false, unsigned steps = kStepsAll,
@@ -410,7 +424,7 @@ static plora_status backward_impl(const plora_desc *desc, const void *x, const v
                                   const void *const *B, const void *dy, const float *h_saved, void *dx, float *const *dA,
                                   float *const *dB, void *workspace, size_t ws_bytes, void *hip_stream, bool lora_only = false,
                                   bool check_only = false, unsigned steps = kStepsAll, bool dx_accumulate = false,
-                                  PrepList *later = nullptr, const Nf4Job *nf4 = nullptr)
+                                  PrepList *later = nullptr, const Nf4Job *nf4 = nullptr, TokcList *later_w = nullptr)
 {
     const bool want_w = (dA != nullptr) || (dB != nullptr);
     if (desc && want_w && desc->n_adapters > 0 && (!dA || !dB)) {
@@ -492,8 +506,12 @@ static plora_status backward_impl(const plora_desc *desc, const void *x, const v
         }
     }
     if (any_w) {
-        if (steps & kStepDb) { Bracket b(4, st); PL_TRY(launch_tokcontract_bf16(mv, m.hdr, false, dy, desc->d_out, zt_h, ws + L.zero, wpart, m.split_dB, m.r16_total, m.n_active, st)); }
-        if (steps & kStepDa) { Bracket b(5, st); PL_TRY(launch_tokcontract_bf16(mv, m.hdr, true, x, desc->d_in, zt_g, ws + L.zero, wpart, m.split_dA, m.r16_total, m.n_active, st)); }
+        // dB and dA in one launch; the smaller set of partial tiles lies where the skinny ones were (summed by now)
+        TokcList own;
+        TokcList &list = later_w ? *later_w : own;
+        if (steps & kStepDb) list.op[list.n++] = TokcOperands{mv, dy, zt_h, desc->d_out, m.small_part_is_dB ? part : wpart, m.split_dB, m.r16_total, m.hdr.max_r16, false};
+        if (steps & kStepDa) list.op[list.n++] = TokcOperands{mv, x, zt_g, desc->d_in, m.small_part_is_dB ? wpart : part, m.split_dA, m.r16_total, m.hdr.max_r16, true};
+        if (own.n > 0) { Bracket b(4, st); PL_TRY(launch_tokcontract_bf16(own.op, own.n, m.hdr.n_adapters, ws + L.zero, st)); }
     }
     if (!(steps & kStepDx)) return PLORA_OK;
     if (dx && desc->T > 0 && lora_only) {
@@ -552,7 +570,7 @@ static size_t cell_part_bytes(const GroupPlan &gp, const plora_desc *d0, const i
         MetaHeader hv = gp.m[members[0]]->hdr;
         hv.max_r16 = c.max_r16;
         const size_t shrink = (size_t)gp.m[members[0]]->split_shrink * hv.n_blocks * kSkinnyRows * c.max_r16 * 4;
-        const int sp = tokc_splits(hv, d0->d_in, gp.m[0]->n_active);
+        const int sp = tokc_splits(hv, d0->d_in, 0, gp.m[0]->n_active);
         const size_t da = sp > 1 ? (size_t)sp * c.r16_total * d0->d_in * 4 : 0;
         most = std::max(most, std::max(shrink, da));
     }
@@ -684,10 +702,11 @@ static plora_status group_backward(const plora_group *g, const void *x, const vo
     char *ws = static_cast<char *>(workspace);
     // dx_sum: every projection's dX GEMM targets the one tensor, the first overwriting it, the others adding to it
     PrepList preps;
+    TokcList grads;
     auto run = [&](int p, bool check, unsigned steps) {
         return backward_impl(&g->desc[p], x, W[p], A ? A[p] : nullptr, B ? B[p] : nullptr, dy[p], h_saved ? h_saved[p] : nullptr,
                              dx_sum ? dx_sum : (dx ? dx[p] : nullptr), dA ? dA[p] : nullptr, dB ? dB[p] : nullptr, ws + gp.ws_off[p],
-                             gp.m[p]->ws.total, hip_stream, false, check, steps, dx_sum != nullptr && p > 0, &preps);
+                             gp.m[p]->ws.total, hip_stream, false, check, steps, dx_sum != nullptr && p > 0, &preps, nullptr, &grads);
     };
     for (int p = 0; p < gp.n; ++p)
         if ((ps = run(p, true, kStepsAll)) != PLORA_OK) return ps;
@@ -724,7 +743,13 @@ static plora_status group_backward(const plora_group *g, const void *x, const vo
                                    reinterpret_cast<float *>(ws + gp.part_off), gp.part_bytes, gp.m[members[0]]->split_shrink, hf, hb, zt, st));
     }
     for (int p = 0; p < gp.n; ++p)
-        if ((ps = run(p, false, kStepDh | kStepDb | (fuse_a[p] ? 0u : kStepDa) | kStepDx)) != PLORA_OK) return ps;
+        if ((ps = run(p, false, kStepDh | kStepDb | (fuse_a[p] ? 0u : kStepDa))) != PLORA_OK) return ps;
+    if (grads.n > 0) {
+        Bracket b(4, st);
+        PL_TRY(launch_tokcontract_bf16(grads.op, grads.n, d0->n_adapters, ws + gp.ws_off[0] + gp.m[0]->ws.zero, st));
+    }
+    for (int p = 0; p < gp.n; ++p)
+        if ((ps = run(p, false, kStepDx)) != PLORA_OK) return ps;
     for (int c = 0; c < gp.n_cells; ++c) {
         int members[kMaxGroup], nm = 0;
         for (int p = 0; p < gp.n; ++p)
@@ -734,7 +759,7 @@ static plora_status group_backward(const plora_group *g, const void *x, const vo
         group_view(gp, ws, members, nm, false, gv, hv);
         Bracket b(5, st);
         PL_TRY(launch_tokc_group_dA(gv, hv, x, d0->d_in, ws + gp.ws_off[members[0]] + gp.m[members[0]]->ws.zero,
-                                    reinterpret_cast<float *>(ws + gp.part_off), gp.part_bytes, tokc_splits(hv, d0->d_in, gp.m[0]->n_active),
+                                    reinterpret_cast<float *>(ws + gp.part_off), gp.part_bytes, tokc_splits(hv, d0->d_in, 0, gp.m[0]->n_active),
                                     gp.m[0]->n_active, st));
     }
     return PLORA_OK;
@@ -853,8 +878,8 @@ int plora_debug_metadata(const plora_desc *desc, plora_debug_info *info, void *t
         info->off_tile_order = m.layout.tile_order;
         info->table_bytes = m.layout.bytes;
         info->shrink_splits = m.split_shrink; info->dh_splits = m.split_dh;
-        info->da_splits = m.split_dA; info->da_tile_cols = m.bc_dA;
-        info->db_splits = m.split_dB; info->db_tile_cols = m.bc_dB;
+        info->da_splits = m.split_dA; info->da_tile_cols = kTokTileColumns;
+        info->db_splits = m.split_dB; info->db_tile_cols = kTokTileColumns;
         info->r16_total = m.r16_total; info->n_active = m.n_active;
         info->ws_zero = m.ws.zero; info->ws_meta = m.ws.meta; info->ws_desc = m.ws.desc; info->ws_at = m.ws.at;
         info->ws_ap = m.ws.ap; info->ws_hb = m.ws.hb; info->ws_zt_h = m.ws.zt_h; info->ws_zt_g = m.ws.zt_g;

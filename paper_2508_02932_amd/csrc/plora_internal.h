@@ -504,23 +504,32 @@ hipError_t launch_gemm_small_bf16(const GemmPlan &p, const MetaView &mv, const M
 // segment, opT = padded small matrices [N][rp], one behind the other.
 hipError_t launch_expand_bf16(const MetaView &mv, const MetaHeader &h, void *C, int64_t N, const void *side, const void *opT,
                               const void *zero, hipStream_t st);
-// Token contraction: out_k = mult * sum_t S[t][c] * zt[j][t] over all segments of adapter k.
+// Token contractions: out_k = mult * sum_t S[t][c] * zt[j][t] over all segments of adapter k, several products in one launch
+// (dB and dA of a call; of every projection of a grouped call: their adapters and segments are the same).
 //   want_dA: S = x, out = dA_k[c][j], mult = 1;  else S = dy, out = dB_k[j][c], mult = scale_k.
 //   n_split > 1: the token walk is split, partial tiles go through `part` ([split][r16_total][C] fp32).
-hipError_t launch_tokcontract_bf16(const MetaView &mv, const MetaHeader &h, bool want_dA, const void *S,
-                                   int64_t C, const void *zt, const void *zero, float *part, int n_split,
-                                   int r16_total, int n_active_adapters, hipStream_t st);
+struct TokcOperands {
+    MetaView mv;
+    const void *S, *zt;
+    int64_t C;
+    float *part;
+    int n_split, r16_total, max_r16;
+    bool want_dA;
+};
+constexpr int kTokMaxPasses = 2 * kMaxGroup;
+hipError_t launch_tokcontract_bf16(const TokcOperands *ops, int n, int n_adapters, const void *zero, hipStream_t st);
 // The same two passes for several projections at once (see GroupView).  hv: projection 0's header with max_r16 replaced
 // by the fused one.  Shrink: hf / hb / zt per projection as in launch_skinny_bf16 (mode 0);
 // n_split: that of the projections' plain calls.  dA: the results go to each
-// projection's own dA_k; n_split must be tokc_splits(hv, C, n_active_adapters).
+// projection's own dA_k; n_split must be tokc_splits(hv, C, 0, n_active_adapters).
 // part_bytes: size of `part`; a pass whose partial tiles do not fit is refused.
 hipError_t launch_skinny_group(const GroupView &gv, const MetaHeader &hv, const void *x, int64_t C, const void *zero, float *part,
                                size_t part_bytes, int n_split, float *const *hf, void *const *hb, void *const *zt, hipStream_t st);
 hipError_t launch_tokc_group_dA(const GroupView &gv, const MetaHeader &hv, const void *x, int64_t C, const void *zero,
                                 float *part, size_t part_bytes, int n_split, int n_active_adapters, hipStream_t st);
-int tokc_splits(const MetaHeader &h, int64_t C, int n_active_adapters);
-int tokc_tile_columns(const MetaHeader &h, int64_t C, int n_active_adapters);
+// C_other: columns of the product that shares the launch (0: none).
+int tokc_splits(const MetaHeader &h, int64_t C, int64_t C_other, int n_active_adapters);
+constexpr int kTokTileColumns = 128;
 int skinny_splits(const MetaHeader &h, int64_t C);
 
 // fp32 path (fp64 accumulation) ---------------------------------------------------------------------

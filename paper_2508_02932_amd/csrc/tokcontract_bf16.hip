@@ -8,7 +8,7 @@
 // The token index is the slow index of the big matrix, so its MFMA operand needs a transpose; it
 // is staged HBM -> LDS as it lies in memory (direct loads into a ring of stages that fills the LDS)
 // and read with the transposing LDS load (ds_read_b64_tr_b16).  The rank stays whole in every tile;
-// tiles are cut along the hidden dimension (256 or 128 columns per workgroup, one wave per 32
+// tiles are cut along the hidden dimension (128 columns per workgroup, one wave per 32
 // columns) and a workgroup walks the tokens of one adapter, longest adapters first.  The MFMA code
 // is specialised per number of 16-wide rank blocks so that every LDS read of a stage is in flight
 // before the first MFMA.  Nothing in the loop may spill: a scratch reload waits on the same counter
@@ -27,6 +27,7 @@ typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;
 
 #define LDS_PTR(T, p) ((__attribute__((address_space(3))) T *)(p))
 
+constexpr int TC_BC = kTokTileColumns;                 // columns of the big matrix per workgroup
 constexpr int TC_BT = 64;                  // tokens per stage (TC_BT / 32 MFMA K steps)
 constexpr int TC_MAX_NST = 8;              // LDS ring stages: as many as fit in the 160 KB of a compute unit, at most this
 constexpr int TC_LDS_BYTES = 160 * 1024;
@@ -51,31 +52,51 @@ __device__ inline void tc_wait_vmcnt(int n)
 #undef W_
 }
 
-// grid (column tiles, adapters, token splits).  part != nullptr: write the fp32 partial tile
-// [r16][C] of this split instead of the final result.
+// One product of a launch: the big matrix [T][C], the small factor, and how the work is cut.
+struct TokcPass {
+    const TokJob *job;
+    const int32_t *seg_list;
+    const SegInfo *seg;
+    const uint16_t *S, *zt;
+    float *part;                  // fp32 partial tiles [split][r16_total][C]; null: the result is written directly
+    int32_t C, tiles, n_split;    // tiles: of TC_BC columns
+    int32_t r16_total, want_da;
+    int32_t unit0, finish0;       // first workgroup along x of this product, in the main and in the finishing launch
+    int32_t reserved;
+};
+struct TokcBatch { TokcPass p[kTokMaxPasses]; };
+
+// grid (column tiles and token splits of every product of the batch; adapters).  dB and dA do not depend on each other, nor do
+// those of the projections of a grouped call, and together they need fewer splits to fill the chip.  In two launches with a finishing launch each, and in one with one: 8192 tokens,
+// 4096 -> 4096, four adapters of rank 8 to 64 47.6 and 34.1 us; 512 tokens, 4096 -> 14336 24.7 and 14.3; 1531 tokens, 1000 ->
+// 2504, five adapters (no split) 22.1 and 12.1; 16384 tokens, 4096 -> 14336, eight adapters 143 and 122; dB of a grouped
+// q / k / v call of 16384 tokens 60 and 46.
 // GROUP (dA only): the small factor of adapter k is the transposed g of several projections that share x, one below
-// the other (GroupView); mv is projection 0's view, `zt` is not used, every projection's dA_k gets its own columns.
-template <bool WANT_DA, int BC, bool GROUP = false>
-__global__ void __launch_bounds__(2 * BC) __attribute__((amdgpu_waves_per_eu(2, 2))) k_tokc(MetaView mv, const uint16_t *__restrict__ S, int C,
-                                             const uint16_t *__restrict__ zt, const uint16_t *__restrict__ zero,
-                                             float *__restrict__ part, int r16_total, int max_r16, int nst,
+// the other (GroupView); the tables are projection 0's, `zt` is not used, every projection's dA_k gets its own columns.
+template <bool GROUP>
+__global__ void __launch_bounds__(2 * TC_BC) __attribute__((amdgpu_waves_per_eu(2, 2))) k_tokc(TokcBatch batch, int n_pass,
+                                             const uint16_t *__restrict__ zero, int max_r16, int nst,
                                              std::conditional_t<GROUP, GroupView, NoGroup> gv)
 {
-    static_assert(!GROUP || WANT_DA, "");
-    // BC columns of the big matrix per workgroup (256 or 128), one wave per 32 columns
-    static_assert(BC == 256 || BC == 128, "");
-    constexpr int TC_BC = BC, TC_NW = BC / 32, TC_S_BYTES = TC_BT * BC * 2;
-    constexpr int CPRW = BC / 8;                                  // 16-byte chunks per row of the big-matrix tile
+    constexpr int TC_NW = TC_BC / 32, TC_S_BYTES = TC_BT * TC_BC * 2;     // one wave per 32 columns
+    constexpr int CPRW = TC_BC / 8;                               // 16-byte chunks per row of the big-matrix tile
     constexpr int RPIW = 64 / CPRW;                               // rows per 1 KB load instruction
     // 16-byte chunk c of token row u is stored at slot c ^ swz(u); chosen so that the 8 rows (u..u+3 and
     // u+8..u+11) that one pass of a transposing read touches fall into 8 different 32-byte bank groups
-    auto swz = [](int u) {
-        return BC == 256 ? 4 * (u & 3) + 2 * ((u >> 3) & 1) : 2 * (u & 3) + 8 * ((u >> 3) & 1);
-    };
+    auto swz = [](int u) { return 2 * (u & 3) + 8 * ((u >> 3) & 1); };
     extern __shared__ __attribute__((aligned(1024))) char lds[];
-    const TokJob a = mv.job[blockIdx.y];             // longest adapters first
+    int pi = 0;
+    for (int i = 1; i < n_pass; ++i)
+        if ((int)blockIdx.x >= batch.p[i].unit0) pi = i;
+    const TokcPass ps = batch.p[pi];
+    const TokJob a = ps.job[blockIdx.y];             // longest adapters first
     const int k = a.k;
-    const int c0 = blockIdx.x * TC_BC;
+    const bool want_da = GROUP || ps.want_da;
+    const uint16_t *__restrict__ S = ps.S, *__restrict__ zt = ps.zt;
+    float *__restrict__ part = ps.part;
+    const int C = ps.C, n_split = ps.n_split, r16_total = ps.r16_total;
+    const int unit = blockIdx.x - ps.unit0, split = unit / ps.tiles;
+    const int c0 = (unit - split * ps.tiles) * TC_BC;
     int r16 = a.r16;
     int p_r16[kMaxGroup];                            // GROUP: rank rows (padded to 16) of each projection
     if constexpr (GROUP) {
@@ -94,10 +115,10 @@ __global__ void __launch_bounds__(2 * BC) __attribute__((amdgpu_waves_per_eu(2, 
 
     // steps (TC_BT tokens each) of this adapter over its own segments, and the
     // slice of them that belongs to this split
-    const int32_t *own = mv.seg_list + a.seg_list0;
+    const int32_t *own = ps.seg_list + a.seg_list0;
     const int n_own = a.n_own, n_steps_all = a.n_steps;
-    const int per = (n_steps_all + gridDim.z - 1) / gridDim.z;
-    const int step0 = blockIdx.z * per;
+    const int per = (n_steps_all + n_split - 1) / n_split;
+    const int step0 = split * per;
     int n_steps = n_steps_all - step0;
     n_steps = n_steps < per ? n_steps : per;
     if (n_steps < 0) n_steps = 0;
@@ -107,7 +128,7 @@ __global__ void __launch_bounds__(2 * BC) __attribute__((amdgpu_waves_per_eu(2, 
     // issue right behind the barrier does not wait for a metadata fetch)
     int cur_li = 0, cur_t = 0;
     for (int skip = step0; skip > 0 && cur_li < n_own;) {
-        const int len = cur_li ? mv.seg[own[cur_li]].row1 - mv.seg[own[cur_li]].row0 : a.len;
+        const int len = cur_li ? ps.seg[own[cur_li]].row1 - ps.seg[own[cur_li]].row0 : a.len;
         const int st_here = (len + TC_BT - 1) / TC_BT;
         if (skip >= st_here) { skip -= st_here; ++cur_li; }
         else { cur_t = skip * TC_BT; skip = 0; }
@@ -139,7 +160,7 @@ __global__ void __launch_bounds__(2 * BC) __attribute__((amdgpu_waves_per_eu(2, 
         }
         if (cur_li < n_own) {
             const int sidx = own[cur_li];
-            const SegInfo g = mv.seg[sidx];
+            const SegInfo g = ps.seg[sidx];
             seg_row0 = g.row0; seg_len = g.row1 - g.row0; seg_lp = g.lp; seg_zt = g.zt_off;
             if constexpr (GROUP) {
 #pragma unroll
@@ -262,7 +283,7 @@ __global__ void __launch_bounds__(2 * BC) __attribute__((amdgpu_waves_per_eu(2, 
     }
 
     // ---- epilogue.  Lane holds rank column j = 16b + i16 and big-matrix columns c = cbase + 4*kg + i.
-    const float mult = WANT_DA ? 1.f : a.scale;
+    const float mult = want_da ? 1.f : a.scale;
     int r16_off = a.r16_off;
     if constexpr (GROUP) {
         r16_off = 0;                                  // rows of the fused factors of the adapters before this one
@@ -278,7 +299,7 @@ __global__ void __launch_bounds__(2 * BC) __attribute__((amdgpu_waves_per_eu(2, 
                 if (part) {
                     float4 v;
                     v.x = acc[cb][b][0]; v.y = acc[cb][b][1]; v.z = acc[cb][b][2]; v.w = acc[cb][b][3];
-                    *reinterpret_cast<float4 *>(part + ((int64_t)blockIdx.z * r16_total + r16_off + j) * C + c) = v;
+                    *reinterpret_cast<float4 *>(part + ((int64_t)split * r16_total + r16_off + j) * C + c) = v;
                 } else if constexpr (GROUP) {
                     int pj = 0, first = 0, cum = 0;   // the projection that owns rank block b, and its first row
 #pragma unroll
@@ -293,7 +314,7 @@ __global__ void __launch_bounds__(2 * BC) __attribute__((amdgpu_waves_per_eu(2, 
                         for (int i = 0; i < 4; ++i) ap.dA[(int64_t)(c + i) * ap.r + jl] = acc[cb][b][i];
                     }
                 } else if (j < a.r) {
-                    if (WANT_DA) {
+                    if (want_da) {
 #pragma unroll
                         for (int i = 0; i < 4; ++i) a.dA[(int64_t)(c + i) * a.r + j] = acc[cb][b][i];
                     } else {
@@ -350,13 +371,19 @@ __device__ inline void finish_matrix(const float *__restrict__ part, int64_t spl
     }
 }
 
-// grid (C / 64, adapters)
-template <bool WANT_DA>
-__global__ void __launch_bounds__(256) k_tokc_finish(MetaView mv, const float *__restrict__ part, int C, int n_split, int r16_total)
+// grid (64-column tiles of the products that were split; adapters)
+__global__ void __launch_bounds__(256) k_tokc_finish(TokcBatch batch, int n_pass)
 {
     extern __shared__ __attribute__((aligned(16))) float tf_lds[];
-    const TokJob a = mv.job[blockIdx.y];
-    finish_matrix<WANT_DA>(part, (int64_t)r16_total * C, n_split, a.r16_off, a.r, C, blockIdx.x * TF_COLS, a.scale, WANT_DA ? a.dA : a.dB, tf_lds);
+    int pi = 0;
+    for (int i = 1; i < n_pass; ++i)
+        if ((int)blockIdx.x >= batch.p[i].finish0) pi = i;
+    const TokcPass ps = batch.p[pi];
+    const TokJob a = ps.job[blockIdx.y];
+    const int c0 = (blockIdx.x - ps.finish0) * TF_COLS;
+    const int64_t stride = (int64_t)ps.r16_total * ps.C;
+    if (ps.want_da) finish_matrix<true>(ps.part, stride, ps.n_split, a.r16_off, a.r, ps.C, c0, 1.f, a.dA, tf_lds);
+    else finish_matrix<false>(ps.part, stride, ps.n_split, a.r16_off, a.r, ps.C, c0, a.scale, a.dB, tf_lds);
 }
 
 // The same for the partial tiles of a fused dA pass: the rows of adapter k's projections lie one below the other.
@@ -373,65 +400,75 @@ __global__ void __launch_bounds__(256) k_tokc_finish_group(GroupView gv, const f
     }
 }
 
-// Launch shape: column-tile width and number of token splits.  128-column tiles throughout: two workgroups then
-// share a compute unit, which pays more than the wider rows of 256-column tiles (measured: dB 8-19 % faster at the
-// wide layers, the rest within a few percent either way; the 256-column instantiation is kept for tuning).  When the
-// tiles alone give fewer than about two workgroups per compute unit the token walk is split as well; the split is
-// capped so that a split keeps about four stages, and so that the fp32 partial tiles (written once, read once) stay
-// below half of the bytes of the big matrix.
-static int tokc_plan(const MetaHeader &h, int64_t C, int n_active_adapters, int *bc_out)
+// Token splits.  128-column tiles throughout: two workgroups then share a compute unit, which pays more than the wider rows of
+// 256-column tiles (measured: dB 8-19 % faster at the wide layers, the rest within a few percent either way).  When the tiles
+// alone give fewer than about two workgroups per compute unit the token walk is split as well; the split is capped so that a
+// split keeps about four stages, and so that the fp32 partial tiles (written once, read once) stay below half of the bytes of
+// the big matrix.  Short walks gain from it too: a stage takes about 1 us, the finishing launch 5 us, and both products of 768
+// tokens, 1024 -> 1024 take 12 us in splits against 16 whole, 2048 tokens, 4096 -> 4096 16 against 34 (512 tokens, 4096 -> 14336
+// the same 14).
+// other: workgroups that the other product brings to the same launch.
+static int tokc_plan(const MetaHeader &h, int64_t C, int n_active_adapters, int64_t other)
 {
-    const int bc = 128;
-    int splits = 1;
-    if (n_active_adapters > 0) {
-        const int64_t wgs = (C + 127) / 128 * n_active_adapters;
-        int want = (int)((512 + wgs - 1) / wgs);
-        int cap = (int)(h.T / TC_BT / n_active_adapters / 4);
-        const int64_t r16_sum = (int64_t)h.n_adapters * (h.max_r16 > 0 ? h.max_r16 : 16);   // upper bound of the partial rows
-        const int cap_bytes = (int)(h.T / (8 * r16_sum));
-        if (cap > cap_bytes) cap = cap_bytes;
-        if (cap < 1) cap = 1;
-        if (want > cap) want = cap;
-        if (want > kTokMaxSplits) want = kTokMaxSplits;
-        splits = want < 1 ? 1 : want;
-    }
-    if (bc_out) *bc_out = bc;
-    return splits;
+    if (n_active_adapters < 1) return 1;
+    const int64_t wgs = (C + TC_BC - 1) / TC_BC * n_active_adapters + other;
+    const int steps = (int)(h.T / TC_BT / n_active_adapters);
+    int want = (int)((512 + wgs - 1) / wgs);
+    int cap = steps / 4;
+    const int64_t r16_sum = (int64_t)h.n_adapters * (h.max_r16 > 0 ? h.max_r16 : 16);   // upper bound of the partial rows
+    const int cap_bytes = (int)(h.T / (8 * r16_sum));
+    if (cap > cap_bytes) cap = cap_bytes;
+    if (cap < 1) cap = 1;
+    if (want > cap) want = cap;
+    if (want > kTokMaxSplits) want = kTokMaxSplits;
+    if (want < 1) want = 1;
+    return want;
 }
 
-int tokc_splits(const MetaHeader &h, int64_t C, int n_active_adapters)
+int tokc_splits(const MetaHeader &h, int64_t C, int64_t C_other, int n_active_adapters)
 {
-    return tokc_plan(h, C, n_active_adapters, nullptr);
+    return tokc_plan(h, C, n_active_adapters, (C_other + TC_BC - 1) / TC_BC * n_active_adapters);
 }
 
-int tokc_tile_columns(const MetaHeader &h, int64_t C, int n_active_adapters)
+// Ring depth: the share of the 160 KB of LDS that lets two workgroups sit on a compute unit, but two stages at least (a second
+// workgroup on the compute unit pays more than a third stage: measured).
+static void tokc_ring(int max_r16, int *nst, size_t *lds)
 {
-    int bc = 256;
-    (void)tokc_plan(h, C, n_active_adapters, &bc);
-    return bc;
-}
-
-template <bool WANT_DA, int BC>
-static hipError_t launch_tokc(const MetaView &mv, const MetaHeader &h, const uint16_t *S, int C, const uint16_t *zt,
-                              const uint16_t *zero, float *part, int n_split, int r16_total, hipStream_t st)
-{
-    // ring depth: the share of the 160 KB of LDS that lets 256 / BC workgroups sit on a compute unit,
-    // but two stages at least (a second workgroup on the compute unit pays more than a third stage: measured)
-    const size_t stage = (size_t)TC_BT * BC * 2 + (size_t)(h.max_r16 > 0 ? h.max_r16 : 16) * TC_BT * 2;
-    size_t budget = (size_t)TC_LDS_BYTES * BC / 256;
+    const size_t stage = (size_t)TC_BT * TC_BC * 2 + (size_t)max_r16 * TC_BT * 2;
+    size_t budget = (size_t)TC_LDS_BYTES / 2;
     if (budget < 2 * stage) budget = 2 * stage;
-    int nst = (int)(budget / stage);
-    nst = nst > TC_MAX_NST ? TC_MAX_NST : nst;
-    const size_t lds = nst * stage;
-    auto kern = k_tokc<WANT_DA, BC>;
-    {
-        hipError_t e = allow_full_lds(reinterpret_cast<const void *>(kern), 1 + (WANT_DA ? 2 : 0) + (BC == 256 ? 1 : 0));
-        if (e != hipSuccess) return e;
-    }
-    const dim3 grid((unsigned)((C + BC - 1) / BC), (unsigned)h.n_adapters, (unsigned)n_split);
-    hipLaunchKernelGGL(kern, grid, dim3(2 * BC), lds, st, mv, S, C, zt, zero, n_split > 1 ? part : nullptr, r16_total,
-                       (int)(h.max_r16 > 0 ? h.max_r16 : 16), nst, NoGroup{0});
+    const int n = (int)(budget / stage);
+    *nst = n > TC_MAX_NST ? TC_MAX_NST : n;
+    *lds = *nst * stage;
+}
+
+template <bool GROUP>
+static hipError_t launch_tokc(TokcBatch &batch, int n_pass, int n_adapters, const void *zero, int max_r16,
+                              const std::conditional_t<GROUP, GroupView, NoGroup> &gv, hipStream_t st)
+{
+    int nst;
+    size_t lds;
+    max_r16 = max_r16 > 0 ? max_r16 : 16;
+    tokc_ring(max_r16, &nst, &lds);
+    auto kern = k_tokc<GROUP>;
+    const hipError_t e = allow_full_lds(reinterpret_cast<const void *>(kern), GROUP ? 8 : 1);
+    if (e != hipSuccess) return e;
+    int units = 0;
+    for (int i = 0; i < n_pass; ++i) { batch.p[i].unit0 = units; units += batch.p[i].tiles * batch.p[i].n_split; }
+    hipLaunchKernelGGL(kern, dim3((unsigned)units, (unsigned)n_adapters), dim3(2 * TC_BC), lds, st, batch, n_pass,
+                       static_cast<const uint16_t *>(zero), max_r16, nst, gv);
     return hipGetLastError();
+}
+
+static TokcPass make_pass(const MetaView &mv, const void *S, int64_t C, const void *zt, float *part, int n_split, int r16_total, bool want_dA)
+{
+    TokcPass p{};
+    p.job = mv.job; p.seg_list = mv.seg_list; p.seg = mv.seg;
+    p.S = static_cast<const uint16_t *>(S); p.zt = static_cast<const uint16_t *>(zt);
+    p.part = n_split > 1 ? part : nullptr;
+    p.C = (int32_t)C; p.tiles = (int32_t)((C + TC_BC - 1) / TC_BC); p.n_split = n_split;
+    p.r16_total = r16_total; p.want_da = want_dA ? 1 : 0;
+    return p;
 }
 
 hipError_t launch_tokc_group_dA(const GroupView &gv, const MetaHeader &hv, const void *x, int64_t C, const void *zero,
@@ -439,49 +476,39 @@ hipError_t launch_tokc_group_dA(const GroupView &gv, const MetaHeader &hv, const
 {
     if (hv.n_adapters == 0) return hipSuccess;
     if (gv.n_proj < 2 || gv.n_proj > kMaxGroup || gv.max_r16 > PLORA_MAX_RANK || hv.max_r16 != gv.max_r16) return hipErrorInvalidValue;
-    int bc = 128;
-    if (tokc_plan(hv, C, n_active_adapters, &bc) != n_split || bc != 128) return hipErrorInvalidValue;
+    if (tokc_splits(hv, C, 0, n_active_adapters) != n_split) return hipErrorInvalidValue;
     if (n_split > 1 && (size_t)n_split * gv.r16_total * C * 4 > part_bytes) return hipErrorInvalidValue;
-    constexpr int BC = 128;
-    const size_t stage = (size_t)TC_BT * BC * 2 + (size_t)(gv.max_r16 > 0 ? gv.max_r16 : 16) * TC_BT * 2;
-    size_t budget = (size_t)TC_LDS_BYTES * BC / 256;
-    if (budget < 2 * stage) budget = 2 * stage;
-    int nst = (int)(budget / stage);
-    nst = nst > TC_MAX_NST ? TC_MAX_NST : nst;
-    auto kern = k_tokc<true, BC, true>;
-    {
-        hipError_t e = allow_full_lds(reinterpret_cast<const void *>(kern), 8);
-        if (e != hipSuccess) return e;
-    }
-    const dim3 grid((unsigned)((C + BC - 1) / BC), (unsigned)hv.n_adapters, (unsigned)n_split);
-    hipLaunchKernelGGL(kern, grid, dim3(2 * BC), nst * stage, st, gv.mv[0], static_cast<const uint16_t *>(x), (int)C,
-                       static_cast<const uint16_t *>(nullptr), static_cast<const uint16_t *>(zero), n_split > 1 ? part : nullptr,
-                       gv.r16_total, (int)(gv.max_r16 > 0 ? gv.max_r16 : 16), nst, gv);
-    hipError_t e = hipGetLastError();
+    TokcBatch batch{};
+    batch.p[0] = make_pass(gv.mv[0], x, C, nullptr, part, n_split, gv.r16_total, true);
+    const hipError_t e = launch_tokc<true>(batch, 1, hv.n_adapters, zero, gv.max_r16, gv, st);
     if (e != hipSuccess || n_split <= 1) return e;
     hipLaunchKernelGGL(k_tokc_finish_group, dim3((unsigned)((C + TF_COLS - 1) / TF_COLS), (unsigned)hv.n_adapters), dim3(256),
                        TF_COLS * (PLORA_MAX_RANK + 1) * 4, st, gv, part, (int)C, n_split);
     return hipGetLastError();
 }
 
-hipError_t launch_tokcontract_bf16(const MetaView &mv, const MetaHeader &h, bool want_dA, const void *S,
-                                   int64_t C, const void *zt, const void *zero, float *part, int n_split,
-                                   int r16_total, int n_active_adapters, hipStream_t st)
+hipError_t launch_tokcontract_bf16(const TokcOperands *ops, int n, int n_adapters, const void *zero, hipStream_t st)
 {
-    if (h.n_adapters == 0) return hipSuccess;
-    int bc = 256;
-    if (tokc_plan(h, C, n_active_adapters, &bc) != n_split) return hipErrorInvalidValue;   // the caller sized `part` from the same plan
-    const uint16_t *s16 = static_cast<const uint16_t *>(S), *z16 = static_cast<const uint16_t *>(zt);
-    const uint16_t *zero16 = static_cast<const uint16_t *>(zero);
-    hipError_t e;
-#define PL_TOKC(DA_, BC_) launch_tokc<DA_, BC_>(mv, h, s16, (int)C, z16, zero16, part, n_split, r16_total, st)
-    if (want_dA) e = bc == 256 ? PL_TOKC(true, 256) : PL_TOKC(true, 128);
-    else e = bc == 256 ? PL_TOKC(false, 256) : PL_TOKC(false, 128);
-#undef PL_TOKC
-    if (e != hipSuccess || n_split <= 1) return e;
-    const dim3 g2((unsigned)((C + TF_COLS - 1) / TF_COLS), (unsigned)h.n_adapters);
-    if (want_dA) hipLaunchKernelGGL(k_tokc_finish<true>, g2, dim3(256), TF_COLS * (PLORA_MAX_RANK + 1) * 4, st, mv, part, (int)C, n_split, r16_total);
-    else hipLaunchKernelGGL(k_tokc_finish<false>, g2, dim3(256), 0, st, mv, part, (int)C, n_split, r16_total);
+    if (n_adapters == 0 || n == 0) return hipSuccess;
+    if (n < 0 || n > kTokMaxPasses) return hipErrorInvalidValue;
+    TokcBatch batch{};
+    int finish = 0, max_r16 = 0;
+    bool finish_dA = false;
+    for (int i = 0; i < n; ++i) {
+        const TokcOperands &o = ops[i];
+        batch.p[i] = make_pass(o.mv, o.S, o.C, o.zt, o.part, o.n_split, o.r16_total, o.want_dA);
+        batch.p[i].finish0 = finish;
+        if (o.n_split > 1) { finish += (int)((o.C + TF_COLS - 1) / TF_COLS); finish_dA = finish_dA || o.want_dA; }
+        max_r16 = o.max_r16 > max_r16 ? o.max_r16 : max_r16;
+    }
+    const hipError_t e = launch_tokc<false>(batch, n, n_adapters, zero, max_r16, NoGroup{0}, st);
+    if (e != hipSuccess || finish == 0) return e;
+    // k_tokc_finish looks for the last product that starts at or before its workgroup: those without a split are left out
+    int m = 0;
+    for (int i = 0; i < n; ++i)
+        if (batch.p[i].n_split > 1) batch.p[m++] = batch.p[i];
+    hipLaunchKernelGGL(k_tokc_finish, dim3((unsigned)finish, (unsigned)n_adapters), dim3(256), finish_dA ? TF_COLS * (PLORA_MAX_RANK + 1) * 4 : 0, st,
+                       batch, m);
     return hipGetLastError();
 }
 
