@@ -86,12 +86,17 @@ struct HostMeta {
     WorkspaceLayout ws_lora;          // plora_lora_fwd / _bwd: the padded small-matrix region holds [max(d_in, d_out)][rp]
     size_t h_elems = 0, hb_elems = 0, zt_elems = 0, at_elems = 0, ap_elems = 0;
     int r16_total = 0, n_active = 0, max_rank = 0, split_dA = 1, split_dB = 1;
-    int split_shrink = 1, split_dh = 1;
+    int split_shrink = 1, split_dh = 1, skinny_cap = 8;   // skinny_cap: splits whose partial tiles the workspace holds
+    int short_cap() const { return skinny_cap > 1 ? skinny_cap / 2 : 1; }     // ... and what one of two short products takes of them
+    int slices16 = 0;                 // 16-token slices with tokens of an adapter
     GemmPlan gemm_fwd, gemm_dx;
     int n_words = 0;
     bool small_part_is_dB = false;    // which of dB and dA has the smaller set of partial tiles
     bool order_is_identity = false;   // the sorted order of the GEMM row tiles is 0, 1, 2, ...: the device need not sort
 };
+
+// Flags of one short product.
+static size_t flag_count(const MetaHeader &h) { return (size_t)h.n_blocks * kShortSlices * kShortMaxSplits; }
 
 static void build_meta(const plora_desc *d, HostMeta &m)
 {
@@ -117,6 +122,7 @@ static void build_meta(const plora_desc *d, HostMeta &m)
         if (g.adapter < 0) continue;
         const int64_t len = g.row1 - g.row0;
         h += len * g.r; hb += len * g.rp; zt += (int64_t)g.r16 * g.lp;
+        m.slices16 += (int)((len + 15) / 16);
     }
     m.r16_total = 0; m.n_active = 0;
     for (int32_t k = 0; k < d->n_adapters; ++k) {
@@ -140,12 +146,13 @@ static void build_meta(const plora_desc *d, HostMeta &m)
     auto split_bytes = [&](const GemmPlan &p, int64_t N) { return p.n_split > 1 ? (size_t)p.n_split * d->T * N * 4 : (size_t)0; };
     int skinny_cap = 8;
     bool packed = bf;                            // A_k and B_k packed: only ever read by tokens with an adapter
-    auto lay_out = [&](WorkspaceLayout &w, size_t meta_bytes, size_t ap_elems, bool split_gemm) {
+    auto lay_out = [&](WorkspaceLayout &w, size_t meta_bytes, size_t ap_elems, bool split_gemm, size_t flag_bytes) {
         size_t o = 0;
         w.zero = o; o += kZeroBytes;
         w.meta_bytes = meta_bytes;
         w.meta = o; o = align_up(o + w.meta_bytes, 256);
         w.desc = o; o = align_up(o + (m.n_words > kChunkWords ? (size_t)m.n_words * 4 : 0), 256);
+        w.flags = o; o = align_up(o + flag_bytes, 256);
         w.at = o;   o = align_up(o + (packed ? m.at_elems * 2 : 0), 256);
         w.ap = o;   o = align_up(o + (packed ? ap_elems * 2 : 0), 256);
         w.hb = o;   o = align_up(o + (bf ? m.hb_elems * 2 : 0), 256);
@@ -164,12 +171,14 @@ static void build_meta(const plora_desc *d, HostMeta &m)
         w.total = o + 256;
     };
     // What plora_linear_fwd_noalloc takes: a description that fits its scratch array with eight skinny splits, no split GEMM
-    // and the tables without their records.  The workspace of such a description must not outgrow the array; any other
+    // and the tables without their records and flags.  The workspace of such a description must not outgrow the array; any other
     // workspace is larger than the array, so its size alone tells the two apart.
-    lay_out(m.ws, m.layout.blk, m.ap_elems, false);
+    const bool any_short = bf && (skinny_is_short(m.hdr, m.slices16, d->d_in) || skinny_is_short(m.hdr, m.slices16, d->d_out));
+    const size_t flag_bytes = any_short ? 2 * flag_count(m.hdr) * sizeof(unsigned long long) : 0;
+    lay_out(m.ws, m.layout.blk, m.ap_elems, false, 0);
     const bool fits_scratch = m.ws.total <= (size_t)PLORA_NOALLOC_SCRATCH_BYTES;
     auto outgrown = [&]() {
-        lay_out(m.ws, m.layout.bytes, m.ap_elems, true);
+        lay_out(m.ws, m.layout.bytes, m.ap_elems, true, flag_bytes);
         return fits_scratch && m.ws.total > (size_t)PLORA_NOALLOC_SCRATCH_BYTES;
     };
     // What sticks out is cut: the split GEMM's partial tiles where they reach furthest, else the skinny ones (the two overlay
@@ -204,7 +213,8 @@ static void build_meta(const plora_desc *d, HostMeta &m)
     }
     int64_t rp_total = 0;
     for (int32_t k = 0; k < d->n_adapters; ++k) rp_total += m.t.ad[k].rp;
-    lay_out(m.ws_lora, m.layout.bytes, (size_t)(rp_total * std::max(d->d_in, d->d_out)), false);
+    lay_out(m.ws_lora, m.layout.bytes, (size_t)(rp_total * std::max(d->d_in, d->d_out)), false, flag_bytes);
+    m.skinny_cap = skinny_cap;
 }
 
 // ---- metadata cache: the last few descriptions and what was derived from them ---------------------
@@ -348,9 +358,16 @@ struct PrepList {
     {
         words[n].assign(j.desc_host, j.desc_host + j.n_words);       // the description lives in the projection's call frame
         job[n] = j;
+        job[n].brief = nullptr; job[n].n_brief = 0;
         job[n].desc_host = words[n].data();
         ++n;
     }
+};
+
+// The same of shrink and dH.
+struct SkinnyList {
+    SkinnyOperands op[kMaxGroup];
+    int n = 0;
 };
 
 // Weight-gradient products, launched together: of one call, or of every projection of a grouped call.
@@ -362,7 +379,7 @@ struct TokcList {
 static plora_status forward_impl(const plora_desc *desc, const void *x, const void *W, const void *const *A,
                                  const void *const *B, void *y, float *h_saved, void *workspace, size_t ws_bytes,
                                  void *hip_stream, bool lora_only = false, bool check_only = false, unsigned steps = kStepsAll,
-                                 PrepList *later = nullptr, const Nf4Job *nf4 = nullptr)
+                                 PrepList *later = nullptr, const Nf4Job *nf4 = nullptr, SkinnyList *later_s = nullptr)
 {
     Call c;
     plora_status ps = prepare(desc, x, W, A, B, nullptr, nullptr, workspace, ws_bytes, lora_only, c);
@@ -379,9 +396,16 @@ static plora_status forward_impl(const plora_desc *desc, const void *x, const vo
     const bool lora = m.hdr.n_blocks > 0;
     const bool bf = desc->dtype == PLORA_BF16;
     const bool w_out_in = m.hdr.w_out_in != 0;
+    // a short batch: the shrink runs in the preparation launch (not in an NF4 call: its registers would cost the waves that
+    // stream the weight, 47 -> 57 us for the two together, and in a launch of its own it is no faster than k_skinny)
+    const bool is_short = bf && lora && !nf4 && skinny_is_short(m.hdr, m.slices16, desc->d_in);
+    const bool brief = is_short && !later && (steps & kStepPrep) && (steps & kStepShrink) && m.n_words <= kChunkWords;
+    const SkinnyOperands shrink{mv, m.hdr, 0, x, desc->d_in, ws + L.at, reinterpret_cast<float *>(ws + L.part), is_short ? m.short_cap() : m.split_shrink,
+                                reinterpret_cast<unsigned long long *>(ws + L.flags), m.slices16, h_saved, ws + L.hb, nullptr, false, is_short};
     if (steps & kStepPrep) {
         const PrepJob job{c.words, m.n_words, m.max_rank, m.hdr, ws + L.meta, reinterpret_cast<uint32_t *>(ws + L.desc), ws + L.zero,
-                          ws + L.at, ws + L.ap, bf && lora, false, bf && lora && (w_out_in || lora_only), nullptr, nullptr};
+                          ws + L.at, ws + L.ap, bf && lora && !brief, false, bf && lora && (w_out_in || lora_only), nullptr, nullptr,
+                          &shrink, brief ? 1 : 0};
         if (later) later->add(job);
         else if (nf4) { Bracket b(9, st); PL_TRY(launch_prep_nf4(job, *nf4, desc->dtype == PLORA_BF16, st)); }
         else { Bracket b(6, st); PL_TRY(launch_prep(&job, 1, st)); }
@@ -402,11 +426,10 @@ static plora_status forward_impl(const plora_desc *desc, const void *x, const vo
         return PLORA_OK;
     }
 
-    void *at = ws + L.at, *hb = ws + L.hb;
-    float *part = reinterpret_cast<float *>(ws + L.part);
-    if (lora && (steps & kStepShrink)) {
-        Bracket b(2, st);
-        PL_TRY(launch_skinny_bf16(mv, m.hdr, 0, x, desc->d_in, at, ws + L.zero, part, m.split_shrink, h_saved, hb, nullptr, false, st));
+    void *hb = ws + L.hb;
+    if (lora && !brief && (steps & kStepShrink)) {
+        if (later_s) later_s->op[later_s->n++] = shrink;
+        else { Bracket b(2, st); PL_TRY(launch_skinny_bf16(&shrink, 1, ws + L.zero, st)); }
     }
     if (!(steps & kStepMain)) return PLORA_OK;
     if (lora_only) {
@@ -424,7 +447,8 @@ static plora_status backward_impl(const plora_desc *desc, const void *x, const v
                                   const void *const *B, const void *dy, const float *h_saved, void *dx, float *const *dA,
                                   float *const *dB, void *workspace, size_t ws_bytes, void *hip_stream, bool lora_only = false,
                                   bool check_only = false, unsigned steps = kStepsAll, bool dx_accumulate = false,
-                                  PrepList *later = nullptr, const Nf4Job *nf4 = nullptr, TokcList *later_w = nullptr)
+                                  PrepList *later = nullptr, const Nf4Job *nf4 = nullptr, TokcList *later_w = nullptr,
+                                  SkinnyList *later_s = nullptr)
 {
     const bool want_w = (dA != nullptr) || (dB != nullptr);
     if (desc && want_w && desc->n_adapters > 0 && (!dA || !dB)) {
@@ -451,16 +475,36 @@ static plora_status backward_impl(const plora_desc *desc, const void *x, const v
     if ((desc->T == 0 && !any_w) || check_only) return PLORA_OK;
 
     const MetaView mv = device_view(m, L, ws);
+    const bool bf = desc->dtype == PLORA_BF16;
+    const bool need_shrink = any_w && !h_saved;
+    // a short batch: dH, and the shrink where h was not saved, run in the preparation launch; both at once share the room for
+    // partial tiles and flags
+    const bool may_short = bf && lora && !nf4;
+    const bool short_sh = may_short && skinny_is_short(m.hdr, m.slices16, desc->d_in), short_dh = may_short && skinny_is_short(m.hdr, m.slices16, desc->d_out);
+    const bool may_brief = !later && (steps & kStepPrep) && m.n_words <= kChunkWords && m.skinny_cap > 1;
+    const bool brief_sh = may_brief && short_sh && need_shrink && (steps & kStepShrink), brief_dh = may_brief && short_dh && (steps & kStepDh);
+    float *part = reinterpret_cast<float *>(ws + L.part);
+    unsigned long long *flags = reinterpret_cast<unsigned long long *>(ws + L.flags);
+    const SkinnyOperands shrink{mv, m.hdr, 0, x, desc->d_in, ws + L.at, part, short_sh ? m.short_cap() : m.split_shrink, flags, m.slices16,
+                                nullptr, nullptr, ws + L.zt_h, false, short_sh};
+    SkinnyOperands dh{mv, m.hdr, 1, dy, desc->d_out, nullptr, part, short_dh ? m.short_cap() : m.split_dh, flags, m.slices16,
+                      nullptr, ws + L.hb, any_w ? ws + L.zt_g : nullptr, true, short_dh};
+    if (brief_sh && brief_dh) {
+        dh.part += (size_t)m.short_cap() * m.hdr.n_blocks * kSkinnyRows * m.hdr.max_r16;
+        dh.flags += flag_count(m.hdr);
+    }
     if (steps & kStepPrep) {
-        const bool bf = desc->dtype == PLORA_BF16;
-        const bool need_shrink = any_w && !h_saved;
         const bool tr = bf && lora && any_w && h_saved;
+        SkinnyOperands brief[kPrepShort];
+        int n_brief = 0;
+        if (brief_sh) brief[n_brief++] = shrink;
+        if (brief_dh) brief[n_brief++] = dh;
         // the low-rank operand of the dX GEMM: padded A_k, or - W stored [d_out][d_in] - the packed A_k^T
         // (the stand-alone low-rank update always reads the padded A_k)
         const bool dx_ap = dx != nullptr && (lora_only || !m.hdr.w_out_in), dx_at = dx != nullptr && !lora_only && m.hdr.w_out_in;
         const PrepJob job{c.words, m.n_words, m.max_rank, m.hdr, ws + L.meta, reinterpret_cast<uint32_t *>(ws + L.desc), ws + L.zero,
-                          ws + L.at, ws + L.ap, bf && lora && (need_shrink || dx_at), bf && lora && dx_ap, false,
-                          tr ? h_saved : nullptr, tr ? ws + L.zt_h : nullptr};
+                          ws + L.at, ws + L.ap, bf && lora && ((need_shrink && !brief_sh) || dx_at), bf && lora && dx_ap, false,
+                          tr ? h_saved : nullptr, tr ? ws + L.zt_h : nullptr, brief, n_brief};
         if (later) later->add(job);
         else if (nf4) { Bracket b(9, st); PL_TRY(launch_prep_nf4(job, *nf4, desc->dtype == PLORA_BF16, st)); }
         else { Bracket b(6, st); PL_TRY(launch_prep(&job, 1, st)); }
@@ -491,18 +535,17 @@ static plora_status backward_impl(const plora_desc *desc, const void *x, const v
         return PLORA_OK;
     }
 
-    void *at = ws + L.at, *ap = ws + L.ap, *gb = ws + L.hb;
+    void *ap = ws + L.ap, *gb = ws + L.hb;
     void *zt_h = ws + L.zt_h, *zt_g = ws + L.zt_g;
-    float *part = reinterpret_cast<float *>(ws + L.part);
     float *wpart = reinterpret_cast<float *>(ws + L.wpart);
     if (lora) {
-        if (any_w && !h_saved && (steps & kStepShrink)) {
-            Bracket b(2, st);
-            PL_TRY(launch_skinny_bf16(mv, m.hdr, 0, x, desc->d_in, at, ws + L.zero, part, m.split_shrink, nullptr, nullptr, zt_h, false, st));
+        if (need_shrink && !brief_sh && (steps & kStepShrink)) {
+            if (later_s) later_s->op[later_s->n++] = shrink;
+            else { Bracket b(2, st); PL_TRY(launch_skinny_bf16(&shrink, 1, ws + L.zero, st)); }
         }
-        if (steps & kStepDh) {
-            Bracket b(3, st);
-            PL_TRY(launch_skinny_bf16(mv, m.hdr, 1, dy, desc->d_out, nullptr, ws + L.zero, part, m.split_dh, nullptr, gb, any_w ? zt_g : nullptr, true, st));
+        if (!brief_dh && (steps & kStepDh)) {
+            if (later_s) later_s->op[later_s->n++] = dh;
+            else { Bracket b(3, st); PL_TRY(launch_skinny_bf16(&dh, 1, ws + L.zero, st)); }
         }
     }
     if (any_w) {
@@ -622,6 +665,9 @@ static plora_status plan_group(const plora_group *g, GroupPlan &gp)
     return PLORA_OK;
 }
 
+// A projection whose plain call takes the routine for short batches takes it here too, and is not fused.
+static bool short_shrink(const GroupPlan &gp, int p, const plora_desc *d0) { return skinny_is_short(gp.m[p]->hdr, gp.m[p]->slices16, d0->d_in); }
+
 // The fused view of the projections `members` of the plan (all of one cell); small: which side buffer the pass gathers.
 static void group_view(const GroupPlan &gp, char *ws, const int *members, int nm, bool small_is_at, GroupView &gv, MetaHeader &hv)
 {
@@ -650,22 +696,26 @@ static plora_status group_forward(const plora_group *g, const void *x, const voi
     if ((reinterpret_cast<uintptr_t>(workspace) & 255u) != 0) return PLORA_ERR_ALIGN;
     char *ws = static_cast<char *>(workspace);
     PrepList preps;
+    SkinnyList shrinks;
     auto run = [&](int p, bool check, unsigned steps) {
         return forward_impl(&g->desc[p], x, W[p], A ? A[p] : nullptr, B ? B[p] : nullptr, y[p], h_saved ? h_saved[p] : nullptr,
-                            ws + gp.ws_off[p], gp.m[p]->ws.total, hip_stream, false, check, steps, &preps);
+                            ws + gp.ws_off[p], gp.m[p]->ws.total, hip_stream, false, check, steps, &preps, nullptr, &shrinks);
     };
     for (int p = 0; p < gp.n; ++p)
         if ((ps = run(p, true, kStepsAll)) != PLORA_OK) return ps;
     if (g->desc[0].T == 0) return PLORA_OK;
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
+    const plora_desc *d0 = &g->desc[0];
     bool fused[kMaxGroup] = {};
     for (int p = 0; p < gp.n; ++p)
-        for (int q = 0; q < gp.n; ++q) fused[p] = fused[p] || (q != p && gp.cell_of[q] == gp.cell_of[p]);
+        for (int q = 0; q < gp.n; ++q)
+            fused[p] = fused[p] || (q != p && gp.cell_of[q] == gp.cell_of[p] && !short_shrink(gp, p, d0) && !short_shrink(gp, q, d0));
     for (int p = 0; p < gp.n; ++p)
         if ((ps = run(p, false, kStepPrep)) != PLORA_OK) return ps;
     { Bracket b(6, st); PL_TRY(launch_prep(preps.job, preps.n, st)); }
     for (int p = 0; p < gp.n; ++p)
         if (!fused[p] && (ps = run(p, false, kStepShrink)) != PLORA_OK) return ps;
+    if (shrinks.n > 0) { Bracket b(2, st); PL_TRY(launch_skinny_bf16(shrinks.op, shrinks.n, ws + gp.ws_off[0] + gp.m[0]->ws.zero, st)); }
     for (int c = 0; c < gp.n_cells; ++c) {
         int members[kMaxGroup], nm = 0;
         for (int p = 0; p < gp.n; ++p)
@@ -703,10 +753,11 @@ static plora_status group_backward(const plora_group *g, const void *x, const vo
     // dx_sum: every projection's dX GEMM targets the one tensor, the first overwriting it, the others adding to it
     PrepList preps;
     TokcList grads;
+    SkinnyList skinny;
     auto run = [&](int p, bool check, unsigned steps) {
         return backward_impl(&g->desc[p], x, W[p], A ? A[p] : nullptr, B ? B[p] : nullptr, dy[p], h_saved ? h_saved[p] : nullptr,
                              dx_sum ? dx_sum : (dx ? dx[p] : nullptr), dA ? dA[p] : nullptr, dB ? dB[p] : nullptr, ws + gp.ws_off[p],
-                             gp.m[p]->ws.total, hip_stream, false, check, steps, dx_sum != nullptr && p > 0, &preps, nullptr, &grads);
+                             gp.m[p]->ws.total, hip_stream, false, check, steps, dx_sum != nullptr && p > 0, &preps, nullptr, &grads, &skinny);
     };
     for (int p = 0; p < gp.n; ++p)
         if ((ps = run(p, true, kStepsAll)) != PLORA_OK) return ps;
@@ -721,7 +772,7 @@ static plora_status group_backward(const plora_group *g, const void *x, const vo
     for (int p = 0; p < gp.n; ++p)
         for (int q = 0; q < gp.n; ++q) {
             if (q == p || gp.cell_of[q] != gp.cell_of[p]) continue;
-            fuse_s[p] = fuse_s[p] || (shrink[p] && shrink[q]);
+            fuse_s[p] = fuse_s[p] || (shrink[p] && shrink[q] && !short_shrink(gp, p, d0) && !short_shrink(gp, q, d0));
             fuse_a[p] = fuse_a[p] || (want_w[p] && want_w[q]);
         }
     for (int p = 0; p < gp.n; ++p)
@@ -729,6 +780,8 @@ static plora_status group_backward(const plora_group *g, const void *x, const vo
     if (preps.n > 0) { Bracket b(6, st); PL_TRY(launch_prep(preps.job, preps.n, st)); }
     for (int p = 0; p < gp.n; ++p)
         if (!fuse_s[p] && (ps = run(p, false, kStepShrink)) != PLORA_OK) return ps;
+    const void *zero = ws + gp.ws_off[0] + gp.m[0]->ws.zero;
+    if (skinny.n > 0) { Bracket b(2, st); PL_TRY(launch_skinny_bf16(skinny.op, skinny.n, zero, st)); skinny.n = 0; }
     for (int c = 0; c < gp.n_cells; ++c) {
         int members[kMaxGroup], nm = 0;
         for (int p = 0; p < gp.n; ++p)
@@ -744,10 +797,8 @@ static plora_status group_backward(const plora_group *g, const void *x, const vo
     }
     for (int p = 0; p < gp.n; ++p)
         if ((ps = run(p, false, kStepDh | kStepDb | (fuse_a[p] ? 0u : kStepDa))) != PLORA_OK) return ps;
-    if (grads.n > 0) {
-        Bracket b(4, st);
-        PL_TRY(launch_tokcontract_bf16(grads.op, grads.n, d0->n_adapters, ws + gp.ws_off[0] + gp.m[0]->ws.zero, st));
-    }
+    if (skinny.n > 0) { Bracket b(3, st); PL_TRY(launch_skinny_bf16(skinny.op, skinny.n, zero, st)); }
+    if (grads.n > 0) { Bracket b(4, st); PL_TRY(launch_tokcontract_bf16(grads.op, grads.n, d0->n_adapters, zero, st)); }
     for (int p = 0; p < gp.n; ++p)
         if ((ps = run(p, false, kStepDx)) != PLORA_OK) return ps;
     for (int c = 0; c < gp.n_cells; ++c) {

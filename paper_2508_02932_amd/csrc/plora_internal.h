@@ -430,7 +430,7 @@ template <class Src> inline void derive_tables(const DescReader<Src> &in, const 
 
 // Byte offsets of the workspace regions, each 256-byte aligned.
 struct WorkspaceLayout {
-    size_t zero, meta, desc, at, ap, hb, zt_h, zt_g, hf, gf, part, wpart, gpart, total;
+    size_t zero, meta, desc, flags, at, ap, hb, zt_h, zt_g, hf, gf, part, wpart, gpart, total;
     size_t meta_bytes;
 };
 
@@ -457,6 +457,49 @@ struct Nf4Job {
     int64_t n_elems;
 };
 int nf4_workgroups(int64_t n_elems);      // 0: no device
+
+// bf16 path -------------------------------------------------------------------------------------
+// Skinny product over token blocks: acc[t][j] = sum_c S[t][c] * Bm_k[j][c]  (c < C).
+//   mode 0 (shrink): S = x (C = d_in), Bm_k = packed A_k^T;  mode 1 (dH): S = dy (C = d_out), Bm_k = B_k.
+//   Several products in one launch (shrink and dH of a call, dH of the projections of a group: same segments, same adapters).
+//   `part` receives the fp32 partial tiles of up to n_split contraction splits (skinny_splits; short batches take what suits
+//   them, at most this), summed by a finishing launch or the last workgroup of a slice, which writes (each optional): hf
+//   fp32 [len][r] (unscaled in mode 0); hb bf16 [len][rp] = scale_k*acc; zt bf16 [r16][lp] transposed, = (zt_scaled ? scale_k : 1) * acc.
+struct SkinnyOperands {
+    MetaView mv;
+    MetaHeader h;
+    int mode;
+    const void *S;
+    int64_t C;
+    const void *at;
+    float *part;
+    int n_split;
+    unsigned long long *flags;    // short products: kShortSlices * kShortMaxSplits per token block
+    int slices16;                 // 16-token slices with tokens, over all segments
+    float *hf;
+    void *hb, *zt;
+    bool zt_scaled, is_short;     // is_short: skinny_short.h
+};
+hipError_t launch_skinny_bf16(const SkinnyOperands *ops, int n, const void *zero, hipStream_t st);
+// Whether a product takes the routine for short batches (skinny_short.h; such products of a grouped call are not fused).
+bool skinny_is_short(const MetaHeader &h, int slices16, int64_t C);
+struct SkinnyOut {                // where the sums go, see above
+    float *hf;
+    uint16_t *hb, *zt;
+    int32_t zt_scaled;
+};
+constexpr int kShortSlices = kSkinnyRows / 16, kShortMaxSplits = 16, kShortMaxBlocks = 64;
+struct ShortJob {
+    const BlkInfo *blk;
+    const uint16_t *S, *small;    // small: packed A_k^T (mode 0, unless A_k is read as it is)
+    float *part;
+    unsigned long long *flags, number;
+    SkinnyOut out;
+    int32_t C, mode, per, n_split, max_r16;      // per: chunks of 64 per split
+    int32_t wg0;                  // first workgroup, where the job shares a launch with the preparation
+};
+ShortJob short_job(const SkinnyOperands &o);
+unsigned long long launch_number();       // never twice the same in a process, never 0
 struct PrepJob {
     const uint32_t *desc_host;    // the compact description
     int n_words, max_rank;        // max_rank: over all adapters
@@ -467,19 +510,13 @@ struct PrepJob {
     bool want_at, want_ap, want_bp;
     const float *hf;
     void *zt;
+    const SkinnyOperands *brief;  // short products to run in the same launch (A_k read as it is); n_brief of them, at most kPrepShort
+    int n_brief;
 };
+constexpr int kPrepShort = 2;
 hipError_t launch_prep(const PrepJob *jobs, int n_jobs, hipStream_t st);
 hipError_t launch_prep_nf4(const PrepJob &job, const Nf4Job &w, bool bf16, hipStream_t st);
 
-// bf16 path -------------------------------------------------------------------------------------
-// Skinny product over token blocks: acc[t][j] = sum_c S[t][c] * Bm_k[j][c]  (c < C).
-//   mode 0 (shrink): S = x (C = d_in), Bm_k = packed A_k^T;  mode 1 (dH): S = dy (C = d_out), Bm_k = B_k.
-//   `part` receives the fp32 partial tiles of the n_split contraction splits (skinny_splits); a finishing kernel sums them and
-//   writes (each optional): hf fp32 [len][r] (unscaled in mode 0); hb bf16 [len][rp] = scale_k*acc;
-//   zt bf16 [r16][lp] transposed, = (zt_scaled ? scale_k : 1) * acc.
-hipError_t launch_skinny_bf16(const MetaView &mv, const MetaHeader &h, int mode, const void *S, int64_t C,
-                              const void *at, const void *zero, float *part, int n_split, float *hf, void *hb, void *zt,
-                              bool zt_scaled, hipStream_t st);
 // C[T][N] = S[T][Kd] * Wop + side[T][rp] * ext_k, rounded to bf16.
 //   w_rows_contract : Wop = W [Kd][N] (contraction index is the row index),  ext_k = GemmSeg::B   [r][N]
 //   otherwise       : Wop = W [N][Kd] (contraction index is contiguous),     ext_k = ap + GemmSeg::ap_off [N][rp]

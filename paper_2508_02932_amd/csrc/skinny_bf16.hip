@@ -11,7 +11,8 @@
 // matrix-core roof.  The rank is never tiled (appendix C.2: tile the sequence and hidden
 // dimensions, not the rank).  Partial tiles of the splits are summed in a fixed order by a small
 // finishing kernel that also writes the bf16 copies the later kernels consume.
-#include "plora_internal.h"
+// Short batches, where a kernel's own time is mostly its start, take skinny_short.h instead.
+#include "skinny_short.h"
 #include <type_traits>
 
 namespace plora {
@@ -21,13 +22,6 @@ typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;
 
 #define LDS_PTR(T, p) ((__attribute__((address_space(3))) T *)(p))
 
-__device__ inline uint16_t bf16_rne(float f)
-{
-    uint32_t u = __float_as_uint(f);
-    u += 0x7FFFu + ((u >> 16) & 1u);
-    return (uint16_t)(u >> 16);
-}
-
 constexpr int SK_BK = 64;                              // contraction elements per stage
 constexpr int SK_NST = 2;                              // ring stages: 32-64 KB of LDS per workgroup, so 2-3 fit on a compute unit
 constexpr int SK_XT = kSkinnyRows * SK_BK * 2;         // 16 KB: [128 tokens][64 k]
@@ -36,6 +30,7 @@ constexpr int SK_XL = kSkinnyRows / 8 / SK_NW;         // token-tile load instru
 constexpr int SK_MB = kSkinnyRows / 16 / SK_NW;        // 16-token MFMA blocks per wave (2)
 constexpr int SK_BL = (PLORA_MAX_RANK / 8 + SK_NW - 1) / SK_NW;   // small-matrix load instructions per wave per stage, at most
 constexpr int SK_MAXNB = PLORA_MAX_RANK / 16;
+constexpr int64_t SH_MAX_BYTES = 80 << 20;
 
 // s_waitcnt vmcnt(n) for a wave-uniform runtime n (the instruction takes an immediate)
 __device__ inline void wait_vmcnt_dyn(int n)
@@ -49,23 +44,38 @@ __device__ inline void wait_vmcnt_dyn(int n)
 #undef W_
 }
 
+// One product of a launch.
+struct SkinnyJob {
+    const BlkInfo *blk;
+    const uint16_t *S, *at;       // the big matrix [T][C]; mode 0: packed A_k^T
+    float *part;                  // fp32 partial tiles
+    SkinnyOut out;
+    int32_t C, mode, per, n_split, max_r16;      // per: stages of 64 per split
+    int32_t reserved;
+};
+struct SkinnyBatch { SkinnyJob j[kMaxGroup]; };
+
 // One workgroup (4 waves) per (token block of 128 rows of one segment, slice of the contraction).
 // Stage = 64 contraction elements: the token tile [128][64] and the small-matrix tile [r16][64]
 // land in LDS by direct loads (16-byte chunks XOR-swizzled by row so that MFMA operand reads are
 // conflict free).  Wave w owns tokens 32w..32w+31 and every rank block, so nothing is reduced
 // across waves.  Output: the fp32 partial tile [128][r16] of this slice.
 //   mode 0: small matrix = packed A_k^T [r16][C] (rows >= r are zero),  mode 1: B_k [r][C].
+// grid.z: the jobs of the batch (dH of the projections of a grouped call).
 // GROUP (mode 0 only): the small matrix of adapter k is the packed A_k^T of several projections, one below the other
-// (GroupView); mv is projection 0's view, `at` is not used.
+// (GroupView); the tables are projection 0's, `at` is not used, and the jobs are where each projection's sums go.
 template <bool GROUP>
-__global__ void __launch_bounds__(64 * SK_NW) k_skinny(MetaView mv, int mode, const uint16_t *__restrict__ S, int C,
-                                               const uint16_t *__restrict__ at, const uint16_t *__restrict__ zero,
-                                               float *__restrict__ part, int stages_per_split, int max_r16,
+__global__ void __launch_bounds__(64 * SK_NW) k_skinny(SkinnyBatch batch, const uint16_t *__restrict__ zero,
                                                std::conditional_t<GROUP, GroupView, NoGroup> gv)
 {
     extern __shared__ __attribute__((aligned(1024))) char lds[];
+    const SkinnyJob job = batch.j[GROUP ? 0 : blockIdx.z];
+    if ((int)blockIdx.y >= job.n_split) return;
+    const uint16_t *__restrict__ S = job.S, *__restrict__ at = job.at;
+    float *__restrict__ part = job.part;
+    const int C = job.C, mode = GROUP ? 0 : job.mode, stages_per_split = job.per, max_r16 = job.max_r16;
     const int blk = blockIdx.x;
-    const BlkInfo a = mv.blk[blk];
+    const BlkInfo a = job.blk[blk];
     const SegInfo g = a.g;
     const int t0 = a.t0;
     const int nt = (g.row1 - g.row0 - t0 < kSkinnyRows) ? g.row1 - g.row0 - t0 : kSkinnyRows;
@@ -221,67 +231,21 @@ __global__ void __launch_bounds__(64 * SK_NW) k_skinny(MetaView mv, int mode, co
             }
 }
 
-// Where the sums go, each optional:
-//   hf fp32 [len][r]   (mode 0: the activation itself; mode 1: scaled by scale_k)
-//   hb bf16 [len][rp]  scale_k * sum, zero beyond r           (K-extension operand of the GEMM)
-//   zt bf16 [r16][lp]  transposed, zero for padding tokens and rows >= r; scaled if zt_scaled
-struct SkinnyOut {
-    float *hf;
-    uint16_t *hb, *zt;
-    int32_t zt_scaled;
-};
-
-// ROWS token rows from t0 on, of which the first nt exist; tile [ROWS][r16] in LDS, 256 threads.
-template <int ROWS>
-__device__ inline void write_outputs(const SegInfo &g, float mult, int mode, const float *tile, int r16, int t0, int nt, const SkinnyOut &out)
-{
-    constexpr int TPR = 256 / ROWS;                   // threads per row
-    const int hi = threadIdx.x / TPR, lo = threadIdx.x % TPR, r = g.r;
-    if (out.hf && hi < nt) {
-        float *dst = out.hf + g.h_off + (int64_t)(t0 + hi) * r;
-        const float m = mode == 0 ? 1.f : mult;
-        for (int j = lo; j < r; j += TPR) dst[j] = m * tile[hi * r16 + j];
-    }
-    if (out.hb && hi < nt) {
-        uint4 *dst = reinterpret_cast<uint4 *>(out.hb + g.hb_off + (int64_t)(t0 + hi) * g.rp);
-        for (int v = lo; v < g.rp / 8; v += TPR) {
-            union { uint4 q; uint16_t h[8]; } u;
-#pragma unroll
-            for (int i = 0; i < 8; ++i) { const int j = v * 8 + i; u.h[i] = j < r ? bf16_rne(mult * tile[hi * r16 + j]) : (uint16_t)0; }
-            dst[v] = u.q;
-        }
-    }
-    if (out.zt) {
-        const float zm = out.zt_scaled ? mult : 1.f;
-        const int tt = (threadIdx.x % (ROWS / 8)) * 8;                       // 8 tokens per thread
-        uint16_t *dst = out.zt + g.zt_off + t0 + tt;
-        for (int j = threadIdx.x / (ROWS / 8); j < r16; j += 256 / (ROWS / 8)) {
-            union { uint4 q; uint16_t h[8]; } u;
-#pragma unroll
-            for (int i = 0; i < 8; ++i) u.h[i] = (j < r && tt + i < nt) ? bf16_rne(zm * tile[(tt + i) * r16 + j]) : (uint16_t)0;
-            *reinterpret_cast<uint4 *>(dst + (int64_t)j * g.lp) = u.q;
-        }
-    }
-}
-
 // Sums the partial tiles of the splits (fixed order) and writes the outputs, 16 rows of a token block per workgroup.
-// GROUP: the partial tiles are those of a fused pass (pitch = the fused rank of the segment's adapter); blockIdx.z is the
-// projection, whose columns start behind those of the projections before it.
-struct GroupOut { SkinnyOut p[kMaxGroup]; };
+// blockIdx.z: the job.  GROUP: the partial tiles are those of a fused pass (pitch = the fused rank of the segment's adapter) and the
+// jobs are its projections; the columns of one start behind those of the projections before it.
 template <bool GROUP>
-__global__ void __launch_bounds__(256) k_skinny_finish(MetaView mv0, int mode, const float *__restrict__ part, int n_split, int max_r16,
-                                                      std::conditional_t<GROUP, GroupOut, SkinnyOut> outs,
-                                                      std::conditional_t<GROUP, GroupView, NoGroup> gv)
+__global__ void __launch_bounds__(256) k_skinny_finish(SkinnyBatch batch, std::conditional_t<GROUP, GroupView, NoGroup> gv)
 {
-    const int proj = GROUP ? blockIdx.z : 0;
-    MetaView mv = mv0;
-    SkinnyOut out;
-    if constexpr (GROUP) { mv = gv.mv[proj]; out = outs.p[proj]; }
-    else out = outs;
+    const int proj = blockIdx.z;
+    const SkinnyJob job = batch.j[proj];
+    const SkinnyOut out = job.out;
+    const float *__restrict__ part = job.part;
+    const int mode = job.mode, n_split = job.n_split, max_r16 = job.max_r16;
     constexpr int FR = 16;                            // token rows per workgroup (grid.y slices of a block)
     __shared__ float tile[FR * PLORA_MAX_RANK];       // [FR][r16], pitch r16
     const int blk = blockIdx.x;
-    const BlkInfo bi = mv.blk[blk];
+    const BlkInfo bi = job.blk[blk];
     const SegInfo g = bi.g;
     const float mult = bi.scale;
     const int r0 = blockIdx.y * FR;                   // first row of this slice inside the block
@@ -340,26 +304,105 @@ int skinny_splits(const MetaHeader &h, int64_t C)
     return fine > n ? fine : n;
 }
 
-hipError_t launch_skinny_bf16(const MetaView &mv, const MetaHeader &h, int mode, const void *S, int64_t C,
-                              const void *at, const void *zero, float *part, int n_split, float *hf, void *hb, void *zt,
-                              bool zt_scaled, hipStream_t st)
+// ---- short batches (skinny_short.h), with the tables in place: the projections of a grouped call ------------------------
+struct ShortBatch { ShortJob j[kMaxGroup]; };
+template <int NB>
+__global__ void __launch_bounds__(64 * SH_NW, 4) k_skinny_short(ShortBatch batch)
 {
-    if (h.n_blocks == 0) return hipSuccess;
-    const int n_stage_all = (int)((C + SK_BK - 1) / SK_BK);
-    const int per = (n_stage_all + n_split - 1) / n_split;
-    const size_t lds = (size_t)SK_NST * (SK_XT + h.max_r16 * SK_BK * 2);
-    {
-        hipError_t e = allow_full_lds(reinterpret_cast<const void *>(k_skinny<false>), 0);
+    extern __shared__ __attribute__((aligned(16))) char lds[];
+    const ShortJob job = batch.j[blockIdx.z];
+    if ((int)blockIdx.y >= job.n_split) return;
+    const BlkInfo a = job.blk[blockIdx.x / kShortSlices];
+    const uint16_t *small = job.mode == 0 ? job.small + a.at_off : static_cast<const uint16_t *>(a.B);
+    skinny_short<NB>(job, a.g, a.scale, a.t0 + blockIdx.x % kShortSlices * 16, blockIdx.x, gridDim.x, blockIdx.y, small, false, lds);
+}
+
+// Which products are short, by what the slices fetch of the small matrix and their own rows out of the L2s; k_skinny reads the
+// small matrix once per 128 tokens, but in a launch of its own with a finishing launch behind it.  Whole steps, k_skinny and short, us: 53 MB (shrink and
+// dH of 64 tokens to 66 MB of 1531 tokens, 1000 -> 2504, rank 100) 57 and 42, 101 and 92; 56 MB (3000 tokens, 1024 -> 1024, rank 128) 97 and
+// 92; 67 MB (4096 tokens, 4096 -> 4096, rank 16) 281 and 267; 147 MB (dH of 1024 tokens, 14336 columns, rank 64) 284 and 295.
+bool skinny_is_short(const MetaHeader &h, int slices16, int64_t C)
+{
+    if (h.n_blocks == 0 || h.n_blocks > kShortMaxBlocks) return false;
+    return (int64_t)slices16 * (16 + h.max_r16) * C * 2 <= SH_MAX_BYTES;
+}
+
+ShortJob short_job(const SkinnyOperands &o)
+{
+    ShortJob j{};
+    j.blk = o.mv.blk; j.S = static_cast<const uint16_t *>(o.S); j.small = static_cast<const uint16_t *>(o.at);
+    j.part = o.part; j.flags = o.flags;
+    j.out = SkinnyOut{o.hf, static_cast<uint16_t *>(o.hb), static_cast<uint16_t *>(o.zt), o.zt_scaled ? 1 : 0};
+    j.C = (int32_t)o.C; j.mode = o.mode; j.max_r16 = o.h.max_r16;
+    // shares of the contraction: about two workgroups per compute unit (four where the rank makes a chunk long: 3000 tokens,
+    // 1024 -> 1024, rank 128 the step takes 95 and 92 us; 2048 tokens, 4096 -> 4096, rank 16 158 and 162), a chunk for every wave
+    // at least (one, two, four, eight chunks: 64 tokens, 2048 -> 2048 the step takes 41, 44, 47, 50 us, 300 tokens, 1024 -> 1024,
+    // rank 128 64, 73, 89, 89)
+    const int n_chunks = (int)((o.C + SH_BK - 1) / SH_BK);
+    int n = (o.h.max_r16 > 64 ? 1024 : 512) / (o.slices16 > 0 ? o.slices16 : 1);
+    if (n > n_chunks / SH_NW) n = n_chunks / SH_NW;
+    if (n > o.n_split) n = o.n_split;
+    if (n > kShortMaxSplits) n = kShortMaxSplits;
+    if (n < 1) n = 1;
+    j.per = (n_chunks + n - 1) / n;
+    j.n_split = (n_chunks + j.per - 1) / j.per;
+    j.number = launch_number();
+    return j;
+}
+
+static hipError_t launch_short(const SkinnyOperands *ops, int n, hipStream_t st)
+{
+    ShortBatch batch{};
+    int max_r16 = 0, grid_y = 0;
+    for (int i = 0; i < n; ++i) {
+        batch.j[i] = short_job(ops[i]);
+        max_r16 = ops[i].h.max_r16 > max_r16 ? ops[i].h.max_r16 : max_r16;
+        grid_y = batch.j[i].n_split > grid_y ? batch.j[i].n_split : grid_y;
+    }
+    const dim3 grid((unsigned)(ops[0].h.n_blocks * kShortSlices), (unsigned)grid_y, (unsigned)n);
+    const size_t lds = short_lds_bytes(max_r16);
+    const int nb = max_r16 / 16;
+    if (nb <= 1) hipLaunchKernelGGL(k_skinny_short<1>, grid, dim3(64 * SH_NW), lds, st, batch);
+    else if (nb <= 2) hipLaunchKernelGGL(k_skinny_short<2>, grid, dim3(64 * SH_NW), lds, st, batch);
+    else if (nb <= 4) hipLaunchKernelGGL(k_skinny_short<4>, grid, dim3(64 * SH_NW), lds, st, batch);
+    else hipLaunchKernelGGL(k_skinny_short<8>, grid, dim3(64 * SH_NW), lds, st, batch);
+    return hipGetLastError();
+}
+
+hipError_t launch_skinny_bf16(const SkinnyOperands *ops, int n, const void *zero, hipStream_t st)
+{
+    if (n < 0 || n > kMaxGroup) return hipErrorInvalidValue;
+    SkinnyOperands brief[kMaxGroup];
+    SkinnyBatch batch{};
+    int n_brief = 0, m = 0, max_r16 = 0, grid_y = 0, n_blocks = 0;
+    for (int i = 0; i < n; ++i) {
+        const SkinnyOperands &o = ops[i];
+        if (o.h.n_blocks == 0) continue;
+        if (o.is_short) { brief[n_brief++] = o; continue; }
+        SkinnyJob &j = batch.j[m++];
+        j.blk = o.mv.blk; j.S = static_cast<const uint16_t *>(o.S); j.at = static_cast<const uint16_t *>(o.at);
+        j.part = o.part;
+        j.out = SkinnyOut{o.hf, static_cast<uint16_t *>(o.hb), static_cast<uint16_t *>(o.zt), o.zt_scaled ? 1 : 0};
+        j.C = (int32_t)o.C; j.mode = o.mode; j.max_r16 = o.h.max_r16; j.n_split = o.n_split;
+        const int n_stage_all = (j.C + SK_BK - 1) / SK_BK;
+        j.per = (n_stage_all + j.n_split - 1) / j.n_split;
+        n_blocks = o.h.n_blocks;
+        max_r16 = o.h.max_r16 > max_r16 ? o.h.max_r16 : max_r16;
+        grid_y = o.n_split > grid_y ? o.n_split : grid_y;
+    }
+    if (n_brief > 0) {
+        const hipError_t e = launch_short(brief, n_brief, st);
         if (e != hipSuccess) return e;
     }
-    hipLaunchKernelGGL(k_skinny<false>, dim3((unsigned)h.n_blocks, (unsigned)n_split), dim3(64 * SK_NW), lds, st, mv, mode,
-                       static_cast<const uint16_t *>(S), (int)C, static_cast<const uint16_t *>(at),
-                       static_cast<const uint16_t *>(zero), part, per, (int)h.max_r16, NoGroup{0});
-    hipError_t e = hipGetLastError();
+    if (m == 0) return hipSuccess;
+    const size_t lds = (size_t)SK_NST * (SK_XT + max_r16 * SK_BK * 2);
+    hipError_t e = allow_full_lds(reinterpret_cast<const void *>(k_skinny<false>), 0);
     if (e != hipSuccess) return e;
-    const SkinnyOut out{hf, static_cast<uint16_t *>(hb), static_cast<uint16_t *>(zt), zt_scaled ? 1 : 0};
-    hipLaunchKernelGGL(k_skinny_finish<false>, dim3((unsigned)h.n_blocks, kSkinnyRows / 16), dim3(256), 0, st, mv, mode, part, n_split, (int)h.max_r16, out,
-                       NoGroup{0});
+    hipLaunchKernelGGL(k_skinny<false>, dim3((unsigned)n_blocks, (unsigned)grid_y, (unsigned)m), dim3(64 * SK_NW), lds, st, batch,
+                       static_cast<const uint16_t *>(zero), NoGroup{0});
+    e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(k_skinny_finish<false>, dim3((unsigned)n_blocks, kSkinnyRows / 16, (unsigned)m), dim3(256), 0, st, batch, NoGroup{0});
     return hipGetLastError();
 }
 
@@ -370,26 +413,22 @@ hipError_t launch_skinny_group(const GroupView &gv, const MetaHeader &hv, const 
     if (gv.n_proj < 2 || gv.n_proj > kMaxGroup || gv.max_r16 > PLORA_MAX_RANK || hv.max_r16 != gv.max_r16) return hipErrorInvalidValue;
     if (n_split < 1 || (size_t)n_split * hv.n_blocks * kSkinnyRows * gv.max_r16 * 4 > part_bytes) return hipErrorInvalidValue;
     const int n_stage_all = (int)((C + SK_BK - 1) / SK_BK);
-    const int per = (n_stage_all + n_split - 1) / n_split;
+    SkinnyBatch batch{};
+    for (int p = 0; p < gv.n_proj; ++p) {
+        SkinnyJob &j = batch.j[p];
+        j.blk = gv.mv[p].blk; j.S = static_cast<const uint16_t *>(x); j.part = part;
+        j.out = SkinnyOut{hf[p], static_cast<uint16_t *>(hb[p]), static_cast<uint16_t *>(zt[p]), 0};
+        j.C = (int32_t)C; j.mode = 0; j.per = (n_stage_all + n_split - 1) / n_split; j.n_split = n_split; j.max_r16 = gv.max_r16;
+    }
     const size_t lds = (size_t)SK_NST * (SK_XT + gv.max_r16 * SK_BK * 2);
-    {
-        hipError_t e = allow_full_lds(reinterpret_cast<const void *>(k_skinny<true>), 7);
-        if (e != hipSuccess) return e;
-    }
-    hipLaunchKernelGGL(k_skinny<true>, dim3((unsigned)hv.n_blocks, (unsigned)n_split), dim3(64 * SK_NW), lds, st, gv.mv[0], 0,
-                       static_cast<const uint16_t *>(x), (int)C, static_cast<const uint16_t *>(nullptr),
-                       static_cast<const uint16_t *>(zero), part, per, (int)gv.max_r16, gv);
-    hipError_t e = hipGetLastError();
+    hipError_t e = allow_full_lds(reinterpret_cast<const void *>(k_skinny<true>), 7);
     if (e != hipSuccess) return e;
-    GroupOut outs;
-    for (int p = 0; p < kMaxGroup; ++p) {
-        const int q = p < gv.n_proj ? p : 0;
-        outs.p[p] = SkinnyOut{hf[q], static_cast<uint16_t *>(hb[q]), static_cast<uint16_t *>(zt[q]), 0};
-    }
-    hipLaunchKernelGGL(k_skinny_finish<true>, dim3((unsigned)hv.n_blocks, kSkinnyRows / 16, (unsigned)gv.n_proj), dim3(256), 0, st, gv.mv[0], 0,
-                       part, n_split, (int)gv.max_r16, outs, gv);
+    hipLaunchKernelGGL(k_skinny<true>, dim3((unsigned)hv.n_blocks, (unsigned)n_split), dim3(64 * SK_NW), lds, st, batch,
+                       static_cast<const uint16_t *>(zero), gv);
     e = hipGetLastError();
-    return e;
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(k_skinny_finish<true>, dim3((unsigned)hv.n_blocks, kSkinnyRows / 16, (unsigned)gv.n_proj), dim3(256), 0, st, batch, gv);
+    return hipGetLastError();
 }
 
 }  // namespace plora

@@ -3,9 +3,12 @@
 // MFMA-friendly bf16 buffers, transposed copy of a saved activation.
 #include "plora_internal.h"
 #include "nf4_expand.h"
+#include "skinny_short.h"
 
+#include <atomic>
 #include <cstring>
 #include <mutex>
+#include <random>
 
 namespace plora {
 
@@ -487,6 +490,51 @@ struct WordsInArg {
     __device__ inline uint32_t word(int i) const { return w[i]; }
 };
 
+// The segment that owns token block blk (one lane per segment, 64 at a time), with its offsets as in the tables; t_block: the
+// block's first token inside the segment.
+template <class Src>
+__device__ inline SegInfo segment_of_block(const DescReader<Src> &in, int blk, int &t_block, float &scale)
+{
+    const int n_seg = in.n_seg(), lane = threadIdx.x & 63;
+    int64_t h = 0, hb = 0, zto = 0;
+    int blk0 = 0;
+    SegInfo g;
+    g.row0 = 0; g.row1 = 0; g.adapter = -1; g.r = 0; g.rp = 0; g.r16 = 0; g.blk0 = 0; g.lp = 0; g.h_off = 0; g.hb_off = 0; g.zt_off = 0;
+    t_block = 0; scale = 0.f;
+    for (int s0 = 0; s0 < n_seg; s0 += 64) {
+        const int s = s0 + lane;
+        int len = 0, r = 0, nb = 0, row0 = 0, k = -1;
+        if (s < n_seg) {
+            k = in.seg_adapter(s);
+            if (k >= 0) {
+                row0 = in.seg_row0(s);
+                len = in.seg_row1(s) - row0;
+                r = in.ad_rank(k);
+                nb = (len + kSkinnyRows - 1) / kSkinnyRows;
+            }
+        }
+        const int r16 = pad_to(r, kRankPadMfma), rp = pad_to(r, kRankPadGemm), lp = pad_to(len, kTokPad);
+        const int64_t he = (int64_t)len * r, be = (int64_t)len * rp, ze = (int64_t)r16 * lp;
+        const int nb_inc = wave_scan(nb);
+        const int64_t h_inc = wave_scan(he), b_inc = wave_scan(be), z_inc = wave_scan(ze);
+        const uint64_t own = __ballot(blk < blk0 + nb_inc && blk >= blk0 + nb_inc - nb);
+        if (own) {
+            const int l = __builtin_ctzll(own);
+            auto at = [&](int v) { return __builtin_amdgcn_readlane(v, l); };
+            auto at64 = [&](int64_t v) { return (int64_t)((uint64_t)(uint32_t)at((int)(uint32_t)v) | ((uint64_t)(uint32_t)at((int)(uint32_t)((uint64_t)v >> 32)) << 32)); };
+            g.row0 = at(row0); g.row1 = g.row0 + at(len); g.adapter = at(k); g.r = at(r); g.rp = at(rp); g.r16 = at(r16); g.lp = at(lp);
+            g.blk0 = blk0 + at(nb_inc) - at(nb);
+            t_block = (blk - g.blk0) * kSkinnyRows;
+            g.h_off = h + at64(h_inc - he); g.hb_off = hb + at64(b_inc - be); g.zt_off = zto + at64(z_inc - ze);
+            scale = in.ad_scale(g.adapter);
+            break;
+        }
+        blk0 += __builtin_amdgcn_readlane(nb_inc, 63);
+        h += __shfl(h_inc, 63); hb += __shfl(b_inc, 63); zto += __shfl(z_inc, 63);
+    }
+    return g;
+}
+
 template <class Src>
 __device__ inline void prep_body(const DescReader<Src> &in, const PrepArgs &pa, int b, char *shared_mem)
 {
@@ -524,39 +572,10 @@ __device__ inline void prep_body(const DescReader<Src> &in, const PrepArgs &pa, 
     b -= pa.n_pack_b;
     constexpr int kSlices = kSkinnyRows / kTrRows;
     const int blk = b / kSlices, slice = b % kSlices;
-    // the segment that owns token block blk, 64 segments at a time, with the running offsets
-    const int n_seg = in.n_seg(), lane = threadIdx.x & 63;
-    int64_t h = 0, zto = 0;
-    int blk0 = 0;
-    TransposeJob g;
-    g.len = 0; g.r = 0; g.r16 = 0; g.lp = 0; g.t_block = 0; g.h_off = 0; g.zt_off = 0;
-    for (int s0 = 0; s0 < n_seg; s0 += 64) {
-        const int s = s0 + lane;
-        int len = 0, r = 0, nb = 0;
-        if (s < n_seg) {
-            const int a = in.seg_adapter(s);
-            if (a >= 0) {
-                len = in.seg_row1(s) - in.seg_row0(s);
-                r = in.ad_rank(a);
-                nb = (len + kSkinnyRows - 1) / kSkinnyRows;
-            }
-        }
-        const int r16 = pad_to(r, kRankPadMfma), lp = pad_to(len, kTokPad);
-        const int64_t he = (int64_t)len * r, ze = (int64_t)r16 * lp;
-        const int nb_inc = wave_scan(nb);
-        const int64_t h_inc = wave_scan(he), z_inc = wave_scan(ze);
-        const uint64_t own = __ballot(blk < blk0 + nb_inc && blk >= blk0 + nb_inc - nb);
-        if (own) {
-            const int l = __builtin_ctzll(own);
-            g.len = __shfl(len, l); g.r = __shfl(r, l); g.r16 = __shfl(r16, l); g.lp = __shfl(lp, l);
-            g.t_block = (blk - (blk0 + __shfl(nb_inc, l) - __shfl(nb, l))) * kSkinnyRows;
-            g.h_off = h + __shfl(h_inc - he, l);
-            g.zt_off = zto + __shfl(z_inc - ze, l);
-            break;
-        }
-        blk0 += __shfl(nb_inc, 63); h += __shfl(h_inc, 63); zto += __shfl(z_inc, 63);
-    }
-    h_to_zt_slice(g, slice, pa.hf, pa.zt, reinterpret_cast<float *>(shared_mem));
+    int t_block;
+    float scale;
+    const SegInfo g = segment_of_block(in, blk, t_block, scale);
+    h_to_zt_slice(TransposeJob{g.row1 - g.row0, g.r, g.r16, g.lp, t_block, g.h_off, g.zt_off}, slice, pa.hf, pa.zt, reinterpret_cast<float *>(shared_mem));
 }
 
 __global__ void __launch_bounds__(256) k_prep_arg(DescChunk c, PrepArgs pa)
@@ -573,6 +592,31 @@ __global__ void __launch_bounds__(256) k_prep_nf4(DescChunk c, PrepArgs pa, Nf4J
     extern __shared__ __attribute__((aligned(16))) char prep_lds[];
     if ((int)blockIdx.x < n_prep) prep_body(DescReader<WordsInArg>{WordsInArg{c.w}}, pa, blockIdx.x, prep_lds);
     else nf4_expand<BF16>(w.codes, w.absmax, w.out, w.n_elems / 8, blockIdx.x - n_prep, gridDim.x - n_prep, reinterpret_cast<float *>(prep_lds));
+}
+
+// Short products in the same launch (skinny_short.h): they read the description's words and the call's own operands alone, so
+// shrink and dH run beside the preparation instead of behind it.  Workgroups: the preparation's, then the products'.
+// Preparation, product and finishing launch before, and this launch now, us: 512 tokens, 4096 columns, rank 16 17 and 10, 14336
+// columns 21 and 14; 48 tokens of eight adapters, 4096 columns 20 and 14; 1531 tokens, 1000 columns, rank 100 22 and 18.
+struct PrepShort { ShortJob j[kPrepShort]; };
+template <int NB>
+__global__ void __launch_bounds__(256, NB == 8 ? 3 : 4) k_prep_short(DescChunk c, PrepArgs pa, PrepShort sj, int n_jobs, int n_units, int n_prep)
+{
+    extern __shared__ __attribute__((aligned(16))) char prep_lds[];
+    const DescReader<WordsInArg> in{WordsInArg{c.w}};
+    int wg = blockIdx.x;
+    if (wg < n_prep) { prep_body(in, pa, wg, prep_lds); return; }
+    wg -= n_prep;
+    const ShortJob job = sj.j[n_jobs > 1 && wg >= sj.j[1].wg0 ? 1 : 0];
+    wg -= job.wg0;
+    const int split = wg / n_units, unit = wg - split * n_units;
+    int t_block;
+    float scale;
+    const SegInfo g = segment_of_block(in, unit / kShortSlices, t_block, scale);
+    const int t0 = t_block + unit % kShortSlices * 16;
+    if (t0 >= g.lp) return;
+    skinny_short<NB>(job, g, scale, t0, unit, n_units, split, static_cast<const uint16_t *>(in.ad_ptr(g.adapter, job.mode == 0 ? 0 : 1)),
+                     job.mode == 0, prep_lds);
 }
 
 __global__ void __launch_bounds__(256) k_prep_batch(PrepBatch c)
@@ -616,8 +660,47 @@ static hipError_t prep_args(const PrepJob &j, PrepArgs &pa, int64_t &n_wg, size_
     return hipSuccess;
 }
 
+unsigned long long launch_number()
+{
+    static std::atomic<unsigned long long> next{((unsigned long long)std::random_device{}() << 32) | 1u};
+    unsigned long long v = next.fetch_add(1);
+    return v ? v : next.fetch_add(1);
+}
+
+// The preparation with the short products of the call.
+static hipError_t launch_prep_short(const PrepJob &j, hipStream_t st)
+{
+    if (j.n_brief < 1 || j.n_brief > kPrepShort || j.n_words > kChunkWords) return hipErrorInvalidValue;
+    PrepArgs pa;
+    int64_t n_wg;
+    size_t lds;
+    hipError_t e = prep_args(j, pa, n_wg, lds);
+    if (e != hipSuccess) return e;
+    const int n_units = j.h.n_blocks * kShortSlices;
+    PrepShort sj{};
+    int n_short = 0;
+    for (int i = 0; i < j.n_brief; ++i) {
+        sj.j[i] = short_job(j.brief[i]);
+        sj.j[i].wg0 = n_short;
+        n_short += n_units * sj.j[i].n_split;
+    }
+    if (lds < short_lds_bytes(j.h.max_r16)) lds = short_lds_bytes(j.h.max_r16);
+    DescChunk c;
+    std::memcpy(c.w, j.desc_host, (size_t)j.n_words * 4);
+    const dim3 grid((unsigned)(n_wg + n_short));
+    const int nb = j.h.max_r16 / 16;
+#define PL_PS(NB_) hipLaunchKernelGGL(k_prep_short<NB_>, grid, dim3(256), lds, st, c, pa, sj, j.n_brief, n_units, (int)n_wg)
+    if (nb <= 1) PL_PS(1);
+    else if (nb <= 2) PL_PS(2);
+    else if (nb <= 4) PL_PS(4);
+    else PL_PS(8);
+#undef PL_PS
+    return hipGetLastError();
+}
+
 static hipError_t launch_prep_one(const PrepJob &j, hipStream_t st)
 {
+    if (j.n_brief > 0) return launch_prep_short(j, st);
     PrepArgs pa;
     int64_t n_wg;
     size_t lds;
@@ -637,6 +720,7 @@ static hipError_t launch_prep_one(const PrepJob &j, hipStream_t st)
 
 hipError_t launch_prep_nf4(const PrepJob &j, const Nf4Job &w, bool bf16, hipStream_t st)
 {
+    if (j.n_brief > 0) return hipErrorInvalidValue;
     PrepArgs pa;
     int64_t n_wg;
     size_t lds;
