@@ -342,6 +342,9 @@ static hipError_t run_gemm(const HostMeta &m, const WorkspaceLayout &L, char *ws
                                   reinterpret_cast<float *>(ws + L.gpart), st);
 }
 
+// Whether the low-rank products of an fp32 call fit the preparation launch (workgroups in 31 bits, two products).
+static bool f32_units_fit(const HostMeta &m) { return (int64_t)m.hdr.n_blocks * kShortSlices * (m.hdr.max_r16 / 16) <= (1 << 22); }
+
 // Steps of a call, so that a grouped call can run a fused pass of its own between them (a plain call runs them all).
 enum : unsigned {
     kStepPrep = 1u, kStepShrink = 2u, kStepMain = 4u,      // forward: prep, shrink, GEMM (or stand-alone update)
@@ -359,6 +362,7 @@ struct PrepList {
         words[n].assign(j.desc_host, j.desc_host + j.n_words);       // the description lives in the projection's call frame
         job[n] = j;
         job[n].brief = nullptr; job[n].n_brief = 0;
+        job[n].f32 = nullptr; job[n].n_f32 = 0;
         job[n].desc_host = words[n].data();
         ++n;
     }
@@ -402,19 +406,22 @@ static plora_status forward_impl(const plora_desc *desc, const void *x, const vo
     const bool brief = is_short && !later && (steps & kStepPrep) && (steps & kStepShrink) && m.n_words <= kChunkWords;
     const SkinnyOperands shrink{mv, m.hdr, 0, x, desc->d_in, ws + L.at, reinterpret_cast<float *>(ws + L.part), is_short ? m.short_cap() : m.split_shrink,
                                 reinterpret_cast<unsigned long long *>(ws + L.flags), m.slices16, h_saved, ws + L.hb, nullptr, false, is_short};
+    // the fp32 path: its shrink runs in the preparation launch as well
+    float *hf = h_saved ? h_saved : reinterpret_cast<float *>(ws + L.hf);
+    const bool f32_early = !bf && lora && !later && !nf4 && (steps & kStepPrep) && (steps & kStepShrink) && m.n_words <= kChunkWords && f32_units_fit(m);
+    const F32LowRank f32_h{static_cast<const float *>(x), hf, desc->d_in, 0};
     if (steps & kStepPrep) {
         const PrepJob job{c.words, m.n_words, m.max_rank, m.hdr, ws + L.meta, reinterpret_cast<uint32_t *>(ws + L.desc), ws + L.zero,
                           ws + L.at, ws + L.ap, bf && lora && !brief, false, bf && lora && (w_out_in || lora_only), nullptr, nullptr,
-                          &shrink, brief ? 1 : 0};
+                          &shrink, brief ? 1 : 0, &f32_h, f32_early ? 1 : 0};
         if (later) later->add(job);
         else if (nf4) { Bracket b(9, st); PL_TRY(launch_prep_nf4(job, *nf4, desc->dtype == PLORA_BF16, st)); }
         else { Bracket b(6, st); PL_TRY(launch_prep(&job, 1, st)); }
     }
-    float *hf = h_saved ? h_saved : reinterpret_cast<float *>(ws + L.hf);
 
     if (desc->dtype == PLORA_F32) {
         const float *xf = static_cast<const float *>(x);
-        if (lora && (steps & kStepShrink)) { Bracket b(2, st); PL_TRY(launch_f32_lowrank(mv, m.hdr, 0, xf, desc->d_in, hf, st)); }
+        if (lora && !f32_early && (steps & kStepShrink)) { Bracket b(2, st); PL_TRY(launch_f32_lowrank(mv, m.hdr, 0, xf, desc->d_in, hf, st)); }
         if (!(steps & kStepMain)) return PLORA_OK;
         if (lora_only) {
             Bracket b(8, st);
@@ -483,6 +490,7 @@ static plora_status backward_impl(const plora_desc *desc, const void *x, const v
     const bool short_sh = may_short && skinny_is_short(m.hdr, m.slices16, desc->d_in), short_dh = may_short && skinny_is_short(m.hdr, m.slices16, desc->d_out);
     const bool may_brief = !later && (steps & kStepPrep) && m.n_words <= kChunkWords && m.skinny_cap > 1;
     const bool brief_sh = may_brief && short_sh && need_shrink && (steps & kStepShrink), brief_dh = may_brief && short_dh && (steps & kStepDh);
+    const bool f32_early = !bf && lora && !later && !nf4 && (steps & kStepsAll) == kStepsAll && m.n_words <= kChunkWords && f32_units_fit(m);
     float *part = reinterpret_cast<float *>(ws + L.part);
     unsigned long long *flags = reinterpret_cast<unsigned long long *>(ws + L.flags);
     const SkinnyOperands shrink{mv, m.hdr, 0, x, desc->d_in, ws + L.at, part, short_sh ? m.short_cap() : m.split_shrink, flags, m.slices16,
@@ -499,12 +507,16 @@ static plora_status backward_impl(const plora_desc *desc, const void *x, const v
         int n_brief = 0;
         if (brief_sh) brief[n_brief++] = shrink;
         if (brief_dh) brief[n_brief++] = dh;
+        F32LowRank f32[kPrepShort];
+        int n_f32 = 0;
+        if (f32_early && need_shrink) f32[n_f32++] = F32LowRank{static_cast<const float *>(x), reinterpret_cast<float *>(ws + L.hf), desc->d_in, 0};
+        if (f32_early) f32[n_f32++] = F32LowRank{static_cast<const float *>(dy), reinterpret_cast<float *>(ws + L.gf), desc->d_out, 1};
         // the low-rank operand of the dX GEMM: padded A_k, or - W stored [d_out][d_in] - the packed A_k^T
         // (the stand-alone low-rank update always reads the padded A_k)
         const bool dx_ap = dx != nullptr && (lora_only || !m.hdr.w_out_in), dx_at = dx != nullptr && !lora_only && m.hdr.w_out_in;
         const PrepJob job{c.words, m.n_words, m.max_rank, m.hdr, ws + L.meta, reinterpret_cast<uint32_t *>(ws + L.desc), ws + L.zero,
                           ws + L.at, ws + L.ap, bf && lora && ((need_shrink && !brief_sh) || dx_at), bf && lora && dx_ap, false,
-                          tr ? h_saved : nullptr, tr ? ws + L.zt_h : nullptr, brief, n_brief};
+                          tr ? h_saved : nullptr, tr ? ws + L.zt_h : nullptr, brief, n_brief, f32, n_f32};
         if (later) later->add(job);
         else if (nf4) { Bracket b(9, st); PL_TRY(launch_prep_nf4(job, *nf4, desc->dtype == PLORA_BF16, st)); }
         else { Bracket b(6, st); PL_TRY(launch_prep(&job, 1, st)); }
@@ -516,10 +528,16 @@ static plora_status backward_impl(const plora_desc *desc, const void *x, const v
         const float *hf = h_saved;
         if (lora && any_w && !hf) {
             float *hw = reinterpret_cast<float *>(ws + L.hf);
-            if (steps & kStepShrink) { Bracket b(2, st); PL_TRY(launch_f32_lowrank(mv, m.hdr, 0, xf, desc->d_in, hw, st)); }
+            if (!f32_early && (steps & kStepShrink)) { Bracket b(2, st); PL_TRY(launch_f32_lowrank(mv, m.hdr, 0, xf, desc->d_in, hw, st)); }
             hf = hw;
         }
-        if (lora && (steps & kStepDh)) { Bracket b(3, st); PL_TRY(launch_f32_lowrank(mv, m.hdr, 1, dyf, desc->d_out, gf, st)); }
+        if (lora && !f32_early && (steps & kStepDh)) { Bracket b(3, st); PL_TRY(launch_f32_lowrank(mv, m.hdr, 1, dyf, desc->d_out, gf, st)); }
+        const bool one = any_w && dx && desc->T > 0 && !lora_only && !dx_accumulate && (steps & kStepDb) && (steps & kStepDx) && f32_bwd_fits(m.hdr, m.max_rank);
+        if (one) {
+            Bracket b(1, st);
+            PL_TRY(launch_f32_bwd(mv, m.hdr, m.max_rank, xf, gf, dyf, hf, static_cast<const float *>(W), static_cast<float *>(dx), st));
+            return PLORA_OK;
+        }
         if (any_w) {
             // (an fp32 call always runs the two steps together: grouped calls do not fuse fp32 projections)
             if (steps & kStepDb) { Bracket b(4, st); PL_TRY(launch_f32_wgrad(mv, m.hdr, m.max_rank, xf, gf, dyf, hf, st)); }

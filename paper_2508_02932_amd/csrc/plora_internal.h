@@ -500,6 +500,12 @@ struct ShortJob {
 };
 ShortJob short_job(const SkinnyOperands &o);
 unsigned long long launch_number();       // never twice the same in a process, never 0
+struct F32LowRank {               // one low-rank product: mode 0 h = x A_k, mode 1 g = scale_k dy B_k^T
+    const float *S;
+    float *out;
+    int64_t C;
+    int32_t mode;
+};
 struct PrepJob {
     const uint32_t *desc_host;    // the compact description
     int n_words, max_rank;        // max_rank: over all adapters
@@ -512,6 +518,8 @@ struct PrepJob {
     void *zt;
     const SkinnyOperands *brief;  // short products to run in the same launch (A_k read as it is); n_brief of them, at most kPrepShort
     int n_brief;
+    const F32LowRank *f32;        // the same of the fp32 path
+    int n_f32;
 };
 constexpr int kPrepShort = 2;
 hipError_t launch_prep(const PrepJob *jobs, int n_jobs, hipStream_t st);
@@ -579,6 +587,10 @@ hipError_t launch_f32_expand(const MetaView &mv, const MetaHeader &h, bool to_y,
 // Both weight gradients: dB from dy and h, dA from x and g (which carries scale_k).  max_rank: over all adapters.
 hipError_t launch_f32_wgrad(const MetaView &mv, const MetaHeader &h, int max_rank, const float *x, const float *gf, const float *dy,
                             const float *hf, hipStream_t st);
+// The same and dx = dy W^T + g A_k^T in one launch, where that fits one (f32_bwd_fits).
+bool f32_bwd_fits(const MetaHeader &h, int max_rank);
+hipError_t launch_f32_bwd(const MetaView &mv, const MetaHeader &h, int max_rank, const float *x, const float *gf, const float *dy,
+                          const float *hf, const float *W, float *dx, hipStream_t st);
 
 // NF4 base weight: out[i] = level[index_i] * absmax[i / 64] for n_elems elements (a multiple of 64), bf16 or fp32.
 hipError_t launch_nf4_dequant(const void *codes, const float *absmax, int64_t n_elems, bool bf16, void *out, hipStream_t st);

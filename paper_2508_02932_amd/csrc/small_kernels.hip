@@ -4,6 +4,7 @@
 #include "plora_internal.h"
 #include "nf4_expand.h"
 #include "skinny_short.h"
+#include "f32_tiles.h"
 
 #include <atomic>
 #include <cstring>
@@ -619,6 +620,27 @@ __global__ void __launch_bounds__(256, NB == 8 ? 3 : 4) k_prep_short(DescChunk c
                      job.mode == 0, prep_lds);
 }
 
+// The fp32 path: its low-rank products of any size (16 tokens x 16 ranks per workgroup; they are a small part of a call).
+struct PrepF32 { F32LowRank j[kPrepShort]; };
+__global__ void __launch_bounds__(256, 2) k_prep_f32(DescChunk c, PrepArgs pa, PrepF32 fj, int n_units, int tiles_j, int n_prep)
+{
+    extern __shared__ __attribute__((aligned(16))) char prep_lds[];
+    const DescReader<WordsInArg> in{WordsInArg{c.w}};
+    int wg = blockIdx.x;
+    if (wg < n_prep) { prep_body(in, pa, wg, prep_lds); return; }
+    wg -= n_prep;
+    const int per_job = n_units * tiles_j, which = wg / per_job;
+    wg -= which * per_job;
+    const F32LowRank job = fj.j[which];
+    const int unit = wg / tiles_j, j0 = (wg - unit * tiles_j) * 16;
+    int t_block;
+    float scale;
+    const SegInfo g = segment_of_block(in, unit / kShortSlices, t_block, scale);
+    if (j0 >= g.r) return;
+    f32_lowrank_tile(job, g, scale, static_cast<const float *>(in.ad_ptr(g.adapter, job.mode == 0 ? 0 : 1)), t_block + unit % kShortSlices * 16, j0,
+                     reinterpret_cast<double *>(prep_lds));
+}
+
 __global__ void __launch_bounds__(256) k_prep_batch(PrepBatch c)
 {
     extern __shared__ __attribute__((aligned(16))) char prep_lds[];
@@ -698,8 +720,28 @@ static hipError_t launch_prep_short(const PrepJob &j, hipStream_t st)
     return hipGetLastError();
 }
 
+static hipError_t launch_prep_f32(const PrepJob &j, hipStream_t st)
+{
+    if (j.n_f32 < 1 || j.n_f32 > kPrepShort || j.n_words > kChunkWords) return hipErrorInvalidValue;
+    PrepArgs pa;
+    int64_t n_wg;
+    size_t lds;
+    hipError_t e = prep_args(j, pa, n_wg, lds);
+    if (e != hipSuccess) return e;
+    const int n_units = j.h.n_blocks * kShortSlices, tiles_j = j.h.max_r16 / 16;
+    PrepF32 fj{};
+    for (int i = 0; i < j.n_f32; ++i) fj.j[i] = j.f32[i];
+    constexpr size_t need = F32_NW * 16 * 16 * sizeof(double);
+    if (lds < need) lds = need;
+    DescChunk c;
+    std::memcpy(c.w, j.desc_host, (size_t)j.n_words * 4);
+    hipLaunchKernelGGL(k_prep_f32, dim3((unsigned)(n_wg + (int64_t)n_units * tiles_j * j.n_f32)), dim3(256), lds, st, c, pa, fj, n_units, tiles_j, (int)n_wg);
+    return hipGetLastError();
+}
+
 static hipError_t launch_prep_one(const PrepJob &j, hipStream_t st)
 {
+    if (j.n_f32 > 0) return launch_prep_f32(j, st);
     if (j.n_brief > 0) return launch_prep_short(j, st);
     PrepArgs pa;
     int64_t n_wg;
@@ -720,7 +762,7 @@ static hipError_t launch_prep_one(const PrepJob &j, hipStream_t st)
 
 hipError_t launch_prep_nf4(const PrepJob &j, const Nf4Job &w, bool bf16, hipStream_t st)
 {
-    if (j.n_brief > 0) return hipErrorInvalidValue;
+    if (j.n_brief > 0 || j.n_f32 > 0) return hipErrorInvalidValue;
     PrepArgs pa;
     int64_t n_wg;
     size_t lds;
