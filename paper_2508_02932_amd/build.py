@@ -1,9 +1,10 @@
-"""Builds libplora.so (HIP kernels + C ABI) for gfx950 with hipcc, in-tree."""
+"""Builds libplora.so (HIP kernels + C ABI) for gfx950 with hipcc, and the binding's marshalling module, in-tree."""
 from __future__ import annotations
 
 import os
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -12,6 +13,7 @@ CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libplora.so")
 BENCH_LIB = os.path.join(HERE, "libplora_bench.so")      # ceiling microkernels for bench.py, not the product
+BINDING = os.path.join(HERE, "_plora_binding.so")         # marshalling for plora.py
 SOURCES = ["plora_api.hip", "small_kernels.hip", "f32_kernels.hip", "skinny_bf16.hip",
            "gemm_bf16.hip", "gemm_small_bf16.hip", "tokcontract_bf16.hip", "adamw.hip", "expand_bf16.hip", "nf4.hip",
            "planner.cpp"]                                     # host only: the packing planner
@@ -32,11 +34,31 @@ def _compile(src: str, obj_dir: str = OBJ, extra=()) -> str:
     return obj
 
 
+def build_binding() -> str:
+    """The marshalling module of plora.py (host code against the headers of the installed torch)."""
+    import torch
+    inc = os.path.join(torch.__path__[0], "include")
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           "-I", os.path.join(ROOT, "include"), "-isystem", inc, "-isystem", os.path.join(inc, "torch", "csrc", "api", "include"),
+           "-isystem", sysconfig.get_paths()["include"], os.path.join(CSRC, "binding.cpp"), "-o", BINDING,
+           "-L", os.path.join(torch.__path__[0], "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10"]
+    res = subprocess.run(cmd, capture_output=True, text=True)
+    if res.returncode != 0:
+        raise RuntimeError("g++ failed on binding.cpp:\n" + res.stderr)
+    if res.stderr.strip():
+        sys.stderr.write(res.stderr + "\n")
+    return BINDING
+
+
 def build(verbose: bool = False) -> str:
     """Compile every HIP source and link the shared library.  Always recompiles."""
     os.makedirs(OBJ, exist_ok=True)
     with ThreadPoolExecutor(max_workers=8) as ex:
+        binding = ex.submit(build_binding)
         objs = list(ex.map(_compile, SOURCES + ["bench_ceilings.hip"]))
+        binding.result()
+    if verbose:
+        print("built", BINDING)
     for lib, parts in ((LIB, objs[:-1]), (BENCH_LIB, objs[-1:])):
         cmd = ["hipcc", "--offload-arch=gfx950", "-shared", "-fPIC", "-o", lib, *parts]
         res = subprocess.run(cmd, capture_output=True, text=True)

@@ -1,4 +1,5 @@
-"""ctypes binding of libplora (include/plora.h).  Argument marshalling only.
+"""Binding of libplora (include/plora.h).  Argument marshalling only: the calls that take device tensors through a small
+native module (csrc/binding.cpp), the others through ctypes.
 
 Every function here has the name and the meaning of the C entry point it calls; torch tensors
 are used as owners of device memory and as the source of the HIP stream, nothing is computed in
@@ -274,15 +275,39 @@ def plora_debug_metadata(d: Desc):
     return info, parse_tables(info, image), image
 
 
+_native = None          # (call, address of each entry point that takes tensors)
+
+
+def _load_native():
+    """The marshalling module, with the addresses of the loaded library's entry points.  Needs a device: the first call with
+    tensors loads it."""
+    global _native
+    import importlib.machinery
+    import importlib.util
+    import torch
+    torch.cuda.current_stream()                                   # the module asks torch for it directly from now on
+    path = os.path.join(_HERE, "_plora_binding.so")
+    if not os.path.exists(path):
+        raise RuntimeError(f"{path} is missing: build it first (python -m paper_2508_02932_amd.build)")
+    spec = importlib.util.spec_from_file_location("_plora_binding", path, loader=importlib.machinery.ExtensionFileLoader("_plora_binding", path))
+    mod = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(mod)
+    L = lib()
+    names = [n for n in EXPORTS if n.startswith(("plora_linear_", "plora_lora_", "plora_group_", "plora_adamw_"))]
+    _native = (mod.call, {n: C.cast(getattr(L, n), C.c_void_p).value for n in names})
+    return _native
+
+
+def _call(name: str, form: str, *args) -> None:
+    """One call of an entry point; the letters of the form say what each argument is (csrc/binding.cpp)."""
+    call, address = _native or _load_native()
+    code = call(address[name], form, *args)
+    if code != PLORA_OK:
+        _check(code)
+
+
 def _ptr(t) -> Optional[int]:
     return None if t is None else int(t.data_ptr())
-
-
-def _ptr_table(tensors: Optional[Sequence]):
-    if tensors is None:
-        return None, None
-    arr = (C.c_void_p * max(len(tensors), 1))(*[int(t.data_ptr()) for t in tensors])
-    return arr, C.cast(arr, C.c_void_p)
 
 
 def _stream(stream) -> Optional[int]:
@@ -294,12 +319,7 @@ def _stream(stream) -> Optional[int]:
 
 def plora_linear_fwd(d: Desc, x, W, A: Sequence, B: Sequence, y, h_saved, workspace, stream=None) -> None:
     """Enqueues the forward call; tensors are torch device tensors (h_saved may be None)."""
-    ka, pa = _ptr_table(A)
-    kb, pb = _ptr_table(B)
-    code = lib().plora_linear_fwd(d.ref, _ptr(x), _ptr(W), pa, pb, _ptr(y), _ptr(h_saved),
-                                  _ptr(workspace), workspace.numel() * workspace.element_size(),
-                                  _stream(stream))
-    _check(code)
+    _call("plora_linear_fwd", "dppttppws", C.addressof(d.c), x, W, A, B, y, h_saved, workspace, stream)
 
 
 NOALLOC_SCRATCH_BYTES = 64 << 20
@@ -307,23 +327,13 @@ NOALLOC_SCRATCH_BYTES = 64 << 20
 
 def plora_linear_fwd_noalloc(d: Desc, x, W, A: Sequence, B: Sequence, y, h_saved, stream=None) -> None:
     """Forward on the library's own per-GPU scratch array (no workspace argument, nothing allocated)."""
-    ka, pa = _ptr_table(A)
-    kb, pb = _ptr_table(B)
-    code = lib().plora_linear_fwd_noalloc(d.ref, _ptr(x), _ptr(W), pa, pb, _ptr(y), _ptr(h_saved), _stream(stream))
-    _check(code)
+    _call("plora_linear_fwd_noalloc", "dppttpps", C.addressof(d.c), x, W, A, B, y, h_saved, stream)
 
 
 def plora_linear_bwd(d: Desc, x, W, A: Sequence, B: Sequence, dy, h_saved, dx, dA: Optional[Sequence],
                      dB: Optional[Sequence], workspace, stream=None) -> None:
     """Enqueues the backward call; dx may be None, dA and dB may both be None."""
-    ka, pa = _ptr_table(A)
-    kb, pb = _ptr_table(B)
-    kda, pda = _ptr_table(dA)
-    kdb, pdb = _ptr_table(dB)
-    code = lib().plora_linear_bwd(d.ref, _ptr(x), _ptr(W), pa, pb, _ptr(dy), _ptr(h_saved), _ptr(dx),
-                                  pda, pdb, _ptr(workspace),
-                                  workspace.numel() * workspace.element_size(), _stream(stream))
-    _check(code)
+    _call("plora_linear_bwd", "dppttpppttws", C.addressof(d.c), x, W, A, B, dy, h_saved, dx, dA, dB, workspace, stream)
 
 
 def plora_lora_workspace_bytes(d: Desc) -> int:
@@ -332,21 +342,13 @@ def plora_lora_workspace_bytes(d: Desc) -> int:
 
 def plora_lora_fwd(d: Desc, x, A: Sequence, B: Sequence, y, h_saved, workspace, stream=None) -> None:
     """Enqueues the stand-alone low-rank forward: y (holding the base product) += scale_k (x A_k) B_k."""
-    ka, pa = _ptr_table(A)
-    kb, pb = _ptr_table(B)
-    _check(lib().plora_lora_fwd(d.ref, _ptr(x), pa, pb, _ptr(y), _ptr(h_saved), _ptr(workspace),
-                                workspace.numel() * workspace.element_size(), _stream(stream)))
+    _call("plora_lora_fwd", "dpttppws", C.addressof(d.c), x, A, B, y, h_saved, workspace, stream)
 
 
 def plora_lora_bwd(d: Desc, x, A: Sequence, B: Sequence, dy, h_saved, dx, dA: Optional[Sequence],
                    dB: Optional[Sequence], workspace, stream=None) -> None:
     """Enqueues the stand-alone low-rank backward: dA, dB, and dx (holding dy W^T, may be None) += g A_k^T."""
-    ka, pa = _ptr_table(A)
-    kb, pb = _ptr_table(B)
-    kda, pda = _ptr_table(dA)
-    kdb, pdb = _ptr_table(dB)
-    _check(lib().plora_lora_bwd(d.ref, _ptr(x), pa, pb, _ptr(dy), _ptr(h_saved), _ptr(dx), pda, pdb, _ptr(workspace),
-                                workspace.numel() * workspace.element_size(), _stream(stream)))
+    _call("plora_lora_bwd", "dpttpppttws", C.addressof(d.c), x, A, B, dy, h_saved, dx, dA, dB, workspace, stream)
 
 
 class Group:
@@ -362,23 +364,6 @@ class Group:
         return C.byref(self.c)
 
 
-def _ptr_array(tensors: Optional[Sequence]):
-    """HOST array of device pointers (entries may be None)."""
-    if tensors is None:
-        return None, None
-    arr = (C.c_void_p * max(len(tensors), 1))(*[None if t is None else int(t.data_ptr()) for t in tensors])
-    return arr, C.cast(arr, C.c_void_p)
-
-
-def _table_array(tables: Optional[Sequence]):
-    """HOST array of HOST pointer tables (entries may be None)."""
-    if tables is None:
-        return None, None
-    keep = [_ptr_table(t) for t in tables]
-    arr = (C.c_void_p * max(len(tables), 1))(*[None if k[1] is None else k[1].value for k in keep])
-    return (keep, arr), C.cast(arr, C.c_void_p)
-
-
 def plora_group_workspace_bytes(g: Group) -> int:
     return int(lib().plora_group_workspace_bytes(g.ref))
 
@@ -386,13 +371,7 @@ def plora_group_workspace_bytes(g: Group) -> int:
 def plora_group_fwd(g: Group, x, W: Sequence, A: Sequence[Sequence], B: Sequence[Sequence], y: Sequence,
                     h_saved: Optional[Sequence], workspace, stream=None) -> None:
     """Enqueues the forward of every projection of the group on one x (entry p of each list belongs to projection p)."""
-    kw, pw = _ptr_array(W)
-    ka, pa = _table_array(A)
-    kb, pb = _table_array(B)
-    ky, py = _ptr_array(y)
-    kh, ph = _ptr_array(h_saved)
-    _check(lib().plora_group_fwd(g.ref, _ptr(x), pw, pa, pb, py, ph, _ptr(workspace),
-                                 workspace.numel() * workspace.element_size(), _stream(stream)))
+    _call("plora_group_fwd", "dpPTTPPws", C.addressof(g.c), x, W, A, B, y, h_saved, workspace, stream)
 
 
 def plora_group_bwd(g: Group, x, W: Sequence, A: Sequence[Sequence], B: Sequence[Sequence], dy: Sequence,
@@ -400,16 +379,7 @@ def plora_group_bwd(g: Group, x, W: Sequence, A: Sequence[Sequence], B: Sequence
                     workspace, stream=None, dx_sum=None) -> None:
     """Enqueues the backward of every projection of the group.  dx[p] is projection p's own input gradient; dx_sum
     (instead of dx) receives their sum, the gradient of the shared input."""
-    kw, pw = _ptr_array(W)
-    ka, pa = _table_array(A)
-    kb, pb = _table_array(B)
-    kdy, pdy = _ptr_array(dy)
-    kh, ph = _ptr_array(h_saved)
-    kdx, pdx = _ptr_array(dx)
-    kda, pda = _table_array(dA)
-    kdb, pdb = _table_array(dB)
-    _check(lib().plora_group_bwd(g.ref, _ptr(x), pw, pa, pb, pdy, ph, pdx, _ptr(dx_sum), pda, pdb, _ptr(workspace),
-                                 workspace.numel() * workspace.element_size(), _stream(stream)))
+    _call("plora_group_bwd", "dpPTTPPPpTTws", C.addressof(g.c), x, W, A, B, dy, h_saved, dx, dx_sum, dA, dB, workspace, stream)
 
 
 # ---- packing planner (host only) --------------------------------------------------------------------------
@@ -490,41 +460,20 @@ def plora_nf4_dequantize(codes, absmax, n_elems: int, dtype: int, out, stream=No
 
 def plora_linear_fwd_nf4(d: Desc, x, W_codes, W_absmax, A: Sequence, B: Sequence, y, h_saved, workspace, stream=None) -> None:
     """plora_linear_fwd on an NF4 base weight (expanded into the workspace first)."""
-    ka, pa = _ptr_table(A)
-    kb, pb = _ptr_table(B)
-    _check(lib().plora_linear_fwd_nf4(d.ref, _ptr(x), _ptr(W_codes), _ptr(W_absmax), pa, pb, _ptr(y), _ptr(h_saved),
-                                      _ptr(workspace), workspace.numel() * workspace.element_size(), _stream(stream)))
+    _call("plora_linear_fwd_nf4", "dpppttppws", C.addressof(d.c), x, W_codes, W_absmax, A, B, y, h_saved, workspace, stream)
 
 
 def plora_linear_bwd_nf4(d: Desc, x, W_codes, W_absmax, A: Sequence, B: Sequence, dy, h_saved, dx,
                          dA: Optional[Sequence], dB: Optional[Sequence], workspace, stream=None) -> None:
     """plora_linear_bwd on an NF4 base weight."""
-    ka, pa = _ptr_table(A)
-    kb, pb = _ptr_table(B)
-    kda, pda = _ptr_table(dA)
-    kdb, pdb = _ptr_table(dB)
-    _check(lib().plora_linear_bwd_nf4(d.ref, _ptr(x), _ptr(W_codes), _ptr(W_absmax), pa, pb, _ptr(dy), _ptr(h_saved),
-                                      _ptr(dx), pda, pdb, _ptr(workspace), workspace.numel() * workspace.element_size(),
-                                      _stream(stream)))
+    _call("plora_linear_bwd_nf4", "dpppttpppttws", C.addressof(d.c), x, W_codes, W_absmax, A, B, dy, h_saved, dx, dA, dB, workspace, stream)
 
 
 def plora_adamw_step(d: Desc, A_side: dict, B_side: dict, hparams: Sequence, stream=None) -> None:
     """Enqueues the per-adapter AdamW step.  A_side / B_side: dicts with the keys param, master, grad, m, v, each a
     list of n_adapters device tensors (param or master may be None); hparams: one (lr, beta1, beta2, eps,
     weight_decay, step[, grad_scale]) tuple per adapter (grad_scale: the adapter's multiplier on its gradient, 1 if left out)."""
-    keep = []
-
-    def side(s):
-        tabs = []
-        for key in ("param", "master", "grad", "m", "v"):
-            arr, ptr = _ptr_table(s.get(key))
-            keep.append(arr)
-            tabs.append(ptr)
-        return plora_adamw_side(*tabs)
-
-    sa, sb = side(A_side), side(B_side)
-    hp = (plora_adamw_hparams * max(len(hparams), 1))(*[plora_adamw_hparams(*(tuple(h) + (1.0,))[:7]) for h in hparams])
-    _check(lib().plora_adamw_step(d.ref, C.byref(sa), C.byref(sb), hp, _stream(stream)))
+    _call("plora_adamw_step", "daahs", C.addressof(d.c), A_side, B_side, hparams, stream)
 
 
 def plora_set_kernel_timing(enabled: bool) -> None:
