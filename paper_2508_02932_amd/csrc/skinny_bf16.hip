@@ -61,6 +61,11 @@ struct SkinnyBatch { SkinnyJob j[kMaxGroup]; };
 // conflict free).  Wave w owns tokens 32w..32w+31 and every rank block, so nothing is reduced
 // across waves.  Output: the fp32 partial tile [128][r16] of this slice.
 //   mode 0: small matrix = packed A_k^T [r16][C] (rows >= r are zero),  mode 1: B_k [r][C].
+// Every workgroup begins its slice at another stage: side by side from the same column on, the workgroups would ask for 128-byte
+// pieces whole rows apart, which lie in few of the memory channels when a row is a power of two long.  Alone, us: 32768 tokens, 8192
+// columns, rank 64 143 -> 134, 16384 x 4096 rank 32 43 -> 39.  The non-temporal hint on the big matrix: with both 110 and 38, 16384 x
+// 14336 115 -> 100 (4.7 TB/s), 8192 x 4096 27 -> 23; k_tokc and the GEMM, which read it next, find less of it on the chip: 2 us
+// each at 8192 x 4096, and at sizes above the 256 MB of the last cache k_tokc's own hint makes up for it.
 // grid.z: the jobs of the batch (dH of the projections of a grouped call).
 // GROUP (mode 0 only): the small matrix of adapter k is the packed A_k^T of several projections, one below the other
 // (GroupView); the tables are projection 0's, `at` is not used, and the jobs are where each projection's sums go.
@@ -153,19 +158,25 @@ __global__ void __launch_bounds__(64 * SK_NW) k_skinny(SkinnyBatch batch, const 
     auto load16 = [&](const uint16_t *gp, uint32_t dst) {
         asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(gp), "s"(dst));
     };
-    auto issue = [&](int st) {       // stage index inside this split; ring slot st % SK_NST
+    // the big matrix goes past the caches' ordinary order of replacement: a launch reads it once
+    auto load16_once = [&](const uint16_t *gp, uint32_t dst) {
+        asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dwordx4 %0, off nt" ::"v"(gp), "s"(dst));
+    };
+    const int turn = n_st > 0 ? (int)((blockIdx.x * 5u + blockIdx.y * 3u) % (unsigned)n_st) : 0;
+    auto issue = [&](int st) {       // step of this split: stage st + turn, round the end; ring slot st % SK_NST
         const uint32_t base = lds_base + (st % SK_NST) * stage_bytes;
-        const int k0 = (st0 + st) * SK_BK;
+        const int sx = st + turn < n_st ? st + turn : st + turn - n_st;
+        const int k0 = (st0 + sx) * SK_BK;
 #pragma unroll
         for (int jj = 0; jj < SK_XL; ++jj) {
             const bool ok = xok[jj] && (k0 + xchunk[jj] * 8 < C);
-            load16(ok ? xp[jj] + (int64_t)st * SK_BK : zero, base + (wave + SK_NW * jj) * 1024);
+            load16_once(ok ? xp[jj] + (int64_t)sx * SK_BK : zero, base + (wave + SK_NW * jj) * 1024);
         }
 #pragma unroll
         for (int jj = 0; jj < SK_BL; ++jj) {
             if (jj < my_b) {
                 const bool ok = bok[jj] && (k0 + bchunk[jj] * 8 < C);
-                load16(ok ? bp[jj] + (int64_t)st * SK_BK : zero, base + SK_XT + (wave + SK_NW * jj) * 1024);
+                load16(ok ? bp[jj] + (int64_t)sx * SK_BK : zero, base + SK_XT + (wave + SK_NW * jj) * 1024);
             }
         }
     };
