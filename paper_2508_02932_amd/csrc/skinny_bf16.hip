@@ -65,7 +65,10 @@ struct SkinnyBatch { SkinnyJob j[kMaxGroup]; };
 // pieces whole rows apart, which lie in few of the memory channels when a row is a power of two long.  Alone, us: 32768 tokens, 8192
 // columns, rank 64 143 -> 134, 16384 x 4096 rank 32 43 -> 39.  The non-temporal hint on the big matrix: with both 110 and 38, 16384 x
 // 14336 115 -> 100 (4.7 TB/s), 8192 x 4096 27 -> 23; k_tokc and the GEMM, which read it next, find less of it on the chip: 2 us
-// each at 8192 x 4096, and at sizes above the 256 MB of the last cache k_tokc's own hint makes up for it.
+// each at 8192 x 4096, and at sizes above the 256 MB of the last cache k_tokc's own hint makes up for it.  Of nine widths one loses by the
+// turn: 32768 tokens of 28672 columns 366 -> 403, against 24576 columns 172 -> 138 (16384 tokens), 16384 columns 114 -> 100, 11008 87 -> 81.
+// Both only where the rows are whole lines of 128 bytes (rows_of_whole_lines): otherwise neighbouring stages share lines, which the
+// hint lets go between them (20000 tokens, 13000 columns 177 us, 195 with it; the turn alone the same).
 // grid.z: the jobs of the batch (dH of the projections of a grouped call).
 // GROUP (mode 0 only): the small matrix of adapter k is the packed A_k^T of several projections, one below the other
 // (GroupView); the tables are projection 0's, `at` is not used, and the jobs are where each projection's sums go.
@@ -158,19 +161,25 @@ __global__ void __launch_bounds__(64 * SK_NW) k_skinny(SkinnyBatch batch, const 
     auto load16 = [&](const uint16_t *gp, uint32_t dst) {
         asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(gp), "s"(dst));
     };
-    // the big matrix goes past the caches' ordinary order of replacement: a launch reads it once
+    const bool past = rows_of_whole_lines(S, C);
     auto load16_once = [&](const uint16_t *gp, uint32_t dst) {
         asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dwordx4 %0, off nt" ::"v"(gp), "s"(dst));
     };
-    const int turn = n_st > 0 ? (int)((blockIdx.x * 5u + blockIdx.y * 3u) % (unsigned)n_st) : 0;
+    const int turn = past && n_st > 0 ? (int)((blockIdx.x * 5u + blockIdx.y * 3u) % (unsigned)n_st) : 0;
     auto issue = [&](int st) {       // step of this split: stage st + turn, round the end; ring slot st % SK_NST
         const uint32_t base = lds_base + (st % SK_NST) * stage_bytes;
         const int sx = st + turn < n_st ? st + turn : st + turn - n_st;
         const int k0 = (st0 + sx) * SK_BK;
+        if (past) {
 #pragma unroll
-        for (int jj = 0; jj < SK_XL; ++jj) {
-            const bool ok = xok[jj] && (k0 + xchunk[jj] * 8 < C);
-            load16_once(ok ? xp[jj] + (int64_t)sx * SK_BK : zero, base + (wave + SK_NW * jj) * 1024);
+            for (int jj = 0; jj < SK_XL; ++jj)
+                load16_once(xok[jj] ? xp[jj] + (int64_t)sx * SK_BK : zero, base + (wave + SK_NW * jj) * 1024);
+        } else {
+#pragma unroll
+            for (int jj = 0; jj < SK_XL; ++jj) {
+                const bool ok = xok[jj] && (k0 + xchunk[jj] * 8 < C);
+                load16(ok ? xp[jj] + (int64_t)sx * SK_BK : zero, base + (wave + SK_NW * jj) * 1024);
+            }
         }
 #pragma unroll
         for (int jj = 0; jj < SK_BL; ++jj) {

@@ -182,7 +182,9 @@ __global__ void __launch_bounds__(2 * TC_BC) __attribute__((amdgpu_waves_per_eu(
         asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(gp), "s"(dst));
     };
     // the big matrix with the non-temporal hint, as in k_skinny: 16384 tokens, 14336 and 4096 columns 157 -> 132 us (4.6 TB/s; 130
-    // where dH had left the end of dy in the last cache), 32768 x 8192 twice 231 -> 206, 8192 x 4096 twice the same
+    // where dH had left the end of dy in the last cache), 32768 x 8192 twice 231 -> 206, 8192 x 4096 twice the same; where
+    // column tiles share lines it costs (20000 x 11000 and 13000 210 -> 246)
+    const bool past = rows_of_whole_lines(S, C);
     auto load16_once = [&](const uint16_t *gp, uint32_t dst) {
         asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dwordx4 %0, off nt" ::"v"(gp), "s"(dst));
     };
@@ -198,7 +200,8 @@ __global__ void __launch_bounds__(2 * TC_BC) __attribute__((amdgpu_waves_per_eu(
             c = c < C ? c : C - 8;                                  // columns past the end only feed outputs that are not stored
             const int t = tbase + u;
             const uint16_t *p = (t < seg_len) ? S + (int64_t)(seg_row0 + t) * C + c : zero;
-            load16_once(p, base + q * 1024);
+            if (past) load16_once(p, base + q * 1024);
+            else load16(p, base + q * 1024);
         }
 #pragma unroll
         for (int jj = 0; jj < (PLORA_MAX_RANK / TC_ZR + TC_NW - 1) / TC_NW; ++jj) {
