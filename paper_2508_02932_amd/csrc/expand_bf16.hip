@@ -28,6 +28,7 @@ constexpr int EX_COLS = 256;                       // columns of C per workgroup
 constexpr int EX_ROWS = 64;                        // token rows per workgroup
 constexpr int EX_NW = EX_COLS / 64;
 constexpr int EX_LDS = EX_ROWS * EX_COLS * 2;      // 32 KB, 8 KB per wave
+constexpr int64_t kLastCacheBytes = 256 << 20;     // shared by the XCDs of an MI355X
 
 __device__ inline uint32_t ex_pack_bf16x2(float lo, float hi)
 {
@@ -41,8 +42,12 @@ __device__ inline uint32_t ex_pack_bf16x2(float lo, float hi)
 // side by side then cover whole rows of C, and with a multiple of 8 tiles an XCD keeps meeting the same columns of opT.
 //   side : bf16 low-rank factor, segment s at side + hb_off, rows of rp elements
 //   opT  : small matrices [N][rp], adapter k behind N * rp elements of every adapter before it
+// PAST: C is larger than the last cache, so nothing of it is there when anything reads it again: it is read and written with the
+// non-temporal hint, if its rows are whole lines of 128 bytes (otherwise neighbouring tiles share lines: 4096 ->
+// 8200 605 -> 635 us).  Forward and backward of 16384 tokens, 4096 -> 14336, eight adapters of rank 8 to 128 808 -> 784 us, rank 32
+// 760 -> 736: 5 us in this kernel, the rest in what runs after it and no longer waits for lines of C to be written back.
 // part0: the first half block of the launch.  KS: 32-rank MFMA steps that the largest rank of the launch needs (1, 2 or 4).
-template <int KS>
+template <int KS, bool PAST>
 __global__ void __launch_bounds__(64 * EX_NW, KS == 4 ? 3 : 4) k_expand(MetaView mv, uint16_t *__restrict__ C, int N, int tiles_n, int part0,
                                                        const uint16_t *__restrict__ side, const uint16_t *__restrict__ opT,
                                                        const uint16_t *__restrict__ zero)
@@ -75,7 +80,8 @@ __global__ void __launch_bounds__(64 * EX_NW, KS == 4 ? 3 : 4) k_expand(MetaView
     for (int j = 0; j < EX_ROWS / 8; ++j) {
         const int u = j * 8 + lrow;
         const void *src = (u < nt && cok) ? static_cast<const void *>(Crow0 + (int64_t)u * N + ccol) : static_cast<const void *>(zero);
-        asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(src), "s"(lds_base + j * 1024));
+        if constexpr (PAST) asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dwordx4 %0, off nt" ::"v"(src), "s"(lds_base + j * 1024));
+        else asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(src), "s"(lds_base + j * 1024));
     }
 
     // ---- low-rank operands straight from memory (they sit in L2).  MFMA 16x16x32: the first operand's rows are columns n
@@ -133,7 +139,11 @@ __global__ void __launch_bounds__(64 * EX_NW, KS == 4 ? 3 : 4) k_expand(MetaView
     for (int j = 0; j < EX_ROWS / 8; ++j) {
         const int u = j * 8 + lrow;
         const u32x4 v = *LDS_PTR(const u32x4, tile + j * 1024 + lane * 16);
-        if (u < nt && cok) *reinterpret_cast<u32x4 *>(Crow0 + (int64_t)u * N + ccol) = v;
+        u32x4 *dst = reinterpret_cast<u32x4 *>(Crow0 + (int64_t)u * N + ccol);
+        if (u < nt && cok) {
+            if constexpr (PAST) __builtin_nontemporal_store(v, dst);
+            else *dst = v;
+        }
     }
 }
 
@@ -142,18 +152,21 @@ hipError_t launch_expand_bf16(const MetaView &mv, const MetaHeader &h, void *C, 
 {
     if (h.n_blocks == 0) return hipSuccess;
     const int64_t tiles_n = (N + EX_COLS - 1) / EX_COLS;
+    const bool past = h.T * N * 2 > kLastCacheBytes && rows_of_whole_lines(C, N);
     // A launch has fewer than 2^32 threads, which one-row segments of a very wide C exceed (1024 of them, 2^22 columns: 2^33):
     // as many launches as it takes, whole half blocks in each.
     const int64_t parts = (int64_t)h.n_blocks * (kSkinnyRows / EX_ROWS), per_launch = ((((int64_t)1 << 32) - 1) / (64 * EX_NW)) / tiles_n;
     for (int64_t p0 = 0; p0 < parts; p0 += per_launch) {
         const unsigned n_wg = (unsigned)((parts - p0 < per_launch ? parts - p0 : per_launch) * tiles_n);
-#define PL_EX(KS_) hipLaunchKernelGGL(k_expand<KS_>, dim3(n_wg), dim3(64 * EX_NW), 0, st, mv, static_cast<uint16_t *>(C), \
+#define PL_EX_(KS_, PAST_) hipLaunchKernelGGL((k_expand<KS_, PAST_>), dim3(n_wg), dim3(64 * EX_NW), 0, st, mv, static_cast<uint16_t *>(C), \
                                       (int)N, (int)tiles_n, (int)p0, static_cast<const uint16_t *>(side), static_cast<const uint16_t *>(opT), \
                                       static_cast<const uint16_t *>(zero))
+#define PL_EX(KS_) do { if (past) PL_EX_(KS_, true); else PL_EX_(KS_, false); } while (0)
         if (h.max_r16 <= 32) PL_EX(1);
         else if (h.max_r16 <= 64) PL_EX(2);
         else PL_EX(4);
 #undef PL_EX
+#undef PL_EX_
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
