@@ -28,7 +28,6 @@ constexpr int EX_COLS = 256;                       // columns of C per workgroup
 constexpr int EX_ROWS = 64;                        // token rows per workgroup
 constexpr int EX_NW = EX_COLS / 64;
 constexpr int EX_LDS = EX_ROWS * EX_COLS * 2;      // 32 KB, 8 KB per wave
-constexpr int64_t kLastCacheBytes = 256 << 20;     // shared by the XCDs of an MI355X
 
 __device__ inline uint32_t ex_pack_bf16x2(float lo, float hi)
 {

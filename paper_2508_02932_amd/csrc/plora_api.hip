@@ -580,8 +580,8 @@ static plora_status backward_impl(const plora_desc *desc, const void *x, const v
         // dB and dA in one launch; the smaller set of partial tiles lies where the skinny ones were (summed by now)
         TokcList own;
         TokcList &list = later_w ? *later_w : own;
-        if (steps & kStepDb) list.op[list.n++] = TokcOperands{mv, dy, zt_h, desc->d_out, m.small_part_is_dB ? part : wpart, m.split_dB, m.r16_total, m.hdr.max_r16, false};
-        if (steps & kStepDa) list.op[list.n++] = TokcOperands{mv, x, zt_g, desc->d_in, m.small_part_is_dB ? wpart : part, m.split_dA, m.r16_total, m.hdr.max_r16, true};
+        if (steps & kStepDb) list.op[list.n++] = TokcOperands{mv, dy, zt_h, desc->d_out, m.small_part_is_dB ? part : wpart, m.split_dB, m.r16_total, m.hdr.max_r16, false, m.hdr.T};
+        if (steps & kStepDa) list.op[list.n++] = TokcOperands{mv, x, zt_g, desc->d_in, m.small_part_is_dB ? wpart : part, m.split_dA, m.r16_total, m.hdr.max_r16, true, m.hdr.T};
         if (own.n > 0) { Bracket b(4, st); PL_TRY(launch_tokcontract_bf16(own.op, own.n, m.hdr.n_adapters, ws + L.zero, st)); }
     }
     if (!(steps & kStepDx)) return PLORA_OK;

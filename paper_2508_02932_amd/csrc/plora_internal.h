@@ -536,7 +536,8 @@ hipError_t launch_gemm_bf16(const MetaView &mv, const MetaHeader &h, bool w_rows
                             const void *S, const void *W, const void *side, const void *ap, const void *zero, void *C,
                             bool accumulate, int row_tiles, hipStream_t st);
 // Rows of a bf16 matrix begin and end on lines of 128 bytes: pieces of 64 columns that different workgroups or stages read share none.
-__host__ __device__ inline bool rows_of_whole_lines(const void *p, int64_t columns)
+constexpr int64_t kLastCacheBytes = 256 << 20;     // shared by the XCDs of an MI355X
+inline bool rows_of_whole_lines(const void *p, int64_t columns)
 {
     return columns % 64 == 0 && reinterpret_cast<uintptr_t>(p) % 128 == 0;
 }
@@ -565,6 +566,7 @@ struct TokcOperands {
     float *part;
     int n_split, r16_total, max_r16;
     bool want_dA;
+    int64_t T;
 };
 constexpr int kTokMaxPasses = 2 * kMaxGroup;
 hipError_t launch_tokcontract_bf16(const TokcOperands *ops, int n, int n_adapters, const void *zero, hipStream_t st);

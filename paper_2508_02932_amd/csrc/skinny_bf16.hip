@@ -51,8 +51,9 @@ struct SkinnyJob {
     float *part;                  // fp32 partial tiles
     SkinnyOut out;
     int32_t C, mode, per, n_split, max_r16;      // per: stages of 64 per split
-    int32_t reserved;
+    int32_t past;                 // S is read past the caches, from another stage in every workgroup
 };
+static int skinny_past(const MetaHeader &h, const void *S, int64_t C) { return h.T * C * 2 >= (48 << 20) && rows_of_whole_lines(S, C); }
 struct SkinnyBatch { SkinnyJob j[kMaxGroup]; };
 
 // One workgroup (4 waves) per (token block of 128 rows of one segment, slice of the contraction).
@@ -68,7 +69,8 @@ struct SkinnyBatch { SkinnyJob j[kMaxGroup]; };
 // each at 8192 x 4096, and at sizes above the 256 MB of the last cache k_tokc's own hint makes up for it.  Of nine widths one loses by the
 // turn: 32768 tokens of 28672 columns 366 -> 403, against 24576 columns 172 -> 138 (16384 tokens), 16384 columns 114 -> 100, 11008 87 -> 81.
 // Both only where the rows are whole lines of 128 bytes (rows_of_whole_lines): otherwise neighbouring stages share lines, which the
-// hint lets go between them (20000 tokens, 13000 columns 177 us, 195 with it; the turn alone the same).
+// hint lets go between them (20000 tokens, 13000 columns 177 us, 195 with it; the turn alone the same), and from 48 MB on: 67 MB gain
+// (above), 25 MB run the same either way and 29 MB are better left for the product that reads them next.
 // grid.z: the jobs of the batch (dH of the projections of a grouped call).
 // GROUP (mode 0 only): the small matrix of adapter k is the packed A_k^T of several projections, one below the other
 // (GroupView); the tables are projection 0's, `at` is not used, and the jobs are where each projection's sums go.
@@ -161,7 +163,7 @@ __global__ void __launch_bounds__(64 * SK_NW) k_skinny(SkinnyBatch batch, const 
     auto load16 = [&](const uint16_t *gp, uint32_t dst) {
         asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(gp), "s"(dst));
     };
-    const bool past = rows_of_whole_lines(S, C);
+    const bool past = job.past != 0;
     auto load16_once = [&](const uint16_t *gp, uint32_t dst) {
         asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dwordx4 %0, off nt" ::"v"(gp), "s"(dst));
     };
@@ -404,6 +406,7 @@ hipError_t launch_skinny_bf16(const SkinnyOperands *ops, int n, const void *zero
         j.part = o.part;
         j.out = SkinnyOut{o.hf, static_cast<uint16_t *>(o.hb), static_cast<uint16_t *>(o.zt), o.zt_scaled ? 1 : 0};
         j.C = (int32_t)o.C; j.mode = o.mode; j.max_r16 = o.h.max_r16; j.n_split = o.n_split;
+        j.past = skinny_past(o.h, o.S, o.C);
         const int n_stage_all = (j.C + SK_BK - 1) / SK_BK;
         j.per = (n_stage_all + j.n_split - 1) / j.n_split;
         n_blocks = o.h.n_blocks;
@@ -439,6 +442,7 @@ hipError_t launch_skinny_group(const GroupView &gv, const MetaHeader &hv, const 
         j.blk = gv.mv[p].blk; j.S = static_cast<const uint16_t *>(x); j.part = part;
         j.out = SkinnyOut{hf[p], static_cast<uint16_t *>(hb[p]), static_cast<uint16_t *>(zt[p]), 0};
         j.C = (int32_t)C; j.mode = 0; j.per = (n_stage_all + n_split - 1) / n_split; j.n_split = n_split; j.max_r16 = gv.max_r16;
+        j.past = skinny_past(hv, x, C);
     }
     const size_t lds = (size_t)SK_NST * (SK_XT + gv.max_r16 * SK_BK * 2);
     hipError_t e = allow_full_lds(reinterpret_cast<const void *>(k_skinny<true>), 7);

@@ -62,7 +62,7 @@ struct TokcPass {
     int32_t C, tiles, n_split;    // tiles: of TC_BC columns
     int32_t r16_total, want_da;
     int32_t unit0, finish0;       // first workgroup along x of this product, in the main and in the finishing launch
-    int32_t reserved;
+    int32_t past;                 // S is read past the caches
 };
 struct TokcBatch { TokcPass p[kTokMaxPasses]; };
 
@@ -182,9 +182,10 @@ __global__ void __launch_bounds__(2 * TC_BC) __attribute__((amdgpu_waves_per_eu(
         asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(gp), "s"(dst));
     };
     // the big matrix with the non-temporal hint, as in k_skinny: 16384 tokens, 14336 and 4096 columns 157 -> 132 us (4.6 TB/s; 130
-    // where dH had left the end of dy in the last cache), 32768 x 8192 twice 231 -> 206, 8192 x 4096 twice the same; where
-    // column tiles share lines it costs (20000 x 11000 and 13000 210 -> 246)
-    const bool past = rows_of_whole_lines(S, C);
+    // where dH had left the end of dy in the last cache), 32768 x 8192 twice 231 -> 206, 8192 x 4096 twice the same.  Not where
+    // column tiles share lines (20000 x 11000 and 13000 210 -> 246), and not where the last cache holds the
+    // matrices of the launch: the product that reads one next finds it there (dX of 1024 tokens 139 us, 134 without)
+    const bool past = ps.past != 0;
     auto load16_once = [&](const uint16_t *gp, uint32_t dst) {
         asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dwordx4 %0, off nt" ::"v"(gp), "s"(dst));
     };
@@ -468,9 +469,10 @@ static hipError_t launch_tokc(TokcBatch &batch, int n_pass, int n_adapters, cons
     return hipGetLastError();
 }
 
-static TokcPass make_pass(const MetaView &mv, const void *S, int64_t C, const void *zt, float *part, int n_split, int r16_total, bool want_dA)
+static TokcPass make_pass(const MetaView &mv, const void *S, int64_t C, const void *zt, float *part, int n_split, int r16_total, bool want_dA, int64_t bytes)
 {
     TokcPass p{};
+    p.past = bytes > kLastCacheBytes && rows_of_whole_lines(S, C);
     p.job = mv.job; p.seg_list = mv.seg_list; p.seg = mv.seg;
     p.S = static_cast<const uint16_t *>(S); p.zt = static_cast<const uint16_t *>(zt);
     p.part = n_split > 1 ? part : nullptr;
@@ -487,7 +489,7 @@ hipError_t launch_tokc_group_dA(const GroupView &gv, const MetaHeader &hv, const
     if (tokc_splits(hv, C, 0, n_active_adapters) != n_split) return hipErrorInvalidValue;
     if (n_split > 1 && (size_t)n_split * gv.r16_total * C * 4 > part_bytes) return hipErrorInvalidValue;
     TokcBatch batch{};
-    batch.p[0] = make_pass(gv.mv[0], x, C, nullptr, part, n_split, gv.r16_total, true);
+    batch.p[0] = make_pass(gv.mv[0], x, C, nullptr, part, n_split, gv.r16_total, true, hv.T * C * 2);
     const hipError_t e = launch_tokc<true>(batch, 1, hv.n_adapters, zero, gv.max_r16, gv, st);
     if (e != hipSuccess || n_split <= 1) return e;
     hipLaunchKernelGGL(k_tokc_finish_group, dim3((unsigned)((C + TF_COLS - 1) / TF_COLS), (unsigned)hv.n_adapters), dim3(256),
@@ -502,9 +504,11 @@ hipError_t launch_tokcontract_bf16(const TokcOperands *ops, int n, int n_adapter
     TokcBatch batch{};
     int finish = 0, max_r16 = 0;
     bool finish_dA = false;
+    int64_t bytes = 0;
+    for (int i = 0; i < n; ++i) bytes += ops[i].T * ops[i].C * 2;
     for (int i = 0; i < n; ++i) {
         const TokcOperands &o = ops[i];
-        batch.p[i] = make_pass(o.mv, o.S, o.C, o.zt, o.part, o.n_split, o.r16_total, o.want_dA);
+        batch.p[i] = make_pass(o.mv, o.S, o.C, o.zt, o.part, o.n_split, o.r16_total, o.want_dA, bytes);
         batch.p[i].finish0 = finish;
         if (o.n_split > 1) { finish += (int)((o.C + TF_COLS - 1) / TF_COLS); finish_dA = finish_dA || o.want_dA; }
         max_r16 = o.max_r16 > max_r16 ? o.max_r16 : max_r16;
