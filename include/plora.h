@@ -25,6 +25,11 @@
  *     ordinary host memory that is read before the call returns (it may be freed afterwards).
  *   - The caller owns every buffer.  The library allocates no device memory; temporary storage
  *     comes from the caller's workspace (plora_workspace_bytes).
+ *   - An output must not overlap anything that the call reads, nor another output, except: dx of
+ *     plora_linear_bwd (and _bwd_nf4) may lie in the memory of x or of h_saved; with PLORA_BF16
+ *     dA_k may lie in that of dy if the call computes no dx, or dx by plora_lora_bwd; in a group
+ *     the weight gradients of a projection may lie in that of an earlier projection's dy.  Such a
+ *     call may take more launches.
  *   - Calls only enqueue work on the given HIP stream (a hipStream_t passed as void*; NULL is
  *     the default stream) and never synchronise.  Two calls that share a workspace must be
  *     ordered on one stream.

@@ -288,6 +288,23 @@ struct Bracket {
 
 static bool misaligned(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15u) != 0; }
 
+// Outputs in memory that the call reads.  Launches that hold several products write some outputs while others still read their
+// operands; a caller may have put an output where, one product after the other, nothing reads any more (plora.h says which), and
+// such a call runs them one after the other.
+struct Span { const void *p; size_t bytes; };
+static bool meet(const Span &a, const Span &b)
+{
+    const uintptr_t a0 = reinterpret_cast<uintptr_t>(a.p), b0 = reinterpret_cast<uintptr_t>(b.p);
+    return a.p && b.p && a.bytes > 0 && b.bytes > 0 && a0 < b0 + b.bytes && b0 < a0 + a.bytes;
+}
+// grads: dA (width d_in) or dB (width d_out)
+static bool meet_any(const plora_desc *d, float *const *grads, int64_t width, const Span &s)
+{
+    for (int32_t k = 0; k < d->n_adapters; ++k)
+        if (meet(Span{grads[k], (size_t)(d->rank[k] * width) * 4}, s)) return true;
+    return false;
+}
+
 // One call's host state: the cached metadata and the compact description with this call's pointers.
 struct Call {
     std::shared_ptr<const HostMeta> m;
@@ -379,6 +396,16 @@ struct TokcList {
     TokcOperands op[kTokMaxPasses];
     int n = 0;
 };
+static hipError_t launch_grads(TokcList &l, bool one_by_one, int n_adapters, const void *zero, hipStream_t st)
+{
+    const int n = l.n, step = one_by_one ? 1 : n;
+    l.n = 0;
+    for (int i = 0; i < n; i += step) {
+        const hipError_t e = launch_tokcontract_bf16(l.op + i, step, n_adapters, zero, st);
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
 
 static plora_status forward_impl(const plora_desc *desc, const void *x, const void *W, const void *const *A,
                                  const void *const *B, void *y, float *h_saved, void *workspace, size_t ws_bytes,
@@ -539,7 +566,8 @@ static plora_status backward_impl(const plora_desc *desc, const void *x, const v
         }
         if (lora && !f32_early && (steps & kStepDh)) { Bracket b(3, st); PL_TRY(launch_f32_lowrank(mv, m.hdr, 1, dyf, desc->d_out, gf, st)); }
         const bool one = any_w && dx && desc->T > 0 && !lora_only && !dx_accumulate && (steps & kStepDb) && (steps & kStepDx) && f32_bwd_fits(m.hdr, m.max_rank);
-        if (one) {
+        const Span dx_span{dx, (size_t)(desc->T * desc->d_in) * 4};
+        if (one && !meet(dx_span, Span{x, dx_span.bytes}) && !meet(dx_span, Span{hf, m.h_elems * 4})) {
             Bracket b(1, st);
             PL_TRY(launch_f32_bwd(mv, m.hdr, m.max_rank, xf, gf, dyf, hf, static_cast<const float *>(W), static_cast<float *>(dx), st));
             return PLORA_OK;
@@ -582,7 +610,10 @@ static plora_status backward_impl(const plora_desc *desc, const void *x, const v
         TokcList &list = later_w ? *later_w : own;
         if (steps & kStepDb) list.op[list.n++] = TokcOperands{mv, dy, zt_h, desc->d_out, m.small_part_is_dB ? part : wpart, m.split_dB, m.r16_total, m.hdr.max_r16, false, m.hdr.T};
         if (steps & kStepDa) list.op[list.n++] = TokcOperands{mv, x, zt_g, desc->d_in, m.small_part_is_dB ? wpart : part, m.split_dA, m.r16_total, m.hdr.max_r16, true, m.hdr.T};
-        if (own.n > 0) { Bracket b(4, st); PL_TRY(launch_tokcontract_bf16(own.op, own.n, m.hdr.n_adapters, ws + L.zero, st)); }
+        if (own.n > 0) {
+            Bracket b(4, st);
+            PL_TRY(launch_grads(own, meet_any(desc, dA, desc->d_in, Span{dy, (size_t)(desc->T * desc->d_out) * 2}), m.hdr.n_adapters, ws + L.zero, st));
+        }
     }
     if (!(steps & kStepDx)) return PLORA_OK;
     if (dx && desc->T > 0 && lora_only) {
@@ -823,12 +854,22 @@ static plora_status group_backward(const plora_group *g, const void *x, const vo
         PL_TRY(launch_skinny_group(gv, hv, x, d0->d_in, ws + gp.ws_off[members[0]] + gp.m[members[0]]->ws.zero,
                                    reinterpret_cast<float *>(ws + gp.part_off), gp.part_bytes, gp.m[members[0]]->split_shrink, hf, hb, zt, st));
     }
-    for (int p = 0; p < gp.n; ++p)
+    // gradients in the memory of a dy of the group: projection by projection, each with its dX
+    bool one_by_one = false;
+    for (int p = 0; p < gp.n; ++p) {
+        const Span dy_span{dy[p], (size_t)(d0->T * g->desc[p].d_out) * (d0->dtype == PLORA_BF16 ? 2 : 4)};
+        for (int q = 0; q < gp.n; ++q)
+            one_by_one = one_by_one || (want_w[q] && (meet_any(&g->desc[q], dA[q], d0->d_in, dy_span) ||
+                                                      meet_any(&g->desc[q], dB[q], g->desc[q].d_out, dy_span)));
+    }
+    for (int p = 0; p < gp.n; ++p) {
         if ((ps = run(p, false, kStepDh | kStepDb | (fuse_a[p] ? 0u : kStepDa))) != PLORA_OK) return ps;
-    if (skinny.n > 0) { Bracket b(3, st); PL_TRY(launch_skinny_bf16(skinny.op, skinny.n, zero, st)); }
-    if (grads.n > 0) { Bracket b(4, st); PL_TRY(launch_tokcontract_bf16(grads.op, grads.n, d0->n_adapters, zero, st)); }
-    for (int p = 0; p < gp.n; ++p)
-        if ((ps = run(p, false, kStepDx)) != PLORA_OK) return ps;
+        if (!one_by_one && p + 1 < gp.n) continue;
+        if (skinny.n > 0) { Bracket b(3, st); PL_TRY(launch_skinny_bf16(skinny.op, skinny.n, zero, st)); skinny.n = 0; }
+        if (grads.n > 0) { Bracket b(4, st); PL_TRY(launch_grads(grads, one_by_one, d0->n_adapters, zero, st)); }
+        for (int q = one_by_one ? p : 0; q <= p; ++q)
+            if ((ps = run(q, false, kStepDx)) != PLORA_OK) return ps;
+    }
     for (int c = 0; c < gp.n_cells; ++c) {
         int members[kMaxGroup], nm = 0;
         for (int p = 0; p < gp.n; ++p)
