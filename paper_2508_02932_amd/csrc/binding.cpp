@@ -151,23 +151,34 @@ template <size_t... I> int invoke(void *fn, const uint64_t *a, std::index_sequen
 {
     return reinterpret_cast<int (*)(decltype((void)I, (uint64_t)0)...)>(fn)(a[I]...);
 }
+template <size_t N> int invoke_words(void *fn, const uint64_t *a) { return invoke(fn, a, std::make_index_sequence<N>()); }
 
-// Integers and pointers all travel as 64-bit words in this platform's calling convention.
-int invoke_n(void *fn, const std::vector<uint64_t> &a)
+// Integers and pointers all travel as 64-bit words in this platform's calling convention.  Looked up with the interpreter lock
+// held: what a number of words that no entry point takes leads to is a Python error.
+using Invoke = int (*)(void *, const uint64_t *);
+Invoke invoke_for(size_t n_words)
 {
-    switch (a.size()) {
-    case 5: return invoke(fn, a.data(), std::make_index_sequence<5>());
-    case 8: return invoke(fn, a.data(), std::make_index_sequence<8>());
-    case 9: return invoke(fn, a.data(), std::make_index_sequence<9>());
-    case 10: return invoke(fn, a.data(), std::make_index_sequence<10>());
-    case 11: return invoke(fn, a.data(), std::make_index_sequence<11>());
-    case 12: return invoke(fn, a.data(), std::make_index_sequence<12>());
-    case 13: return invoke(fn, a.data(), std::make_index_sequence<13>());
-    case 14: return invoke(fn, a.data(), std::make_index_sequence<14>());
+    switch (n_words) {
+    case 5: return invoke_words<5>;
+    case 8: return invoke_words<8>;
+    case 9: return invoke_words<9>;
+    case 10: return invoke_words<10>;
+    case 11: return invoke_words<11>;
+    case 12: return invoke_words<12>;
+    case 13: return invoke_words<13>;
+    case 14: return invoke_words<14>;
     }
     PyErr_SetString(PyExc_RuntimeError, "no entry point takes this many arguments");
     throw PythonError();
 }
+
+struct Unlocked {                                              // the interpreter lock is given up for this scope, however it is left
+    PyThreadState *state = PyEval_SaveThread();
+    Unlocked() = default;
+    ~Unlocked() { PyEval_RestoreThread(state); }
+    Unlocked(const Unlocked &) = delete;
+    Unlocked &operator=(const Unlocked &) = delete;
+};
 
 // call(address, form, argument, ...): one letter of the form per argument:
 //   d  address of a description            p  tensor or None               t  list of tensors or None
@@ -204,9 +215,11 @@ PyObject *call(PyObject *, PyObject *const *args, Py_ssize_t n_args)
             }
         }
         int code = 0;
-        Py_BEGIN_ALLOW_THREADS
-        code = invoke_n(fn, a);
-        Py_END_ALLOW_THREADS
+        const Invoke call_it = invoke_for(a.size());
+        {
+            const Unlocked unlocked;
+            code = call_it(fn, a.data());
+        }
         return PyLong_FromLong(code);
     } catch (const PythonError &) {
         return nullptr;
