@@ -2,6 +2,7 @@
 from __future__ import annotations
 
 import os
+import re
 import subprocess
 import sys
 import sysconfig
@@ -21,14 +22,43 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-u
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
          "-I", os.path.join(ROOT, "include"), "-I", CSRC]
 
+# Sources with kernels on the fp64 matrix instruction (f32_tiles.h): their sums must lie in ordinary vector registers.
+F64_SOURCES = ("f32_kernels.hip", "small_kernels.hip")
+REMARK = "kernel-resource-usage"
+
+
+def kernels_with_accumulation_registers(remarks: str) -> list:
+    """The fp32 path's kernels (k_f32_*, k_prep_f32) that the compiler's resource remarks give accumulation registers."""
+    found, name = [], ""
+    seen = 0
+    for line in remarks.splitlines():
+        m = re.search(r"remark: Function Name: (\S+)", line)
+        if m:
+            name = m.group(1)
+        m = re.search(r"remark:\s+AGPRs: (\d+)", line)
+        if m and re.search(r"k_f32_|k_prep_f32", name):
+            seen += 1
+            if int(m.group(1)) > 0:
+                found.append(name)
+    if not seen:
+        raise RuntimeError("no resource remarks of the fp32 path's kernels")
+    return found
+
 
 def _compile(src: str, obj_dir: str = OBJ, extra=()) -> str:
     obj = os.path.join(obj_dir, os.path.splitext(src)[0] + ".o")
-    cmd = ["hipcc", *FLAGS, *extra, "-c", os.path.join(CSRC, src), "-o", obj]
+    checked = src in F64_SOURCES
+    flags = ["-Rpass-analysis=" + REMARK, "-fno-caret-diagnostics"] if checked else []
+    cmd = ["hipcc", *FLAGS, *flags, *extra, "-c", os.path.join(CSRC, src), "-o", obj]
     res = subprocess.run(cmd, capture_output=True, text=True)
-    err = "\n".join(l for l in res.stderr.splitlines() if "packed-fp32-ops" not in l and "argument unused during compilation" not in l)
+    lines = res.stderr.splitlines()
+    err = "\n".join(l for l in lines if "packed-fp32-ops" not in l and "argument unused during compilation" not in l and REMARK not in l)
     if res.returncode != 0:
         raise RuntimeError(f"hipcc failed on {src}:\n{err}")
+    if checked:
+        bad = kernels_with_accumulation_registers("\n".join(l for l in lines if REMARK in l))
+        if bad:
+            raise RuntimeError(f"{src}: sums in accumulation registers, which are read too early (see f32_tiles.h): {', '.join(bad)}")
     if err.strip():
         sys.stderr.write(err + "\n")
     return obj

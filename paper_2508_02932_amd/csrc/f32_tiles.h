@@ -81,7 +81,7 @@ __device__ inline void multiply_chunk(const float (*a)[8], const float (*b)[8], 
 // In front of the first vector-ALU read of a matrix instruction's sums.  The compiler pads that distance itself, but not where
 // the two meet at a join of branches: a loop that kept its sums in accumulation registers read the last of them one instruction
 // behind the product (seen in its assembly; rows 12 to 15 of a tile were wrong).  The kernels below are therefore bounded to two
-// waves per SIMD, at which the compiler leaves the sums in vector registers, and wait here.
+// waves per SIMD, at which the compiler leaves the sums in vector registers (build.py refuses anything else), and wait here.
 template <int RB, int CB> __device__ inline void settle(f64x4 (*acc)[CB])
 {
 #pragma unroll
