@@ -66,6 +66,10 @@ typedef struct {
     /* how the base products are cut, [0] forward, [1] dX: rows of the small output tiles (64 or 128; 0: 256 x 256 tiles
      * alone), splits of the contraction, and the 256-row tiles that are left to the 256 x 256 kernel */
     int32_t gemm_rows[2], gemm_splits[2], gemm_big_tiles[2];
+    /* [0] shrink, [1] dH of a call over a bf16 weight: workgroups that the routine for short batches deals a contraction to;
+     * 0: the product is not short (it takes shrink_splits, dh_splits) */
+    int32_t short_shares[2];
+    uint64_t ws_flags, flag_bytes;   /* arrival flags of that routine: all zero again behind a call (0 bytes: none) */
 } plora_debug_info;
 
 /* Fills *info and, if tables_out is not NULL, copies the table image (info->table_bytes bytes;

@@ -1010,7 +1010,12 @@ int plora_debug_metadata(const plora_desc *desc, plora_debug_info *info, void *t
         for (int i = 0; i < 2; ++i) {
             const GemmPlan &p = i == 0 ? m.gemm_fwd : m.gemm_dx;
             info->gemm_rows[i] = p.bm; info->gemm_splits[i] = p.n_split; info->gemm_big_tiles[i] = p.big_tiles;
+            const int64_t C = i == 0 ? desc->d_in : desc->d_out;
+            const bool is_short = desc->dtype == PLORA_BF16 && skinny_is_short(m.hdr, m.slices16, C);
+            info->short_shares[i] = is_short ? short_shares(m.hdr, m.slices16, C, m.short_cap()).n : 0;
         }
+        info->ws_flags = m.ws.flags;
+        info->flag_bytes = info->short_shares[0] + info->short_shares[1] > 0 ? 2 * flag_count(m.hdr) * sizeof(unsigned long long) : 0;
         if (tables_out) {
             if (cap < m.layout.bytes) return -1;
             std::memcpy(tables_out, m.image.data(), m.layout.bytes);

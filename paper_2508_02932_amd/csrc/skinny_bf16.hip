@@ -349,6 +349,22 @@ bool skinny_is_short(const MetaHeader &h, int slices16, int64_t C)
     return (int64_t)slices16 * (16 + h.max_r16) * C * 2 <= SH_MAX_BYTES;
 }
 
+// Shares of the contraction: about two workgroups per compute unit (four where the rank makes a chunk long: 3000 tokens,
+// 1024 -> 1024, rank 128 the step takes 95 and 92 us; 2048 tokens, 4096 -> 4096, rank 16 158 and 162), a chunk for every wave
+// at least (one, two, four, eight chunks: 64 tokens, 2048 -> 2048 the step takes 41, 44, 47, 50 us, 300 tokens, 1024 -> 1024,
+// rank 128 64, 73, 89, 89)
+ShortShares short_shares(const MetaHeader &h, int slices16, int64_t C, int most)
+{
+    const int n_chunks = (int)((C + SH_BK - 1) / SH_BK);
+    int n = (h.max_r16 > 64 ? 1024 : 512) / (slices16 > 0 ? slices16 : 1);
+    if (n > n_chunks / SH_NW) n = n_chunks / SH_NW;
+    if (n > most) n = most;
+    if (n > kShortMaxSplits) n = kShortMaxSplits;
+    if (n < 1) n = 1;
+    const int per = (n_chunks + n - 1) / n;
+    return ShortShares{(n_chunks + per - 1) / per, per};
+}
+
 ShortJob short_job(const SkinnyOperands &o)
 {
     ShortJob j{};
@@ -356,18 +372,8 @@ ShortJob short_job(const SkinnyOperands &o)
     j.part = o.part; j.flags = o.flags;
     j.out = SkinnyOut{o.hf, static_cast<uint16_t *>(o.hb), static_cast<uint16_t *>(o.zt), o.zt_scaled ? 1 : 0};
     j.C = (int32_t)o.C; j.mode = o.mode; j.max_r16 = o.h.max_r16;
-    // shares of the contraction: about two workgroups per compute unit (four where the rank makes a chunk long: 3000 tokens,
-    // 1024 -> 1024, rank 128 the step takes 95 and 92 us; 2048 tokens, 4096 -> 4096, rank 16 158 and 162), a chunk for every wave
-    // at least (one, two, four, eight chunks: 64 tokens, 2048 -> 2048 the step takes 41, 44, 47, 50 us, 300 tokens, 1024 -> 1024,
-    // rank 128 64, 73, 89, 89)
-    const int n_chunks = (int)((o.C + SH_BK - 1) / SH_BK);
-    int n = (o.h.max_r16 > 64 ? 1024 : 512) / (o.slices16 > 0 ? o.slices16 : 1);
-    if (n > n_chunks / SH_NW) n = n_chunks / SH_NW;
-    if (n > o.n_split) n = o.n_split;
-    if (n > kShortMaxSplits) n = kShortMaxSplits;
-    if (n < 1) n = 1;
-    j.per = (n_chunks + n - 1) / n;
-    j.n_split = (n_chunks + j.per - 1) / j.per;
+    const ShortShares s = short_shares(o.h, o.slices16, o.C, o.n_split);
+    j.n_split = s.n; j.per = s.per;
     j.number = launch_number();
     return j;
 }

@@ -100,7 +100,8 @@ class plora_debug_info(C.Structure):
                 + [(n, C.c_uint64) for n in ("ws_zero", "ws_meta", "ws_desc", "ws_at", "ws_ap", "ws_hb", "ws_zt_h",
                                              "ws_zt_g", "ws_hf", "ws_gf", "ws_part", "ws_wpart", "ws_total", "h_elems",
                                              "off_tile_order")]
-                + [(n, C.c_int32 * 2) for n in ("gemm_rows", "gemm_splits", "gemm_big_tiles")])
+                + [(n, C.c_int32 * 2) for n in ("gemm_rows", "gemm_splits", "gemm_big_tiles", "short_shares")]
+                + [(n, C.c_uint64) for n in ("ws_flags", "flag_bytes")])
 
 
 # numpy views of the records of the table image (include/plora_debug.h)

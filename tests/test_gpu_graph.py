@@ -115,3 +115,93 @@ def test_capture_and_replay_grouped():
         gh.check_guards(dp)
     for name, base, nbytes in guards:
         assert bool((base[:gh.GUARD_BYTES] == gh.GUARD_BYTE).all()) and bool((base[gh.GUARD_BYTES + nbytes:] == gh.GUARD_BYTE).all()), name
+
+
+@pytest.mark.parametrize("mode", ["saved", "recomputed", "lora_only", "noalloc", "grouped"])
+def test_replay_of_short_products_with_several_shares(mode):
+    """The workgroups of a short product that share a contraction announce themselves with a number that a captured launch keeps:
+    every replay finds its flags at zero again, and sums what this replay wrote.  The inputs change between the replays, the
+    workspace is left as the replay before left it, then scribbled over."""
+    import torch
+    import gpu_harness as gh
+    Ks = (2504, 1032) if mode == "grouped" else (2504,)
+    lora = mode == "lora_only"
+    lins = [wl.small(f"graph_shares_{K}", "bf16", 1000, K, lengths=[300, 201], seg_adapter=[0, 1], ranks=[100, 7], scales=[2.0, 0.5],
+                     seed=571 + p) for p, K in enumerate(Ks)]
+    dps = [gh.upload(lin, lin.tensors(), lora_only=lora) for lin in lins]
+    infos = [plora.plora_debug_metadata(dp.desc)[0] for dp in dps]
+    assert all(min(i.short_shares) > 1 for i in infos)
+    dp, x = dps[0], dps[0].x
+    group = plora.Group([d.desc for d in dps])
+    size = {"grouped": lambda: plora.plora_group_workspace_bytes(group), "lora_only": lambda: plora.plora_lora_workspace_bytes(dp.desc)}.get(
+        mode, lambda: plora.plora_workspace_bytes(dp.desc))()
+    ws, other_ws = torch.zeros(size, dtype=torch.uint8, device="cuda"), torch.zeros(size, dtype=torch.uint8, device="cuda")
+    bases = [torch.randn_like(dp.y), torch.randn_like(dp.dx)]
+    lists = lambda name: [getattr(d, name) for d in dps]
+
+    def step(w, captured):
+        h = None if mode == "recomputed" else dp.h
+        if mode == "grouped":
+            plora.plora_group_fwd(group, x, lists("W"), lists("A"), lists("B"), lists("y"), lists("h"), w)
+            plora.plora_group_bwd(group, x, lists("W"), lists("A"), lists("B"), lists("dy"), None, lists("dx"), lists("dA"), lists("dB"), w)
+        elif lora:
+            dp.y.copy_(bases[0])
+            dp.dx.copy_(bases[1])
+            plora.plora_lora_fwd(dp.desc, x, dp.A, dp.B, dp.y, h, w)
+            plora.plora_lora_bwd(dp.desc, x, dp.A, dp.B, dp.dy, h, dp.dx, dp.dA, dp.dB, w)
+        elif mode == "noalloc" and captured:
+            plora.plora_linear_fwd_noalloc(dp.desc, x, dp.W, dp.A, dp.B, dp.y, h)
+        else:
+            plora.plora_linear_fwd(dp.desc, x, dp.W, dp.A, dp.B, dp.y, h, w)
+            if mode != "noalloc":
+                plora.plora_linear_bwd(dp.desc, x, dp.W, dp.A, dp.B, dp.dy, h, dp.dx, dp.dA, dp.dB, w)
+
+    backward = [] if mode == "noalloc" else [b for d in dps for b in (d.dx, *d.dA, *d.dB)]
+    outputs = [b for d in dps for b in (d.y, d.h)] + backward
+
+    def snapshot():
+        torch.cuda.synchronize()
+        return [b.clone() for b in outputs]
+
+    inputs = [x] + lists("dy")
+    sets = [[b.clone() for b in inputs], [torch.randn_like(b) for b in inputs], [torch.randn_like(b) for b in inputs]]
+
+    def load(i):
+        for b, v in zip(inputs, sets[i]):
+            b.copy_(v)
+
+    want = []
+    for i in range(3):
+        load(i)
+        step(other_ws, False)
+        want.append(snapshot())
+    say(f"[case] graph, several shares, {mode}")
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.stream(side):
+        step(ws, True)
+        torch.cuda.synchronize()
+        with torch.cuda.graph(graph, stream=side):
+            step(ws, True)
+    torch.cuda.synchronize()
+    flags = []
+    if mode not in ("noalloc", "lora_only"):                     # (their workspaces are laid out elsewhere)
+        at = 0
+        for d, i in zip(dps, infos):
+            flags.append(ws[at + i.ws_flags:at + i.ws_flags + i.flag_bytes])
+            at += (plora.plora_workspace_bytes(d.desc) + 255) // 256 * 256
+    for rep in range(7):
+        i = (0, 1, 2, 0, 1, 0, 2)[rep]
+        load(i)
+        for b in outputs:
+            b.fill_(float("nan"))
+        if rep >= 5:
+            ws.fill_(0xAB)
+        torch.cuda.synchronize()
+        graph.replay()
+        for a, b in zip(snapshot(), want[i]):
+            assert torch.equal(a.view(torch.uint8), b.view(torch.uint8)), f"replay {rep} differs from the eager run"
+        assert rep >= 5 or all(f.numel() > 0 and not bool(f.any()) for f in flags), f"flags left behind by replay {rep}"
+    for d in dps:
+        gh.check_guards(d)

@@ -65,6 +65,21 @@ CASES = {
 }
 
 
+def behind_many_segments(c, D):
+    """The same projections with 66 short segments more, so that the shrink is not short (at most 64 token blocks are)."""
+    n = len(c["ranks"][0])
+    return dict(c, D=D, lengths=c["lengths"] + tuple(1 + 3 * i % 7 for i in range(66)),
+                seg_adapter=c["seg_adapter"] + tuple(i % n for i in range(66)))
+
+
+# The cases above with few rows take the routine for short batches, projection by projection; these the fused shrink.
+CASES.update(qkv_one_pass_fused=behind_many_segments(CASES["qkv_one_pass"], 320), cut_in_two_fused=behind_many_segments(CASES["cut_in_two"], 256),
+             four_fused=behind_many_segments(CASES["four"], 520),
+             gate_up_fused=behind_many_segments(CASES["gate_up"], 2056),       # 33 stages in four splits: the last one is shorter
+             long_fused=dict(CASES["long"], lengths=(4096, 4000, 100), seg_adapter=(0, 1, 0)))
+NOT_SHORT = {"many_adapters", "two_of_three", "f32"} | {c for c in CASES if c.endswith("_fused")}
+
+
 def run_group(case, w_layouts, save_h, want_w, want_dx, seed=3):
     import torch
     import gpu_harness as gh
@@ -73,6 +88,7 @@ def run_group(case, w_layouts, save_h, want_w, want_dx, seed=3):
     lins, tens = make_group(c["dtype"], c["D"], c["Ks"], c["lengths"], c["seg_adapter"], c["ranks"], c["scales"], seed)
     n = len(lins)
     dps = [gh.upload(lins[p], tens[p], w_layouts[p]) for p in range(n)]
+    assert all((plora.plora_debug_metadata(dp.desc)[0].short_shares[0] == 0) == (case in NOT_SHORT) for dp in dps)
     group = plora.Group([dp.desc for dp in dps])
     ws_bytes = plora.plora_group_workspace_bytes(group)
     assert ws_bytes >= sum(plora.plora_workspace_bytes(dp.desc) for dp in dps)
@@ -126,13 +142,13 @@ def test_group_equals_each_projection_alone(case, save_h):
     n = len(CASES[case]["Ks"])
     print(f"[case] group {case} save_h={save_h}", flush=True)
     sys.stdout.flush()
-    layouts = [(p + 1) % 2 if case in ("qkv_one_pass", "four") else 0 for p in range(n)]
+    layouts = [(p + 1) % 2 if case.startswith(("qkv_one_pass", "four")) else 0 for p in range(n)]
     sh, ww, wd = [save_h] * n, [True] * n, [True] * n
     lins, tens, dps = run_group(case, layouts, sh, ww, wd)
     check_against_oracle(lins, tens, dps, sh, ww, wd)
 
 
-@pytest.mark.parametrize("case", ["qkv_one_pass", "cut_in_two", "four", "two_of_three"])
+@pytest.mark.parametrize("case", ["qkv_one_pass", "cut_in_two", "four", "two_of_three", "qkv_one_pass_fused", "cut_in_two_fused", "four_fused"])
 def test_group_per_projection_options(case):
     """Saved activation for some projections only, weight gradients for some only, dx for some only: the fused passes
     take the projections that need them, the others run alone or not at all."""
@@ -146,16 +162,19 @@ def test_group_per_projection_options(case):
     check_against_oracle(lins, tens, dps, sh, ww, wd)
 
 
-@pytest.mark.parametrize("case", ["qkv_one_pass", "gate_up"])
+@pytest.mark.parametrize("case", ["qkv_one_pass", "gate_up", "qkv_one_pass_fused", "gate_up_fused"])
 def test_group_forward_is_bitwise_the_plain_call(case):
     """The fused shrink sums every element over the contraction in the same order as the plain kernel (same stages,
-    same splits), so the saved activation and y are bit for bit those of plora_linear_fwd."""
+    same splits), so the saved activation and y are bit for bit those of plora_linear_fwd.  So does the routine for short
+    batches, which a grouped call runs on the packed A_k in a launch of its own and a plain one on A_k as it lies in memory."""
     import torch
     import gpu_harness as gh
+    from paper_2508_02932_amd import plora
     n = len(CASES[case]["Ks"])
     print(f"[case] group bitwise {case}", flush=True)
     sys.stdout.flush()
     lins, tens, dps = run_group(case, [0] * n, [True] * n, [True] * n, [True] * n)
+    assert not case.startswith("gate_up") or plora.plora_debug_metadata(dps[0].desc)[0].shrink_splits > 1
     for p in range(n):
         ref = gh.upload(lins[p], tens[p], 0)
         gh.forward(ref, save_h=True)
@@ -165,20 +184,24 @@ def test_group_forward_is_bitwise_the_plain_call(case):
         assert torch.equal(ref.y, dps[p].y), f"projection {p}: y differs"
 
 
+@pytest.mark.parametrize("length,whole", [(260, 21), (150, 32)], ids=["fused", "short"])
 @pytest.mark.parametrize("w_layouts", [(0, 0), (0, 1)], ids=["cut_alike", "one_cut"])
-def test_group_forward_is_bitwise_the_plain_call_when_the_workspace_cuts_the_splits(w_layouts):
+def test_group_forward_is_bitwise_the_plain_call_when_the_workspace_cuts_the_splits(w_layouts, length, whole):
     """Many adapters bring the workspace close to the scratch array's size, and the shrink is split less often than its rule
-    says, in one projection or in both: the grouped call still sums as the plain calls do."""
+    says, in one projection or in both: the grouped call still sums as the plain calls do.  (length 260: projections cut alike
+    are fused, the others are not; length 150: short, the room for partial tiles bounds the shares.)"""
     import torch
     import gpu_harness as gh
     from paper_2508_02932_amd import plora
-    print(f"[case] group bitwise, cut splits {w_layouts}", flush=True)
+    print(f"[case] group bitwise, cut splits {w_layouts} {length}", flush=True)
     n_ad = 28
-    lins, tens = make_group("bf16", 8192, (64, 64), (150,) * 4 + (0,) * (n_ad - 4), tuple(range(n_ad)), ((64,) * n_ad,) * 2,
+    lins, tens = make_group("bf16", 8192, (64, 64), (length,) * 4 + (0,) * (n_ad - 4), tuple(range(n_ad)), ((64,) * n_ad,) * 2,
                             ((1.0,) * n_ad,) * 2, seed=7)
     dps = [gh.upload(l, t, w) for l, t, w in zip(lins, tens, w_layouts)]
-    splits = [int(plora.plora_debug_metadata(dp.desc)[0].shrink_splits) for dp in dps]
-    assert splits[0] < 32 and splits[1] == (splits[0] if w_layouts[1] == 0 else 32), splits
+    infos = [plora.plora_debug_metadata(dp.desc)[0] for dp in dps]
+    splits = [int(i.shrink_splits) for i in infos]
+    assert splits[0] < whole and splits[1] == (splits[0] if w_layouts[1] == 0 else whole), splits
+    assert all((i.short_shares[0] > 0) == (length == 150) for i in infos)
     group = plora.Group([dp.desc for dp in dps])
     ws = torch.empty(plora.plora_group_workspace_bytes(group), dtype=torch.uint8, device="cuda")
     lists = lambda name: [getattr(dp, name) for dp in dps]
@@ -247,7 +270,7 @@ def test_config4_groups_full_size(members):
     assert torch.equal(dx_sum, chain)
 
 
-@pytest.mark.parametrize("case", ["qkv_one_pass", "cut_in_two", "four", "gate_up", "f32", "single"])
+@pytest.mark.parametrize("case", ["qkv_one_pass", "cut_in_two", "four", "gate_up", "f32", "single", "four_fused"])
 def test_group_input_gradient_summed_in_the_epilogue(case):
     """dx_sum: the gradient of the shared input, sum over the projections of dy_p W_p^T + g_p A_p^T, against the oracle's
     per-projection dx added up in fp64; in bf16 also bit for bit against the chain of bf16 additions of the per-projection
