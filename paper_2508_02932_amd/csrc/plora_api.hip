@@ -89,6 +89,7 @@ struct HostMeta {
     int split_shrink = 1, split_dh = 1, skinny_cap = 8;   // skinny_cap: splits whose partial tiles the workspace holds
     int short_cap() const { return skinny_cap > 1 ? skinny_cap / 2 : 1; }     // ... and what one of two short products takes of them
     int slices16 = 0;                 // 16-token slices with tokens of an adapter
+    int mean_r16 = 0;                 // their rank padded to 16, on average over the tokens
     GemmPlan gemm_fwd, gemm_dx;
     int n_words = 0;
     bool small_part_is_dB = false;    // which of dB and dA has the smaller set of partial tiles
@@ -116,14 +117,16 @@ static void build_meta(const plora_desc *d, HostMeta &m)
     for (int64_t i = 0; i < m.layout.n_tiles; ++i) m.order_is_identity = m.order_is_identity && m.t.tile_order[i] == (int32_t)i;
     m.hdr = *m.t.hdr;
 
-    int64_t h = 0, hb = 0, zt = 0, at = 0, ap = 0;
+    int64_t h = 0, hb = 0, zt = 0, at = 0, ap = 0, rows = 0, row_ranks = 0;
     for (int32_t s = 0; s < d->n_seg; ++s) {
         const SegInfo &g = m.t.seg[s];
         if (g.adapter < 0) continue;
         const int64_t len = g.row1 - g.row0;
         h += len * g.r; hb += len * g.rp; zt += (int64_t)g.r16 * g.lp;
         m.slices16 += (int)((len + 15) / 16);
+        rows += len; row_ranks += len * g.r16;
     }
+    m.mean_r16 = rows > 0 ? (int)((row_ranks + rows - 1) / rows) : 0;
     m.r16_total = 0; m.n_active = 0;
     for (int32_t k = 0; k < d->n_adapters; ++k) {
         const AdapterInfo &a = m.t.ad[k];
@@ -432,7 +435,8 @@ static plora_status forward_impl(const plora_desc *desc, const void *x, const vo
     const bool is_short = bf && lora && !nf4 && skinny_is_short(m.hdr, m.slices16, desc->d_in);
     const bool brief = is_short && !later && (steps & kStepPrep) && (steps & kStepShrink) && m.n_words <= kChunkWords;
     const SkinnyOperands shrink{mv, m.hdr, 0, x, desc->d_in, ws + L.at, reinterpret_cast<float *>(ws + L.part), is_short ? m.short_cap() : m.split_shrink,
-                                reinterpret_cast<unsigned long long *>(ws + L.flags), m.slices16, h_saved, ws + L.hb, nullptr, false, is_short};
+                                reinterpret_cast<unsigned long long *>(ws + L.flags), m.slices16, h_saved, ws + L.hb, nullptr, false, is_short, lora_only,
+                                m.mean_r16};
     // the fp32 path: its shrink runs in the preparation launch as well
     float *hf = h_saved ? h_saved : reinterpret_cast<float *>(ws + L.hf);
     const bool f32_early = !bf && lora && !later && !nf4 && (steps & kStepPrep) && (steps & kStepShrink) && m.n_words <= kChunkWords && f32_units_fit(m);
@@ -521,9 +525,9 @@ static plora_status backward_impl(const plora_desc *desc, const void *x, const v
     float *part = reinterpret_cast<float *>(ws + L.part);
     unsigned long long *flags = reinterpret_cast<unsigned long long *>(ws + L.flags);
     const SkinnyOperands shrink{mv, m.hdr, 0, x, desc->d_in, ws + L.at, part, short_sh ? m.short_cap() : m.split_shrink, flags, m.slices16,
-                                nullptr, nullptr, ws + L.zt_h, false, short_sh};
+                                nullptr, nullptr, ws + L.zt_h, false, short_sh, lora_only, m.mean_r16};
     SkinnyOperands dh{mv, m.hdr, 1, dy, desc->d_out, nullptr, part, short_dh ? m.short_cap() : m.split_dh, flags, m.slices16,
-                      nullptr, ws + L.hb, any_w ? ws + L.zt_g : nullptr, true, short_dh};
+                      nullptr, ws + L.hb, any_w ? ws + L.zt_g : nullptr, true, short_dh, lora_only, m.mean_r16};
     if (brief_sh && brief_dh) {
         dh.part += (size_t)m.short_cap() * m.hdr.n_blocks * kSkinnyRows * m.hdr.max_r16;
         dh.flags += flag_count(m.hdr);

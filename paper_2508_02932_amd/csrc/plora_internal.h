@@ -479,6 +479,8 @@ struct SkinnyOperands {
     float *hf;
     void *hb, *zt;
     bool zt_scaled, is_short;     // is_short: skinny_short.h
+    bool alone;                   // of a stand-alone low-rank call: no base product reads S afterwards
+    int mean_r16;                 // rank rows that a token reads on average
 };
 hipError_t launch_skinny_bf16(const SkinnyOperands *ops, int n, const void *zero, hipStream_t st);
 // Whether a product takes the routine for short batches (skinny_short.h; such products of a grouped call are not fused).

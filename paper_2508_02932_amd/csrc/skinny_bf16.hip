@@ -51,9 +51,15 @@ struct SkinnyJob {
     float *part;                  // fp32 partial tiles
     SkinnyOut out;
     int32_t C, mode, per, n_split, max_r16;      // per: stages of 64 per split
-    int32_t past;                 // S is read past the caches, from another stage in every workgroup
+    int32_t past;                 // S is read past the caches ...
+    int32_t turn;                 // ... and from another stage in every workgroup
 };
-static int skinny_past(const MetaHeader &h, const void *S, int64_t C) { return h.T * C * 2 >= (48 << 20) && rows_of_whole_lines(S, C); }
+// How S is read, see k_skinny.  alone: of a stand-alone low-rank call; mean_r16: rank rows that a token reads on average.
+static void set_past(SkinnyJob &j, const MetaHeader &h, bool alone, int mean_r16)
+{
+    j.past = h.T * j.C * 2 >= (48 << 20) && rows_of_whole_lines(j.S, j.C);
+    j.turn = j.past && (alone || j.mode == 1) && mean_r16 <= 52 && (int64_t)mean_r16 * j.C * 2 <= (3 << 19);
+}
 struct SkinnyBatch { SkinnyJob j[kMaxGroup]; };
 
 // One workgroup (4 waves) per (token block of 128 rows of one segment, slice of the contraction).
@@ -62,15 +68,17 @@ struct SkinnyBatch { SkinnyJob j[kMaxGroup]; };
 // conflict free).  Wave w owns tokens 32w..32w+31 and every rank block, so nothing is reduced
 // across waves.  Output: the fp32 partial tile [128][r16] of this slice.
 //   mode 0: small matrix = packed A_k^T [r16][C] (rows >= r are zero),  mode 1: B_k [r][C].
-// Every workgroup begins its slice at another stage: side by side from the same column on, the workgroups would ask for 128-byte
-// pieces whole rows apart, which lie in few of the memory channels when a row is a power of two long.  Alone, us: 32768 tokens, 8192
-// columns, rank 64 143 -> 134, 16384 x 4096 rank 32 43 -> 39.  The non-temporal hint on the big matrix: with both 110 and 38, 16384 x
-// 14336 115 -> 100 (4.7 TB/s), 8192 x 4096 27 -> 23; k_tokc and the GEMM, which read it next, find less of it on the chip: 2 us
-// each at 8192 x 4096, and at sizes above the 256 MB of the last cache k_tokc's own hint makes up for it.  Of nine widths one loses by the
-// turn: 32768 tokens of 28672 columns 366 -> 403, against 24576 columns 172 -> 138 (16384 tokens), 16384 columns 114 -> 100, 11008 87 -> 81.
-// Both only where the rows are whole lines of 128 bytes (rows_of_whole_lines): otherwise neighbouring stages share lines, which the
-// hint lets go between them (20000 tokens, 13000 columns 177 us, 195 with it; the turn alone the same), and from 48 MB on: 67 MB gain
-// (above), 25 MB run the same either way and 29 MB are better left for the product that reads them next.
+// The big matrix may be read with the non-temporal hint, where its rows are whole lines of 128 bytes (rows_of_whole_lines; otherwise
+// neighbouring stages share lines, which the hint lets go between them: 20000 tokens, 13000 columns 177 us, 195 with it).  With its
+// finishing launch, us, without and with the hint: 32768 tokens, ranks 8 to 128, 8192 columns 147 and 133, 28672 columns 432 and 409;
+// 16384 tokens of rank 64, 4096 columns 48 and 42, 14336 columns 127 and 116; of 142 shapes from 48 MB on none is slower with it.
+// With the hint, and where the ranks are small, every workgroup begins its slice at another stage: side by side from the same column on,
+// the workgroups ask for 128-byte pieces whole rows apart, which lie in few of the memory channels (8192 tokens, rank 16, 16384 columns
+// 59 -> 51, 32768 columns 118 -> 92; 16384 tokens, rank 8 to 64, 8192 columns 74 -> 69).  Side by side they also share each stage of the
+// small matrix in the L2, which turned they read all over at once.  Rows of it per token on average, change over the widths from 4096
+// to 49152 columns: 16 to 32 -22 to +4 %, 48 -7 to +6 %, 51 -5 %, 54 -3 to +3 %, 64 -1 to +18 %, 128 0 to +21 % (28672 columns 164 -> 191): up to
+// 52, and 1.5 MB (26 rows, 49152 columns 338 -> 350).  Not the shrink of the other calls: a fused one has to sum as the plain ones of its
+// projections do, whose ranks differ.
 // grid.z: the jobs of the batch (dH of the projections of a grouped call).
 // GROUP (mode 0 only): the small matrix of adapter k is the packed A_k^T of several projections, one below the other
 // (GroupView); the tables are projection 0's, `at` is not used, and the jobs are where each projection's sums go.
@@ -167,7 +175,7 @@ __global__ void __launch_bounds__(64 * SK_NW) k_skinny(SkinnyBatch batch, const 
     auto load16_once = [&](const uint16_t *gp, uint32_t dst) {
         asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dwordx4 %0, off nt" ::"v"(gp), "s"(dst));
     };
-    const int turn = past && n_st > 0 ? (int)((blockIdx.x * 5u + blockIdx.y * 3u) % (unsigned)n_st) : 0;
+    const int turn = job.turn && n_st > 0 ? (int)((blockIdx.x * 5u + blockIdx.y * 3u) % (unsigned)n_st) : 0;
     auto issue = [&](int st) {       // step of this split: stage st + turn, round the end; ring slot st % SK_NST
         const uint32_t base = lds_base + (st % SK_NST) * stage_bytes;
         const int sx = st + turn < n_st ? st + turn : st + turn - n_st;
@@ -412,7 +420,7 @@ hipError_t launch_skinny_bf16(const SkinnyOperands *ops, int n, const void *zero
         j.part = o.part;
         j.out = SkinnyOut{o.hf, static_cast<uint16_t *>(o.hb), static_cast<uint16_t *>(o.zt), o.zt_scaled ? 1 : 0};
         j.C = (int32_t)o.C; j.mode = o.mode; j.max_r16 = o.h.max_r16; j.n_split = o.n_split;
-        j.past = skinny_past(o.h, o.S, o.C);
+        set_past(j, o.h, o.alone, o.mean_r16);
         const int n_stage_all = (j.C + SK_BK - 1) / SK_BK;
         j.per = (n_stage_all + j.n_split - 1) / j.n_split;
         n_blocks = o.h.n_blocks;
@@ -448,7 +456,7 @@ hipError_t launch_skinny_group(const GroupView &gv, const MetaHeader &hv, const 
         j.blk = gv.mv[p].blk; j.S = static_cast<const uint16_t *>(x); j.part = part;
         j.out = SkinnyOut{hf[p], static_cast<uint16_t *>(hb[p]), static_cast<uint16_t *>(zt[p]), 0};
         j.C = (int32_t)C; j.mode = 0; j.per = (n_stage_all + n_split - 1) / n_split; j.n_split = n_split; j.max_r16 = gv.max_r16;
-        j.past = skinny_past(hv, x, C);
+        set_past(j, hv, false, 0);
     }
     const size_t lds = (size_t)SK_NST * (SK_XT + gv.max_r16 * SK_BK * 2);
     hipError_t e = allow_full_lds(reinterpret_cast<const void *>(k_skinny<true>), 7);
