@@ -57,7 +57,9 @@ struct SkinnyJob {
 // How S is read, see k_skinny.  alone: of a stand-alone low-rank call; mean_r16: rank rows that a token reads on average.
 static void set_past(SkinnyJob &j, const MetaHeader &h, bool alone, int mean_r16)
 {
-    j.past = h.T * j.C * 2 >= (48 << 20) && rows_of_whole_lines(j.S, j.C);
+    const int64_t bytes = h.T * j.C * 2;
+    const bool worth = bytes >= (170 << 20) || (bytes >= (64 << 20) && (j.mode == 0 ? h.K >= 1024 : j.max_r16 <= 64));
+    j.past = (alone ? bytes >= (48 << 20) : worth) && rows_of_whole_lines(j.S, j.C);
     j.turn = j.past && (alone || j.mode == 1) && mean_r16 <= 52 && (int64_t)mean_r16 * j.C * 2 <= (3 << 19);
 }
 struct SkinnyBatch { SkinnyJob j[kMaxGroup]; };
@@ -71,7 +73,18 @@ struct SkinnyBatch { SkinnyJob j[kMaxGroup]; };
 // The big matrix may be read with the non-temporal hint, where its rows are whole lines of 128 bytes (rows_of_whole_lines; otherwise
 // neighbouring stages share lines, which the hint lets go between them: 20000 tokens, 13000 columns 177 us, 195 with it).  With its
 // finishing launch, us, without and with the hint: 32768 tokens, ranks 8 to 128, 8192 columns 147 and 133, 28672 columns 432 and 409;
-// 16384 tokens of rank 64, 4096 columns 48 and 42, 14336 columns 127 and 116; of 142 shapes from 48 MB on none is slower with it.
+// 16384 tokens of rank 64, 4096 columns 48 and 42, 14336 columns 127 and 116; of 142 shapes from 48 MB on none is slower with it.  But
+// the product that reads the matrix next does not find it in the last cache (256 MB).  Whole steps over inputs that change, without
+// and with the hint on all matrices from 48 MB on:
+//   - from 170 MB on little would be left there: 21019 tokens, 8192 -> 512 (328 MB) 626 and 599, 20615 tokens, 512 -> 8192 (322 MB) 602
+//     and 585
+//   - x before a GEMM that is bound by its operations, from 64 MB on: 16462 tokens, 2048 -> 2048 (64 MB) 383 and 375, 17635 tokens, 2048 ->
+//     1024 (69 MB) 271 and 264; a narrow one is not: 5912 tokens, 8192 -> 512 (92 MB) 256 and 266, 15639 tokens, 4096 -> 512 (122 MB) 405
+//     and 420
+//   - dy before k_tokc, which then reads it from memory: of small ranks dH gains more than that (16384 tokens, 4096 columns, rank 8 to 32 dH
+//     48 -> 35, k_tokc 54 -> 62), of large ones less (4326 tokens, 14336 columns, rank 64 to 128 dH 61 -> 55, k_tokc 33 -> 44)
+//   - in the stand-alone calls nothing but k_tokc reads it again: 9645 tokens, 8192 -> 1024 (151 MB) 283 and 275, 3812 tokens, 1024 -> 14336
+//     (104 MB) 229 and 224
 // With the hint, and where the ranks are small, every workgroup begins its slice at another stage: side by side from the same column on,
 // the workgroups ask for 128-byte pieces whole rows apart, which lie in few of the memory channels (8192 tokens, rank 16, 16384 columns
 // 59 -> 51, 32768 columns 118 -> 92; 16384 tokens, rank 8 to 64, 8192 columns 74 -> 69).  Side by side they also share each stage of the
