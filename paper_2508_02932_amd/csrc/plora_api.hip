@@ -176,7 +176,7 @@ static void build_meta(const plora_desc *d, HostMeta &m)
     // What plora_linear_fwd_noalloc takes: a description that fits its scratch array with eight skinny splits, no split GEMM
     // and the tables without their records and flags.  The workspace of such a description must not outgrow the array; any other
     // workspace is larger than the array, so its size alone tells the two apart.
-    const bool any_short = bf && (skinny_is_short(m.hdr, m.slices16, d->d_in) || skinny_is_short(m.hdr, m.slices16, d->d_out));
+    const bool any_short = bf && (skinny_is_short(m.hdr, m.slices16, m.r16_total, d->d_in) || skinny_is_short(m.hdr, m.slices16, m.r16_total, d->d_out));
     const size_t flag_bytes = any_short ? 2 * flag_count(m.hdr) * sizeof(unsigned long long) : 0;
     lay_out(m.ws, m.layout.blk, m.ap_elems, false, 0);
     const bool fits_scratch = m.ws.total <= (size_t)PLORA_NOALLOC_SCRATCH_BYTES;
@@ -432,7 +432,7 @@ static plora_status forward_impl(const plora_desc *desc, const void *x, const vo
     const bool w_out_in = m.hdr.w_out_in != 0;
     // a short batch: the shrink runs in the preparation launch (not in an NF4 call: its registers would cost the waves that
     // stream the weight, 47 -> 57 us for the two together, and in a launch of its own it is no faster than k_skinny)
-    const bool is_short = bf && lora && !nf4 && skinny_is_short(m.hdr, m.slices16, desc->d_in);
+    const bool is_short = bf && lora && !nf4 && skinny_is_short(m.hdr, m.slices16, m.r16_total, desc->d_in);
     const bool brief = is_short && !later && (steps & kStepPrep) && (steps & kStepShrink) && m.n_words <= kChunkWords;
     const SkinnyOperands shrink{mv, m.hdr, 0, x, desc->d_in, ws + L.at, reinterpret_cast<float *>(ws + L.part), is_short ? m.short_cap() : m.split_shrink,
                                 reinterpret_cast<unsigned long long *>(ws + L.flags), m.slices16, h_saved, ws + L.hb, nullptr, false, is_short, lora_only,
@@ -518,7 +518,7 @@ static plora_status backward_impl(const plora_desc *desc, const void *x, const v
     // a short batch: dH, and the shrink where h was not saved, run in the preparation launch; both at once share the room for
     // partial tiles and flags
     const bool may_short = bf && lora && !nf4;
-    const bool short_sh = may_short && skinny_is_short(m.hdr, m.slices16, desc->d_in), short_dh = may_short && skinny_is_short(m.hdr, m.slices16, desc->d_out);
+    const bool short_sh = may_short && skinny_is_short(m.hdr, m.slices16, m.r16_total, desc->d_in), short_dh = may_short && skinny_is_short(m.hdr, m.slices16, m.r16_total, desc->d_out);
     const bool may_brief = !later && (steps & kStepPrep) && m.n_words <= kChunkWords && m.skinny_cap > 1;
     const bool brief_sh = may_brief && short_sh && need_shrink && (steps & kStepShrink), brief_dh = may_brief && short_dh && (steps & kStepDh);
     const bool f32_early = !bf && lora && !later && !nf4 && (steps & kStepsAll) == kStepsAll && m.n_words <= kChunkWords && f32_units_fit(m);
@@ -729,7 +729,7 @@ static plora_status plan_group(const plora_group *g, GroupPlan &gp)
 }
 
 // A projection whose plain call takes the routine for short batches takes it here too, and is not fused.
-static bool short_shrink(const GroupPlan &gp, int p, const plora_desc *d0) { return skinny_is_short(gp.m[p]->hdr, gp.m[p]->slices16, d0->d_in); }
+static bool short_shrink(const GroupPlan &gp, int p, const plora_desc *d0) { return skinny_is_short(gp.m[p]->hdr, gp.m[p]->slices16, gp.m[p]->r16_total, d0->d_in); }
 
 // The fused view of the projections `members` of the plan (all of one cell); small: which side buffer the pass gathers.
 static void group_view(const GroupPlan &gp, char *ws, const int *members, int nm, bool small_is_at, GroupView &gv, MetaHeader &hv)
@@ -1015,7 +1015,7 @@ int plora_debug_metadata(const plora_desc *desc, plora_debug_info *info, void *t
             const GemmPlan &p = i == 0 ? m.gemm_fwd : m.gemm_dx;
             info->gemm_rows[i] = p.bm; info->gemm_splits[i] = p.n_split; info->gemm_big_tiles[i] = p.big_tiles;
             const int64_t C = i == 0 ? desc->d_in : desc->d_out;
-            const bool is_short = desc->dtype == PLORA_BF16 && skinny_is_short(m.hdr, m.slices16, C);
+            const bool is_short = desc->dtype == PLORA_BF16 && skinny_is_short(m.hdr, m.slices16, m.r16_total, C);
             info->short_shares[i] = is_short ? short_shares(m.hdr, m.slices16, C, m.short_cap()).n : 0;
         }
         info->ws_flags = m.ws.flags;

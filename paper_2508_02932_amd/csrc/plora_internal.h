@@ -484,7 +484,7 @@ struct SkinnyOperands {
 };
 hipError_t launch_skinny_bf16(const SkinnyOperands *ops, int n, const void *zero, hipStream_t st);
 // Whether a product takes the routine for short batches (skinny_short.h; such products of a grouped call are not fused).
-bool skinny_is_short(const MetaHeader &h, int slices16, int64_t C);
+bool skinny_is_short(const MetaHeader &h, int slices16, int r16_total, int64_t C);
 struct ShortShares { int n, per; };       // workgroups that a slice's contraction is dealt to, chunks of 64 for each
 ShortShares short_shares(const MetaHeader &h, int slices16, int64_t C, int most);
 struct SkinnyOut {                // where the sums go, see above

@@ -13,6 +13,7 @@
 // finishing kernel that also writes the bf16 copies the later kernels consume.
 // Short batches, where a kernel's own time is mostly its start, take skinny_short.h instead.
 #include "skinny_short.h"
+#include <algorithm>
 #include <type_traits>
 
 namespace plora {
@@ -30,7 +31,7 @@ constexpr int SK_XL = kSkinnyRows / 8 / SK_NW;         // token-tile load instru
 constexpr int SK_MB = kSkinnyRows / 16 / SK_NW;        // 16-token MFMA blocks per wave (2)
 constexpr int SK_BL = (PLORA_MAX_RANK / 8 + SK_NW - 1) / SK_NW;   // small-matrix load instructions per wave per stage, at most
 constexpr int SK_MAXNB = PLORA_MAX_RANK / 16;
-constexpr int64_t SH_MAX_BYTES = 80 << 20;
+constexpr int64_t SH_MAX_BYTES = 64 << 20, SH_MAX_SMALL = 24000000, SH_MAX_SMALL_8 = 10000000;
 
 // s_waitcnt vmcnt(n) for a wave-uniform runtime n (the instruction takes an immediate)
 __device__ inline void wait_vmcnt_dyn(int n)
@@ -360,14 +361,26 @@ __global__ void __launch_bounds__(64 * SH_NW, 4) k_skinny_short(ShortBatch batch
     skinny_short<NB>(job, a.g, a.scale, a.t0 + blockIdx.x % kShortSlices * 16, blockIdx.x, gridDim.x, blockIdx.y, small, false, lds);
 }
 
-// Which products are short, by what the slices fetch of the small matrix and their own rows out of the L2s; k_skinny reads the
-// small matrix once per 128 tokens, but in a launch of its own with a finishing launch behind it.  Whole steps, k_skinny and short, us: 53 MB (shrink and
-// dH of 64 tokens to 66 MB of 1531 tokens, 1000 -> 2504, rank 100) 57 and 42, 101 and 92; 56 MB (3000 tokens, 1024 -> 1024, rank 128) 97 and
-// 92; 67 MB (4096 tokens, 4096 -> 4096, rank 16) 281 and 267; 147 MB (dH of 1024 tokens, 14336 columns, rank 64) 284 and 295.
-bool skinny_is_short(const MetaHeader &h, int slices16, int64_t C)
+// Which products are short.  k_skinny reads the small matrix once per 128 tokens, in a launch of its own with a finishing launch
+// behind it.  The bounds, by whole steps with k_skinny and short, us:
+//   - what the slices fetch of the small matrix and their own rows out of the L2s: 47 MiB (dH of 1852 tokens, 4096 columns, rank 32) 123 and
+//     111, 54 MiB (1341 tokens, 4096 -> 512, rank 64) 83 and 77; above 64 MiB some gain and some lose: 72 MiB (2250 tokens, 1536 -> 8320,
+//     rank 16) 191 and 179, 68 MiB (1209 tokens, 5120 -> 3072, rank 128) 163 and 173, 80 MiB (1301 tokens, 5120 -> 512, rank 64) 123 and
+//     128, (1018 tokens, 14336 -> 8192, rank 64) 536 and 547
+//   - A_k and B_k of all adapters, which come from memory and whose packing shares the launch.  Up to rank 64: 18 MB (1734 tokens,
+//     4096 -> 512, 30 adapters) 108 and 97, 21 MB (187 tokens, 8192 -> 2048, 16 adapters) 114 and 111, 34 MB (450 tokens, 14336 -> 2048, 16
+//     adapters) 217 and 226.  Above, where a wave has half a chunk in flight and its registers are those of the preparation: 8.6 MB (132
+//     tokens, 2048 -> 1024, 24 adapters) 104 and 89, 10.1 MB (976 tokens, 3072 -> 4096, 16 adapters) 135 and 144, 25 MB (487 tokens,
+//     4096 -> 4096, 16 adapters) 138 and 163, 67 MB (174 tokens, 8192 -> 1024, 30 adapters) 169 and 255
+//   - above rank 64 at most two chunks for a wave: three or four (75 tokens, 14336 -> 1536, 4 adapters) 106 and 129
+bool skinny_is_short(const MetaHeader &h, int slices16, int r16_total, int64_t C)
 {
     if (h.n_blocks == 0 || h.n_blocks > kShortMaxBlocks) return false;
-    return (int64_t)slices16 * (16 + h.max_r16) * C * 2 <= SH_MAX_BYTES;
+    if ((int64_t)slices16 * (16 + h.max_r16) * C * 2 > SH_MAX_BYTES) return false;
+    const int most = std::max(8, std::max(skinny_splits(h, h.D), skinny_splits(h, h.K)));     // splits that the workspace has room for, uncut
+    const int64_t small = (int64_t)r16_total * (h.D + h.K) * 2;
+    if (h.max_r16 <= 64) return small <= SH_MAX_SMALL;
+    return small <= SH_MAX_SMALL_8 && short_shares(h, slices16, C, most / 2).per <= 2 * SH_NW;
 }
 
 // Shares of the contraction: about two workgroups per compute unit (four where the rank makes a chunk long: 3000 tokens,

@@ -184,24 +184,23 @@ def test_group_forward_is_bitwise_the_plain_call(case):
         assert torch.equal(ref.y, dps[p].y), f"projection {p}: y differs"
 
 
-@pytest.mark.parametrize("length,whole", [(260, 21), (150, 32)], ids=["fused", "short"])
+@pytest.mark.parametrize("n_ad,rank,length,whole", [(28, 64, 260, 21), (28, 64, 150, 32), (50, 16, 150, 32)], ids=["fused", "few_rows", "short"])
 @pytest.mark.parametrize("w_layouts", [(0, 0), (0, 1)], ids=["cut_alike", "one_cut"])
-def test_group_forward_is_bitwise_the_plain_call_when_the_workspace_cuts_the_splits(w_layouts, length, whole):
+def test_group_forward_is_bitwise_the_plain_call_when_the_workspace_cuts_the_splits(w_layouts, n_ad, rank, length, whole):
     """Many adapters bring the workspace close to the scratch array's size, and the shrink is split less often than its rule
-    says, in one projection or in both: the grouped call still sums as the plain calls do.  (length 260: projections cut alike
-    are fused, the others are not; length 150: short, the room for partial tiles bounds the shares.)"""
+    says, in one projection or in both: the grouped call still sums as the plain calls do.  (Projections
+    cut alike are fused, the others are not; with rank 16 the shrink is short, and the room for partial tiles bounds its shares.)"""
     import torch
     import gpu_harness as gh
     from paper_2508_02932_amd import plora
-    print(f"[case] group bitwise, cut splits {w_layouts} {length}", flush=True)
-    n_ad = 28
-    lins, tens = make_group("bf16", 8192, (64, 64), (length,) * 4 + (0,) * (n_ad - 4), tuple(range(n_ad)), ((64,) * n_ad,) * 2,
+    print(f"[case] group bitwise, cut splits {w_layouts} {n_ad} {rank} {length}", flush=True)
+    lins, tens = make_group("bf16", 8192, (64, 64), (length,) * 4 + (0,) * (n_ad - 4), tuple(range(n_ad)), ((rank,) * n_ad,) * 2,
                             ((1.0,) * n_ad,) * 2, seed=7)
     dps = [gh.upload(l, t, w) for l, t, w in zip(lins, tens, w_layouts)]
     infos = [plora.plora_debug_metadata(dp.desc)[0] for dp in dps]
     splits = [int(i.shrink_splits) for i in infos]
     assert splits[0] < whole and splits[1] == (splits[0] if w_layouts[1] == 0 else whole), splits
-    assert all((i.short_shares[0] > 0) == (length == 150) for i in infos)
+    assert [i.short_shares[0] for i in infos] == ([10 if s < whole else 12 for s in splits] if rank == 16 else [0, 0])
     group = plora.Group([dp.desc for dp in dps])
     ws = torch.empty(plora.plora_group_workspace_bytes(group), dtype=torch.uint8, device="cuda")
     lists = lambda name: [getattr(dp, name) for dp in dps]
