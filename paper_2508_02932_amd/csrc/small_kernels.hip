@@ -195,13 +195,6 @@ __device__ inline void pack_bt_block(const PackBJob &a, int64_t K, int bx, uint1
 }
 
 // ---- transposed bf16 copy of a saved fp32 activation ------------------------------------------------
-__device__ inline uint16_t f32_to_bf16_rne(float f)
-{
-    uint32_t u = __float_as_uint(f);
-    u += 0x7FFFu + ((u >> 16) & 1u);
-    return (uint16_t)(u >> 16);
-}
-
 // zt[j][t] = bf16(h[t][j]); rows j >= r and the padding tokens are written as zero.  One workgroup per
 // (token block of kSkinnyRows rows, half of it): 64 tokens, so that every row of zt is written in whole 128-byte pieces.
 struct TransposeJob {
@@ -230,7 +223,7 @@ __device__ inline void h_to_zt_slice(const TransposeJob &g, int slice, const flo
     for (int j = threadIdx.x >> 3; j < g.r16; j += 32) {
         union { uint4 q; uint16_t h[8]; } u;
 #pragma unroll
-        for (int t = 0; t < 8; ++t) u.h[t] = (j < g.r && tt + t < nt) ? f32_to_bf16_rne(tile[(tt + t) * g.r + j]) : (uint16_t)0;
+        for (int t = 0; t < 8; ++t) u.h[t] = (j < g.r && tt + t < nt) ? bf16_rne(tile[(tt + t) * g.r + j]) : (uint16_t)0;
         *reinterpret_cast<uint4 *>(dst + (int64_t)j * g.lp) = u.q;
     }
 }
