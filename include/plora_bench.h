@@ -6,9 +6,10 @@
  * call's own stream.  Enabling clears earlier records; at most 16384 brackets are kept.
  * plora_kernel_time sums the recorded durations of one class (milliseconds) and counts them; the
  * caller must have synchronised the streams first.
- * Classes: 0 base GEMM forward (with the fused expand), 1 dX GEMM (with the fused low-rank term),
- * 2 shrink, 3 dH, 4 dB, 5 dA (an fp32 call makes both gradients in one launch, class 4), 6 the preparation launch (metadata, packing of A_k, conversion of a
- * saved activation), 7 the optimizer step (all launches of one plora_adamw_step call), 8 the stand-alone
+ * Classes: 0 base GEMM forward (with the fused expand), 1 dX GEMM (with the fused low-rank term; in an fp32 call
+ * also the weight gradients where they share its launch), 2 shrink, 3 dH (and a shrink that shares its launch), 4 dB and
+ * dA (one launch), 5 the fused dA of a grouped call, 6 the preparation launch (metadata, packing of A_k, conversion of a
+ * saved activation; short shrinks and dHs share it), 7 the optimizer step (all launches of one plora_adamw_step call), 8 the stand-alone
  * low-rank update of plora_lora_fwd / plora_lora_bwd, 9 the expansion of an NF4 base weight (in a layer call together with
  * its preparation, which then is not counted as class 6).
  * Returns 0, or -1 on a bad argument or event error.  Process-global state, NOT thread-safe: one

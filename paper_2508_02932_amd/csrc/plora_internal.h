@@ -539,8 +539,8 @@ hipError_t launch_prep_nf4(const PrepJob &job, const Nf4Job &w, bool bf16, hipSt
 hipError_t launch_gemm_bf16(const MetaView &mv, const MetaHeader &h, bool w_rows_contract, int64_t Kd, int64_t N,
                             const void *S, const void *W, const void *side, const void *ap, const void *zero, void *C,
                             bool accumulate, int row_tiles, hipStream_t st);
-// Rows of a bf16 matrix begin and end on lines of 128 bytes: pieces of 64 columns that different workgroups or stages read share none.
 constexpr int64_t kLastCacheBytes = 256 << 20;     // shared by the XCDs of an MI355X
+// Rows of a bf16 matrix begin and end on lines of 128 bytes: pieces of 64 columns that different workgroups or stages read share none.
 inline bool rows_of_whole_lines(const void *p, int64_t columns)
 {
     return columns % 64 == 0 && reinterpret_cast<uintptr_t>(p) % 128 == 0;
