@@ -51,6 +51,15 @@ def test_short_behind_a_long_description(save_h):
     run_and_compare(lin, impl=oracle.matmul, save_h=save_h)
 
 
+def test_not_short_behind_a_long_description():
+    n = 90
+    lin = wl.small("long_description", "bf16", 328, 264, lengths=[1 + i % 20 for i in range(n)], seg_adapter=list(range(n)),
+                   ranks=[1 + 5 * i % 64 for i in range(n)], scales=[1.0 + i % 3 for i in range(n)], seed=449)
+    info = plora.plora_debug_metadata(gh().desc_of(lin))[0]
+    assert info.n_blocks > 64 and info.desc_words > 896 and list(info.short_shares) == [0, 0]
+    run_and_compare(lin, impl=oracle.matmul, save_h=False)
+
+
 def test_neither_product_is_short():
     """More than 64 token blocks: the kernel for long batches, with segments and ranks at the same edges."""
     lin = wl.small("not_short", "bf16", 1032, 1544, lengths=[1, 15, 16, 17, 63, 64, 65, 129] + [1 + i % 9 for i in range(64)],
