@@ -8,64 +8,74 @@ namespace plora {
 typedef double f64x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4_a4 __attribute__((ext_vector_type(4), aligned(4)));   // rows of any length: 4-byte aligned
 
-constexpr int F32_CK = 32;                 // contraction elements per chunk
+constexpr int F32_CK = 16;                 // contraction elements per chunk
 
-// Operand fragment of one chunk for 16 rows (or columns): lane (i = lane % 16, q = lane / 16) holds, of row i, the
-// elements k0 + 16 s + 4 q + j in v[4 s + j].  MFMA step (s, j) then contracts the four k of its four lane groups; both
-// operands number k the same way, so which k a step takes does not matter.
+// NB blocks of 16 rows (or columns) of an operand.  Fragment of one chunk: lane (i = lane % 16, q = lane / 16) holds, of row i,
+// the elements k0 + 4 q + j in v[block][j].  MFMA step j then contracts the four k of its four lane groups; both operands
+// number k the same way, so which k a step takes does not matter.
 // An operand is addressed by a uniform pointer, which the chunk moves, and a byte offset of the lane, which stays: registers
 // decide how many workgroups share a compute unit, and with them how much of the latency is hidden.
-// k contiguous in memory: base = row 0 of the tile; off: the lane's row, in bytes, plus 16 q
-__device__ inline void frag_k_contiguous(const float *base, uint32_t off, int64_t k0, int64_t n_k, int q, float *v)
-{
-    const char *p = reinterpret_cast<const char *>(base + k0);
-    if (k0 + F32_CK <= n_k) {
+// ROWS true: k is the row index of a [n_k][ld] matrix, 16 lanes read 64 bytes of a row.  false: k contiguous in memory, base =
+// row 0 of the tile, rows ld apart; there the four lanes that read the 64 bytes of a row are neighbours (one access to the
+// L1 instead of four) and the elements go to their lanes afterwards.
+template <bool ROWS, int NB> struct F32Operand {
+    const float *base;
+    int64_t ld;
+    uint32_t off[NB];                      // bytes; of 31 rows of at most 2^22 elements, or 15 rows and a column
+    // row (or column) of the tile whose offset the lane keeps, and its place in the chunk, in elements
+    __device__ static inline int own_row() { const int lane = threadIdx.x & 63; return ROWS ? lane & 15 : lane >> 2; }
+    __device__ static inline int own_k() { const int lane = threadIdx.x & 63; return 4 * (ROWS ? lane >> 4 : lane & 3); }
+    // i: own_row() of block b, clamped to the rows that there are
+    __device__ inline void row(int b, int i) { off[b] = ROWS ? ((uint32_t)own_k() * (uint32_t)ld + (uint32_t)i) * 4u : ((uint32_t)i * (uint32_t)ld + (uint32_t)own_k()) * 4u; }
+    // the chunk k0 .. k0 + F32_CK - 1, all of it there
+    __device__ inline void load(int64_t k0, float (*v)[4]) const
+    {
+        const char *p = reinterpret_cast<const char *>(ROWS ? base + k0 * ld : base + k0);
 #pragma unroll
-        for (int s = 0; s < 2; ++s) {
-            const f32x4_a4 t = *reinterpret_cast<const f32x4_a4 *>(p + 64 * s + off);
+        for (int b = 0; b < NB; ++b) {
+            if (ROWS) {
 #pragma unroll
-            for (int j = 0; j < 4; ++j) v[4 * s + j] = t[j];
+                for (int j = 0; j < 4; ++j) v[b][j] = *reinterpret_cast<const float *>(p + j * ld * 4 + off[b]);
+            } else {
+                const f32x4_a4 t = *reinterpret_cast<const f32x4_a4 *>(p + off[b]);
+#pragma unroll
+                for (int j = 0; j < 4; ++j) v[b][j] = t[j];
+            }
         }
-        return;
     }
-    const int left = (int)(n_k - k0) - 4 * q;                         // elements of the lane's row from its first on
-#pragma unroll
-    for (int s = 0; s < 2; ++s)
+    // the elements of a chunk that are among the contraction's n_k, zeros for the others
+    __device__ inline void load_part(int64_t k0, int64_t n_k, float (*v)[4]) const
+    {
+        const char *p = reinterpret_cast<const char *>(ROWS ? base + k0 * ld : base + k0);
+        const int left = (int)(n_k - k0);
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-            const int e = 16 * s + j;
-            const float t = *reinterpret_cast<const float *>(p + (int64_t)off + 4 * (e < left ? e : -4 * q));   // past the end: the row's first, not used
-            v[4 * s + j] = e < left ? t : 0.f;
+            const bool in = own_k() + j < left;
+            const int step = (in ? j : -own_k()) * (ROWS ? (int)ld : 1);      // past the end: the row's first, not used
+#pragma unroll
+            for (int b = 0; b < NB; ++b) {
+                const float t = *reinterpret_cast<const float *>(p + (off[b] + (uint32_t)step * 4u));
+                v[b][j] = in ? t : 0.f;
+            }
         }
-}
-
-// k is the row index of a [n_k][ld] matrix: base = row 0; off: the lane's column, in bytes, plus 4 q rows
-__device__ inline void frag_k_rows(const float *base, uint32_t off, int64_t ld, int64_t k0, int64_t n_k, int q, float *v)
-{
-    const char *p = reinterpret_cast<const char *>(base + k0 * ld);
-    if (k0 + F32_CK <= n_k) {
-#pragma unroll
-        for (int s = 0; s < 2; ++s)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) v[4 * s + j] = *reinterpret_cast<const float *>(p + (16 * s + j) * ld * 4 + off);
-        return;
     }
-    const int left = (int)(n_k - k0) - 4 * q;
+    // from the lanes that loaded the elements to those that multiply them
+    __device__ static inline void arrange(float (*v)[4])
+    {
+        if (ROWS) return;
+        const int lane = threadIdx.x & 63, from = 4 * (4 * (lane & 15) + (lane >> 4));
 #pragma unroll
-    for (int s = 0; s < 2; ++s)
+        for (int b = 0; b < NB; ++b)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int e = 16 * s + j;
-            const float t = *reinterpret_cast<const float *>(p + (int64_t)off + (e < left ? e : -4 * q) * ld * 4);
-            v[4 * s + j] = e < left ? t : 0.f;
-        }
-}
+            for (int j = 0; j < 4; ++j) v[b][j] = __int_as_float(__builtin_amdgcn_ds_bpermute(from, __float_as_int(v[b][j])));
+    }
+};
 
 template <int RB, int CB>
-__device__ inline void multiply_chunk(const float (*a)[8], const float (*b)[8], f64x4 (*acc)[CB])
+__device__ inline void multiply_chunk(const float (*a)[4], const float (*b)[4], f64x4 (*acc)[CB])
 {
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
+    for (int e = 0; e < 4; ++e) {
         double bd[CB];
 #pragma unroll
         for (int cb = 0; cb < CB; ++cb) bd[cb] = (double)b[cb][e];
@@ -80,7 +90,7 @@ __device__ inline void multiply_chunk(const float (*a)[8], const float (*b)[8], 
 
 // In front of the first vector-ALU read of a matrix instruction's sums.  The compiler pads that distance itself, but not where
 // the two meet at a join of branches: a loop that kept its sums in accumulation registers read the last of them one instruction
-// behind the product (seen in its assembly; rows 12 to 15 of a tile were wrong).  The kernels below are therefore bounded to two
+// behind the product (seen in its assembly; rows 12 to 15 of a tile were wrong).  The kernels below are therefore bounded to four
 // waves per SIMD, at which the compiler leaves the sums in vector registers (build.py refuses anything else), and wait here.
 template <int RB, int CB> __device__ inline void settle(f64x4 (*acc)[CB])
 {
@@ -90,30 +100,61 @@ template <int RB, int CB> __device__ inline void settle(f64x4 (*acc)[CB])
         for (int cb = 0; cb < CB; ++cb) asm volatile("s_nop 15\n\ts_nop 7" : "+v"(acc[rb][cb]));
 }
 
-// Chunks first, first + step, ... of a contraction with n_k elements; load_a(k0, a) and load_b(k0, b) fetch the operands
-// of a chunk.  The next chunk is requested before the current one is multiplied.
-template <int RB, int CB, class LA, class LB>
-__device__ inline void contract(int first, int step, int64_t n_k, const LA &load_a, const LB &load_b, f64x4 (*acc)[CB])
+// The pairs of chunks first, first + step, ... (a pair is a line of 128 bytes where k is contiguous) of a contraction with n_k
+// elements.  DEPTH chunks are held, so DEPTH - 1 are in flight while one is multiplied; behind the last one the last is
+// requested again: a request under a condition would make every wait one for all that is in flight.  A last chunk that is not
+// whole starts earlier and leaves out what the chunk before it held.
+template <int RB, int CB, int DEPTH, class OA, class OB>
+__device__ inline void contract(int first, int step, int64_t n_k, const OA &oa, const OB &ob, f64x4 (*acc)[CB])
 {
-    const int n_chunks = (int)((n_k + F32_CK - 1) / F32_CK);
-    if (first >= n_chunks) return;
-    float a[RB][8], b[CB][8], an[RB][8], bn[CB][8];
-    load_a((int64_t)first * F32_CK, a);
-    load_b((int64_t)first * F32_CK, b);
-    for (int c = first; c < n_chunks; c += step) {
-        const bool more = c + step < n_chunks;
-        if (more) {
-            load_a((int64_t)(c + step) * F32_CK, an);
-            load_b((int64_t)(c + step) * F32_CK, bn);
-        }
-        multiply_chunk<RB, CB>(a, b, acc);
-        if (more) {
+    const int q = (threadIdx.x & 63) >> 4;
+    float a[DEPTH][RB][4], b[DEPTH][CB][4];
+    if (n_k < F32_CK) {
+        if (first != 0 || n_k <= 0) return;
+        oa.load_part(0, n_k, a[0]);
+        ob.load_part(0, n_k, b[0]);
+        oa.arrange(a[0]);
+        ob.arrange(b[0]);
+        multiply_chunk<RB, CB>(a[0], b[0], acc);
+        return;
+    }
+    const int n_chunks = (int)((n_k + F32_CK - 1) / F32_CK), n_pairs = (n_chunks + 1) / 2;
+    if (first >= n_pairs) return;
+    const int own = (n_pairs - 1 - first) / step;                     // pairs of this wave behind its first
+    const int n = 2 * own + (2 * (first + own * step) + 1 < n_chunks ? 2 : 1);
+    auto start = [&](int i) {                                          // of the wave's chunk i
+        const int c = 2 * (first + (i >> 1) * step) + (i & 1);
+        const int64_t k0 = (int64_t)c * F32_CK, k_last = n_k - F32_CK;
+        return k0 < k_last ? k0 : k_last;
+    };
 #pragma unroll
-            for (int e = 0; e < 8; ++e) {
+    for (int u = 0; u < DEPTH - 1; ++u) {
+        const int64_t k0 = start(u < n ? u : n - 1);
+        oa.load(k0, a[u]);
+        ob.load(k0, b[u]);
+    }
+    for (int i0 = 0; i0 < n; i0 += DEPTH) {
 #pragma unroll
-                for (int rb = 0; rb < RB; ++rb) a[rb][e] = an[rb][e];
+        for (int u = 0; u < DEPTH; ++u) {
+            const int i = i0 + u, ahead = i + DEPTH - 1 < n ? i + DEPTH - 1 : n - 1;
+            const int64_t k0 = start(ahead);
+            oa.load(k0, a[(u + DEPTH - 1) % DEPTH]);
+            ob.load(k0, b[(u + DEPTH - 1) % DEPTH]);
+            if (i < n) {
+                const int c = 2 * (first + (i >> 1) * step) + (i & 1);
+                const int skip = (int)((int64_t)(c + 1) * F32_CK - n_k) - 4 * q;
+                oa.arrange(a[u]);
+                ob.arrange(b[u]);
+                if (c == n_chunks - 1) {
 #pragma unroll
-                for (int cb = 0; cb < CB; ++cb) b[cb][e] = bn[cb][e];
+                    for (int j = 0; j < 4; ++j) {
+#pragma unroll
+                        for (int rb = 0; rb < RB; ++rb) a[u][rb][j] = j < skip ? 0.f : a[u][rb][j];
+#pragma unroll
+                        for (int cb = 0; cb < CB; ++cb) b[u][cb][j] = j < skip ? 0.f : b[u][cb][j];
+                    }
+                }
+                multiply_chunk<RB, CB>(a[u], b[u], acc);
             }
         }
     }
@@ -169,20 +210,21 @@ __device__ inline void f32_lowrank_tile(const F32LowRank &job, const SegInfo &g,
     const int len = g.row1 - g.row0, r = g.r, mode = job.mode;
     if (t0 >= len || j0 >= r) return;
     const int64_t C = job.C;
-    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), i16 = lane & 15, q = lane >> 4;
-    const int t = t0 + i16 < len ? t0 + i16 : len - 1;              // clamped rows and columns are not stored
-    const int j = j0 + i16 < r ? j0 + i16 : r - 1;
-    const float *rows = job.S + (int64_t)(g.row0 + t0) * C;
-    const uint32_t off_x = ((uint32_t)(t - t0) * (uint32_t)C + 4 * q) * 4u;       // 15 rows of at most 2^22 elements
-    const uint32_t off_m = mode == 0 ? ((uint32_t)(4 * q * r) + (uint32_t)j) * 4u : ((uint32_t)(j - j0) * (uint32_t)C + 4 * q) * 4u;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     f64x4 acc[1][1];
     clear<1, 1>(acc);
-    auto load_a = [&](int64_t k0, float (*v)[8]) { frag_k_contiguous(rows, off_x, k0, C, q, v[0]); };
-    auto load_b = [&](int64_t k0, float (*v)[8]) {
-        if (mode == 0) frag_k_rows(M, off_m, r, k0, C, q, v[0]);
-        else frag_k_contiguous(M + (int64_t)j0 * C, off_m, k0, C, q, v[0]);
-    };
-    contract<1, 1>(wave, F32_NW, C, load_a, load_b, acc);
+    auto clamped = [](int i, int n) { return i < n ? i : n - 1; };   // rows and columns past the end are not stored
+    F32Operand<false, 1> rows{job.S + (int64_t)(g.row0 + t0) * C, C, {}};
+    rows.row(0, clamped(rows.own_row(), len - t0));
+    if (mode == 0) {
+        F32Operand<true, 1> m{M + j0, r, {}};
+        m.row(0, clamped(m.own_row(), r - j0));
+        contract<1, 1, 6>(wave, F32_NW, C, rows, m, acc);
+    } else {
+        F32Operand<false, 1> m{M + (int64_t)j0 * C, C, {}};
+        m.row(0, clamped(m.own_row(), r - j0));
+        contract<1, 1, 6>(wave, F32_NW, C, rows, m, acc);
+    }
     const double mult = mode == 0 ? 1.0 : (double)scale;
     sum_waves<1, 1, F32_NW>(acc, lds, [&](int rr, int cc, double v) {
         if (t0 + rr < len && j0 + cc < r) job.out[g.h_off + (int64_t)(t0 + rr) * r + j0 + cc] = (float)(v * mult);

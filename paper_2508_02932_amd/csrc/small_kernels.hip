@@ -615,7 +615,7 @@ __global__ void __launch_bounds__(256, NB == 8 ? 3 : 4) k_prep_short(DescChunk c
 
 // The fp32 path: its low-rank products of any size (16 tokens x 16 ranks per workgroup; they are a small part of a call).
 struct PrepF32 { F32LowRank j[kPrepShort]; };
-__global__ void __launch_bounds__(256, 2) k_prep_f32(DescChunk c, PrepArgs pa, PrepF32 fj, int n_units, int tiles_j, int n_prep)
+__global__ void __launch_bounds__(256, 4) k_prep_f32(DescChunk c, PrepArgs pa, PrepF32 fj, int n_units, int tiles_j, int n_prep)
 {
     extern __shared__ __attribute__((aligned(16))) char prep_lds[];
     const DescReader<WordsInArg> in{WordsInArg{c.w}};

@@ -1,4 +1,4 @@
-"""The fp32 path at the edges of its tiles (16 and 32 rows, 32 columns, 32 contraction elements, 32 ranks): sizes one below
+"""The fp32 path at the edges of its tiles (16 and 32 rows, 32 columns, 16 and 32 contraction elements, 16 ranks): sizes one below
 and above them, rows that are not 16-byte aligned, ranks from 1 to 128, segments shorter than a tile, both weight orders,
 against the fp64 oracle.  Tolerance 1e-5 as for every fp32 call (sums are in fp64, results rounded to fp32: 6e-8)."""
 import pytest
@@ -26,6 +26,25 @@ def test_f32_tile_edges(case, save_h, w_layout):
     assert sum(lengths) == T
     lin = wl.small(f"f32_{case}", "f32", D, K, lengths=lengths, seg_adapter=owner, ranks=ranks, scales=[1.5] * len(ranks), seed=307)
     run_and_compare(lin, save_h=save_h, w_layout=w_layout)
+
+
+SIDES = {   # 16 x 16 output tiles up to 1024 of them, 32 x 32 above; contractions around one and two chunks of 16
+    "small_tiles": (512, 512, 512, [200, 312], [0, 1], [16, 9]),
+    "large_tiles": (515, 31, 530, [500, 15], [0, 1], [17, 3]),                # the last segment ends in a row tile of three rows
+    "large_forward": (700, 16, 400, [333, 0, 367], [1, 0, -1], [5, 20]),
+    "large_backward": (1040, 300, 15, [7, 1000, 33], [0, 1, 2], [48, 1, 16]),
+    "one_chunk": (530, 17, 500, [17, 513], [0, 1], [15, 16]),
+}
+
+
+@pytest.mark.parametrize("w_layout", [0, 1])
+@pytest.mark.parametrize("case", sorted(SIDES))
+def test_f32_tile_sides(case, w_layout):
+    import oracle
+    T, D, K, lengths, owner, ranks = SIDES[case]
+    lin = wl.small(f"f32_{case}", "f32", D, K, lengths=lengths, seg_adapter=owner, ranks=ranks, scales=[1.5] * len(ranks), seed=313)
+    assert lin.layout.T == T
+    run_and_compare(lin, impl=oracle.matmul, w_layout=w_layout)
 
 
 def test_f32_infinity_stays_in_its_own_rows():
