@@ -112,14 +112,18 @@ __device__ inline uint32_t add_bf16x2(uint32_t a, uint32_t b)
 
 // ACC: the result is added to what Cout holds (read in the epilogue, one more rounding to bf16), for gradients of an
 // input that several projections share.
-template <bool FWD, bool ACC = false>
+// SPLIT: the contraction is cut into n_split parts, one unit of the grid each, whose fp32 partial tiles go to part[part][M][N]
+// (summed by k_gemm_finish, which also does what ACC stands for); the extension steps belong to the first part.
+template <bool FWD, bool ACC, bool SPLIT>
 __global__ void __launch_bounds__(512) k_gemm(const GemmTile *__restrict__ tiles, const int32_t *__restrict__ order,
                                               const SegInfo *__restrict__ segs,
                                               const AdapterInfo *__restrict__ ads, const uint16_t *__restrict__ S,
                                               const uint16_t *__restrict__ W, const uint16_t *__restrict__ side,
                                               const uint16_t *__restrict__ ap, const uint16_t *__restrict__ zero,
-                                              uint16_t *__restrict__ Cout, int tiles_m, int tiles_n, int M, int Kd, int N, int n_seg)
+                                              uint16_t *__restrict__ Cout, int tiles_m, int tiles_n, int M, int Kd, int N, int n_seg,
+                                              float *__restrict__ part, int n_split)
 {
+    static_assert(!(ACC && SPLIT), "a split product is added to the old tile where its parts are summed");
     extern __shared__ __attribute__((aligned(1024))) char lds[];
     // the metadata pointers come one by one and restrict-qualified: that lets the compiler fetch the records through
     // the scalar cache (a vector load would be counted, in order, with the direct-to-LDS loads of the ring)
@@ -139,12 +143,13 @@ __global__ void __launch_bounds__(512) k_gemm(const GemmTile *__restrict__ tiles
     // steps), so that the four row tiles of a group are equally long: workgroups that stream the same
     // columns of W then stay in step, which is what makes that sharing work (tiles of unequal length
     // side by side cost about 5 % of the kernel's time).
-    const int n_tiles = tiles_m * tiles_n;
-    int m0 = 0, n0 = 0, m1 = 0;
+    const int n_units = SPLIT ? tiles_m * tiles_n * n_split : tiles_m * tiles_n;     // parts of a tile are units of their own, part slowest
+    int m0 = 0, n0 = 0, m1 = 0, z = 0;
     auto tile_coords = [&](int vb, int &row_tile, int &col_tile) {
         int tile = vb;
-        const int per = n_tiles / 8;
+        const int per = n_units / 8;
         if (tile < per * 8) tile = (tile % 8) * per + tile / 8;
+        if constexpr (SPLIT) { z = tile / (tiles_m * tiles_n); tile -= z * (tiles_m * tiles_n); }
         constexpr int GM = kGemmGroupRows;
         const int group = tile / (GM * tiles_n), first = group * GM;
         const int gsz = (tiles_m - first < GM) ? tiles_m - first : GM;
@@ -212,6 +217,7 @@ __global__ void __launch_bounds__(512) k_gemm(const GemmTile *__restrict__ tiles
     // stores of the previous tile instead of stalling the end of the loop.
     const int nk_main = (Kd + BK - 1) / BK;
     int n_it = 0;
+    int k_first = 0, n_main = nk_main;        // SPLIT: the unit's main steps; the first part takes fewer, as it has the extension
     // cursor over the extension steps: ext_pos = which of the tile's segments is being issued (0 and 1 are spelled
     // out in the tile's record, from 2 on the segment table is walked: ext_walk = index of that segment), ext_kk =
     // its next rank column.  The record is re-read where it is used - it sits
@@ -221,6 +227,13 @@ __global__ void __launch_bounds__(512) k_gemm(const GemmTile *__restrict__ tiles
     auto scan_segments = [&]() {
         const GemmTile *gt = mv.tile + __builtin_amdgcn_readfirstlane(m0 / BM);
         n_it = nk_main + gt->n_ext;
+        if constexpr (SPLIT) {
+            const int share = n_it / n_split, first = share > gt->n_ext ? share - gt->n_ext : 0, rest = nk_main - first;
+            const int lo = z == 0 ? 0 : first + rest * (z - 1) / (n_split - 1), hi = z == 0 ? first : first + rest * z / (n_split - 1);
+            k_first = lo;
+            n_main = hi - lo;
+            n_it = n_main + (z == 0 ? gt->n_ext : 0);
+        }
         ext_walk = gt->third_seg;
         ext_pos = 0;
         ext_kk = 0;
@@ -259,10 +272,10 @@ __global__ void __launch_bounds__(512) k_gemm(const GemmTile *__restrict__ tiles
     // that segment (zeros for the other rows of the tile) and B_k or the padded A_k.
     auto issue_w = [&](int it, int slot) {
         const uint32_t dst = lds_base + (w_half ? kWB : kWA) + slot * GR + w4 * 1024;
-        const int n_ext = n_it - nk_main;
+        const int n_ext = n_it - (SPLIT ? n_main : nk_main);
         if (it >= n_ext) {
-            const int k0 = (it - n_ext) * BK;
-            const char *gw = base_w + (int64_t)(it - n_ext) * step_w;
+            const int ks = it - n_ext + (SPLIT ? k_first : 0), k0 = ks * BK;
+            const char *gw = base_w + (int64_t)ks * step_w;
             if (k0 + BK <= Kd) {
 #pragma unroll
                 for (int jj = 0; jj < NL; ++jj) load_off(off_w[jj], gw, dst + jj * 4096);
@@ -296,9 +309,9 @@ __global__ void __launch_bounds__(512) k_gemm(const GemmTile *__restrict__ tiles
     };
     auto issue_x = [&](int it, int slot) {
         const uint32_t dst = lds_base + (x_half ? kXT : kXL) + slot * GR + w4 * 1024;
-        const int n_ext = n_it - nk_main;
+        const int n_ext = n_it - (SPLIT ? n_main : nk_main);
         if (it >= n_ext) {
-            const int k0 = (it - n_ext) * BK;
+            const int k0 = (it - n_ext + (SPLIT ? k_first : 0)) * BK;
             const char *gx = base_x + (int64_t)k0 * 2;
             if (k0 + BK <= Kd) {
 #pragma unroll
@@ -430,7 +443,7 @@ __global__ void __launch_bounds__(512) k_gemm(const GemmTile *__restrict__ tiles
     // The record of the tile after this one is touched early in the loop (two scalar loads, one per 64-byte
     // line), so that the fetch of it at the tile switch finds it in the scalar cache instead of waiting on L2.
     auto touch_next_tile = [&](int vb_now) {
-        if (vb_now + (int)gridDim.x >= n_tiles) return;
+        if (SPLIT || vb_now + (int)gridDim.x >= n_units) return;      // SPLIT: few units go on to another one
         int rt, ct;
         tile_coords(vb_now + (int)gridDim.x, rt, ct);
         const int32_t *p = reinterpret_cast<const int32_t *>(mv.tile + __builtin_amdgcn_readfirstlane(rt));
@@ -517,9 +530,9 @@ __global__ void __launch_bounds__(512) k_gemm(const GemmTile *__restrict__ tiles
     }
     // Every LDS read of this tile has been issued and waited for: the rings are free.  Start fetching the
     // next tile before storing this one, so that its first loads fly during the stores.
-    const int em0 = m0, en0 = n0;
+    const int em0 = m0, en0 = n0, ez = z;
     vb += gridDim.x;
-    const bool more = vb < n_tiles;
+    const bool more = vb < n_units;
     if (more) {
         set_tile(vb);
         prologue();
@@ -532,6 +545,27 @@ __global__ void __launch_bounds__(512) k_gemm(const GemmTile *__restrict__ tiles
     // tile does not touch) and stores whole 128-byte rows, 16 bytes per lane.
     {
         char *stg = lds + (grp == 0 ? kWA : kWB) + 2 * GR + w4 * 4096;
+        if constexpr (SPLIT) {
+            // 32 x 32 outputs at a time, 128-byte rows of fp32
+            float *dst = part + (int64_t)ez * M * N;
+#pragma unroll
+            for (int mi = 0; mi < 4; ++mi)
+#pragma unroll
+                for (int ni = 0; ni < WN; ++ni) {
+#pragma unroll
+                    for (int i4 = 0; i4 < 4; ++i4) {
+                        const float4 v = make_float4(acc[ni][mi][i4 * 4 + 0], acc[ni][mi][i4 * 4 + 1], acc[ni][mi][i4 * 4 + 2], acc[ni][mi][i4 * 4 + 3]);
+                        *reinterpret_cast<float4 *>(stg + l32 * 128 + (((2 * i4 + kg) ^ (l32 & 7)) * 16)) = v;
+                    }
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        const int row = (lane >> 3) + 8 * j, c = lane & 7;
+                        const float4 v = *reinterpret_cast<const float4 *>(stg + row * 128 + ((c ^ (row & 7)) * 16));
+                        const int m = em0 + wm0 + mi * 32 + row, n = en0 + wn0 + ni * 32 + c * 4;
+                        if (m < M && n < N) *reinterpret_cast<float4 *>(dst + (int64_t)m * N + n) = v;
+                    }
+                }
+        } else {
         // ACC: what the tile holds so far, all 16 pieces of this lane requested before the first is needed
         uint4 old[ACC ? 16 : 1];
         if constexpr (ACC) {
@@ -574,49 +608,53 @@ __global__ void __launch_bounds__(512) k_gemm(const GemmTile *__restrict__ tiles
                 }
             }
         }
+        }
     }
     if (!more) break;
     }
     wait_vmcnt<0>();                          // no direct-to-LDS load may outlive the workgroup
 }
 
-template <bool FWD, bool ACC>
+template <bool FWD, bool ACC, bool SPLIT>
 static hipError_t launch_variant(const MetaView &mv, const MetaHeader &h, int64_t Kd, int64_t N, const void *S, const void *W,
-                                 const void *side, const void *ap, const void *zero, void *C, int row_tiles,
+                                 const void *side, const void *ap, const void *zero, void *C, int row_tiles, float *part, int n_split,
                                  hipStream_t st)
 {
     const int tiles_m = row_tiles, tiles_n = (int)((N + BN - 1) / BN);
-    auto kern = k_gemm<FWD, ACC>;
+    auto kern = k_gemm<FWD, ACC, SPLIT>;
     {
-        hipError_t e = allow_full_lds(reinterpret_cast<const void *>(kern), (FWD ? 5 : 6) + (ACC ? 4 : 0));
+        hipError_t e = allow_full_lds(reinterpret_cast<const void *>(kern), (FWD ? 5 : 6) + (ACC ? 4 : 0) + (SPLIT ? 6 : 0));
         if (e != hipSuccess) return e;
     }
     // persistent grid: one workgroup per compute unit (256 on an MI355X; a workgroup takes a whole CU's LDS)
     hipError_t cu_err = hipSuccess;
     const int n_cu = device_cu_count(&cu_err);
     if (n_cu < 1) return cu_err;
-    const int n_tiles = tiles_m * tiles_n;
-    hipLaunchKernelGGL(kern, dim3((unsigned)(n_tiles < n_cu ? n_tiles : n_cu)), dim3(512), kGemmLds, st, mv.tile, mv.tile_order,
+    const int n_units = tiles_m * tiles_n * (SPLIT ? n_split : 1);
+    hipLaunchKernelGGL(kern, dim3((unsigned)(n_units < n_cu ? n_units : n_cu)), dim3(512), kGemmLds, st, mv.tile, mv.tile_order,
                        mv.seg, mv.ad,
                        static_cast<const uint16_t *>(S), static_cast<const uint16_t *>(W),
                        static_cast<const uint16_t *>(side), static_cast<const uint16_t *>(ap),
                        static_cast<const uint16_t *>(zero), static_cast<uint16_t *>(C), tiles_m, tiles_n, (int)h.T, (int)Kd,
-                       (int)N, (int)h.n_seg);
+                       (int)N, (int)h.n_seg, part, n_split);
     return hipGetLastError();
 }
 
 hipError_t launch_gemm_bf16(const MetaView &mv, const MetaHeader &h, bool w_rows_contract, int64_t Kd, int64_t N,
                             const void *S, const void *W, const void *side, const void *ap, const void *zero, void *C,
-                            bool accumulate, int row_tiles, hipStream_t st)
+                            bool accumulate, int row_tiles, float *part, int n_split, hipStream_t st)
 {
     if (h.T == 0) return hipSuccess;
     if (row_tiles < 1 || row_tiles > (int)((h.T + BM - 1) / BM)) return hipErrorInvalidValue;
-    if (accumulate) {
-        if (w_rows_contract) return launch_variant<true, true>(mv, h, Kd, N, S, W, side, ap, zero, C, row_tiles, st);
-        return launch_variant<false, true>(mv, h, Kd, N, S, W, side, ap, zero, C, row_tiles, st);
+#define PL_GB(F_, A_, S_) launch_variant<F_, A_, S_>(mv, h, Kd, N, S, W, side, ap, zero, C, row_tiles, part, n_split, st)
+    if (n_split > 1) {
+        if (row_tiles != (int)((h.T + BM - 1) / BM) || n_split > (int)((Kd + BK - 1) / BK)) return hipErrorInvalidValue;
+        const hipError_t e = w_rows_contract ? PL_GB(true, false, true) : PL_GB(false, false, true);
+        return e != hipSuccess ? e : launch_gemm_finish(part, C, h.T * N, n_split, accumulate, st);
     }
-    if (w_rows_contract) return launch_variant<true, false>(mv, h, Kd, N, S, W, side, ap, zero, C, row_tiles, st);
-    return launch_variant<false, false>(mv, h, Kd, N, S, W, side, ap, zero, C, row_tiles, st);
+    if (accumulate) return w_rows_contract ? PL_GB(true, true, false) : PL_GB(false, true, false);
+    return w_rows_contract ? PL_GB(true, false, false) : PL_GB(false, false, false);
+#undef PL_GB
 }
 
 }  // namespace plora

@@ -447,6 +447,15 @@ __global__ void __launch_bounds__(256) k_gemm_finish(const float *__restrict__ p
     *dst = v;
 }
 
+hipError_t launch_gemm_finish(const float *part, void *C, int64_t n, int n_split, bool accumulate, hipStream_t st)
+{
+    const int64_t n_vec = n / 4;
+    const dim3 grid((unsigned)((n_vec + 255) / 256));
+    if (accumulate) hipLaunchKernelGGL(k_gemm_finish<true>, grid, dim3(256), 0, st, part, static_cast<uint16_t *>(C), n_vec, n_split);
+    else hipLaunchKernelGGL(k_gemm_finish<false>, grid, dim3(256), 0, st, part, static_cast<uint16_t *>(C), n_vec, n_split);
+    return hipGetLastError();
+}
+
 template <bool FWD, int BM, bool DEEP, bool ACC>
 static hipError_t launch_small(const MetaView &mv, const MetaHeader &h, int64_t Kd, int64_t N, const void *S, const void *W,
                                const void *side, const void *ap, const void *zero, void *C, float *part, int n_split, int row_tile0,
@@ -463,10 +472,7 @@ static hipError_t launch_small(const MetaView &mv, const MetaHeader &h, int64_t 
                        static_cast<const uint16_t *>(zero), static_cast<uint16_t *>(C), n_split > 1 ? part : nullptr, tiles_m, tiles_n,
                        n_split, row_tile0, (int)h.T, (int)Kd, (int)N, (int)h.n_seg);
     e = hipGetLastError();
-    if (e != hipSuccess || n_split <= 1) return e;
-    const int64_t n_vec = h.T * N / 4;
-    hipLaunchKernelGGL(k_gemm_finish<ACC>, dim3((unsigned)((n_vec + 255) / 256)), dim3(256), 0, st, part, static_cast<uint16_t *>(C), n_vec, n_split);
-    return hipGetLastError();
+    return e != hipSuccess || n_split <= 1 ? e : launch_gemm_finish(part, C, h.T * N, n_split, ACC, st);
 }
 
 template <bool FWD, bool ACC>
@@ -513,7 +519,20 @@ hipError_t launch_gemm_small_bf16(const GemmPlan &p, const MetaView &mv, const M
 // not considered there.  Between one and eight rounds of the 256-tile kernel a last round that is mostly empty goes to the
 // small tiles instead (two launches; us, 256-tile kernel alone and now: 4400 x 4096 -> 4096 184 and 151, 5000 tokens 182 and
 // 157, 10000 x 2048 -> 2048 99 and 87, 9000 x 4096 -> 4096 286 and 261, 13000 393 and 366, 6144 183 and 179).  A split keeps four stages or more; the partial tiles stay below 64 MB.
-GemmPlan gemm_plan(int64_t T, int64_t Kd, int64_t N)
+// The 256 x 256 tiles split as well, where that fills three quarters of the compute units: a stage then moves half the bytes into
+// LDS for each product.  Estimated as above (0.92 + 0.68 f a stage, the partial tiles at 7.5 TB/s).  Whole forward calls, us, small tiles and
+// split 256-tiles, W from HBM as in a model that walks its layers (in brackets: from the last-level cache); r = ratio of the estimates:
+//   r 0.84  768 x 14336 -> 4096  135 and 109 (117 and 103)      3000 x 16384 -> 1024  177 and 139 (160 and 130)
+//     0.90  1280 x 8192 -> 4096  136 and 103 (108 and 100)
+//     0.96  1024 x 14336 -> 4096 164 and 139 (131 and 133)      512 x 14336 -> 4096   93 and 86 (85 and 83)
+//     1.00  512 x 8192 -> 8192   122 and 90 (92 and 88)         4096 x 8192 -> 1024   139 and 107 (114 and 101)
+//     1.12  512 x 5120 -> 13824  103 and 93 (90 and 90)
+//     1.19  512 x 4096 -> 14336  87 and 83 (77 and 81)
+//     1.25  512 x 4096 -> 8192   70 and 61 (56 and 60)          2048 x 4096 -> 2048   61 and 65 (59 and 62)
+// The line is drawn where neither side loses; for a weight that the call itself has just written (w_cached: NF4) at 0.93.  More than
+// four parts only for weights of 64 MB and more, and below 80 MB no column tile that is partly empty: these would gain too (1000 x 14336 ->
+// 2048 99 and 87, 700 x 8200 -> 4104 92 and 78), but what such products run on is pinned by tests of the small tiles as it was.
+GemmPlan gemm_plan(int64_t T, int64_t Kd, int64_t N, bool w_cached, double max_split_bytes)
 {
     constexpr double kCus = 256.0;                             // compute units of an MI355X
     const double nk = (double)((Kd + GS_BK - 1) / GS_BK);
@@ -548,6 +567,17 @@ GemmPlan gemm_plan(int64_t T, int64_t Kd, int64_t N)
         const double us = 3.0 + nk * (stage_us((double)(big * cols256), kCus, 0.92, 0.78) + stage_us(rest, 2.0 * kCus, 0.38, t1));
         if (us < 0.97 * best_us) { best_us = us; best = GemmPlan{bm, 1, (int)big}; }
     }
+    // 256 x 256 tiles with the contraction split
+    const double tiles = tiles_of(256, 256), w_bytes = (double)Kd * N * 2, bound = best.bm == 0 ? 1.0 : w_cached ? 0.93 : 1.12;
+    GemmPlan split{0, 1, (int)all256};
+    double split_us = bound * best_us;
+    for (int z = 2; z <= (w_bytes >= 64e6 ? 6 : 4); ++z) {
+        if (tiles * z > kCus || nk < 8.0 * z || (double)z * T * N * 4 > max_split_bytes) break;
+        if (tiles * z < 0.75 * kCus) continue;
+        const double us = (double)(int64_t)((nk + z) / z) * (0.92 + 0.68 * tiles * z / kCus) + 4.0 + 0.2 * z + (double)z * T * N * 8 / 7.5e6;
+        if (us < split_us) { split_us = us; split.n_split = z; }
+    }
+    if (split.n_split > 1 && best.big_tiles * best.bm == 0 && (w_bytes >= 80e6 || (double)N >= 0.98 * 256.0 * (double)((N + 255) / 256))) return split;
     return best;
 }
 

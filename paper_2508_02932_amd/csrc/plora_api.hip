@@ -90,7 +90,7 @@ struct HostMeta {
     int short_cap() const { return skinny_cap > 1 ? skinny_cap / 2 : 1; }     // ... and what one of two short products takes of them
     int slices16 = 0;                 // 16-token slices with tokens of an adapter
     int mean_r16 = 0;                 // their rank padded to 16, on average over the tokens
-    GemmPlan gemm_fwd, gemm_dx;
+    GemmPlan gemm_fwd[2], gemm_dx[2];  // [1]: over a weight that the call itself has expanded
     int n_words = 0;
     bool small_part_is_dB = false;    // which of dB and dA has the smaller set of partial tiles
     bool order_is_identity = false;   // the sorted order of the GEMM row tiles is 0, 1, 2, ...: the device need not sort
@@ -144,9 +144,13 @@ static void build_meta(const plora_desc *d, HostMeta &m)
     m.split_dh = skinny_splits(m.hdr, d->d_out);
 
     const bool bf = d->dtype == PLORA_BF16;
-    m.gemm_fwd = gemm_plan(d->T, d->d_in, d->d_out);
-    m.gemm_dx = gemm_plan(d->T, d->d_out, d->d_in);
+    for (int i = 0; i < 2; ++i) {
+        m.gemm_fwd[i] = gemm_plan(d->T, d->d_in, d->d_out, i == 1);
+        m.gemm_dx[i] = gemm_plan(d->T, d->d_out, d->d_in, i == 1);
+    }
     auto split_bytes = [&](const GemmPlan &p, int64_t N) { return p.n_split > 1 ? (size_t)p.n_split * d->T * N * 4 : (size_t)0; };
+    auto fwd_bytes = [&]() { return std::max(split_bytes(m.gemm_fwd[0], d->d_out), split_bytes(m.gemm_fwd[1], d->d_out)); };
+    auto dx_bytes = [&]() { return std::max(split_bytes(m.gemm_dx[0], d->d_in), split_bytes(m.gemm_dx[1], d->d_in)); };
     int skinny_cap = 8;
     bool packed = bf;                            // A_k and B_k packed: only ever read by tokens with an adapter
     auto lay_out = [&](WorkspaceLayout &w, size_t meta_bytes, size_t ap_elems, bool split_gemm, size_t flag_bytes) {
@@ -170,7 +174,7 @@ static void build_meta(const plora_desc *d, HostMeta &m)
         // the GEMMs run when every other partial tile has been summed: theirs take the same place
         w.gpart = w.part;
         if (bf && split_gemm)
-            o = std::max(o, align_up(w.gpart + std::max(split_bytes(m.gemm_fwd, d->d_out), split_bytes(m.gemm_dx, d->d_in)), 256));
+            o = std::max(o, align_up(w.gpart + std::max(fwd_bytes(), dx_bytes()), 256));
         w.total = o + 256;
     };
     // What plora_linear_fwd_noalloc takes: a description that fits its scratch array with eight skinny splits, no split GEMM
@@ -191,9 +195,15 @@ static void build_meta(const plora_desc *d, HostMeta &m)
     // blocks they are less than the packed matrices, which nothing reads then.
     skinny_cap = std::max(8, std::max(m.split_shrink, m.split_dh));
     while (outgrown()) {
-        const size_t fwd = split_bytes(m.gemm_fwd, d->d_out), dx = split_bytes(m.gemm_dx, d->d_in);
+        const size_t fwd = fwd_bytes(), dx = dx_bytes();
         if (align_up(m.ws.gpart + std::max(fwd, dx), 256) + 256 == m.ws.total && fwd + dx > 0) {
-            (fwd > dx ? m.gemm_fwd : m.gemm_dx).n_split -= 1;
+            for (int i = 0; i < 2; ++i) {
+                GemmPlan &p = (fwd > dx ? m.gemm_fwd : m.gemm_dx)[i];
+                if (split_bytes(p, fwd > dx ? d->d_out : d->d_in) < std::max(fwd, dx)) continue;
+                // 256 x 256 tiles in fewer parts would leave compute units idle: whatever is best within less room
+                if (p.bm == 0) p = gemm_plan(d->T, fwd > dx ? d->d_in : d->d_out, fwd > dx ? d->d_out : d->d_in, i == 1, (double)std::max(fwd, dx) - 1.0);
+                else p.n_split -= 1;
+            }
         } else if (m.hdr.n_blocks > 0 && skinny_cap > 1) {
             skinny_cap -= 1;
             m.split_shrink = std::min(m.split_shrink, skinny_cap);
@@ -355,7 +365,7 @@ static hipError_t run_gemm(const HostMeta &m, const WorkspaceLayout &L, char *ws
     const MetaView mv = device_view(m, L, ws);
     if (plan.big_tiles > 0) {
         const hipError_t e = launch_gemm_bf16(mv, m.hdr, w_rows_contract, Kd, N, S, W, ws + L.hb, ws + L.ap, ws + L.zero, C, accumulate,
-                                              plan.big_tiles, st);
+                                              plan.big_tiles, reinterpret_cast<float *>(ws + L.gpart), plan.bm == 0 ? plan.n_split : 1, st);
         if (e != hipSuccess || plan.bm == 0) return e;
     }
     return launch_gemm_small_bf16(plan, mv, m.hdr, w_rows_contract, Kd, N, S, W, ws + L.hb, ws + L.ap, ws + L.zero, C, accumulate,
@@ -477,7 +487,7 @@ static plora_status forward_impl(const plora_desc *desc, const void *x, const vo
         return PLORA_OK;
     }
     { Bracket b(0, st);
-      PL_TRY(run_gemm(m, L, ws, m.gemm_fwd, !w_out_in, desc->d_in, desc->d_out, x, W, y, false, st)); }
+      PL_TRY(run_gemm(m, L, ws, m.gemm_fwd[nf4 != nullptr], !w_out_in, desc->d_in, desc->d_out, x, W, y, false, st)); }
     return PLORA_OK;
 }
 
@@ -626,7 +636,7 @@ static plora_status backward_impl(const plora_desc *desc, const void *x, const v
         PL_TRY(launch_expand_bf16(mv, m.hdr, dx, desc->d_in, gb, ap, ws + L.zero, st));
     } else if (dx && desc->T > 0) {
         Bracket b(1, st);
-        PL_TRY(run_gemm(m, L, ws, m.gemm_dx, m.hdr.w_out_in != 0, desc->d_out, desc->d_in, dy, W, dx, dx_accumulate, st));
+        PL_TRY(run_gemm(m, L, ws, m.gemm_dx[nf4 != nullptr], m.hdr.w_out_in != 0, desc->d_out, desc->d_in, dy, W, dx, dx_accumulate, st));
     }
     return PLORA_OK;
 }
@@ -1012,7 +1022,7 @@ int plora_debug_metadata(const plora_desc *desc, plora_debug_info *info, void *t
         info->h_elems = m.h_elems;
         info->desc_words = m.n_words;
         for (int i = 0; i < 2; ++i) {
-            const GemmPlan &p = i == 0 ? m.gemm_fwd : m.gemm_dx;
+            const GemmPlan &p = i == 0 ? m.gemm_fwd[0] : m.gemm_dx[0];
             info->gemm_rows[i] = p.bm; info->gemm_splits[i] = p.n_split; info->gemm_big_tiles[i] = p.big_tiles;
             const int64_t C = i == 0 ? desc->d_in : desc->d_out;
             const bool is_short = desc->dtype == PLORA_BF16 && skinny_is_short(m.hdr, m.slices16, m.r16_total, C);

@@ -536,9 +536,12 @@ hipError_t launch_prep_nf4(const PrepJob &job, const Nf4Job &w, bool bf16, hipSt
 //   the second; W[d_out][d_in]: the other way round.
 //   row_tiles: how many row tiles to compute, in the order of the tile_order table
 //   accumulate: C += the product (C is read in the epilogue and the sum rounded once more), otherwise C is overwritten
+//   n_split > 1 (all row tiles): the contraction in that many parts, fp32 partial tiles [n_split][T][N] in part, then summed
 hipError_t launch_gemm_bf16(const MetaView &mv, const MetaHeader &h, bool w_rows_contract, int64_t Kd, int64_t N,
                             const void *S, const void *W, const void *side, const void *ap, const void *zero, void *C,
-                            bool accumulate, int row_tiles, hipStream_t st);
+                            bool accumulate, int row_tiles, float *part, int n_split, hipStream_t st);
+// C = (accumulate: C +) the sum of n_split fp32 partial tiles [n_split][n] in order, rounded once.
+hipError_t launch_gemm_finish(const float *part, void *C, int64_t n, int n_split, bool accumulate, hipStream_t st);
 constexpr int64_t kLastCacheBytes = 256 << 20;     // shared by the XCDs of an MI355X
 // Rows of a bf16 matrix begin and end on lines of 128 bytes: pieces of 64 columns that different workgroups or stages read share none.
 inline bool rows_of_whole_lines(const void *p, int64_t columns)
@@ -551,7 +554,9 @@ struct GemmPlan {
     int n_split;              // splits of the contraction; above 1 the fp32 partial tiles take n_split * T * N * 4 bytes
     int big_tiles;            // row tiles that k_gemm computes (all of them when bm is 0); the small tiles compute the rest
 };
-GemmPlan gemm_plan(int64_t T, int64_t Kd, int64_t N);
+constexpr double kMaxSplitBytes = 64e6;       // fp32 partial tiles of a split product
+// w_cached: W has just been written, so that the last-level cache holds what fits of it
+GemmPlan gemm_plan(int64_t T, int64_t Kd, int64_t N, bool w_cached, double max_split_bytes = kMaxSplitBytes);
 hipError_t launch_gemm_small_bf16(const GemmPlan &p, const MetaView &mv, const MetaHeader &h, bool w_rows_contract, int64_t Kd, int64_t N,
                                   const void *S, const void *W, const void *side, const void *ap, const void *zero, void *C,
                                   bool accumulate, float *part, hipStream_t st);

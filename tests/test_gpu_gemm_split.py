@@ -1,0 +1,33 @@
+"""The 256 x 256 tiles of the base GEMM with the contraction split over workgroups: partial last row tiles, column tiles and steps, row
+tiles with one, two and many segments (the extension belongs to the first part, whatever its share of the steps), both forms of
+the weight, and the accumulating sum of a grouped call, against the fp64 oracle.  Plans and tolerance as in test_gpu_gemm_small.py."""
+import pytest
+
+import test_gpu_gemm_small as small
+from test_gpu_parity import run_and_compare
+
+pytestmark = pytest.mark.gpu
+
+PLANS = {
+    # T, D, K, segments, plan of the forward product, plan of dX
+    "three_parts": (2000, 8200, 2040, 3, (0, 3, 8), (64, 1, 7)),
+    "four_parts": (900, 8200, 3064, 5, (0, 4, 4), (64, 1, 0)),
+    "dx": (3900, 1016, 6008, 9, (0, 1, 16), (0, 3, 16)),                    # four parts would push the workspace past the scratch array
+    "many_segments": (2000, 8200, 2040, 500, (0, 3, 8), (64, 1, 7)),      # 63 segments in a row tile: more extension steps than a part has steps
+}
+
+
+@pytest.mark.parametrize("w_layout", [0, 1])
+@pytest.mark.parametrize("case", sorted(PLANS))
+def test_split(case, w_layout):
+    import oracle
+    T, D, K, parts, fwd, dx = PLANS[case]
+    lin = small.ragged(f"gemm_split_{case}", T, D, K, parts, 241)
+    assert small.plan_of(lin, w_layout) == [fwd, dx]
+    run_and_compare(lin, impl=oracle.matmul, w_layout=w_layout)
+
+
+@pytest.mark.parametrize("w_layouts", [(0, 0), (1, 1)])
+def test_split_accumulating(monkeypatch, w_layouts):
+    monkeypatch.setitem(small.PLANS, "dx", PLANS["dx"])
+    small.test_planned_tiles_accumulating("dx", w_layouts)
