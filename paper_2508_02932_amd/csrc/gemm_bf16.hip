@@ -623,7 +623,7 @@ static hipError_t launch_variant(const MetaView &mv, const MetaHeader &h, int64_
     const int tiles_m = row_tiles, tiles_n = (int)((N + BN - 1) / BN);
     auto kern = k_gemm<FWD, ACC, SPLIT>;
     {
-        hipError_t e = allow_full_lds(reinterpret_cast<const void *>(kern), (FWD ? 5 : 6) + (ACC ? 4 : 0) + (SPLIT ? 6 : 0));
+        hipError_t e = allow_full_lds(reinterpret_cast<const void *>(kern), (FWD ? 5 : 6) + (ACC ? 4 : 0) + (SPLIT ? 23 : 0));
         if (e != hipSuccess) return e;
     }
     // persistent grid: one workgroup per compute unit (256 on an MI355X; a workgroup takes a whole CU's LDS)
