@@ -89,6 +89,8 @@ struct HostMeta {
     int split_shrink = 1, split_dh = 1, skinny_cap = 8;   // skinny_cap: splits whose partial tiles the workspace holds
     int short_cap() const { return skinny_cap > 1 ? skinny_cap / 2 : 1; }     // ... and what one of two short products takes of them
     int slices16 = 0;                 // 16-token slices with tokens of an adapter
+    int slices_all = 0;               // the same with those of the base model alone
+    size_t fwd_parts = 0;             // forward in two launches (gemm_short_bf16.hip): bytes of the shrink's partial sums, in front of the product's; else 0
     int mean_r16 = 0;                 // their rank padded to 16, on average over the tokens
     GemmPlan gemm_fwd[2], gemm_dx[2];  // [1]: over a weight that the call itself has expanded
     int n_words = 0;
@@ -120,6 +122,7 @@ static void build_meta(const plora_desc *d, HostMeta &m)
     int64_t h = 0, hb = 0, zt = 0, at = 0, ap = 0, rows = 0, row_ranks = 0;
     for (int32_t s = 0; s < d->n_seg; ++s) {
         const SegInfo &g = m.t.seg[s];
+        m.slices_all += (g.row1 - g.row0 + 15) / 16;
         if (g.adapter < 0) continue;
         const int64_t len = g.row1 - g.row0;
         h += len * g.r; hb += len * g.rp; zt += (int64_t)g.r16 * g.lp;
@@ -228,6 +231,21 @@ static void build_meta(const plora_desc *d, HostMeta &m)
     for (int32_t k = 0; k < d->n_adapters; ++k) rp_total += m.t.ad[k].rp;
     lay_out(m.ws_lora, m.layout.bytes, (size_t)(rp_total * std::max(d->d_in, d->d_out)), false, flag_bytes);
     m.skinny_cap = skinny_cap;
+    // Forward in two launches: where the shrink is short and the base product is split anyway, or its one set of fp32 sums costs less
+    // than the launch saved.  Whole calls, us, before and now: 2048 x 1024 -> 1024 27.5 and 24.2, 512 x 1024 -> 4096 24.1 and 23.0, 384 x
+    // 2048 -> 6144 (2.4 M sums) 38.1 and 35.1, 300 x 512 -> 8192 (2.5 M) 23.6 and 22.6, 400 x 768 -> 8192 (3.3 M) 28.7 and 29.3, 1500 x 768 ->
+    // 2048 (3.1 M) 25.0 and 26.8, 2048 x 512 -> 3072 (6.3 M) 27.9 and 35.5.  Both sets of partial sums are needed at once.
+    const GemmPlan &p = m.gemm_fwd[0];
+    if (bf && m.hdr.n_blocks > 0 && m.n_words <= kChunkWords && p.bm != 0 && p.big_tiles == 0 && (p.n_split > 1 || d->T * d->d_out <= 2250000) &&
+        skinny_is_short(m.hdr, m.slices16, m.r16_total, d->d_in)) {
+        const int n = short_shares(m.hdr, m.slices16, d->d_in, m.short_cap()).n;
+        const size_t parts = align_up((size_t)n * m.slices_all * 16 * m.hdr.max_r16 * 4, 256);
+        const size_t total = align_up(m.ws.part + parts + (size_t)p.n_split * d->T * d->d_out * 4, 256) + 256;
+        if (!fits_scratch || total <= (size_t)PLORA_NOALLOC_SCRATCH_BYTES) {
+            m.fwd_parts = parts;
+            m.ws.total = std::max(m.ws.total, total);
+        }
+    }
 }
 
 // ---- metadata cache: the last few descriptions and what was derived from them ---------------------
@@ -420,10 +438,24 @@ static hipError_t launch_grads(TokcList &l, bool one_by_one, int n_adapters, con
     return hipSuccess;
 }
 
+// Forwards in two launches, launched together.
+struct ForwardList {
+    ShortForward op[kMaxGroup];
+    std::vector<uint32_t> words[kMaxGroup];
+    int n = 0;
+    void add(const ShortForward &f)
+    {
+        words[n].assign(f.desc_host, f.desc_host + f.n_words);       // the description lives in the projection's call frame
+        op[n] = f;
+        op[n].desc_host = words[n].data();
+        ++n;
+    }
+};
+
 static plora_status forward_impl(const plora_desc *desc, const void *x, const void *W, const void *const *A,
                                  const void *const *B, void *y, float *h_saved, void *workspace, size_t ws_bytes,
                                  void *hip_stream, bool lora_only = false, bool check_only = false, unsigned steps = kStepsAll,
-                                 PrepList *later = nullptr, const Nf4Job *nf4 = nullptr, SkinnyList *later_s = nullptr)
+                                 PrepList *later = nullptr, const Nf4Job *nf4 = nullptr, SkinnyList *later_s = nullptr, ForwardList *later_f = nullptr)
 {
     Call c;
     plora_status ps = prepare(desc, x, W, A, B, nullptr, nullptr, workspace, ws_bytes, lora_only, c);
@@ -444,6 +476,15 @@ static plora_status forward_impl(const plora_desc *desc, const void *x, const vo
     // stream the weight, 47 -> 57 us for the two together, and in a launch of its own it is no faster than k_skinny)
     const bool is_short = bf && lora && !nf4 && skinny_is_short(m.hdr, m.slices16, m.r16_total, desc->d_in);
     const bool brief = is_short && !later && (steps & kStepPrep) && (steps & kStepShrink) && m.n_words <= kChunkWords;
+    if (brief && !lora_only && m.fwd_parts > 0) {
+        float *h_part = reinterpret_cast<float *>(ws + L.part), *y_part = reinterpret_cast<float *>(ws + L.part + m.fwd_parts);
+        const ShortForward f{c.words, m.n_words, m.hdr, ws + L.meta, ws + L.zero, x, W, y, h_saved, h_part, y_part, m.slices_all,
+                             short_shares(m.hdr, m.slices16, desc->d_in, m.short_cap()), m.gemm_fwd[0]};
+        if (later_f) { later_f->add(f); return PLORA_OK; }
+        Bracket b(0, st);
+        PL_TRY(launch_short_forward(&f, 1, st));
+        return PLORA_OK;
+    }
     const SkinnyOperands shrink{mv, m.hdr, 0, x, desc->d_in, ws + L.at, reinterpret_cast<float *>(ws + L.part), is_short ? m.short_cap() : m.split_shrink,
                                 reinterpret_cast<unsigned long long *>(ws + L.flags), m.slices16, h_saved, ws + L.hb, nullptr, false, is_short, lora_only,
                                 m.mean_r16};
@@ -783,11 +824,20 @@ static plora_status group_forward(const plora_group *g, const void *x, const voi
     for (int p = 0; p < gp.n; ++p)
         for (int q = 0; q < gp.n; ++q)
             fused[p] = fused[p] || (q != p && gp.cell_of[q] == gp.cell_of[p] && !short_shrink(gp, p, d0) && !short_shrink(gp, q, d0));
+    // projections whose plain call takes two launches in all take those together, and no step of the group's
+    bool whole[kMaxGroup];
+    ForwardList wholes;
+    for (int p = 0; p < gp.n; ++p) {
+        whole[p] = gp.m[p]->fwd_parts > 0;
+        ps = whole[p] ? forward_impl(&g->desc[p], x, W[p], A ? A[p] : nullptr, B ? B[p] : nullptr, y[p], h_saved ? h_saved[p] : nullptr,
+                                     ws + gp.ws_off[p], gp.m[p]->ws.total, hip_stream, false, false, kStepsAll, nullptr, nullptr, nullptr, &wholes)
+                      : run(p, false, kStepPrep);
+        if (ps != PLORA_OK) return ps;
+    }
+    if (wholes.n > 0) { Bracket b(0, st); PL_TRY(launch_short_forward(wholes.op, wholes.n, st)); }
+    if (preps.n > 0) { Bracket b(6, st); PL_TRY(launch_prep(preps.job, preps.n, st)); }
     for (int p = 0; p < gp.n; ++p)
-        if ((ps = run(p, false, kStepPrep)) != PLORA_OK) return ps;
-    { Bracket b(6, st); PL_TRY(launch_prep(preps.job, preps.n, st)); }
-    for (int p = 0; p < gp.n; ++p)
-        if (!fused[p] && (ps = run(p, false, kStepShrink)) != PLORA_OK) return ps;
+        if (!fused[p] && !whole[p] && (ps = run(p, false, kStepShrink)) != PLORA_OK) return ps;
     if (shrinks.n > 0) { Bracket b(2, st); PL_TRY(launch_skinny_bf16(shrinks.op, shrinks.n, ws + gp.ws_off[0] + gp.m[0]->ws.zero, st)); }
     for (int c = 0; c < gp.n_cells; ++c) {
         int members[kMaxGroup], nm = 0;
@@ -806,7 +856,7 @@ static plora_status group_forward(const plora_group *g, const void *x, const voi
                                    reinterpret_cast<float *>(ws + gp.part_off), gp.part_bytes, gp.m[members[0]]->split_shrink, hf, hb, zt, st));
     }
     for (int p = 0; p < gp.n; ++p)
-        if ((ps = run(p, false, kStepMain)) != PLORA_OK) return ps;
+        if (!whole[p] && (ps = run(p, false, kStepMain)) != PLORA_OK) return ps;
     return PLORA_OK;
 }
 

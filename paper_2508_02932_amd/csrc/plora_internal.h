@@ -560,6 +560,22 @@ GemmPlan gemm_plan(int64_t T, int64_t Kd, int64_t N, bool w_cached, double max_s
 hipError_t launch_gemm_small_bf16(const GemmPlan &p, const MetaView &mv, const MetaHeader &h, bool w_rows_contract, int64_t Kd, int64_t N,
                                   const void *S, const void *W, const void *side, const void *ap, const void *zero, void *C,
                                   bool accumulate, float *part, hipStream_t st);
+// The forward of a short batch whose base product is split in small tiles, in two launches (gemm_short_bf16.hip).
+struct ShortForward {
+    const uint32_t *desc_host;
+    int n_words;
+    MetaHeader h;
+    char *meta_dev;
+    void *zero_dev;
+    const void *x, *W;
+    void *y;
+    float *hf;                // h to keep, or null
+    float *h_part, *y_part;   // [shares.n][slices][16][max_r16], [plan.n_split][T][K]
+    int slices;               // of 16 tokens, over all segments
+    ShortShares shares;
+    GemmPlan plan;
+};
+hipError_t launch_short_forward(const ShortForward *ops, int n, hipStream_t st);      // one call, or projections of a group
 // Stand-alone low-rank update C[T][N] += side * op_k (bf16, one rounding): side = bf16 low-rank factor [len][rp] per
 // segment, opT = padded small matrices [N][rp], one behind the other.
 hipError_t launch_expand_bf16(const MetaView &mv, const MetaHeader &h, void *C, int64_t N, const void *side, const void *opT,

@@ -97,8 +97,9 @@ __host__ __device__ inline size_t short_lds_bytes(int r16) { return (size_t)SH_N
 
 // g, scale: the slice's segment; t0: its first token inside the segment; unit: index of the slice; small: B_k (mode 1: [r][C]),
 // A_k as it is (mode 0, natural: [C][r]) or packed (mode 0: [r16][C]).
-template <int NB>
-__device__ inline void skinny_short(const ShortJob &job, const SegInfo &g, float scale, int t0, int unit, int n_units, int split,
+// PARTS: the sums of every share go to `part` and are added by a later launch.
+template <int NB, bool PARTS = false>
+__device__ __forceinline__ void skinny_short(const ShortJob &job, const SegInfo &g, float scale, int t0, int unit, int n_units, int split,
                                     const uint16_t *small, bool natural, char *lds)
 {
     float *red = reinterpret_cast<float *>(lds);                      // [SH_NW][16][r16]
@@ -119,8 +120,8 @@ __device__ inline void skinny_short(const ShortJob &job, const SegInfo &g, float
     const int c_hi = c_lo + job.per < n_chunks ? c_lo + job.per : n_chunks;
     const sh_bf16x8 none = {};
     char *slab = lds + wave * (64 * r16);                             // the wave's 32 rows of A_k
-    // H: half chunks (32 elements) of a wave in flight together
-    constexpr int H = NB <= 1 ? 8 : NB <= 2 ? 4 : NB <= 4 ? 2 : 1;
+    // H: half chunks (32 elements) of a wave in flight together (PARTS: beside a product that leaves twice the registers)
+    constexpr int H = (NB <= 1 ? 8 : NB <= 2 ? 4 : NB <= 4 ? 2 : 1) * (PARTS && NB > 1 ? 2 : 1);
     const int n_half = c_hi > c_lo + wave ? ((c_hi - c_lo - wave - 1) / SH_NW + 1) * 2 : 0;     // of this wave
     for (int h0 = 0; h0 < n_half; h0 += H) {
         sh_bf16x8 xf[H], bf[H][NB];
@@ -198,9 +199,11 @@ __device__ inline void skinny_short(const ShortJob &job, const SegInfo &g, float
         sh_f32x4 v = red4[e];
 #pragma unroll
         for (int w = 1; w < SH_NW; ++w) v += red4[w * n_vec + e];
-        if (job.n_split > 1) store_agent(part4 + split * stride + e, v);
+        if constexpr (PARTS) part4[split * stride + e] = v;
+        else if (job.n_split > 1) store_agent(part4 + split * stride + e, v);
         else red4[e] = v;
     }
+    if constexpr (PARTS) return;
     if (job.n_split > 1) {
         wait_memory();
         __syncthreads();
