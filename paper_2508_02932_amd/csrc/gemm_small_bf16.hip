@@ -11,6 +11,8 @@
 // 4 and 6 stages and 256 x 128 tiles of eight waves were all no faster, and stages of 32 (64-byte pieces of rows) 20 % slower.
 #include "gemm_small.h"
 
+#include <algorithm>
+
 namespace plora {
 
 template <bool FWD, int BM, bool DEEP, bool ACC>
@@ -133,7 +135,7 @@ hipError_t launch_gemm_small_bf16(const GemmPlan &p, const MetaView &mv, const M
 // The line is drawn where neither side loses; for a weight that the call itself has just written (w_cached: NF4) at 0.93.  More than
 // four parts only for weights of 64 MB and more, and below 80 MB no column tile that is partly empty: these would gain too (1000 x 14336 ->
 // 2048 99 and 87, 700 x 8200 -> 4104 92 and 78), but what such products run on is pinned by tests of the small tiles as it was.
-GemmPlan gemm_plan(int64_t T, int64_t Kd, int64_t N, bool w_cached, double max_split_bytes)
+GemmPlan gemm_plan(int64_t T, int64_t Kd, int64_t N, int max_ext, bool w_cached, double max_split_bytes)
 {
     constexpr double kCus = 256.0;                             // compute units of an MI355X
     const double nk = (double)((Kd + GS_BK - 1) / GS_BK);
@@ -175,7 +177,10 @@ GemmPlan gemm_plan(int64_t T, int64_t Kd, int64_t N, bool w_cached, double max_s
     for (int z = 2; z <= (w_bytes >= 64e6 ? 6 : 4); ++z) {
         if (tiles * z > kCus || nk < 8.0 * z || (double)z * T * N * 4 > max_split_bytes) break;
         if (tiles * z < 0.75 * kCus) continue;
-        const double us = (double)(int64_t)((nk + z) / z) * (0.92 + 0.68 * tiles * z / kCus) + 4.0 + 0.2 * z + (double)z * T * N * 8 / 7.5e6;
+        // the first part has all extension steps: with more of them than a part has steps (many short segments) it runs longer.
+        // 88 tokens of 29 adapters, 4480 -> 9984: 29 steps against 12, 38 us in small tiles and 83
+        const double steps = std::max((double)(int64_t)((nk + z) / z), (double)max_ext);
+        const double us = steps * (0.92 + 0.68 * tiles * z / kCus) + 4.0 + 0.2 * z + (double)z * T * N * 8 / 7.5e6;
         if (us < split_us) { split_us = us; split.n_split = z; }
     }
     if (split.n_split > 1 && best.big_tiles * best.bm == 0 && (w_bytes >= 80e6 || (double)N >= 0.98 * 256.0 * (double)((N + 255) / 256))) return split;

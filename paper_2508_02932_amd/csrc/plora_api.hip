@@ -147,9 +147,11 @@ static void build_meta(const plora_desc *d, HostMeta &m)
     m.split_dh = skinny_splits(m.hdr, d->d_out);
 
     const bool bf = d->dtype == PLORA_BF16;
+    int max_ext = 0;
+    for (int64_t i = 0; i < m.layout.n_tiles; ++i) max_ext = std::max(max_ext, (int)m.t.tile[i].n_ext);
     for (int i = 0; i < 2; ++i) {
-        m.gemm_fwd[i] = gemm_plan(d->T, d->d_in, d->d_out, i == 1);
-        m.gemm_dx[i] = gemm_plan(d->T, d->d_out, d->d_in, i == 1);
+        m.gemm_fwd[i] = gemm_plan(d->T, d->d_in, d->d_out, max_ext, i == 1);
+        m.gemm_dx[i] = gemm_plan(d->T, d->d_out, d->d_in, max_ext, i == 1);
     }
     auto split_bytes = [&](const GemmPlan &p, int64_t N) { return p.n_split > 1 ? (size_t)p.n_split * d->T * N * 4 : (size_t)0; };
     auto fwd_bytes = [&]() { return std::max(split_bytes(m.gemm_fwd[0], d->d_out), split_bytes(m.gemm_fwd[1], d->d_out)); };
@@ -204,7 +206,7 @@ static void build_meta(const plora_desc *d, HostMeta &m)
                 GemmPlan &p = (fwd > dx ? m.gemm_fwd : m.gemm_dx)[i];
                 if (split_bytes(p, fwd > dx ? d->d_out : d->d_in) < std::max(fwd, dx)) continue;
                 // 256 x 256 tiles in fewer parts would leave compute units idle: whatever is best within less room
-                if (p.bm == 0) p = gemm_plan(d->T, fwd > dx ? d->d_in : d->d_out, fwd > dx ? d->d_out : d->d_in, i == 1, (double)std::max(fwd, dx) - 1.0);
+                if (p.bm == 0) p = gemm_plan(d->T, fwd > dx ? d->d_in : d->d_out, fwd > dx ? d->d_out : d->d_in, max_ext, i == 1, (double)std::max(fwd, dx) - 1.0);
                 else p.n_split -= 1;
             }
         } else if (m.hdr.n_blocks > 0 && skinny_cap > 1) {

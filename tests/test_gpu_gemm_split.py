@@ -13,7 +13,8 @@ PLANS = {
     "three_parts": (2000, 8200, 2040, 3, (0, 3, 8), (64, 1, 7)),
     "four_parts": (900, 8200, 3064, 5, (0, 4, 4), (64, 1, 0)),
     "dx": (3900, 1016, 6008, 9, (0, 1, 16), (0, 3, 16)),                    # four parts would push the workspace past the scratch array
-    "many_segments": (2000, 8200, 2040, 500, (0, 3, 8), (64, 1, 7)),      # 63 segments in a row tile: more extension steps than a part has steps
+    "many_segments": (2000, 8200, 2040, 295, (0, 3, 8), (64, 1, 7)),      # 49 extension steps in a row tile, 44 steps in a part
+    "short_segments": (88, 9984, 4480, 29, (64, 4, 0), (64, 2, 0)),       # so many that small tiles, which share them, are faster
 }
 
 
