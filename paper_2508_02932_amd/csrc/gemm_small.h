@@ -419,4 +419,31 @@ __device__ __forceinline__ void gemm_small_tile(const MetaView &mv, const GemmSm
     }
 }
 
+// Sums the fp32 partial tiles [split][M][N] in split order and rounds to bf16 (ACC: added to what Cout holds, as the
+// epilogue of an unsplit call does).  4 elements per thread, eight partial tiles requested at a time.
+template <bool ACC>
+__device__ inline void gemm_finish(const float *__restrict__ part, uint16_t *__restrict__ Cout, int64_t n_vec, int n_split, int64_t i)
+{
+    if (i >= n_vec) return;
+    const float4 *p = reinterpret_cast<const float4 *>(part) + i;
+    float4 a = make_float4(0.f, 0.f, 0.f, 0.f);
+    for (int z0 = 0; z0 < n_split; z0 += 8) {
+        float4 v[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j)
+            if (z0 + j < n_split) v[j] = p[(z0 + j) * n_vec];
+#pragma unroll
+        for (int j = 0; j < 8; ++j)
+            if (z0 + j < n_split) { a.x += v[j].x; a.y += v[j].y; a.z += v[j].z; a.w += v[j].w; }
+    }
+    uint2 v;
+    v.x = gs_pack_bf16x2(a.x, a.y); v.y = gs_pack_bf16x2(a.z, a.w);
+    uint2 *dst = reinterpret_cast<uint2 *>(Cout) + i;
+    if constexpr (ACC) {
+        const uint2 o = *dst;
+        v.x = gs_add_bf16x2(o.x, v.x); v.y = gs_add_bf16x2(o.y, v.y);
+    }
+    *dst = v;
+}
+
 }  // namespace plora

@@ -22,32 +22,10 @@ __global__ void __launch_bounds__(256, 2) k_gemm_small(MetaView mv, GemmSmallArg
     gemm_small_tile<FWD, BM, DEEP, ACC, true>(mv, ga, blockIdx.x, lds);
 }
 
-// Sums the fp32 partial tiles [split][M][N] in split order and rounds to bf16 (ACC: added to what Cout holds, as the
-// epilogue of an unsplit call does).  4 elements per thread, eight partial tiles requested at a time.
 template <bool ACC>
 __global__ void __launch_bounds__(256) k_gemm_finish(const float *__restrict__ part, uint16_t *__restrict__ Cout, int64_t n_vec, int n_split)
 {
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (i >= n_vec) return;
-    const float4 *p = reinterpret_cast<const float4 *>(part) + i;
-    float4 a = make_float4(0.f, 0.f, 0.f, 0.f);
-    for (int z0 = 0; z0 < n_split; z0 += 8) {
-        float4 v[8];
-#pragma unroll
-        for (int j = 0; j < 8; ++j)
-            if (z0 + j < n_split) v[j] = p[(z0 + j) * n_vec];
-#pragma unroll
-        for (int j = 0; j < 8; ++j)
-            if (z0 + j < n_split) { a.x += v[j].x; a.y += v[j].y; a.z += v[j].z; a.w += v[j].w; }
-    }
-    uint2 v;
-    v.x = gs_pack_bf16x2(a.x, a.y); v.y = gs_pack_bf16x2(a.z, a.w);
-    uint2 *dst = reinterpret_cast<uint2 *>(Cout) + i;
-    if constexpr (ACC) {
-        const uint2 o = *dst;
-        v.x = gs_add_bf16x2(o.x, v.x); v.y = gs_add_bf16x2(o.y, v.y);
-    }
-    *dst = v;
+    gemm_finish<ACC>(part, Cout, n_vec, n_split, (int64_t)blockIdx.x * 256 + threadIdx.x);
 }
 
 hipError_t launch_gemm_finish(const float *part, void *C, int64_t n, int n_split, bool accumulate, hipStream_t st)

@@ -91,6 +91,7 @@ struct HostMeta {
     int slices16 = 0;                 // 16-token slices with tokens of an adapter
     int slices_all = 0;               // the same with those of the base model alone
     size_t fwd_parts = 0;             // forward in two launches (gemm_short_bf16.hip): bytes of the shrink's partial sums, in front of the product's; else 0
+    size_t dx_part[2] = {};           // dX in the launch of the weight gradients: where its partial tiles lie; else 0 ([1]: as gemm_dx)
     int mean_r16 = 0;                 // their rank padded to 16, on average over the tokens
     GemmPlan gemm_fwd[2], gemm_dx[2];  // [1]: over a weight that the call itself has expanded
     int n_words = 0;
@@ -247,6 +248,19 @@ static void build_meta(const plora_desc *d, HostMeta &m)
             m.fwd_parts = parts;
             m.ws.total = std::max(m.ws.total, total);
         }
+    }
+    // dX beside the weight gradients: in small tiles alone.  Its partial tiles lie behind theirs, or, where theirs are none, in the
+    // place of the skinny ones as otherwise.
+    for (int i = 0; i < 2; ++i) {
+        const GemmPlan &q = m.gemm_dx[i];
+        if (!bf || m.hdr.n_blocks == 0 || q.bm == 0 || q.big_tiles != 0) continue;
+        const size_t a_bytes = m.split_dA > 1 ? (size_t)m.split_dA * m.r16_total * d->d_in * 4 : 0;
+        const size_t b_bytes = m.split_dB > 1 ? (size_t)m.split_dB * m.r16_total * d->d_out * 4 : 0;
+        const size_t at = a_bytes + b_bytes > 0 ? m.ws.wpart + align_up(std::max(a_bytes, b_bytes), 256) : m.ws.gpart;
+        const size_t total = align_up(at + split_bytes(q, d->d_in), 256) + 256;
+        if (fits_scratch && total > (size_t)PLORA_NOALLOC_SCRATCH_BYTES) continue;
+        m.dx_part[i] = at;
+        m.ws.total = std::max(m.ws.total, total);
     }
 }
 
@@ -429,12 +443,12 @@ struct TokcList {
     TokcOperands op[kTokMaxPasses];
     int n = 0;
 };
-static hipError_t launch_grads(TokcList &l, bool one_by_one, int n_adapters, const void *zero, hipStream_t st)
+static hipError_t launch_grads(TokcList &l, bool one_by_one, int n_adapters, const void *zero, const GradsDx *dx, hipStream_t st)
 {
     const int n = l.n, step = one_by_one ? 1 : n;
     l.n = 0;
     for (int i = 0; i < n; i += step) {
-        const hipError_t e = launch_tokcontract_bf16(l.op + i, step, n_adapters, zero, st);
+        const hipError_t e = launch_tokcontract_bf16(l.op + i, step, n_adapters, zero, dx, st);
         if (e != hipSuccess) return e;
     }
     return hipSuccess;
@@ -668,8 +682,17 @@ static plora_status backward_impl(const plora_desc *desc, const void *x, const v
         if (steps & kStepDb) list.op[list.n++] = TokcOperands{mv, dy, zt_h, desc->d_out, m.small_part_is_dB ? part : wpart, m.split_dB, m.r16_total, m.hdr.max_r16, false, m.hdr.T};
         if (steps & kStepDa) list.op[list.n++] = TokcOperands{mv, x, zt_g, desc->d_in, m.small_part_is_dB ? wpart : part, m.split_dA, m.r16_total, m.hdr.max_r16, true, m.hdr.T};
         if (own.n > 0) {
-            Bracket b(4, st);
-            PL_TRY(launch_grads(own, meet_any(desc, dA, desc->d_in, Span{dy, (size_t)(desc->T * desc->d_out) * 2}), m.hdr.n_adapters, ws + L.zero, st));
+            const Span x_span{x, (size_t)(desc->T * desc->d_in) * 2};
+            const bool one_by_one = meet_any(desc, dA, desc->d_in, Span{dy, (size_t)(desc->T * desc->d_out) * 2});
+            const GemmPlan &plan = m.gemm_dx[nf4 != nullptr];
+            // dX in the same launch; not where it would be written over the x that dA reads
+            const bool joint = m.dx_part[nf4 != nullptr] > 0 && own.n == 2 && !one_by_one && dx && desc->T > 0 && !lora_only && !dx_accumulate &&
+                               (steps & kStepDx) && !meet(Span{dx, x_span.bytes}, x_span);
+            const GradsDx gd{mv, m.hdr, plan, m.hdr.w_out_in != 0, desc->d_out, desc->d_in, dy, W, gb, ap, ws + L.zero, dx,
+                             reinterpret_cast<float *>(ws + m.dx_part[nf4 != nullptr])};
+            Bracket b(joint ? 1 : 4, st);
+            PL_TRY(launch_grads(own, one_by_one, m.hdr.n_adapters, ws + L.zero, joint ? &gd : nullptr, st));
+            if (joint) return PLORA_OK;
         }
     }
     if (!(steps & kStepDx)) return PLORA_OK;
@@ -932,7 +955,7 @@ static plora_status group_backward(const plora_group *g, const void *x, const vo
         if ((ps = run(p, false, kStepDh | kStepDb | (fuse_a[p] ? 0u : kStepDa))) != PLORA_OK) return ps;
         if (!one_by_one && p + 1 < gp.n) continue;
         if (skinny.n > 0) { Bracket b(3, st); PL_TRY(launch_skinny_bf16(skinny.op, skinny.n, zero, st)); skinny.n = 0; }
-        if (grads.n > 0) { Bracket b(4, st); PL_TRY(launch_grads(grads, one_by_one, d0->n_adapters, zero, st)); }
+        if (grads.n > 0) { Bracket b(4, st); PL_TRY(launch_grads(grads, one_by_one, d0->n_adapters, zero, nullptr, st)); }
         for (int q = one_by_one ? p : 0; q <= p; ++q)
             if ((ps = run(q, false, kStepDx)) != PLORA_OK) return ps;
     }

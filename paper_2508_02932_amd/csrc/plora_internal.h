@@ -441,7 +441,7 @@ int device_cu_count(hipError_t *err);
 // Lets `kernel` use up to the 160 KB of LDS of a compute unit; done once per device and kernel (slot: a small
 // index that is unique per kernel), thread-safe.
 hipError_t allow_full_lds(const void *kernel, int slot);
-constexpr int kLdsSlots = 48;
+constexpr int kLdsSlots = 54;
 
 // Metadata and the small jobs in front of the heavy kernels, in one launch when the compact description fits a
 // kernel argument (otherwise it is first uploaded in chunks to desc_stage): derived tables and zero page into the
@@ -595,7 +595,18 @@ struct TokcOperands {
     int64_t T;
 };
 constexpr int kTokMaxPasses = 2 * kMaxGroup;
-hipError_t launch_tokcontract_bf16(const TokcOperands *ops, int n, int n_adapters, const void *zero, hipStream_t st);
+// dx: the dX product in small tiles, in the same launches; its fp32 partial tiles lie apart from those of the ops.
+struct GradsDx {
+    MetaView mv;
+    MetaHeader h;
+    GemmPlan plan;            // small tiles alone
+    bool w_rows_contract;
+    int64_t Kd, N;
+    const void *S, *W, *side, *ap, *zero;
+    void *C;
+    float *part;
+};
+hipError_t launch_tokcontract_bf16(const TokcOperands *ops, int n, int n_adapters, const void *zero, const GradsDx *dx, hipStream_t st);
 // The same two passes for several projections at once (see GroupView).  hv: projection 0's header with max_r16 replaced
 // by the fused one.  Shrink: hf / hb / zt per projection as in launch_skinny_bf16 (mode 0);
 // n_split: that of the projections' plain calls.  dA: the results go to each

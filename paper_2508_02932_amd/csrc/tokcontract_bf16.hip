@@ -16,16 +16,12 @@
 // When that gives too few workgroups to fill the chip the token walk is split as well and
 // the fp32 partial tiles are summed, in a fixed order, by a small finishing kernel; otherwise the
 // result is written directly.  No atomics anywhere: the summation order is fixed.
-#include "plora_internal.h"
+#include "gemm_small.h"
+
+#include <algorithm>
 #include <type_traits>
 
 namespace plora {
-
-typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
-typedef __attribute__((__vector_size__(4 * sizeof(__bf16)))) __bf16 bf16x4;
-typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;
-
-#define LDS_PTR(T, p) ((__attribute__((address_space(3))) T *)(p))
 
 constexpr int TC_BC = kTokTileColumns;                 // columns of the big matrix per workgroup
 constexpr int TC_BT = 64;                  // tokens per stage (TC_BT / 32 MFMA K steps)
@@ -74,9 +70,8 @@ struct TokcBatch { TokcPass p[kTokMaxPasses]; };
 // GROUP (dA only): the small factor of adapter k is the transposed g of several projections that share x, one below
 // the other (GroupView); the tables are projection 0's, `zt` is not used, every projection's dA_k gets its own columns.
 template <bool GROUP>
-__global__ void __launch_bounds__(2 * TC_BC) __attribute__((amdgpu_waves_per_eu(2, 2))) k_tokc(TokcBatch batch, int n_pass,
-                                             const uint16_t *__restrict__ zero, int max_r16, int nst,
-                                             std::conditional_t<GROUP, GroupView, NoGroup> gv)
+__device__ __forceinline__ void tokc_tile(const TokcBatch &batch, int n_pass, const uint16_t *__restrict__ zero, int max_r16, int nst,
+                                          const std::conditional_t<GROUP, GroupView, NoGroup> &gv, int bx, int by, char *lds)
 {
     constexpr int TC_NW = TC_BC / 32, TC_S_BYTES = TC_BT * TC_BC * 2;     // one wave per 32 columns
     constexpr int CPRW = TC_BC / 8;                               // 16-byte chunks per row of the big-matrix tile
@@ -84,18 +79,17 @@ __global__ void __launch_bounds__(2 * TC_BC) __attribute__((amdgpu_waves_per_eu(
     // 16-byte chunk c of token row u is stored at slot c ^ swz(u); chosen so that the 8 rows (u..u+3 and
     // u+8..u+11) that one pass of a transposing read touches fall into 8 different 32-byte bank groups
     auto swz = [](int u) { return 2 * (u & 3) + 8 * ((u >> 3) & 1); };
-    extern __shared__ __attribute__((aligned(1024))) char lds[];
     int pi = 0;
     for (int i = 1; i < n_pass; ++i)
-        if ((int)blockIdx.x >= batch.p[i].unit0) pi = i;
+        if (bx >= batch.p[i].unit0) pi = i;
     const TokcPass ps = batch.p[pi];
-    const TokJob a = ps.job[blockIdx.y];             // longest adapters first
+    const TokJob a = ps.job[by];                     // longest adapters first
     const int k = a.k;
     const bool want_da = GROUP || ps.want_da;
     const uint16_t *__restrict__ S = ps.S, *__restrict__ zt = ps.zt;
     float *__restrict__ part = ps.part;
     const int C = ps.C, n_split = ps.n_split, r16_total = ps.r16_total;
-    const int unit = blockIdx.x - ps.unit0, split = unit / ps.tiles;
+    const int unit = bx - ps.unit0, split = unit / ps.tiles;
     const int c0 = (unit - split * ps.tiles) * TC_BC;
     int r16 = a.r16;
     int p_r16[kMaxGroup];                            // GROUP: rank rows (padded to 16) of each projection
@@ -338,6 +332,36 @@ __global__ void __launch_bounds__(2 * TC_BC) __attribute__((amdgpu_waves_per_eu(
     }
 }
 
+template <bool GROUP>
+__global__ void __launch_bounds__(2 * TC_BC) __attribute__((amdgpu_waves_per_eu(2, 2))) k_tokc(TokcBatch batch, int n_pass,
+                                             const uint16_t *__restrict__ zero, int max_r16, int nst,
+                                             std::conditional_t<GROUP, GroupView, NoGroup> gv)
+{
+    extern __shared__ __attribute__((aligned(1024))) char lds[];
+    tokc_tile<GROUP>(batch, n_pass, zero, max_r16, nst, gv, blockIdx.x, blockIdx.y, lds);
+}
+
+// dB, dA and, in small tiles, dX of a call: the three need g and nothing of one another.  The product's workgroups come first, they
+// are the longer ones.
+template <bool FWD, int BM, bool DEEP>
+__global__ void __launch_bounds__(2 * TC_BC) __attribute__((amdgpu_waves_per_eu(2, 2))) k_grads(TokcBatch batch, int n_pass, int units, int max_r16, int nst,
+                                             MetaView mv, GemmSmallArgs ga, int n_gemm)
+{
+    static_assert(2 * TC_BC == 256, "both parts have four waves");
+    extern __shared__ __attribute__((aligned(1024))) char lds[];
+    int id = blockIdx.x;
+    // the compiler lets the branches run into one another: without these waits it would wait for loads of one in every stage of the other
+    __builtin_amdgcn_s_waitcnt(0);
+    if (id < n_gemm) {
+        gemm_small_tile<FWD, BM, DEEP, false, true>(mv, ga, id, lds);
+        return;
+    }
+    __builtin_amdgcn_s_waitcnt(0);
+    id -= n_gemm;
+    const int by = id / units;
+    tokc_tile<false>(batch, n_pass, ga.zero, max_r16, nst, NoGroup{0}, id - by * units, by, lds);
+}
+
 // Sums the partial tiles [split][r16 rows][C] of one matrix in split order, for 64 columns and all of its r rows (the first
 // at row0): dB_k[j][c] scaled by scale_k straight from the sums, dA_k[c][j] through LDS, so that both leave in whole rows.
 // 16 threads x 4 columns per row, all splits of a row requested at once.
@@ -380,19 +404,34 @@ __device__ inline void finish_matrix(const float *__restrict__ part, int64_t spl
     }
 }
 
+__device__ inline void tokc_finish(const TokcBatch &batch, int n_pass, int bx, int by, float *lds)
+{
+    int pi = 0;
+    for (int i = 1; i < n_pass; ++i)
+        if (bx >= batch.p[i].finish0) pi = i;
+    const TokcPass ps = batch.p[pi];
+    const TokJob a = ps.job[by];
+    const int c0 = (bx - ps.finish0) * TF_COLS;
+    const int64_t stride = (int64_t)ps.r16_total * ps.C;
+    if (ps.want_da) finish_matrix<true>(ps.part, stride, ps.n_split, a.r16_off, a.r, ps.C, c0, 1.f, a.dA, lds);
+    else finish_matrix<false>(ps.part, stride, ps.n_split, a.r16_off, a.r, ps.C, c0, a.scale, a.dB, lds);
+}
+
 // grid (64-column tiles of the products that were split; adapters)
 __global__ void __launch_bounds__(256) k_tokc_finish(TokcBatch batch, int n_pass)
 {
     extern __shared__ __attribute__((aligned(16))) float tf_lds[];
-    int pi = 0;
-    for (int i = 1; i < n_pass; ++i)
-        if ((int)blockIdx.x >= batch.p[i].finish0) pi = i;
-    const TokcPass ps = batch.p[pi];
-    const TokJob a = ps.job[blockIdx.y];
-    const int c0 = (blockIdx.x - ps.finish0) * TF_COLS;
-    const int64_t stride = (int64_t)ps.r16_total * ps.C;
-    if (ps.want_da) finish_matrix<true>(ps.part, stride, ps.n_split, a.r16_off, a.r, ps.C, c0, 1.f, a.dA, tf_lds);
-    else finish_matrix<false>(ps.part, stride, ps.n_split, a.r16_off, a.r, ps.C, c0, a.scale, a.dB, tf_lds);
+    tokc_finish(batch, n_pass, blockIdx.x, blockIdx.y, tf_lds);
+}
+
+// The same and the sums of a split dX: finish x n_adapters workgroups, then the product's.
+__global__ void __launch_bounds__(256) k_grads_finish(TokcBatch batch, int n_pass, int finish, int n_adapters, const float *__restrict__ part,
+                                                      uint16_t *__restrict__ C, int64_t n_vec, int n_split)
+{
+    extern __shared__ __attribute__((aligned(16))) float tf_lds[];
+    const int id = (int)blockIdx.x - finish * n_adapters;
+    if (id < 0) tokc_finish(batch, n_pass, blockIdx.x % finish, blockIdx.x / finish, tf_lds);
+    else gemm_finish<false>(part, C, n_vec, n_split, (int64_t)id * 256 + threadIdx.x);
 }
 
 // The same for the partial tiles of a fused dA pass: the rows of adapter k's projections lie one below the other.
@@ -497,7 +536,30 @@ hipError_t launch_tokc_group_dA(const GroupView &gv, const MetaHeader &hv, const
     return hipGetLastError();
 }
 
-hipError_t launch_tokcontract_bf16(const TokcOperands *ops, int n, int n_adapters, const void *zero, hipStream_t st)
+template <bool FWD, int BM, bool DEEP>
+static hipError_t launch_grads_and_dx(TokcBatch &batch, int n_pass, int n_adapters, int max_r16, const GradsDx &g, hipStream_t st)
+{
+    constexpr size_t ring = (size_t)(gs_ring_x(BM) * BM + gs_ring_w(BM, DEEP) * GS_BN) * GS_BK * 2;
+    int nst;
+    size_t lds;
+    max_r16 = max_r16 > 0 ? max_r16 : 16;
+    tokc_ring(max_r16, &nst, &lds);
+    auto kern = k_grads<FWD, BM, DEEP>;
+    const hipError_t e = allow_full_lds(reinterpret_cast<const void *>(kern), 48 + (FWD ? 3 : 0) + (BM == 64 ? 0 : DEEP ? 1 : 2));
+    if (e != hipSuccess) return e;
+    int units = 0;
+    for (int i = 0; i < n_pass; ++i) { batch.p[i].unit0 = units; units += batch.p[i].tiles * batch.p[i].n_split; }
+    GemmSmallArgs ga{static_cast<const uint16_t *>(g.S), static_cast<const uint16_t *>(g.W), static_cast<const uint16_t *>(g.side),
+                     static_cast<const uint16_t *>(g.ap), static_cast<const uint16_t *>(g.zero), static_cast<uint16_t *>(g.C),
+                     g.plan.n_split > 1 ? g.part : nullptr, (int)((g.h.T + BM - 1) / BM), (int)((g.N + GS_BN - 1) / GS_BN), g.plan.n_split, 0,
+                     (int)g.h.T, (int)g.Kd, (int)g.N, (int)g.h.n_seg};
+    const int n_gemm = ga.tiles_m * ga.tiles_n * ga.n_split;
+    hipLaunchKernelGGL(kern, dim3((unsigned)(n_gemm + units * n_adapters)), dim3(2 * TC_BC), std::max(lds, ring), st, batch, n_pass, units, max_r16, nst,
+                       g.mv, ga, n_gemm);
+    return hipGetLastError();
+}
+
+hipError_t launch_tokcontract_bf16(const TokcOperands *ops, int n, int n_adapters, const void *zero, const GradsDx *dx, hipStream_t st)
 {
     if (n_adapters == 0 || n == 0) return hipSuccess;
     if (n < 0 || n > kTokMaxPasses) return hipErrorInvalidValue;
@@ -513,14 +575,31 @@ hipError_t launch_tokcontract_bf16(const TokcOperands *ops, int n, int n_adapter
         if (o.n_split > 1) { finish += (int)((o.C + TF_COLS - 1) / TF_COLS); finish_dA = finish_dA || o.want_dA; }
         max_r16 = o.max_r16 > max_r16 ? o.max_r16 : max_r16;
     }
-    const hipError_t e = launch_tokc<false>(batch, n, n_adapters, zero, max_r16, NoGroup{0}, st);
-    if (e != hipSuccess || finish == 0) return e;
+    hipError_t e;
+    if (dx) {
+        const bool deep = gemm_small_deep(dx->h.T);
+#define PL_GD(FWD_, BM_, DEEP_) launch_grads_and_dx<FWD_, BM_, DEEP_>(batch, n, n_adapters, max_r16, *dx, st)
+        if (dx->w_rows_contract) e = dx->plan.bm == 64 ? PL_GD(true, 64, false) : deep ? PL_GD(true, 128, true) : PL_GD(true, 128, false);
+        else e = dx->plan.bm == 64 ? PL_GD(false, 64, false) : deep ? PL_GD(false, 128, true) : PL_GD(false, 128, false);
+#undef PL_GD
+        if (e != hipSuccess) return e;
+        if (finish == 0) return dx->plan.n_split > 1 ? launch_gemm_finish(dx->part, dx->C, dx->h.T * dx->N, dx->plan.n_split, false, st) : hipSuccess;
+    } else {
+        e = launch_tokc<false>(batch, n, n_adapters, zero, max_r16, NoGroup{0}, st);
+        if (e != hipSuccess || finish == 0) return e;
+    }
     // k_tokc_finish looks for the last product that starts at or before its workgroup: those without a split are left out
     int m = 0;
     for (int i = 0; i < n; ++i)
         if (batch.p[i].n_split > 1) batch.p[m++] = batch.p[i];
-    hipLaunchKernelGGL(k_tokc_finish, dim3((unsigned)finish, (unsigned)n_adapters), dim3(256), finish_dA ? TF_COLS * (PLORA_MAX_RANK + 1) * 4 : 0, st,
-                       batch, m);
+    const size_t lds = finish_dA ? TF_COLS * (PLORA_MAX_RANK + 1) * 4 : 0;
+    if (dx && dx->plan.n_split > 1) {
+        const int64_t n_vec = dx->h.T * dx->N / 4;
+        hipLaunchKernelGGL(k_grads_finish, dim3((unsigned)(finish * n_adapters + (n_vec + 255) / 256)), dim3(256), lds, st, batch, m, finish, n_adapters,
+                           dx->part, static_cast<uint16_t *>(dx->C), n_vec, dx->plan.n_split);
+    } else {
+        hipLaunchKernelGGL(k_tokc_finish, dim3((unsigned)finish, (unsigned)n_adapters), dim3(256), lds, st, batch, m);
+    }
     return hipGetLastError();
 }
 
