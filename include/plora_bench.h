@@ -7,8 +7,8 @@
  * plora_kernel_time sums the recorded durations of one class (milliseconds) and counts them; the
  * caller must have synchronised the streams first.
  * Classes: 0 base GEMM forward (with the fused expand; of a short batch that takes two launches in all, both of them), 1 dX GEMM (with the fused low-rank term; in an fp32 call
- * also the weight gradients where they share its launch), 2 shrink, 3 dH (and a shrink that shares its launch), 4 dB and
- * dA (one launch), 5 the fused dA of a grouped call, 6 the preparation launch (metadata, packing of A_k, conversion of a
+ * also the weight gradients where they share its launch), 2 shrink, 3 dH (and a shrink or the preparation that
+ * shares its launch), 4 dB and dA (one launch; with dX in small tiles counted as 1), 5 the fused dA of a grouped call, 6 the preparation launch (metadata, packing of A_k, conversion of a
  * saved activation; short shrinks and dHs share it), 7 the optimizer step (all launches of one plora_adamw_step call), 8 the stand-alone
  * low-rank update of plora_lora_fwd / plora_lora_bwd, 9 the expansion of an NF4 base weight (in a layer call together with
  * its preparation, which then is not counted as class 6).

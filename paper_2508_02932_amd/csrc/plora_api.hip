@@ -427,6 +427,7 @@ struct PrepList {
         job[n] = j;
         job[n].brief = nullptr; job[n].n_brief = 0;
         job[n].f32 = nullptr; job[n].n_f32 = 0;
+        job[n].dh = nullptr;
         job[n].desc_host = words[n].data();
         ++n;
     }
@@ -511,7 +512,7 @@ static plora_status forward_impl(const plora_desc *desc, const void *x, const vo
     if (steps & kStepPrep) {
         const PrepJob job{c.words, m.n_words, m.max_rank, m.hdr, ws + L.meta, reinterpret_cast<uint32_t *>(ws + L.desc), ws + L.zero,
                           ws + L.at, ws + L.ap, bf && lora && !brief, false, bf && lora && (w_out_in || lora_only), nullptr, nullptr,
-                          &shrink, brief ? 1 : 0, &f32_h, f32_early ? 1 : 0};
+                          &shrink, brief ? 1 : 0, &f32_h, f32_early ? 1 : 0, nullptr};
         if (later) later->add(job);
         else if (nf4) { Bracket b(9, st); PL_TRY(launch_prep_nf4(job, *nf4, desc->dtype == PLORA_BF16, st)); }
         else { Bracket b(6, st); PL_TRY(launch_prep(&job, 1, st)); }
@@ -605,6 +606,13 @@ static plora_status backward_impl(const plora_desc *desc, const void *x, const v
     const bool pair = lora && bf && !later && need_shrink && (steps & kStepShrink) && (steps & kStepDh) && !short_sh && !short_dh &&
                       (size_t)m.split_dh * m.hdr.n_blocks * kSkinnyRows * m.hdr.max_r16 * 4 <= L.total - 256 - L.wpart;
     if (pair) dh.part = reinterpret_cast<float *>(ws + L.wpart);
+    // dH that is not short shares the launch of the preparation, up to eight workgroups of that for one of dH: they then have its LDS, two
+    // or three on a compute unit.  Whole steps, us, apart and together: 8192 tokens, 1024 -> 1024, 16 adapters (288 and 512) 122 and 114;
+    // 4096 tokens, 2048 -> 2048, 8 adapters 148 and 142; 16384 tokens, 4096 -> 14336, low-rank calls alone 789 and 783; 8192 tokens, 8192 ->
+    // 28672, 32 adapters (6 for one) 6139 and 6131; 4096 tokens, 8192 -> 8192, 32 adapters (12 for one) 1097 and 1105
+    const int64_t pack_wgs = dx ? (desc->d_in + 63) / 64 * m.hdr.n_adapters : 0;
+    const bool early_dh = lora && bf && !later && !nf4 && (steps & kStepPrep) && (steps & kStepDh) && !short_dh && !pair && !need_shrink &&
+                          m.n_words <= kChunkWords && pack_wgs <= 8 * (int64_t)m.hdr.n_blocks * m.split_dh;
     if (steps & kStepPrep) {
         const bool tr = bf && lora && any_w && h_saved;
         SkinnyOperands brief[kPrepShort];
@@ -620,10 +628,10 @@ static plora_status backward_impl(const plora_desc *desc, const void *x, const v
         const bool dx_ap = dx != nullptr && (lora_only || !m.hdr.w_out_in), dx_at = dx != nullptr && !lora_only && m.hdr.w_out_in;
         const PrepJob job{c.words, m.n_words, m.max_rank, m.hdr, ws + L.meta, reinterpret_cast<uint32_t *>(ws + L.desc), ws + L.zero,
                           ws + L.at, ws + L.ap, bf && lora && ((need_shrink && !brief_sh) || dx_at), bf && lora && dx_ap, false,
-                          tr ? h_saved : nullptr, tr ? ws + L.zt_h : nullptr, brief, n_brief, f32, n_f32};
+                          tr ? h_saved : nullptr, tr ? ws + L.zt_h : nullptr, brief, n_brief, f32, n_f32, early_dh ? &dh : nullptr};
         if (later) later->add(job);
         else if (nf4) { Bracket b(9, st); PL_TRY(launch_prep_nf4(job, *nf4, desc->dtype == PLORA_BF16, st)); }
-        else { Bracket b(6, st); PL_TRY(launch_prep(&job, 1, st)); }
+        else { Bracket b(early_dh ? 3 : 6, st); PL_TRY(launch_prep(&job, 1, st)); }
     }
 
     if (desc->dtype == PLORA_F32) {
@@ -670,7 +678,7 @@ static plora_status backward_impl(const plora_desc *desc, const void *x, const v
             if (later_s) later_s->op[later_s->n++] = shrink;
             else { Bracket b(2, st); PL_TRY(launch_skinny_bf16(&shrink, 1, ws + L.zero, st)); }
         }
-        if (!brief_dh && (steps & kStepDh)) {
+        if (!brief_dh && !early_dh && (steps & kStepDh)) {
             if (later_s) later_s->op[later_s->n++] = dh;
             else { Bracket b(3, st); PL_TRY(launch_skinny_bf16(&dh, 1, ws + L.zero, st)); }
         }

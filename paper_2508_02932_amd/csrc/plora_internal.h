@@ -524,9 +524,11 @@ struct PrepJob {
     int n_brief;
     const F32LowRank *f32;        // the same of the fp32 path
     int n_f32;
+    const SkinnyOperands *dh;     // a dH that is not short, in the same launch and with its finishing launch behind it; or null
 };
 constexpr int kPrepShort = 2;
 hipError_t launch_prep(const PrepJob *jobs, int n_jobs, hipStream_t st);
+hipError_t launch_prep_dh(const PrepJob &job, hipStream_t st);
 hipError_t launch_prep_nf4(const PrepJob &job, const Nf4Job &w, bool bf16, hipStream_t st);
 
 // C[T][N] = S[T][Kd] * Wop + side[T][rp] * ext_k, rounded to bf16.

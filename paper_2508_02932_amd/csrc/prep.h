@@ -509,4 +509,30 @@ __device__ inline void prep_body(const DescReader<Src> &in, const PrepArgs &pa, 
     h_to_zt_slice(TransposeJob{g.row1 - g.row0, g.r, g.r16, g.lp, t_block, g.h_off, g.zt_off}, slice, pa.hf, pa.zt, reinterpret_cast<float *>(shared_mem));
 }
 
+// The launch arguments of one description, its number of workgroups and the LDS they need.
+inline hipError_t prep_args(const PrepJob &j, PrepArgs &pa, int64_t &n_wg, size_t &lds)
+{
+    static_assert(PLORA_MAX_ADAPTERS == 256, "one adapter per thread of workgroup 0");
+    static_assert(kZeroBytes == 1024, "the zero page is written by one 256-thread workgroup");
+    if (j.want_ap && j.want_bp) return hipErrorInvalidValue;            // both live in `ap`
+    const MetaHeader &h = j.h;
+    const bool pack = h.n_adapters > 0 && (j.want_at || j.want_ap);
+    pa.meta_dst = j.meta_dev; pa.zero_page = static_cast<uint32_t *>(j.zero_dev);
+    pa.at = static_cast<uint16_t *>(j.at); pa.ap = static_cast<uint16_t *>(j.ap);
+    pa.zt = static_cast<uint16_t *>(j.zt); pa.hf = j.hf;
+    pa.want_at = j.want_at ? 1 : 0; pa.want_ap = j.want_ap ? 1 : 0;
+    pa.pack_bx = (int)((h.D + 63) / 64);
+    pa.n_pack = pack ? pa.pack_bx * h.n_adapters : 0;
+    pa.pack_bx_b = (int)((h.K + 63) / 64);
+    pa.n_pack_b = (j.want_bp && h.n_adapters > 0) ? pa.pack_bx_b * h.n_adapters : 0;
+    pa.word0 = 0; pa.block0 = 0;
+    const int n_tr = (j.hf && j.zt) ? h.n_blocks * (kSkinnyRows / kTrRows) : 0;
+    n_wg = 1 + (int64_t)pa.n_pack + pa.n_pack_b + n_tr;
+    // LDS: the derivation of workgroup 0, a pack tile of 64 rows, or 64 tokens of a saved activation
+    lds = derive_lds_bytes(j.n_words, h.n_seg);
+    if ((pa.n_pack || pa.n_pack_b) && lds < (size_t)128 * j.max_rank) lds = (size_t)128 * j.max_rank;
+    if (n_tr && lds < (size_t)256 * j.max_rank) lds = (size_t)256 * j.max_rank;
+    return hipSuccess;
+}
+
 }  // namespace plora

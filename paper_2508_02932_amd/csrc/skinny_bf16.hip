@@ -12,8 +12,10 @@
 // dimensions, not the rank).  Partial tiles of the splits are summed in a fixed order by a small
 // finishing kernel that also writes the bf16 copies the later kernels consume.
 // Short batches, where a kernel's own time is mostly its start, take skinny_short.h instead.
+#include "prep.h"
 #include "skinny_short.h"
 #include <algorithm>
+#include <cstring>
 #include <type_traits>
 
 namespace plora {
@@ -96,18 +98,14 @@ struct SkinnyBatch { SkinnyJob j[kMaxGroup]; };
 // grid.z: the jobs of the batch (dH of the projections of a grouped call).
 // GROUP (mode 0 only): the small matrix of adapter k is the packed A_k^T of several projections, one below the other
 // (GroupView); the tables are projection 0's, `at` is not used, and the jobs are where each projection's sums go.
+// a: the token block blk of n_blocks; split: the share of the contraction.
 template <bool GROUP>
-__global__ void __launch_bounds__(64 * SK_NW) k_skinny(SkinnyBatch batch, const uint16_t *__restrict__ zero,
-                                               std::conditional_t<GROUP, GroupView, NoGroup> gv)
+__device__ __forceinline__ void skinny_tile(const SkinnyJob &job, const BlkInfo &a, const uint16_t *__restrict__ zero,
+                                            const std::conditional_t<GROUP, GroupView, NoGroup> &gv, int blk, int n_blocks, int split, char *lds)
 {
-    extern __shared__ __attribute__((aligned(1024))) char lds[];
-    const SkinnyJob job = batch.j[GROUP ? 0 : blockIdx.z];
-    if ((int)blockIdx.y >= job.n_split) return;
     const uint16_t *__restrict__ S = job.S, *__restrict__ at = job.at;
     float *__restrict__ part = job.part;
     const int C = job.C, mode = GROUP ? 0 : job.mode, stages_per_split = job.per, max_r16 = job.max_r16;
-    const int blk = blockIdx.x;
-    const BlkInfo a = job.blk[blk];
     const SegInfo g = a.g;
     const int t0 = a.t0;
     const int nt = (g.row1 - g.row0 - t0 < kSkinnyRows) ? g.row1 - g.row0 - t0 : kSkinnyRows;
@@ -134,7 +132,7 @@ __global__ void __launch_bounds__(64 * SK_NW) k_skinny(SkinnyBatch batch, const 
     const uint32_t lds_base = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)LDS_PTR(char, lds));
 
     const int n_stage_all = (C + SK_BK - 1) / SK_BK;
-    const int st0 = blockIdx.y * stages_per_split;
+    const int st0 = split * stages_per_split;
     int n_st = n_stage_all - st0;
     n_st = n_st < stages_per_split ? n_st : stages_per_split;
     if (n_st < 0) n_st = 0;
@@ -189,7 +187,7 @@ __global__ void __launch_bounds__(64 * SK_NW) k_skinny(SkinnyBatch batch, const 
     auto load16_once = [&](const uint16_t *gp, uint32_t dst) {
         asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dwordx4 %0, off nt" ::"v"(gp), "s"(dst));
     };
-    const int turn = job.turn && n_st > 0 ? (int)((blockIdx.x * 5u + blockIdx.y * 3u) % (unsigned)n_st) : 0;
+    const int turn = job.turn && n_st > 0 ? (int)(((unsigned)blk * 5u + (unsigned)split * 3u) % (unsigned)n_st) : 0;
     auto issue = [&](int st) {       // step of this split: stage st + turn, round the end; ring slot st % SK_NST
         const uint32_t base = lds_base + (st % SK_NST) * stage_bytes;
         const int sx = st + turn < n_st ? st + turn : st + turn - n_st;
@@ -263,7 +261,7 @@ __global__ void __launch_bounds__(64 * SK_NW) k_skinny(SkinnyBatch batch, const 
     }
 
     // partial tile [128][r16] of this (block, split): lane holds column 16b + lm, rows 16*(2w+mb) + 4kg + i
-    float *dst = part + ((int64_t)blockIdx.y * gridDim.x + blk) * (kSkinnyRows * max_r16);
+    float *dst = part + ((int64_t)split * n_blocks + blk) * (kSkinnyRows * max_r16);
 #pragma unroll
     for (int mb = 0; mb < SK_MB; ++mb)
 #pragma unroll
@@ -273,6 +271,36 @@ __global__ void __launch_bounds__(64 * SK_NW) k_skinny(SkinnyBatch batch, const 
                 for (int i = 0; i < 4; ++i)
                     dst[((wave * SK_MB + mb) * 16 + kg * 4 + i) * r16 + b * 16 + lm] = acc[mb][b][i];
             }
+}
+
+template <bool GROUP>
+__global__ void __launch_bounds__(64 * SK_NW) k_skinny(SkinnyBatch batch, const uint16_t *__restrict__ zero,
+                                               std::conditional_t<GROUP, GroupView, NoGroup> gv)
+{
+    extern __shared__ __attribute__((aligned(1024))) char lds[];
+    const SkinnyJob job = batch.j[GROUP ? 0 : blockIdx.z];
+    if ((int)blockIdx.y >= job.n_split) return;
+    const BlkInfo a = job.blk[blockIdx.x];
+    skinny_tile<GROUP>(job, a, zero, gv, blockIdx.x, gridDim.x, blockIdx.y, lds);
+}
+
+// dH in the launch of the preparation: it reads B_k as it lies in memory and no table, a workgroup finds its token block in the
+// description itself.  The tables come first (a long chain), then dH, and the short packing workgroups in what room it leaves: the other
+// way round 8192 tokens, 4096 -> 4096 gained nothing, for dH then began its 512 workgroups behind 385 others (7 us of preparation saved, 0 to
+// 8 of a step; backward_impl has the line).
+__device__ __attribute__((aligned(16))) const uint32_t g_skinny_zeros[4] = {0u, 0u, 0u, 0u};     // the zero page is written in the same launch
+__global__ void __launch_bounds__(64 * SK_NW) k_prep_dh(DescChunk c, PrepArgs pa, SkinnyJob job, int n_prep, int n_blocks)
+{
+    extern __shared__ __attribute__((aligned(1024))) char lds[];
+    const DescReader<WordsInArg> in{WordsInArg{c.w}};
+    const int n_dh = (int)gridDim.x - n_prep, wg = (int)blockIdx.x - 1;      // the tables, then dH, then the rest of the preparation
+    if (wg < 0 || wg >= n_dh) { prep_body(in, pa, wg < 0 ? 0 : wg - n_dh + 1, lds); return; }
+    const int split = wg / n_blocks, blk = wg - split * n_blocks;
+    BlkInfo a;
+    a.g = segment_of_block(in, blk, a.t0, a.scale);
+    a.at_off = 0; a.B = in.ad_ptr(a.g.adapter, 1);
+    __builtin_amdgcn_s_waitcnt(0);                   // the compiler would wait in every stage for what the other branch has in flight
+    skinny_tile<false>(job, a, reinterpret_cast<const uint16_t *>(g_skinny_zeros), NoGroup{0}, blk, n_blocks, split, lds);
 }
 
 // Sums the partial tiles of the splits (fixed order) and writes the outputs, 16 rows of a token block per workgroup.
@@ -431,6 +459,42 @@ static hipError_t launch_short(const SkinnyOperands *ops, int n, hipStream_t st)
     return hipGetLastError();
 }
 
+static SkinnyJob skinny_job(const SkinnyOperands &o)
+{
+    SkinnyJob j{};
+    j.blk = o.mv.blk; j.S = static_cast<const uint16_t *>(o.S); j.at = static_cast<const uint16_t *>(o.at);
+    j.part = o.part;
+    j.out = SkinnyOut{o.hf, static_cast<uint16_t *>(o.hb), static_cast<uint16_t *>(o.zt), o.zt_scaled ? 1 : 0};
+    j.C = (int32_t)o.C; j.mode = o.mode; j.max_r16 = o.h.max_r16; j.n_split = o.n_split;
+    set_past(j, o.h, o.alone, o.mean_r16);
+    const int n_stage_all = (j.C + SK_BK - 1) / SK_BK;
+    j.per = (n_stage_all + j.n_split - 1) / j.n_split;
+    return j;
+}
+
+hipError_t launch_prep_dh(const PrepJob &p, hipStream_t st)
+{
+    const SkinnyOperands &o = *p.dh;
+    if (o.mode != 1 || o.is_short || o.h.n_blocks == 0 || p.n_words > kChunkWords) return hipErrorInvalidValue;
+    PrepArgs pa;
+    int64_t n_wg;
+    size_t lds;
+    hipError_t e = prep_args(p, pa, n_wg, lds);
+    if (e != hipSuccess) return e;
+    SkinnyBatch batch{};
+    batch.j[0] = skinny_job(o);
+    DescChunk c;
+    std::memcpy(c.w, p.desc_host, (size_t)p.n_words * 4);
+    lds = std::max(lds, (size_t)SK_NST * (SK_XT + o.h.max_r16 * SK_BK * 2));
+    e = allow_full_lds(reinterpret_cast<const void *>(k_prep_dh), 2);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(k_prep_dh, dim3((unsigned)(n_wg + (int64_t)o.h.n_blocks * o.n_split)), dim3(64 * SK_NW), lds, st, c, pa, batch.j[0], (int)n_wg, o.h.n_blocks);
+    e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(k_skinny_finish<false>, dim3((unsigned)o.h.n_blocks, kSkinnyRows / 16, 1), dim3(256), 0, st, batch, NoGroup{0});
+    return hipGetLastError();
+}
+
 hipError_t launch_skinny_bf16(const SkinnyOperands *ops, int n, const void *zero, hipStream_t st)
 {
     if (n < 0 || n > kMaxGroup) return hipErrorInvalidValue;
@@ -441,14 +505,7 @@ hipError_t launch_skinny_bf16(const SkinnyOperands *ops, int n, const void *zero
         const SkinnyOperands &o = ops[i];
         if (o.h.n_blocks == 0) continue;
         if (o.is_short) { brief[n_brief++] = o; continue; }
-        SkinnyJob &j = batch.j[m++];
-        j.blk = o.mv.blk; j.S = static_cast<const uint16_t *>(o.S); j.at = static_cast<const uint16_t *>(o.at);
-        j.part = o.part;
-        j.out = SkinnyOut{o.hf, static_cast<uint16_t *>(o.hb), static_cast<uint16_t *>(o.zt), o.zt_scaled ? 1 : 0};
-        j.C = (int32_t)o.C; j.mode = o.mode; j.max_r16 = o.h.max_r16; j.n_split = o.n_split;
-        set_past(j, o.h, o.alone, o.mean_r16);
-        const int n_stage_all = (j.C + SK_BK - 1) / SK_BK;
-        j.per = (n_stage_all + j.n_split - 1) / j.n_split;
+        batch.j[m++] = skinny_job(o);
         n_blocks = o.h.n_blocks;
         max_r16 = o.h.max_r16 > max_r16 ? o.h.max_r16 : max_r16;
         grid_y = o.n_split > grid_y ? o.n_split : grid_y;

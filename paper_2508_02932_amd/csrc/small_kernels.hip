@@ -148,32 +148,6 @@ __global__ void __launch_bounds__(256) k_prep_mem(const uint32_t *desc, PrepArgs
     prep_body(DescReader<WordsInMemory>{WordsInMemory{desc}}, pa, blockIdx.x, prep_lds);
 }
 
-// The launch arguments of one description, its number of workgroups and the LDS they need.
-static hipError_t prep_args(const PrepJob &j, PrepArgs &pa, int64_t &n_wg, size_t &lds)
-{
-    static_assert(PLORA_MAX_ADAPTERS == 256, "one adapter per thread of workgroup 0");
-    static_assert(kZeroBytes == 1024, "the zero page is written by one 256-thread workgroup");
-    if (j.want_ap && j.want_bp) return hipErrorInvalidValue;            // both live in `ap`
-    const MetaHeader &h = j.h;
-    const bool pack = h.n_adapters > 0 && (j.want_at || j.want_ap);
-    pa.meta_dst = j.meta_dev; pa.zero_page = static_cast<uint32_t *>(j.zero_dev);
-    pa.at = static_cast<uint16_t *>(j.at); pa.ap = static_cast<uint16_t *>(j.ap);
-    pa.zt = static_cast<uint16_t *>(j.zt); pa.hf = j.hf;
-    pa.want_at = j.want_at ? 1 : 0; pa.want_ap = j.want_ap ? 1 : 0;
-    pa.pack_bx = (int)((h.D + 63) / 64);
-    pa.n_pack = pack ? pa.pack_bx * h.n_adapters : 0;
-    pa.pack_bx_b = (int)((h.K + 63) / 64);
-    pa.n_pack_b = (j.want_bp && h.n_adapters > 0) ? pa.pack_bx_b * h.n_adapters : 0;
-    pa.word0 = 0; pa.block0 = 0;
-    const int n_tr = (j.hf && j.zt) ? h.n_blocks * (kSkinnyRows / kTrRows) : 0;
-    n_wg = 1 + (int64_t)pa.n_pack + pa.n_pack_b + n_tr;
-    // LDS: the derivation of workgroup 0, a pack tile of 64 rows, or 64 tokens of a saved activation
-    lds = derive_lds_bytes(j.n_words, h.n_seg);
-    if ((pa.n_pack || pa.n_pack_b) && lds < (size_t)128 * j.max_rank) lds = (size_t)128 * j.max_rank;
-    if (n_tr && lds < (size_t)256 * j.max_rank) lds = (size_t)256 * j.max_rank;
-    return hipSuccess;
-}
-
 unsigned long long launch_number()
 {
     static std::atomic<unsigned long long> next{((unsigned long long)std::random_device{}() << 32) | 1u};
@@ -234,6 +208,7 @@ static hipError_t launch_prep_f32(const PrepJob &j, hipStream_t st)
 static hipError_t launch_prep_one(const PrepJob &j, hipStream_t st)
 {
     if (j.n_f32 > 0) return launch_prep_f32(j, st);
+    if (j.dh) return launch_prep_dh(j, st);
     if (j.n_brief > 0) return launch_prep_short(j, st);
     PrepArgs pa;
     int64_t n_wg;
@@ -254,7 +229,7 @@ static hipError_t launch_prep_one(const PrepJob &j, hipStream_t st)
 
 hipError_t launch_prep_nf4(const PrepJob &j, const Nf4Job &w, bool bf16, hipStream_t st)
 {
-    if (j.n_brief > 0 || j.n_f32 > 0) return hipErrorInvalidValue;
+    if (j.n_brief > 0 || j.n_f32 > 0 || j.dh) return hipErrorInvalidValue;
     PrepArgs pa;
     int64_t n_wg;
     size_t lds;
