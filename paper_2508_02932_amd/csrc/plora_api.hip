@@ -963,8 +963,16 @@ static plora_status group_backward(const plora_group *g, const void *x, const vo
         if ((ps = run(p, false, kStepDh | kStepDb | (fuse_a[p] ? 0u : kStepDa))) != PLORA_OK) return ps;
         if (!one_by_one && p + 1 < gp.n) continue;
         if (skinny.n > 0) { Bracket b(3, st); PL_TRY(launch_skinny_bf16(skinny.op, skinny.n, zero, st)); skinny.n = 0; }
-        if (grads.n > 0) { Bracket b(4, st); PL_TRY(launch_grads(grads, one_by_one, d0->n_adapters, zero, nullptr, st)); }
-        for (int q = one_by_one ? p : 0; q <= p; ++q)
+        // dX of the first projection beside the gradients, as in a plain call (the others, which may add to it, come behind)
+        const HostMeta &m0 = *gp.m[0];
+        char *ws0 = ws + gp.ws_off[0];
+        void *dx0 = dx_sum ? dx_sum : (dx ? dx[0] : nullptr);
+        const bool joint = grads.n > 0 && !one_by_one && m0.dx_part[0] > 0 && dx0 && d0->T > 0 &&
+                           !meet(Span{dx0, (size_t)(d0->T * d0->d_in) * 2}, Span{x, (size_t)(d0->T * d0->d_in) * 2});
+        const GradsDx gd{device_view(m0, m0.ws, ws0), m0.hdr, m0.gemm_dx[0], m0.hdr.w_out_in != 0, d0->d_out, d0->d_in, dy[0], W[0], ws0 + m0.ws.hb,
+                         ws0 + m0.ws.ap, ws0 + m0.ws.zero, dx0, reinterpret_cast<float *>(ws0 + m0.dx_part[0])};
+        if (grads.n > 0) { Bracket b(joint ? 1 : 4, st); PL_TRY(launch_grads(grads, one_by_one, d0->n_adapters, zero, joint ? &gd : nullptr, st)); }
+        for (int q = one_by_one ? p : joint ? 1 : 0; q <= p; ++q)
             if ((ps = run(q, false, kStepDx)) != PLORA_OK) return ps;
     }
     for (int c = 0; c < gp.n_cells; ++c) {

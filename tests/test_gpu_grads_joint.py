@@ -49,3 +49,45 @@ def test_grads_and_dx(case, w_layout):
         finally:
             plora.plora_set_kernel_timing(False)
         assert all(torch.equal(a, b) for a, b in zip(want, (dx, *dp.dA, *dp.dB)))
+
+
+@pytest.mark.parametrize("total", [False, True])
+@pytest.mark.parametrize("w_layout", [0, 1])
+def test_first_projection_of_a_group(w_layout, total):
+    """dX of the first projection beside dB of all, the second's behind it: the bits of the plain calls and of their sum."""
+    import torch
+    import gpu_harness as gh
+    D, lengths, ranks = 520, [700, 460], [24, 8]
+    lins = [wl.small(f"grads_group_{p}", "bf16", D, K, lengths=lengths, seg_adapter=[0, 1], ranks=ranks, scales=[2.0, 0.5], seed=491 + p)
+            for p, K in enumerate((4104, 392))]
+    tens = [l.tensors() for l in lins]
+    tens[1].x = tens[0].x
+    dps = [gh.upload(l, t, w_layout) for l, t in zip(lins, tens)]
+    for dp in dps:
+        gh.forward(dp)
+        gh.backward(dp)
+    want = [[t.clone() for t in (dp.dx, *dp.dA, *dp.dB)] for dp in dps]
+    for dp in dps:
+        for t in (dp.dx, *dp.dA, *dp.dB):
+            t.fill_(float("nan"))
+    lists = lambda name: [getattr(dp, name) for dp in dps]
+    group = plora.Group(lists("desc"))
+    ws = torch.empty(plora.plora_group_workspace_bytes(group), dtype=torch.uint8, device="cuda")
+    out = torch.full_like(dps[0].dx, float("nan"))
+    plora.plora_set_kernel_timing(True)
+    try:
+        plora.plora_group_bwd(group, dps[0].x, lists("W"), lists("A"), lists("B"), lists("dy"), lists("h"), None if total else lists("dx"),
+                              lists("dA"), lists("dB"), ws, dx_sum=out if total else None)
+        torch.cuda.synchronize()
+        assert plora.plora_kernel_time(4)[1] == 0
+    finally:
+        plora.plora_set_kernel_timing(False)
+    if total:
+        assert torch.equal(out, want[0][0] + want[1][0])
+    for dp, w in zip(dps, want):
+        if not total:
+            assert torch.equal(dp.dx, w[0])
+        assert all(torch.equal(a, b) for a, b in zip((*dp.dB,), w[1 + len(ranks):]))
+        # the fused pass may split the token walk otherwise: fp32 sums over 700 tokens in another order, sqrt(700) 2^-24 = 1.6e-6 of them
+        for a, b in zip(dp.dA, w[1:]):
+            assert (a - b).abs().max() <= 1e-5 * b.abs().max()
