@@ -344,8 +344,9 @@ __global__ void __launch_bounds__(2 * TC_BC) __attribute__((amdgpu_waves_per_eu(
 // dB, dA and, in small tiles, dX of a call (of the first projection of a grouped one): the three need g and nothing of one another.  The
 // product's workgroups come first, they are the longer ones; the token walks fill the compute units beside and behind them.  Either part
 // takes two workgroups of a compute unit alone, so the larger LDS and the 208 registers cost neither anything.  Taken wherever dX runs in
-// small tiles alone: of 46 steps none was slower.  Whole steps, us, in two launches and in one: 1531 tokens, 1000 -> 2504 88.1 and 76.4;
-// 700 tokens, 4224 -> 2712 102 and 91; 24 groups 1.05 on average; 1024 tokens, 4096 -> 14336, where 512 tiles fill the chip by themselves, the same.
+// small tiles alone: of 46 steps none that takes it was slower.  Whole steps, us, apart and together: 1531 tokens, 1000 -> 2504 88.0 and
+// 76.4; 1024 tokens, 1024 -> 1024 49.5 and 38.4; 700 tokens, 4224 -> 2712 101 and 90; 74 tokens, 2688 -> 20224 159 and 142; 24 groups 1.05 on
+// average; 1024 tokens, 4096 -> 14336, where 512 tiles fill the chip by themselves, the same.
 template <bool FWD, int BM, bool DEEP>
 __global__ void __launch_bounds__(2 * TC_BC) __attribute__((amdgpu_waves_per_eu(2, 2))) k_grads(TokcBatch batch, int n_pass, int units, int max_r16, int nst,
                                              MetaView mv, GemmSmallArgs ga, int n_gemm)
