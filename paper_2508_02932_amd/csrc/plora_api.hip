@@ -607,9 +607,9 @@ static plora_status backward_impl(const plora_desc *desc, const void *x, const v
                       (size_t)m.split_dh * m.hdr.n_blocks * kSkinnyRows * m.hdr.max_r16 * 4 <= L.total - 256 - L.wpart;
     if (pair) dh.part = reinterpret_cast<float *>(ws + L.wpart);
     // dH that is not short shares the launch of the preparation, up to eight workgroups of that for one of dH: they then have its LDS, two
-    // or three on a compute unit.  Whole steps, us, apart and together: 8192 tokens, 1024 -> 1024, 16 adapters (288 and 512) 122 and 114;
+    // or three on a compute unit.  Whole steps, us, apart and together: 8192 tokens, 1024 -> 1024, 16 adapters (256 packing, 213 of dH) 122 and 114;
     // 4096 tokens, 2048 -> 2048, 8 adapters 148 and 142; 16384 tokens, 4096 -> 14336, low-rank calls alone 789 and 783; 8192 tokens, 8192 ->
-    // 28672, 32 adapters (6 for one) 6139 and 6131; 4096 tokens, 8192 -> 8192, 32 adapters (12 for one) 1097 and 1105
+    // 28672, 32 adapters (6 for one) 6139 and 6131; 4096 tokens, 8192 -> 8192, 32 adapters (10 for one) 1097 and 1105
     const int64_t pack_wgs = dx ? (desc->d_in + 63) / 64 * m.hdr.n_adapters : 0;
     const bool early_dh = lora && bf && !later && !nf4 && (steps & kStepPrep) && (steps & kStepDh) && !short_dh && !pair && !need_shrink &&
                           m.n_words <= kChunkWords && pack_wgs <= 8 * (int64_t)m.hdr.n_blocks * m.split_dh;
