@@ -314,10 +314,13 @@ static hipError_t launch_batch(const ShortForward *const *ops, int n, hipStream_
 #undef PL_SP
     if (e != hipSuccess) return e;
     const int64_t narrow = (widest + 127) / 128, wide = (widest + 255) / 256;
-    if (n * o.slices * narrow <= 1024)
+    if (n * o.slices * narrow <= 1024) {
         hipLaunchKernelGGL((k_short_finish<2, NP>), dim3((unsigned)o.slices, (unsigned)narrow, (unsigned)n), dim3(256), (size_t)max_steps * (1024 + 4 * 2048), st, fb);
-    else
+    } else {
+        e = allow_full_lds(reinterpret_cast<const void *>(&k_short_finish<4, NP>), NP > 1 ? 55 : 54);       // 68 KB at ranks above 96
+        if (e != hipSuccess) return e;
         hipLaunchKernelGGL((k_short_finish<4, NP>), dim3((unsigned)o.slices, (unsigned)wide, (unsigned)n), dim3(256), (size_t)max_steps * (1024 + 4 * 4096), st, fb);
+    }
     return hipGetLastError();
 }
 

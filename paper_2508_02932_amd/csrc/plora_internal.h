@@ -441,7 +441,7 @@ int device_cu_count(hipError_t *err);
 // Lets `kernel` use up to the 160 KB of LDS of a compute unit; done once per device and kernel (slot: a small
 // index that is unique per kernel), thread-safe.
 hipError_t allow_full_lds(const void *kernel, int slot);
-constexpr int kLdsSlots = 54;
+constexpr int kLdsSlots = 56;
 
 // Metadata and the small jobs in front of the heavy kernels, in one launch when the compact description fits a
 // kernel argument (otherwise it is first uploaded in chunks to desc_stage): derived tables and zero page into the

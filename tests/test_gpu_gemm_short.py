@@ -20,7 +20,17 @@ CASES = {
     "wide_finish": (320, 4104, [200, 3, 150], [0, -1, 1], [24, 96], 64, False),
     "ring_of_three_split": (4104, 8200, [100, 60, 40], [0, 1, 0], [16, 40], 128, True),
     "128_rows_split": (8200, 4104, [300, 380, 20], [0, 1, -1], [33, 8], 128, True),
+    # the finishing launch with four blocks of columns and four steps of rank: 68 KB of LDS
+    "wide_rank_117": (328, 5680, [120, 130, 129], [0, 1, 2], [8, 117, 30], 64, False),
+    "wide_rank_128": (2056, 4200, [90, 310, 100], [0, -1, 1], [16, 128], 64, False),
+    "wide_split": (4200, 7432, [83, 82, 82], [0, 1, 2], [112, 16, 16], 64, True),
 }
+WIDE = ("128_rows_split", "wide_rank_117", "wide_rank_128", "wide_split")
+
+
+def finish_workgroups(lengths, K, n=1):
+    """Of the finishing launch in its narrow form; above 1024 of them it takes the wide one."""
+    return n * sum((v + 15) // 16 for v in lengths) * ((K + 127) // 128)
 
 
 def takes_two_launches(desc, tile_rows, split):
@@ -43,6 +53,8 @@ def test_two_launches(case, save_h, w_layout):
     import gpu_harness as gh
     lin = problem(case, CASES[case])
     takes_two_launches(gh.desc_of(lin, w_layout), *CASES[case][5:])
+    D, K, lengths = CASES[case][:3]
+    assert (finish_workgroups(lengths, K) > 1024) == (case in WIDE)
     run_and_compare(lin, impl=oracle.matmul, save_h=save_h, w_layout=w_layout)
 
 
@@ -63,6 +75,11 @@ def test_group_is_bitwise_the_plain_calls(w_layouts):
     want = [(dp.y.clone(), dp.h.clone()) for dp in dps]
     for dp in dps:
         dp.y.fill_(float("nan")); dp.h.fill_(float("nan"))
+    group_is_the_plain_calls(dps, want)
+
+
+def group_is_the_plain_calls(dps, want):
+    import torch
     lists = lambda name: [getattr(dp, name) for dp in dps]
     group = plora.Group(lists("desc"))
     ws = torch.empty(plora.plora_group_workspace_bytes(group), dtype=torch.uint8, device="cuda")
@@ -71,3 +88,23 @@ def test_group_is_bitwise_the_plain_calls(w_layouts):
     for dp, (y, h) in zip(dps, want):
         n = plora.plora_h_elems(dp.desc)
         assert torch.equal(dp.y, y) and torch.equal(dp.h[:n], h[:n])
+
+
+@pytest.mark.parametrize("w_layout", [0, 1])
+def test_group_with_the_wide_finish(w_layout):
+    """Two projections whose plain calls finish in the narrow form and together in the wide one, at four steps of rank (68 KB of LDS)."""
+    import gpu_harness as gh
+    D, lengths, owner, ranks = 328, [120, 130, 129], [0, 1, 2], [8, 117, 30]
+    lins = [problem(f"group_wide_{p}", (D, K, lengths, owner, ranks), 503 + p) for p, K in enumerate((2808, 2200))]
+    tens = [l.tensors() for l in lins]
+    tens[1].x = tens[0].x
+    dps = [gh.upload(l, t, w_layout) for l, t in zip(lins, tens)]
+    for dp in dps:
+        takes_two_launches(dp.desc, 64, False)
+        assert finish_workgroups(lengths, dp.desc.d_out) <= 1024
+        gh.forward(dp)
+    assert finish_workgroups(lengths, 2808, 2) > 1024
+    want = [(dp.y.clone(), dp.h.clone()) for dp in dps]
+    for dp in dps:
+        dp.y.fill_(float("nan")); dp.h.fill_(float("nan"))
+    group_is_the_plain_calls(dps, want)
