@@ -83,6 +83,7 @@ struct HostMeta {
     Tables t;
     MetaHeader hdr;
     WorkspaceLayout ws;               // plora_linear_fwd / _bwd
+    WorkspaceLayout ws_nf4;           // plora_linear_fwd_nf4 / _bwd_nf4: the same places, but only the partial tiles of their own plans
     WorkspaceLayout ws_lora;          // plora_lora_fwd / _bwd: the padded small-matrix region holds [max(d_in, d_out)][rp]
     size_t h_elems = 0, hb_elems = 0, zt_elems = 0, at_elems = 0, ap_elems = 0;
     int r16_total = 0, n_active = 0, max_rank = 0, split_dA = 1, split_dB = 1;
@@ -220,6 +221,11 @@ static void build_meta(const plora_desc *d, HostMeta &m)
             break;
         }
     }
+    // the dense calls and those on an expanded weight (index 1) have the partial tiles of their own products alone
+    lay_out(m.ws, m.layout.bytes, m.ap_elems, false, flag_bytes);
+    size_t total[2];
+    for (int i = 0; i < 2; ++i)
+        total[i] = !bf ? m.ws.total : std::max(m.ws.total, align_up(m.ws.gpart + std::max(split_bytes(m.gemm_fwd[i], d->d_out), split_bytes(m.gemm_dx[i], d->d_in)), 256) + 256);
     packed = bf;
     // dB and dA share a launch: the larger set of their partial tiles has the region of its own, the smaller lies over the
     // skinny ones and is split no further than fits there
@@ -243,10 +249,10 @@ static void build_meta(const plora_desc *d, HostMeta &m)
         skinny_is_short(m.hdr, m.slices16, m.r16_total, d->d_in)) {
         const int n = short_shares(m.hdr, m.slices16, d->d_in, m.short_cap()).n;
         const size_t parts = align_up((size_t)n * m.slices_all * 16 * m.hdr.max_r16 * 4, 256);
-        const size_t total = align_up(m.ws.part + parts + (size_t)p.n_split * d->T * d->d_out * 4, 256) + 256;
-        if (!fits_scratch || total <= (size_t)PLORA_NOALLOC_SCRATCH_BYTES) {
+        const size_t end = align_up(m.ws.part + parts + (size_t)p.n_split * d->T * d->d_out * 4, 256) + 256;
+        if (!fits_scratch || end <= (size_t)PLORA_NOALLOC_SCRATCH_BYTES) {
             m.fwd_parts = parts;
-            m.ws.total = std::max(m.ws.total, total);
+            total[0] = std::max(total[0], end);
         }
     }
     // dX beside the weight gradients: in small tiles alone.  Its partial tiles lie behind theirs, or, where theirs are none, in the
@@ -257,11 +263,17 @@ static void build_meta(const plora_desc *d, HostMeta &m)
         const size_t a_bytes = m.split_dA > 1 ? (size_t)m.split_dA * m.r16_total * d->d_in * 4 : 0;
         const size_t b_bytes = m.split_dB > 1 ? (size_t)m.split_dB * m.r16_total * d->d_out * 4 : 0;
         const size_t at = a_bytes + b_bytes > 0 ? m.ws.wpart + align_up(std::max(a_bytes, b_bytes), 256) : m.ws.gpart;
-        const size_t total = align_up(at + split_bytes(q, d->d_in), 256) + 256;
-        if (fits_scratch && total > (size_t)PLORA_NOALLOC_SCRATCH_BYTES) continue;
+        const size_t end = align_up(at + split_bytes(q, d->d_in), 256) + 256;
+        if (fits_scratch && end > (size_t)PLORA_NOALLOC_SCRATCH_BYTES) continue;
         m.dx_part[i] = at;
-        m.ws.total = std::max(m.ws.total, total);
+        total[i] = std::max(total[i], end);
     }
+    // (backward_impl runs a recomputed shrink beside dH where the workspace reaches that far: with an expanded weight where the dense one does)
+    const size_t pair_end = m.ws.wpart + (size_t)m.split_dh * m.hdr.n_blocks * kSkinnyRows * m.hdr.max_r16 * 4 + 256;
+    if (bf && pair_end <= total[0]) total[1] = std::max(total[1], align_up(pair_end, 256));
+    m.ws_nf4 = m.ws;
+    m.ws.total = total[0];
+    m.ws_nf4.total = total[1];
 }
 
 // ---- metadata cache: the last few descriptions and what was derived from them ---------------------
@@ -361,15 +373,18 @@ struct Call {
     const uint32_t *words = nullptr;
 };
 
-// Checks shared by forward and backward.  lora_only: the stand-alone low-rank calls (no W, their own workspace layout).
+// Which calls: with a dense W, with one that the call expands, or the stand-alone low-rank ones (no W).
+enum class Form { kDense, kNf4, kLoraOnly };
+
+// Checks shared by forward and backward.
 static plora_status prepare(const plora_desc *d, const void *x, const void *W, const void *const *A,
                             const void *const *B, float *const *dA, float *const *dB, void *workspace, size_t ws_bytes,
-                            bool lora_only, Call &c)
+                            Form form, Call &c)
 {
     plora_status st = validate(d);
     if (st != PLORA_OK) return st;
     if (!x && d->T > 0) return PLORA_ERR_NULL;
-    if (!W && !lora_only) return PLORA_ERR_NULL;
+    if (!W && form != Form::kLoraOnly) return PLORA_ERR_NULL;
     if (d->n_adapters > 0 && (!A || !B)) return PLORA_ERR_NULL;
     for (int32_t k = 0; k < d->n_adapters; ++k) {
         if (!A[k] || !B[k]) return PLORA_ERR_NULL;
@@ -377,7 +392,7 @@ static plora_status prepare(const plora_desc *d, const void *x, const void *W, c
     }
     if (misaligned(x) || misaligned(W)) return PLORA_ERR_ALIGN;
     c.m = meta_of(d);
-    c.L = lora_only ? &c.m->ws_lora : &c.m->ws;
+    c.L = form == Form::kLoraOnly ? &c.m->ws_lora : form == Form::kNf4 ? &c.m->ws_nf4 : &c.m->ws;
     if (!workspace || ws_bytes < c.L->total) return PLORA_ERR_WORKSPACE;
     if ((reinterpret_cast<uintptr_t>(workspace) & 255u) != 0) return PLORA_ERR_ALIGN;
     uint32_t *w = c.small;
@@ -471,11 +486,12 @@ struct ForwardList {
 
 static plora_status forward_impl(const plora_desc *desc, const void *x, const void *W, const void *const *A,
                                  const void *const *B, void *y, float *h_saved, void *workspace, size_t ws_bytes,
-                                 void *hip_stream, bool lora_only = false, bool check_only = false, unsigned steps = kStepsAll,
+                                 void *hip_stream, Form form = Form::kDense, bool check_only = false, unsigned steps = kStepsAll,
                                  PrepList *later = nullptr, const Nf4Job *nf4 = nullptr, SkinnyList *later_s = nullptr, ForwardList *later_f = nullptr)
 {
+    const bool lora_only = form == Form::kLoraOnly;
     Call c;
-    plora_status ps = prepare(desc, x, W, A, B, nullptr, nullptr, workspace, ws_bytes, lora_only, c);
+    plora_status ps = prepare(desc, x, W, A, B, nullptr, nullptr, workspace, ws_bytes, form, c);
     if (ps != PLORA_OK) return ps;
     const HostMeta &m = *c.m;
     const WorkspaceLayout &L = *c.L;
@@ -551,18 +567,18 @@ static plora_status forward_impl(const plora_desc *desc, const void *x, const vo
 
 static plora_status backward_impl(const plora_desc *desc, const void *x, const void *W, const void *const *A,
                                   const void *const *B, const void *dy, const float *h_saved, void *dx, float *const *dA,
-                                  float *const *dB, void *workspace, size_t ws_bytes, void *hip_stream, bool lora_only = false,
+                                  float *const *dB, void *workspace, size_t ws_bytes, void *hip_stream, Form form = Form::kDense,
                                   bool check_only = false, unsigned steps = kStepsAll, bool dx_accumulate = false,
                                   PrepList *later = nullptr, const Nf4Job *nf4 = nullptr, TokcList *later_w = nullptr,
                                   SkinnyList *later_s = nullptr)
 {
-    const bool want_w = (dA != nullptr) || (dB != nullptr);
+    const bool lora_only = form == Form::kLoraOnly, want_w = (dA != nullptr) || (dB != nullptr);
     if (desc && want_w && desc->n_adapters > 0 && (!dA || !dB)) {
         plora_status v = validate(desc);
         return v != PLORA_OK ? v : PLORA_ERR_NULL;
     }
     Call c;
-    plora_status ps = prepare(desc, x, W, A, B, want_w ? dA : nullptr, want_w ? dB : nullptr, workspace, ws_bytes, lora_only, c);
+    plora_status ps = prepare(desc, x, W, A, B, want_w ? dA : nullptr, want_w ? dB : nullptr, workspace, ws_bytes, form, c);
     if (ps != PLORA_OK) return ps;
     const HostMeta &m = *c.m;
     const WorkspaceLayout &L = *c.L;
@@ -846,7 +862,7 @@ static plora_status group_forward(const plora_group *g, const void *x, const voi
     SkinnyList shrinks;
     auto run = [&](int p, bool check, unsigned steps) {
         return forward_impl(&g->desc[p], x, W[p], A ? A[p] : nullptr, B ? B[p] : nullptr, y[p], h_saved ? h_saved[p] : nullptr,
-                            ws + gp.ws_off[p], gp.m[p]->ws.total, hip_stream, false, check, steps, &preps, nullptr, &shrinks);
+                            ws + gp.ws_off[p], gp.m[p]->ws.total, hip_stream, Form::kDense, check, steps, &preps, nullptr, &shrinks);
     };
     for (int p = 0; p < gp.n; ++p)
         if ((ps = run(p, true, kStepsAll)) != PLORA_OK) return ps;
@@ -863,7 +879,7 @@ static plora_status group_forward(const plora_group *g, const void *x, const voi
     for (int p = 0; p < gp.n; ++p) {
         whole[p] = gp.m[p]->fwd_parts > 0;
         ps = whole[p] ? forward_impl(&g->desc[p], x, W[p], A ? A[p] : nullptr, B ? B[p] : nullptr, y[p], h_saved ? h_saved[p] : nullptr,
-                                     ws + gp.ws_off[p], gp.m[p]->ws.total, hip_stream, false, false, kStepsAll, nullptr, nullptr, nullptr, &wholes)
+                                     ws + gp.ws_off[p], gp.m[p]->ws.total, hip_stream, Form::kDense, false, kStepsAll, nullptr, nullptr, nullptr, &wholes)
                       : run(p, false, kStepPrep);
         if (ps != PLORA_OK) return ps;
     }
@@ -913,7 +929,7 @@ static plora_status group_backward(const plora_group *g, const void *x, const vo
     auto run = [&](int p, bool check, unsigned steps) {
         return backward_impl(&g->desc[p], x, W[p], A ? A[p] : nullptr, B ? B[p] : nullptr, dy[p], h_saved ? h_saved[p] : nullptr,
                              dx_sum ? dx_sum : (dx ? dx[p] : nullptr), dA ? dA[p] : nullptr, dB ? dB[p] : nullptr, ws + gp.ws_off[p],
-                             gp.m[p]->ws.total, hip_stream, false, check, steps, dx_sum != nullptr && p > 0, &preps, nullptr, &grads, &skinny);
+                             gp.m[p]->ws.total, hip_stream, Form::kDense, check, steps, dx_sum != nullptr && p > 0, &preps, nullptr, &grads, &skinny);
     };
     for (int p = 0; p < gp.n; ++p)
         if ((ps = run(p, true, kStepsAll)) != PLORA_OK) return ps;
@@ -1230,7 +1246,7 @@ plora_status plora_linear_bwd(const plora_desc *desc, const void *x, const void 
 }
 
 // Workspace of the NF4 calls: the ordinary workspace, then the expanded weight.
-static size_t nf4_weight_offset(const HostMeta &m) { return align_up(m.ws.total, 256); }
+static size_t nf4_weight_offset(const HostMeta &m) { return align_up(m.ws_nf4.total, 256); }
 static size_t nf4_weight_bytes(const plora_desc *d) { return (size_t)d->d_in * (size_t)d->d_out * (d->dtype == PLORA_BF16 ? 2 : 4); }
 
 size_t plora_nf4_workspace_bytes(const plora_desc *desc)
@@ -1284,10 +1300,10 @@ plora_status plora_linear_fwd_nf4(const plora_desc *desc, const void *x, const v
         plora_status ps = nf4_prepare(desc, W_codes, W_absmax, workspace, ws_bytes, &W, &inner);
         if (ps != PLORA_OK) return ps;
         // every other argument is checked before the weight is expanded, so that an error enqueues nothing
-        ps = forward_impl(desc, x, W, A, B, y, h_saved, workspace, inner, hip_stream, false, true);
+        ps = forward_impl(desc, x, W, A, B, y, h_saved, workspace, inner, hip_stream, Form::kNf4, true);
         if (ps != PLORA_OK) return ps;
         const Nf4Job job{static_cast<const uint32_t *>(W_codes), W_absmax, W, desc->d_in * desc->d_out};
-        return forward_impl(desc, x, W, A, B, y, h_saved, workspace, inner, hip_stream, false, false, kStepsAll, nullptr, &job);
+        return forward_impl(desc, x, W, A, B, y, h_saved, workspace, inner, hip_stream, Form::kNf4, false, kStepsAll, nullptr, &job);
     )
 }
 
@@ -1300,10 +1316,10 @@ plora_status plora_linear_bwd_nf4(const plora_desc *desc, const void *x, const v
         size_t inner = 0;
         plora_status ps = nf4_prepare(desc, W_codes, W_absmax, workspace, ws_bytes, &W, &inner);
         if (ps != PLORA_OK) return ps;
-        ps = backward_impl(desc, x, W, A, B, dy, h_saved, dx, dA, dB, workspace, inner, hip_stream, false, true);
+        ps = backward_impl(desc, x, W, A, B, dy, h_saved, dx, dA, dB, workspace, inner, hip_stream, Form::kNf4, true);
         if (ps != PLORA_OK) return ps;
         const Nf4Job job{static_cast<const uint32_t *>(W_codes), W_absmax, W, desc->d_in * desc->d_out};
-        return backward_impl(desc, x, W, A, B, dy, h_saved, dx, dA, dB, workspace, inner, hip_stream, false, false, kStepsAll, false, nullptr,
+        return backward_impl(desc, x, W, A, B, dy, h_saved, dx, dA, dB, workspace, inner, hip_stream, Form::kNf4, false, kStepsAll, false, nullptr,
                              dx && desc->T > 0 ? &job : nullptr);
     )
 }
@@ -1320,7 +1336,7 @@ plora_status plora_lora_fwd(const plora_desc *desc, const void *x, const void *c
                             float *h_saved, void *workspace, size_t ws_bytes, void *hip_stream)
 {
     PL_GUARDED(PLORA_ERR_INTERNAL,
-        return forward_impl(desc, x, nullptr, A, B, y, h_saved, workspace, ws_bytes, hip_stream, true);
+        return forward_impl(desc, x, nullptr, A, B, y, h_saved, workspace, ws_bytes, hip_stream, Form::kLoraOnly);
     )
 }
 
@@ -1329,7 +1345,7 @@ plora_status plora_lora_bwd(const plora_desc *desc, const void *x, const void *c
                             void *workspace, size_t ws_bytes, void *hip_stream)
 {
     PL_GUARDED(PLORA_ERR_INTERNAL,
-        return backward_impl(desc, x, nullptr, A, B, dy, h_saved, dx, dA, dB, workspace, ws_bytes, hip_stream, true);
+        return backward_impl(desc, x, nullptr, A, B, dy, h_saved, dx, dA, dB, workspace, ws_bytes, hip_stream, Form::kLoraOnly);
     )
 }
 

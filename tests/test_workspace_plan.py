@@ -92,3 +92,18 @@ def test_the_scratch_array_takes_a_description_within_100_kb_of_its_size():
     """85400 tokens of four adapters of rank 16: 67 061 504 bytes without the records, 67 108 864 is the limit."""
     d = desc(512, 512, [21350] * 4, range(4), [16] * 4)
     assert size_without_records(d) == 67061504 and plora.plora_workspace_bytes(d) <= LIMIT
+
+
+@pytest.mark.parametrize("w_layout", [0, 1])
+@pytest.mark.parametrize("D,K,T,dense_split", [(2816, 6528, 2554, 2), (768, 7296, 6144, 3), (768, 2048, 1024, 1)])
+def test_the_nf4_calls_have_no_room_for_partial_tiles_of_the_dense_ones(D, K, T, dense_split, w_layout):
+    """Their product of an expanded weight is not split here, and their forward never takes the two launches of a short batch: behind
+    the tables and copies there are the partial tiles of shrink, dH and the weight gradients and nothing else.  (The dense calls: a dX in parts,
+    or a shrink's sums and an unsplit product's.)"""
+    d = desc(D, K, [T // 2, T - T // 2], [0, 1], [16, 8], w_layout)
+    info, _, _ = plora.plora_debug_metadata(d)
+    assert info.gemm_splits[1] == dense_split
+    grads = max([s * int(info.r16_total) * w * 4 for s, w in ((info.da_splits, D), (info.db_splits, K)) if s > 1] + [0])
+    dh = int(info.dh_splits) * int(info.n_blocks) * 128 * int(info.max_r16) * 4
+    most = int(info.ws_wpart) + max(grads, dh) + 1024
+    assert plora.lib().plora_nf4_workspace_bytes(d.ref) - 2 * D * K <= most < int(info.ws_total)
