@@ -113,7 +113,7 @@ hipError_t launch_gemm_small_bf16(const GemmPlan &p, const MetaView &mv, const M
 // The line is drawn where neither side loses; for a weight that the call itself has just written (w_cached: NF4) at 0.93.  More than
 // four parts only for weights of 64 MB and more, and below 80 MB no column tile that is partly empty: these would gain too (1000 x 14336 ->
 // 2048 99 and 87, 700 x 8200 -> 4104 92 and 78), but what such products run on is pinned by tests of the small tiles as it was.
-GemmPlan gemm_plan(int64_t T, int64_t Kd, int64_t N, int max_ext, bool w_cached, double max_split_bytes)
+GemmPlan gemm_plan(int64_t T, int64_t Kd, int64_t N, int max_ext, bool w_cached, double big_split_bytes)
 {
     constexpr double kCus = 256.0;                             // compute units of an MI355X
     const double nk = (double)((Kd + GS_BK - 1) / GS_BK);
@@ -131,7 +131,7 @@ GemmPlan gemm_plan(int64_t T, int64_t Kd, int64_t N, int max_ext, bool w_cached,
     for (int bm = 64; bm <= 128; bm += 64) {
         const double tiles = tiles_of(bm, GS_BN), t1 = bm == 64 ? 0.24 : 0.62;
         for (int z = 1; z <= 16; ++z) {
-            if (tiles * z > 4.0 * kCus || (z > 1 && (nk < 4.0 * z || (double)z * T * N * 4 > 64e6))) break;
+            if (tiles * z > 4.0 * kCus || (z > 1 && (nk < 4.0 * z || (double)z * T * N * 4 > kMaxSplitBytes))) break;
             const double steps = (double)(int64_t)((nk + z - 1.0) / z);
             double us = steps * stage_us(tiles * z, 2.0 * kCus, 0.38, t1);
             const double stream = stream_us * (tiles * z < kCus ? kCus / (tiles * z) : 1.0);
@@ -153,7 +153,7 @@ GemmPlan gemm_plan(int64_t T, int64_t Kd, int64_t N, int max_ext, bool w_cached,
     GemmPlan split{0, 1, (int)all256};
     double split_us = bound * best_us;
     for (int z = 2; z <= (w_bytes >= 64e6 ? 6 : 4); ++z) {
-        if (tiles * z > kCus || nk < 8.0 * z || (double)z * T * N * 4 > max_split_bytes) break;
+        if (tiles * z > kCus || nk < 8.0 * z || (double)z * T * N * 4 > big_split_bytes) break;
         if (tiles * z < 0.75 * kCus) continue;
         // the first part has all extension steps: with more of them than a part has steps (many short segments) it runs longer.
         // 88 tokens of 29 adapters, 4480 -> 9984: 29 steps against 12, 38 us in small tiles and 83

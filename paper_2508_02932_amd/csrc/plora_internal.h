@@ -558,8 +558,8 @@ struct GemmPlan {
 };
 constexpr double kMaxSplitBytes = 64e6;       // fp32 partial tiles of a split product
 // w_cached: W has just been written, so that the last-level cache holds what fits of it
-// max_ext: most extension steps of a 256-row tile
-GemmPlan gemm_plan(int64_t T, int64_t Kd, int64_t N, int max_ext, bool w_cached, double max_split_bytes = kMaxSplitBytes);
+// max_ext: most extension steps of a 256-row tile; big_split_bytes: room for the partial tiles of split 256 x 256 tiles
+GemmPlan gemm_plan(int64_t T, int64_t Kd, int64_t N, int max_ext, bool w_cached, double big_split_bytes = kMaxSplitBytes);
 hipError_t launch_gemm_small_bf16(const GemmPlan &p, const MetaView &mv, const MetaHeader &h, bool w_rows_contract, int64_t Kd, int64_t N,
                                   const void *S, const void *W, const void *side, const void *ap, const void *zero, void *C,
                                   bool accumulate, float *part, hipStream_t st);
