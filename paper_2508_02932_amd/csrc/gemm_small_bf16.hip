@@ -110,11 +110,22 @@ hipError_t launch_gemm_small_bf16(const GemmPlan &p, const MetaView &mv, const M
 //     1.12  512 x 5120 -> 13824  103 and 93 (90 and 90)
 //     1.19  512 x 4096 -> 14336  87 and 83 (77 and 81)
 //     1.25  512 x 4096 -> 8192   70 and 61 (56 and 60)          2048 x 4096 -> 2048   61 and 65 (59 and 62)
+// Not up to 64 tokens, which fill a quarter of a 256-row tile (8 tokens, 8192 -> 8192 32 and 49; 48 tokens, 14336 -> 8192 54 and 77; 26 tokens,
+// 6800 -> 8064, seven adapters 46 and 66).  The first part has all extension steps, and walks the segment table for them: from the seventh on
+// each costs 2.5 us (1 where the contraction lies along W's rows) more than the small tiles pay, which share them (80 tokens, 8192 -> 8192, one adapter 54
+// and 57, eight of rank 64 57 and 91, sixteen of rank 32 56 and 103; 512 tokens, 8192 -> 14336, 128 adapters 247 and 344; from 2048 tokens on both
+// sides pay alike: 3000 tokens, 16384 -> 1024, 128 adapters 267 and 249, 256 adapters 413 and 408; in between, 2000 tokens, 8192 -> 2048, 256 adapters
+// 251 and 286, for the split ones are far ahead without them: 123 and 103).  And where small tiles in three parts or more would run
+// in two launches with the shrink, the launch that the 256-tiles give up is worth 12 us (640 tokens, 8192 -> 4096 69 and 79, 14336 -> 4096 104 and 112; 330
+// tokens, 7168 -> 7168 67 and 78), unless rows of W share lines of 128 bytes, for which small tiles are slower (72 tokens, 11464 -> 16824 165
+// and 121; 256 tokens, 6800 -> 8064 77 and 66).  Of 730 products these lines make 27 slower than small tiles, by 2 to 17 % (80 tokens, 5120 -> 13824, four adapters
+// 56 and 65), and leave 8 in small tiles that would gain, up to 11 %; without them 123 were slower, up to 1.83 times.
 // The line is drawn where neither side loses; for a weight that the call itself has just written (w_cached: NF4) at 0.93.  More than
 // four parts only for weights of 64 MB and more, and below 80 MB no column tile that is partly empty: these would gain too (1000 x 14336 ->
 // 2048 99 and 87, 700 x 8200 -> 4104 92 and 78), but what such products run on is pinned by tests of the small tiles as it was.
-GemmPlan gemm_plan(int64_t T, int64_t Kd, int64_t N, int max_ext, bool w_cached, double big_split_bytes)
+GemmPlan gemm_plan(const GemmShape &s, double big_split_bytes)
 {
+    const int64_t T = s.T, Kd = s.Kd, N = s.N;
     constexpr double kCus = 256.0;                             // compute units of an MI355X
     const double nk = (double)((Kd + GS_BK - 1) / GS_BK);
     auto tiles_of = [&](int64_t bm, int64_t bn) { return (double)((T + bm - 1) / bm) * (double)((N + bn - 1) / bn); };
@@ -149,19 +160,20 @@ GemmPlan gemm_plan(int64_t T, int64_t Kd, int64_t N, int max_ext, bool w_cached,
         if (us < 0.97 * best_us) { best_us = us; best = GemmPlan{bm, 1, (int)big}; }
     }
     // 256 x 256 tiles with the contraction split
-    const double tiles = tiles_of(256, 256), w_bytes = (double)Kd * N * 2, bound = best.bm == 0 ? 1.0 : w_cached ? 0.93 : 1.12;
+    const double tiles = tiles_of(256, 256), w_bytes = (double)Kd * N * 2, bound = best.bm == 0 ? 1.0 : s.w_cached ? 0.93 : 1.12;
+    const double ext_us = all256 >= 8 || s.max_ext <= 6 ? 0.0 : (s.max_ext - 6) * (s.w_rows_contract ? 2.5 : 1.0);
+    const bool whole_lines = (s.w_rows_contract ? N : Kd) % 64 == 0;
+    const double lost_us = ext_us + (s.short_shrink && product_in_two_launches(best, T, N) && best.n_split >= 3 && whole_lines ? 12.0 : 0.0);
     GemmPlan split{0, 1, (int)all256};
     double split_us = bound * best_us;
     for (int z = 2; z <= (w_bytes >= 64e6 ? 6 : 4); ++z) {
         if (tiles * z > kCus || nk < 8.0 * z || (double)z * T * N * 4 > big_split_bytes) break;
         if (tiles * z < 0.75 * kCus) continue;
-        // the first part has all extension steps: with more of them than a part has steps (many short segments) it runs longer.
-        // 88 tokens of 29 adapters, 4480 -> 9984: 29 steps against 12, 38 us in small tiles and 83
-        const double steps = std::max((double)(int64_t)((nk + z) / z), (double)max_ext);
-        const double us = steps * (0.92 + 0.68 * tiles * z / kCus) + 4.0 + 0.2 * z + (double)z * T * N * 8 / 7.5e6;
+        const double steps = std::max((double)(int64_t)((nk + z) / z), (double)s.max_ext);
+        const double us = lost_us + steps * (0.92 + 0.68 * tiles * z / kCus) + 4.0 + 0.2 * z + (double)z * T * N * 8 / 7.5e6;
         if (us < split_us) { split_us = us; split.n_split = z; }
     }
-    if (split.n_split > 1 && best.big_tiles * best.bm == 0 && (w_bytes >= 80e6 || (double)N >= 0.98 * 256.0 * (double)((N + 255) / 256))) return split;
+    if (T > 64 && split.n_split > 1 && best.big_tiles * best.bm == 0 && (w_bytes >= 80e6 || (double)N >= 0.98 * 256.0 * (double)((N + 255) / 256))) return split;
     return best;
 }
 

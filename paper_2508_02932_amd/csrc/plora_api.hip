@@ -151,9 +151,14 @@ static void build_meta(const plora_desc *d, HostMeta &m)
     const bool bf = d->dtype == PLORA_BF16;
     int max_ext = 0;
     for (int64_t i = 0; i < m.layout.n_tiles; ++i) max_ext = std::max(max_ext, (int)m.t.tile[i].n_ext);
+    const bool w_out_in = m.hdr.w_out_in != 0;
+    const bool short_shrink = bf && m.hdr.n_blocks > 0 && m.n_words <= kChunkWords && skinny_is_short(m.hdr, m.slices16, m.r16_total, d->d_in);
+    GemmShape fwd_shape[2], dx_shape[2];
     for (int i = 0; i < 2; ++i) {
-        m.gemm_fwd[i] = gemm_plan(d->T, d->d_in, d->d_out, max_ext, i == 1);
-        m.gemm_dx[i] = gemm_plan(d->T, d->d_out, d->d_in, max_ext, i == 1);
+        fwd_shape[i] = GemmShape{d->T, d->d_in, d->d_out, !w_out_in, i == 1, short_shrink && i == 0, max_ext};
+        dx_shape[i] = GemmShape{d->T, d->d_out, d->d_in, w_out_in, i == 1, false, max_ext};
+        m.gemm_fwd[i] = gemm_plan(fwd_shape[i]);
+        m.gemm_dx[i] = gemm_plan(dx_shape[i]);
     }
     auto split_bytes = [&](const GemmPlan &p, int64_t N) { return p.n_split > 1 ? (size_t)p.n_split * d->T * N * 4 : (size_t)0; };
     auto fwd_bytes = [&]() { return std::max(split_bytes(m.gemm_fwd[0], d->d_out), split_bytes(m.gemm_fwd[1], d->d_out)); };
@@ -211,7 +216,7 @@ static void build_meta(const plora_desc *d, HostMeta &m)
                 // then cut part by part.  Planned within less room as well they would mostly be whole; 24 such steps, us, cut and whole: 3 %
                 // for the whole ones on average (880 x 27696 -> 3280 630 and 553, 1304 x 3208 -> 21360 691 and 644), but 498 x 10600 ->
                 // 15648 554 and 610, 396 x 15104 -> 10360 472 and 519, 433 x 10016 -> 14096 506 and 549, 758 x 6928 -> 24568 806 and 846
-                if (p.bm == 0) p = gemm_plan(d->T, fwd > dx ? d->d_in : d->d_out, fwd > dx ? d->d_out : d->d_in, max_ext, i == 1, (double)std::max(fwd, dx) - 1.0);
+                if (p.bm == 0) p = gemm_plan(fwd > dx ? fwd_shape[i] : dx_shape[i], (double)std::max(fwd, dx) - 1.0);
                 else p.n_split -= 1;
             }
         } else if (m.hdr.n_blocks > 0 && skinny_cap > 1) {
@@ -248,8 +253,7 @@ static void build_meta(const plora_desc *d, HostMeta &m)
     // 2048 -> 6144 (2.4 M sums) 38.1 and 35.1, 300 x 512 -> 8192 (2.5 M) 23.6 and 22.6, 400 x 768 -> 8192 (3.3 M) 28.7 and 29.3, 1500 x 768 ->
     // 2048 (3.1 M) 25.0 and 26.8, 2048 x 512 -> 3072 (6.3 M) 27.9 and 35.5.  Both sets of partial sums are needed at once.
     const GemmPlan &p = m.gemm_fwd[0];
-    if (bf && m.hdr.n_blocks > 0 && m.n_words <= kChunkWords && p.bm != 0 && p.big_tiles == 0 && (p.n_split > 1 || d->T * d->d_out <= 2250000) &&
-        skinny_is_short(m.hdr, m.slices16, m.r16_total, d->d_in)) {
+    if (short_shrink && product_in_two_launches(p, d->T, d->d_out)) {
         const int n = short_shares(m.hdr, m.slices16, d->d_in, m.short_cap()).n;
         const size_t parts = align_up((size_t)n * m.slices_all * 16 * m.hdr.max_r16 * 4, 256);
         const size_t end = align_up(m.ws.part + parts + (size_t)p.n_split * d->T * d->d_out * 4, 256) + 256;

@@ -556,10 +556,22 @@ struct GemmPlan {
     int n_split;              // splits of the contraction; above 1 the fp32 partial tiles take n_split * T * N * 4 bytes
     int big_tiles;            // row tiles that k_gemm computes (all of them when bm is 0); the small tiles compute the rest
 };
+struct GemmShape {
+    int64_t T, Kd, N;
+    bool w_rows_contract;     // as in launch_gemm_bf16
+    bool w_cached;            // W has just been written, so that the last-level cache holds what fits of it
+    bool short_shrink;        // behind a short shrink: small tiles may be part of a forward in two launches
+    int max_ext;              // most extension steps of a 256-row tile
+};
 constexpr double kMaxSplitBytes = 64e6;       // fp32 partial tiles of a split product
-// w_cached: W has just been written, so that the last-level cache holds what fits of it
-// max_ext: most extension steps of a 256-row tile; big_split_bytes: room for the partial tiles of split 256 x 256 tiles
-GemmPlan gemm_plan(int64_t T, int64_t Kd, int64_t N, int max_ext, bool w_cached, double big_split_bytes = kMaxSplitBytes);
+// big_split_bytes: room for the partial tiles of split 256 x 256 tiles
+GemmPlan gemm_plan(const GemmShape &s, double big_split_bytes = kMaxSplitBytes);
+// Whether a base product with this plan can be part of a forward in two launches (gemm_short_bf16.hip): in small tiles alone that are
+// split anyway, or whose one set of fp32 sums costs less than the launch saved (build_meta has the figures).
+inline bool product_in_two_launches(const GemmPlan &p, int64_t T, int64_t N)
+{
+    return p.bm != 0 && p.big_tiles == 0 && (p.n_split > 1 || T * N <= 2250000);
+}
 hipError_t launch_gemm_small_bf16(const GemmPlan &p, const MetaView &mv, const MetaHeader &h, bool w_rows_contract, int64_t Kd, int64_t N,
                                   const void *S, const void *W, const void *side, const void *ap, const void *zero, void *C,
                                   bool accumulate, float *part, hipStream_t st);
