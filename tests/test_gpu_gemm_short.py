@@ -33,6 +33,18 @@ def finish_workgroups(lengths, K, n=1):
     return n * sum((v + 15) // 16 for v in lengths) * ((K + 127) // 128)
 
 
+def counted(call):
+    """Brackets of the classes base product, shrink and preparation that a call records."""
+    import torch
+    plora.plora_set_kernel_timing(True)
+    try:
+        call()
+        torch.cuda.synchronize()
+        return tuple(plora.plora_kernel_time(c)[1] for c in (0, 2, 6))
+    finally:
+        plora.plora_set_kernel_timing(False)
+
+
 def takes_two_launches(desc, tile_rows, split):
     info = plora.plora_debug_metadata(desc)[0]
     assert info.desc_words <= 896 and info.short_shares[0] > 0
@@ -55,7 +67,8 @@ def test_two_launches(case, save_h, w_layout):
     takes_two_launches(gh.desc_of(lin, w_layout), *CASES[case][5:])
     D, K, lengths = CASES[case][:3]
     assert (finish_workgroups(lengths, K) > 1024) == (case in WIDE)
-    run_and_compare(lin, impl=oracle.matmul, save_h=save_h, w_layout=w_layout)
+    dp, _ = run_and_compare(lin, impl=oracle.matmul, save_h=save_h, w_layout=w_layout)
+    assert counted(lambda: gh.forward(dp, save_h)) == (1, 0, 0)        # shrink, preparation and product in one bracket
 
 
 @pytest.mark.parametrize("w_layouts", [(0, 0, 0), (1, 0, 1)])
@@ -75,16 +88,15 @@ def test_group_is_bitwise_the_plain_calls(w_layouts):
     want = [(dp.y.clone(), dp.h.clone()) for dp in dps]
     for dp in dps:
         dp.y.fill_(float("nan")); dp.h.fill_(float("nan"))
-    group_is_the_plain_calls(dps, want)
+    group_is_the_plain_calls(dps, want, 1)
 
 
-def group_is_the_plain_calls(dps, want):
+def group_is_the_plain_calls(dps, want, brackets):
     import torch
     lists = lambda name: [getattr(dp, name) for dp in dps]
     group = plora.Group(lists("desc"))
     ws = torch.empty(plora.plora_group_workspace_bytes(group), dtype=torch.uint8, device="cuda")
-    plora.plora_group_fwd(group, dps[0].x, lists("W"), lists("A"), lists("B"), lists("y"), lists("h"), ws)
-    torch.cuda.synchronize()
+    assert counted(lambda: plora.plora_group_fwd(group, dps[0].x, lists("W"), lists("A"), lists("B"), lists("y"), lists("h"), ws)) == (brackets, 0, 0)
     for dp, (y, h) in zip(dps, want):
         n = plora.plora_h_elems(dp.desc)
         assert torch.equal(dp.y, y) and torch.equal(dp.h[:n], h[:n])
@@ -107,4 +119,4 @@ def test_group_with_the_wide_finish(w_layout):
     want = [(dp.y.clone(), dp.h.clone()) for dp in dps]
     for dp in dps:
         dp.y.fill_(float("nan")); dp.h.fill_(float("nan"))
-    group_is_the_plain_calls(dps, want)
+    group_is_the_plain_calls(dps, want, 1)
