@@ -12,6 +12,9 @@ PLANS = {
     # T, D, K, segments, plan of the forward product, plan of dX
     "three_parts": (2000, 8200, 2040, 3, (0, 3, 8), (64, 1, 7)),
     "four_parts": (900, 8200, 3064, 5, (0, 4, 4), (64, 1, 0)),
+    "five_parts": (520, 11272, 4104, 5, (0, 5, 3), (128, 1, 0)),
+    "six_parts": (400, 14344, 4104, 5, (0, 6, 2), (0, 2, 2)),
+    "six_parts_dx": (400, 4104, 14344, 2, (0, 2, 2), (0, 6, 2)),
     "dx": (3900, 1016, 6008, 9, (0, 1, 16), (0, 3, 16)),                    # four parts would push the workspace past the scratch array
     "many_segments": (2000, 8200, 2040, 295, (0, 3, 8), (64, 1, 7)),      # 49 extension steps in a row tile, 44 steps in a part
     "short_segments": (88, 9984, 4480, 29, (64, 4, 0), (64, 2, 0)),       # so many that small tiles, which share them, are faster
