@@ -42,7 +42,7 @@ constexpr int BM = 256, BN = 256;
 
 // no-ops behind the alignment point in front of the kernel's loops, per form (see the kernel)
 #ifndef PLORA_GEMM_PAD_FWD
-#define PLORA_GEMM_PAD_FWD 1
+#define PLORA_GEMM_PAD_FWD 6
 #endif
 #ifndef PLORA_GEMM_PAD_DX
 #define PLORA_GEMM_PAD_DX 4
@@ -453,8 +453,8 @@ __global__ void __launch_bounds__(512) k_gemm(const GemmTile *__restrict__ tiles
 
     // Placement of the loops below in the instruction stream, fixed here so that it does not move when code above
     // changes: a 256-byte boundary plus a few 4-byte no-ops.  The kernel's time depends on where its loops fall
-    // inside the 32-byte windows instructions are fetched in, by up to 10 % at the largest shapes (8192 -> 28672,
-    // 32768 tokens: 12.15 to 13.43 ms over the eight possible offsets for the first form, 11.50 to 12.33 ms for the
+    // inside the 32-byte windows instructions are fetched in, by up to 8 % at the largest shapes (8192 -> 28672,
+    // 32768 tokens: 12.16 to 13.09 ms over the eight possible offsets for the first form, 11.38 to 11.89 ms for the
     // second) and through a second-order effect: compute units that share an instruction cache fall a few cycles out
     // of step with one another, and that decides whether the workgroups that stream the same rows of S and columns
     // of W ask the L2 for a line one after the other (one miss, the rest hits) or at the same instant (every one a
