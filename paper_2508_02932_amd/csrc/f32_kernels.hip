@@ -7,10 +7,11 @@
 // the kernels follows from that: small output tiles for many workgroups, the contraction of a tile dealt to its waves in
 // pairs of chunks of 16, operands straight from memory into registers (no staging, no barrier until the waves' sums meet in LDS), the
 // next two chunks (16 x 16 outputs: five) in flight while one is multiplied.  Four waves per SIMD: an operand of 16 elements a chunk and
-// nothing kept across tiles leaves room for that without a spill, and then the tiles of a batch are on the chip all at once (two waves,
-// chunks of 32: 600 tiles took two rounds of 512).  Measured (256-token configuration, then 777 tokens, 500 -> 750, in us; a launch that does
-// nothing takes 2.5 - 3): base product 49 and 145 with 64 x 64 tiles on the vector ALU, 11 and 29 at two waves per SIMD, now 6 and 23
-// (the matrix instructions alone: 8.3 on average over the SIMDs, 12 where three tiles meet); weight gradients with the gradient
+// nothing kept across tiles leaves room for that (one form, the forward with W [d_out][d_in] in 32 x 32 tiles, spills two registers, outside its
+// main loop), and then the tiles of a batch are on the chip all at once (two waves, chunks of 32: 600 tiles took two rounds of 512).
+// Measured (256-token configuration, then 777 tokens, 500 -> 750, in us; a launch that does nothing takes 2.5 - 3): base product 49 and 145 with 64 x 64 tiles on the vector ALU, 11 and 29 at two waves per SIMD, now 6 and 23
+// (the matrix instructions alone: 8.3 on average over the SIMDs, 12 where three tiles meet; a wave lives 15, of which it waits 58 % to issue,
+// mostly for the matrix instructions of the others on its SIMD, and 26 % for loads and the LDS); weight gradients with the gradient
 // of x 11 and 29.5, now 7 and 24.5; low-rank products beside the preparation 5.7 and 8.2.  The whole step: 322 -> 33 -> 22.8 and 1948 -> 73 -> 60.
 // Larger ones, 4 adapters of rank 16: 1024 tokens, 1024 -> 1024 138 -> 103; 4096 tokens, 4096 -> 4096 5500 -> 4380 (63 TFLOP/s of
 // the nominal 78.6).

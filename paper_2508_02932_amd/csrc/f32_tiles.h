@@ -90,8 +90,8 @@ __device__ inline void multiply_chunk(const float (*a)[4], const float (*b)[4], 
 
 // In front of the first vector-ALU read of a matrix instruction's sums.  The compiler pads that distance itself, but not where
 // the two meet at a join of branches: a loop that kept its sums in accumulation registers read the last of them one instruction
-// behind the product (seen in its assembly; rows 12 to 15 of a tile were wrong).  The kernels below are therefore bounded to four
-// waves per SIMD, at which the compiler leaves the sums in vector registers (build.py refuses anything else), and wait here.
+// behind the product (seen in its assembly; rows 12 to 15 of a tile were wrong).  The kernels of this path are therefore bounded
+// to four waves per SIMD (k_f32_lowrank: two), at which the compiler leaves the sums in vector registers (build.py refuses anything else), and wait here.
 template <int RB, int CB> __device__ inline void settle(f64x4 (*acc)[CB])
 {
 #pragma unroll

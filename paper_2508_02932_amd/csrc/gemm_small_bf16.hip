@@ -101,28 +101,31 @@ hipError_t launch_gemm_small_bf16(const GemmPlan &p, const MetaView &mv, const M
 // small tiles instead (two launches; us, 256-tile kernel alone and now: 4400 x 4096 -> 4096 184 and 151, 5000 tokens 182 and
 // 157, 10000 x 2048 -> 2048 99 and 87, 9000 x 4096 -> 4096 286 and 261, 13000 393 and 366, 6144 183 and 179).  A split keeps four stages or more; the partial tiles stay below 64 MB.
 // The 256 x 256 tiles split as well, where that fills three quarters of the compute units: a stage then moves half the bytes into
-// LDS for each product.  Estimated as above (0.92 + 0.68 f a stage, the partial tiles at 7.5 TB/s).  Whole forward calls, us, small tiles and
-// split 256-tiles, W from HBM as in a model that walks its layers (in brackets: from the last-level cache); r = ratio of the estimates:
-//   r 0.84  768 x 14336 -> 4096  135 and 109 (117 and 103)      3000 x 16384 -> 1024  177 and 139 (160 and 130)
-//     0.90  1280 x 8192 -> 4096  136 and 103 (108 and 100)
-//     0.96  1024 x 14336 -> 4096 164 and 139 (131 and 133)      512 x 14336 -> 4096   93 and 86 (85 and 83)
-//     1.00  512 x 8192 -> 8192   122 and 90 (92 and 88)         4096 x 8192 -> 1024   139 and 107 (114 and 101)
-//     1.12  512 x 5120 -> 13824  103 and 93 (90 and 90)
-//     1.19  512 x 4096 -> 14336  87 and 83 (77 and 81)
-//     1.25  512 x 4096 -> 8192   70 and 61 (56 and 60)          2048 x 4096 -> 2048   61 and 65 (59 and 62)
-// Not up to 64 tokens, which fill a quarter of a 256-row tile (8 tokens, 8192 -> 8192 32 and 49; 48 tokens, 14336 -> 8192 54 and 77; 26 tokens,
-// 6800 -> 8064, seven adapters 46 and 66).  The first part has all extension steps, and walks the segment table for them: from the seventh on
-// each costs 2.5 us (1 where the contraction lies along W's rows) more than the small tiles pay, which share them (80 tokens, 8192 -> 8192, one adapter 54
-// and 57, eight of rank 64 57 and 91, sixteen of rank 32 56 and 103; 512 tokens, 8192 -> 14336, 128 adapters 247 and 344; from 2048 tokens on both
-// sides pay alike: 3000 tokens, 16384 -> 1024, 128 adapters 267 and 249, 256 adapters 413 and 408; in between, 2000 tokens, 8192 -> 2048, 256 adapters
-// 251 and 286, for the split ones are far ahead without them: 123 and 103).  And where small tiles in three parts or more would run
-// in two launches with the shrink, the launch that the 256-tiles give up is worth 12 us (640 tokens, 8192 -> 4096 69 and 79, 14336 -> 4096 104 and 112; 330
-// tokens, 7168 -> 7168 67 and 78), unless rows of W share lines of 128 bytes, for which small tiles are slower (72 tokens, 11464 -> 16824 165
-// and 121; 256 tokens, 6800 -> 8064 77 and 66).  Of 730 products these lines make 27 slower than small tiles, by 2 to 17 % (80 tokens, 5120 -> 13824, four adapters
-// 56 and 65), and leave 8 in small tiles that would gain, up to 11 %; without them 123 were slower, up to 1.83 times.
-// The line is drawn where neither side loses; for a weight that the call itself has just written (w_cached: NF4) at 0.93.  More than
-// four parts only for weights of 64 MB and more, and below 80 MB no column tile that is partly empty: these would gain too (1000 x 14336 ->
-// 2048 99 and 87, 700 x 8200 -> 4104 92 and 78), but what such products run on is pinned by tests of the small tiles as it was.
+// LDS for each product.  Estimated as above (0.92 + 0.68 f a stage, the partial tiles at 7.5 TB/s).  Whole backward calls without weight
+// gradients, us, T x contraction -> columns, small tiles and split 256-tiles, W from HBM as in a model that walks its layers; r = ratio of the estimates:
+//   r 0.80  768 x 28672 -> 4096  236 and 187      0.87  400 x 8296 -> 10368  183 and 112      0.91  768 x 8064 -> 6800   132 and 107
+//     0.96  1024 x 14336 -> 4096 163 and 140      0.98  192 x 14336 -> 8192  98 and 91        1.00  512 x 8192 -> 14336  149 and 134
+//     1.03  320 x 8192 -> 8192   89 and 83        1.09  330 x 7680 -> 5312   60 and 60        1.11  256 x 4096 -> 8192   51 and 50
+//     1.12  320 x 8192 -> 14336  139 and 123      1.16  128 x 4096 -> 8192   39 and 41        1.19  512 x 4096 -> 14336  85 and 87
+//     1.22  256 x 4096 -> 14336  68 and 69        1.24  128 x 4096 -> 14336  49 and 61        1.27  320 x 4096 -> 14336  79 and 75
+// The line is drawn at 1.12; for a weight that the call itself has just written (w_cached: NF4) at 0.93, for small tiles gain more from the
+// last-level cache (forward calls with W there: 1024 x 14336 -> 4096 131 and 133, 512 x 4096 -> 8192 56 and 60).
+// Six parts at most: seven and eight at 62 products that six put on three quarters of the compute units or more took 0.95 to 1.24 times as
+// long, 1.03 on average (192 x 8192 -> 8192 62 and 71, 400 x 14336 -> 4096 90 and 86).  Below three quarters the best of six and eight parts ran 36
+// products in 0.79 to 1.22 times the time of small tiles, 0.97 on average, and the estimate does not tell them apart (128 x 13824 -> 5120, 160
+// workgroups, 75 and 63; 192 x 8192 -> 4096, 128 workgroups, 39 and 48).  More than four parts only for weights of 64 MB and more, and below 80 MB
+// no column tile that is partly empty: these would gain too (1000 x 14336 -> 2048 99 and 87, 700 x 8200 -> 4104 92 and 78), but what such
+// products run on is pinned by tests of the small tiles as it was.
+// Not up to 64 tokens, which fill a quarter of a 256-row tile (forward calls: 8 x 8192 -> 8192 32 and 49, 48 x 14336 -> 8192 54 and 77, 26 x
+// 6800 -> 8064, seven adapters, 46 and 66).  The first part has all extension steps and walks the segment table for them: from the seventh on
+// each costs 2.5 us (1 where the contraction lies along W's rows) more than the small tiles pay, which share them (80 x 8192 -> 8192, one adapter
+// 54 and 57, eight of rank 64 57 and 91, sixteen of rank 32 56 and 103; 512 x 8192 -> 14336, 128 adapters, 247 and 344).  With eight row tiles and
+// more few segments meet in one of them, and both sides pay alike (3000 x 16384 -> 1024, 128 adapters 267 and 249, 256 adapters 413 and 408; 2000 x
+// 8192 -> 2048 128 and 106 for one adapter, 251 and 286 for 256).  And where small tiles in three parts or more would run in two launches
+// with the shrink, the launch that the 256-tiles give up is worth 12 us (640 x 8192 -> 4096 69 and 79, 640 x 14336 -> 4096 104 and 112, 330 x 7168 ->
+// 7168 67 and 78), unless rows of W share lines of 128 bytes, for which small tiles are slower (72 x 11464 -> 16824 165 and 121, 256 x 6800
+// -> 8064 77 and 66).  Of 730 products that the estimates alone would split these lines leave 27 slower than in small tiles, by 2 to 17 % (80 x
+// 5120 -> 13824, four adapters, 56 and 65), and keep 8 in small tiles that would gain, up to 11 %; without them 123 were slower, up to 1.83 times.
 GemmPlan gemm_plan(const GemmShape &s, double big_split_bytes)
 {
     const int64_t T = s.T, Kd = s.Kd, N = s.N;

@@ -249,9 +249,10 @@ static void build_meta(const plora_desc *d, HostMeta &m)
     lay_out(m.ws_lora, m.layout.bytes, (size_t)(rp_total * std::max(d->d_in, d->d_out)), false, flag_bytes);
     m.skinny_cap = skinny_cap;
     // Forward in two launches: where the shrink is short and the base product is split anyway, or its one set of fp32 sums costs less
-    // than the launch saved.  Whole calls, us, before and now: 2048 x 1024 -> 1024 27.5 and 24.2, 512 x 1024 -> 4096 24.1 and 23.0, 384 x
-    // 2048 -> 6144 (2.4 M sums) 38.1 and 35.1, 300 x 512 -> 8192 (2.5 M) 23.6 and 22.6, 400 x 768 -> 8192 (3.3 M) 28.7 and 29.3, 1500 x 768 ->
-    // 2048 (3.1 M) 25.0 and 26.8, 2048 x 512 -> 3072 (6.3 M) 27.9 and 35.5.  Both sets of partial sums are needed at once.
+    // than the launch saved.  Both ways at 84 unsplit products, time in two launches over that in three: up to 1.4 M sums 0.78 to 0.79, 1.4 - 1.9 M
+    // 0.75 to 0.93, 1.9 - 2.4 M 0.70 to 1.01 (2020 x 968 -> 1080 26.6 and 26.9 us), 2.4 - 2.6 M 0.87 to 1.01, 2.6 - 3.1 M 0.85 to 1.09 (1588 x 760 -> 1720 23.1 and
+    // 25.1), 3.1 - 3.6 M 0.94 to 1.12 (2139 x 800 -> 1512 32.9 and 36.9).  The line is drawn below the first of them that lose.  Both sets of partial
+    // sums are needed at once.
     const GemmPlan &p = m.gemm_fwd[0];
     if (short_shrink && product_in_two_launches(p, d->T, d->d_out)) {
         const int n = short_shares(m.hdr, m.slices16, d->d_in, m.short_cap()).n;
