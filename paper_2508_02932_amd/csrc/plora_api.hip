@@ -881,11 +881,21 @@ static plora_status group_forward(const plora_group *g, const void *x, const voi
     for (int p = 0; p < gp.n; ++p)
         for (int q = 0; q < gp.n; ++q)
             fused[p] = fused[p] || (q != p && gp.cell_of[q] == gp.cell_of[p] && !short_shrink(gp, p, d0) && !short_shrink(gp, q, d0));
-    // projections whose plain call takes two launches in all take those together, and no step of the group's
-    bool whole[kMaxGroup];
+    // Projections whose plain call takes two launches in all take those together, and no step of the group's.  Where others need these
+    // steps anyway, unsplit products do so only up to 2.5 M sums in all (their bits are the same either way): 43 such groups, us, together
+    // and not: 461 x 1024 -> 5408, 1352, 1352 (1.25 M) 184 and 199, 1575 x 1792 -> 2944, 736, 736 (2.3 M) 179 and 186, 3183 x 1144 -> 1664, 416, 416
+    // (2.6 M) 173 and 168, 1240 x 864 -> 4904, 1224, 1224 (3.0 M) 230 and 215, 3684 x 640 -> 2304, 576, 576 (4.2 M) 214 and 188.  Groups that take the
+    // two launches whole gain up to the largest there are (4.4 M, 1008 x 1536 -> 2176, 2176 133 and 141).
+    bool whole[kMaxGroup], all_whole = true;
+    int64_t sums = 0;
+    for (int p = 0; p < gp.n; ++p) {
+        const HostMeta &m = *gp.m[p];
+        all_whole = all_whole && m.fwd_parts > 0;
+        if (m.fwd_parts > 0 && m.gemm_fwd[0].n_split == 1) sums += d0->T * g->desc[p].d_out;
+    }
     ForwardList wholes;
     for (int p = 0; p < gp.n; ++p) {
-        whole[p] = gp.m[p]->fwd_parts > 0;
+        whole[p] = gp.m[p]->fwd_parts > 0 && (all_whole || gp.m[p]->gemm_fwd[0].n_split > 1 || sums <= 2500000);
         ps = whole[p] ? forward_impl(&g->desc[p], x, W[p], A ? A[p] : nullptr, B ? B[p] : nullptr, y[p], h_saved ? h_saved[p] : nullptr,
                                      ws + gp.ws_off[p], gp.m[p]->ws.total, hip_stream, Form::kDense, false, kStepsAll, nullptr, nullptr, nullptr, &wholes)
                       : run(p, false, kStepPrep);

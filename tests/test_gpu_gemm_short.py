@@ -88,7 +88,7 @@ def test_group_is_bitwise_the_plain_calls(w_layouts):
     want = [(dp.y.clone(), dp.h.clone()) for dp in dps]
     for dp in dps:
         dp.y.fill_(float("nan")); dp.h.fill_(float("nan"))
-    group_is_the_plain_calls(dps, want, 1)
+    group_is_the_plain_calls(dps, want, (1, 0, 0))
 
 
 def group_is_the_plain_calls(dps, want, brackets):
@@ -96,7 +96,7 @@ def group_is_the_plain_calls(dps, want, brackets):
     lists = lambda name: [getattr(dp, name) for dp in dps]
     group = plora.Group(lists("desc"))
     ws = torch.empty(plora.plora_group_workspace_bytes(group), dtype=torch.uint8, device="cuda")
-    assert counted(lambda: plora.plora_group_fwd(group, dps[0].x, lists("W"), lists("A"), lists("B"), lists("y"), lists("h"), ws)) == (brackets, 0, 0)
+    assert counted(lambda: plora.plora_group_fwd(group, dps[0].x, lists("W"), lists("A"), lists("B"), lists("y"), lists("h"), ws)) == brackets
     for dp, (y, h) in zip(dps, want):
         n = plora.plora_h_elems(dp.desc)
         assert torch.equal(dp.y, y) and torch.equal(dp.h[:n], h[:n])
@@ -119,4 +119,31 @@ def test_group_with_the_wide_finish(w_layout):
     want = [(dp.y.clone(), dp.h.clone()) for dp in dps]
     for dp in dps:
         dp.y.fill_(float("nan")); dp.h.fill_(float("nan"))
-    group_is_the_plain_calls(dps, want, 1)
+    group_is_the_plain_calls(dps, want, (1, 0, 0))
+
+
+MIXED = {   # tokens, d_in, widths: the first projection does not take the two launches; brackets of products, shrinks, preparations
+    "few_sums": (461, 1024, (5408, 1352, 1352), (2, 1, 1)),             # the others do, 1.25 M sums
+    "many_sums": (1240, 864, (4904, 1224, 1224), (3, 1, 1)),            # 3.0 M: they share the group's steps
+    "split": (432, 4736, (8944, 2232, 2232), (2, 1, 1)),                # split anyway
+}
+
+
+@pytest.mark.parametrize("w_layout", [0, 1])
+@pytest.mark.parametrize("case", sorted(MIXED))
+def test_group_of_both_kinds(case, w_layout):
+    """Projections in two launches beside one that is not, and the same in the group's own steps: the bits of the plain calls."""
+    import gpu_harness as gh
+    T, D, widths, brackets = MIXED[case]
+    lengths, owner, ranks = [T // 3, 5, T - T // 3 - 5], [0, -1, 1], [30, 8]
+    lins = [problem(f"group_{case}_{p}", (D, K, lengths, owner, ranks), 509 + p) for p, K in enumerate(widths)]
+    tens = [l.tensors() for l in lins]
+    for t in tens[1:]:
+        t.x = tens[0].x
+    dps = [gh.upload(l, t, w_layout) for l, t in zip(lins, tens)]
+    for dp, plain in zip(dps, ((1, 0, 1), (1, 0, 0), (1, 0, 0))):
+        assert counted(lambda: gh.forward(dp)) == plain
+    want = [(dp.y.clone(), dp.h.clone()) for dp in dps]
+    for dp in dps:
+        dp.y.fill_(float("nan")); dp.h.fill_(float("nan"))
+    group_is_the_plain_calls(dps, want, brackets)
