@@ -17,7 +17,7 @@ def calls_driver(jobs):
     import ctypes as C
     import numpy as np
     from paper_2508_02932_amd import plora
-    L, rec = plora.lib(), C.CDLL(os.environ["LD_PRELOAD"])
+    L, rec = plora.lib(), C.CDLL(os.environ["PLORA_RECORDER"])
     rec.recorder_kernel.restype = C.c_char_p
     for f in (rec.recorder_workgroups, rec.recorder_lds, rec.recorder_allowed):
         f.restype = C.c_uint64
@@ -84,7 +84,7 @@ def launches(tmp_path_factory):
         code = "import json, sys; sys.path[:0] = [%r, %r]; import test_launches_host as t; print(json.dumps(t.calls_driver(json.load(sys.stdin))))" % (
             ROOT, os.path.join(ROOT, "tests"))
         run = subprocess.run([sys.executable, "-c", code], input=json.dumps(jobs), capture_output=True, text=True, timeout=600,
-                             env=dict(os.environ, LD_PRELOAD=lib))
+                             env=dict(os.environ, PLORA_RECORDER=lib, LD_PRELOAD=":".join([lib] + [v for v in [os.environ.get("LD_PRELOAD")] if v])))
         assert run.returncode == 0, run.stderr[-3000:]
         out = json.loads(run.stdout)
         assert len(out) == len(jobs) and all(code == 0 for codes, _ in out for code in codes)
